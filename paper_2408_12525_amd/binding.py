@@ -4,10 +4,15 @@ Argument marshalling only: tensors are checked (device, dtype, shape, contiguity
 as raw device pointers together with the current HIP stream.  Every step of the environment runs
 in the library's kernels.  There is no fallback: if the compiled library is missing or cannot be
 loaded, the first call raises.
+
+The calls a program makes over and over go through the compiled module of csrc/pcgrl_py.cpp, which
+does these checks and the call without Python in between; where an argument is not plainly right it
+answers LOOK, and the checks here say what is wrong with it.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 import torch
@@ -51,6 +56,8 @@ EXPORTS = [
 ]
 
 _lib = None
+_py = None
+_LOOK = 1000  # the compiled module's answer to arguments that are not plainly right
 
 
 class PcgrlError(RuntimeError):
@@ -105,6 +112,24 @@ def load():
     L.pcgrl_strerror.restype = C.c_char_p
     _lib = L
     return L
+
+
+def _load_py():
+    """The compiled call path (csrc/pcgrl_py.cpp), next to the library it is linked against."""
+    global _py
+    if _py is None:
+        load()
+        if not os.path.exists(_build.PY_LIB):
+            try:
+                _build.build_py()
+            except Exception as e:
+                raise PcgrlError(f"{_build.PY_LIB} is missing and could not be built ({e})") from e
+        spec = importlib.util.spec_from_file_location("pcgrl_py", _build.PY_LIB)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        assert mod.LOOK == _LOOK
+        _py = mod
+    return _py
 
 
 def _check(rc: int, what: str):
@@ -172,8 +197,12 @@ class Pcgrl:
         self.M = self.L.pcgrl_num_metrics(self.h)
         self.K = self.L.pcgrl_num_tiles(self.h)
         self.Hm, self.Wm = self.cfg.max_h, self.cfg.max_w
+        self._env = _load_py().Env(self.h.value, device, self.M, self.Hm, self.Wm, tuple(self.obs_shape),
+                                   tuple(self.onehot_shape))
 
     def close(self):
+        if getattr(self, "_env", None) is not None:
+            self._env.close()
         if getattr(self, "h", None) is not None and self.h:
             _check(self.L.pcgrl_destroy(self.h), "pcgrl_destroy")
             self.h = C.c_void_p()
@@ -218,45 +247,65 @@ class Pcgrl:
     def _st(self):
         return C.c_void_p(_stream_ptr(self.device))
 
-    # -- the C entry points
+    # -- the C entry points (each asks the compiled call path first, see the top of this file)
     def pcgrl_reset(self, seed: int, obs=None):
-        o = self._dev(obs, torch.uint8, self.obs_shape, "obs", optional=True)
-        _check(self.L.pcgrl_reset(self.h, C.c_uint64(seed), o, self._st()), "pcgrl_reset")
+        rc = self._env.reset(seed, obs)
+        if rc == _LOOK:
+            o = self._dev(obs, torch.uint8, self.obs_shape, "obs", optional=True)
+            rc = self.L.pcgrl_reset(self.h, C.c_uint64(seed), o, self._st())
+        if rc:
+            _check(rc, "pcgrl_reset")
 
     def pcgrl_step(self, actions, obs=None, reward=None, done=None):
-        a = self._dev(actions, torch.int32, (self.B,), "actions")
-        o = self._dev(obs, torch.uint8, self.obs_shape, "obs", optional=True)
-        r = self._dev(reward, torch.float32, (self.B,), "reward", optional=True)
-        d = self._dev(done, torch.uint8, (self.B,), "done", optional=True)
-        _check(self.L.pcgrl_step(self.h, a, o, r, d, self._st()), "pcgrl_step")
+        rc = self._env.step(actions, obs, reward, done)
+        if rc == _LOOK:
+            a = self._dev(actions, torch.int32, (self.B,), "actions")
+            o = self._dev(obs, torch.uint8, self.obs_shape, "obs", optional=True)
+            r = self._dev(reward, torch.float32, (self.B,), "reward", optional=True)
+            d = self._dev(done, torch.uint8, (self.B,), "done", optional=True)
+            rc = self.L.pcgrl_step(self.h, a, o, r, d, self._st())
+        if rc:
+            _check(rc, "pcgrl_step")
 
     def pcgrl_rollout(self, actions, obs=None, reward=None, done=None):
         """actions [T, B]; obs [slots, B, C, ow, ow] (slots <= T); reward / done [T, B]."""
-        if not isinstance(actions, torch.Tensor) or actions.dim() != 2:
-            raise PcgrlError("actions must be a [T, batch] tensor")
-        T = actions.shape[0]
-        a = self._dev(actions, torch.int32, (T, self.B), "actions")
-        slots = 1
-        o = None
-        if obs is not None:
-            slots = obs.shape[0] if obs.dim() == len(self.obs_shape) + 1 else 0
-            o = self._dev(obs, torch.uint8, (slots,) + tuple(self.obs_shape), "obs")
-        r = self._dev(reward, torch.float32, (T, self.B), "reward", optional=True)
-        d = self._dev(done, torch.uint8, (T, self.B), "done", optional=True)
-        _check(self.L.pcgrl_rollout(self.h, a, T, o, slots, r, d, self._st()), "pcgrl_rollout")
+        rc = self._env.rollout(actions, obs, reward, done)
+        if rc == _LOOK:
+            if not isinstance(actions, torch.Tensor) or actions.dim() != 2:
+                raise PcgrlError("actions must be a [T, batch] tensor")
+            T = actions.shape[0]
+            a = self._dev(actions, torch.int32, (T, self.B), "actions")
+            slots = 1
+            o = None
+            if obs is not None:
+                slots = obs.shape[0] if obs.dim() == len(self.obs_shape) + 1 else 0
+                o = self._dev(obs, torch.uint8, (slots,) + tuple(self.obs_shape), "obs")
+            r = self._dev(reward, torch.float32, (T, self.B), "reward", optional=True)
+            d = self._dev(done, torch.uint8, (T, self.B), "done", optional=True)
+            rc = self.L.pcgrl_rollout(self.h, a, T, o, slots, r, d, self._st())
+        if rc:
+            _check(rc, "pcgrl_rollout")
 
     def pcgrl_metrics(self, out=None):
         if out is None:
             out = torch.empty((self.B, self.M), dtype=torch.int32, device=self.device)
-        o = self._dev(out, torch.int32, (self.B, self.M), "out")
-        _check(self.L.pcgrl_metrics(self.h, o, self._st()), "pcgrl_metrics")
+        rc = self._env.metrics(out)
+        if rc == _LOOK:
+            o = self._dev(out, torch.int32, (self.B, self.M), "out")
+            rc = self.L.pcgrl_metrics(self.h, o, self._st())
+        if rc:
+            _check(rc, "pcgrl_metrics")
         return out
 
     def pcgrl_exact_diameter(self, out=None):
         if out is None:
             out = torch.empty((self.B,), dtype=torch.int32, device=self.device)
-        o = self._dev(out, torch.int32, (self.B,), "out")
-        _check(self.L.pcgrl_exact_diameter(self.h, o, self._st()), "pcgrl_exact_diameter")
+        rc = self._env.exact_diameter(out)
+        if rc == _LOOK:
+            o = self._dev(out, torch.int32, (self.B,), "out")
+            rc = self.L.pcgrl_exact_diameter(self.h, o, self._st())
+        if rc:
+            _check(rc, "pcgrl_exact_diameter")
         return out
 
     def pcgrl_exact_diameter_static(self, out, parts_log2: int = -1):
@@ -268,40 +317,49 @@ class Pcgrl:
 
     def pcgrl_unpack_obs(self, packed, out=None, dtype=torch.uint8):
         """Bit-packed observations [batch, stride] -> one-hot [batch, C, ow, ow] of `dtype`."""
-        pk = self._dev(packed, torch.uint8, self.obs_shape, "packed")
         if out is None:
             out = torch.empty(self.onehot_shape, dtype=dtype, device=self.device)
-        if out.dtype not in self.UNPACK_TYPES:
-            raise PcgrlError(f"cannot unpack into {out.dtype}")
-        o = self._dev(out, out.dtype, self.onehot_shape, "out")
-        _check(self.L.pcgrl_unpack_obs(self.h, pk, o, self.UNPACK_TYPES[out.dtype], self._st()), "pcgrl_unpack_obs")
+        rc = self._env.unpack_obs(packed, out)
+        if rc == _LOOK:
+            pk = self._dev(packed, torch.uint8, self.obs_shape, "packed")
+            if out.dtype not in self.UNPACK_TYPES:
+                raise PcgrlError(f"cannot unpack into {out.dtype}")
+            o = self._dev(out, out.dtype, self.onehot_shape, "out")
+            rc = self.L.pcgrl_unpack_obs(self.h, pk, o, self.UNPACK_TYPES[out.dtype], self._st())
+        if rc:
+            _check(rc, "pcgrl_unpack_obs")
         return out
 
     def pcgrl_observe(self, obs=None):
         if obs is None:
             obs = self.new_obs()
-        o = self._dev(obs, torch.uint8, self.obs_shape, "obs")
-        _check(self.L.pcgrl_observe(self.h, o, self._st()), "pcgrl_observe")
+        rc = self._env.observe(obs)
+        if rc == _LOOK:
+            o = self._dev(obs, torch.uint8, self.obs_shape, "obs")
+            rc = self.L.pcgrl_observe(self.h, o, self._st())
+        if rc:
+            _check(rc, "pcgrl_observe")
         return obs
 
     def pcgrl_get_state(self):
-        dev = self.device
-        tiles = torch.empty((self.B, self.Hm, self.Wm), dtype=torch.int8, device=dev)
-        frozen = torch.empty((self.B, self.Hm, self.Wm), dtype=torch.uint8, device=dev)
-        hw = torch.empty((self.B, 2), dtype=torch.int16, device=dev)
-        pos = torch.empty((self.B, 2), dtype=torch.int16, device=dev)
-        ctr = torch.empty((self.B, 3), dtype=torch.int32, device=dev)
-        _check(self.L.pcgrl_get_state(self.h, C.c_void_p(tiles.data_ptr()), C.c_void_p(frozen.data_ptr()),
-                                      C.c_void_p(hw.data_ptr()), C.c_void_p(pos.data_ptr()),
-                                      C.c_void_p(ctr.data_ptr()), self._st()), "pcgrl_get_state")
+        got = self._env.get_state()
+        if got == _LOOK:  # (a closed environment)
+            _check(self.L.pcgrl_get_state(self.h, None, None, None, None, None, self._st()), "pcgrl_get_state")
+        rc, tiles, frozen, hw, pos, ctr = got
+        if rc:
+            _check(rc, "pcgrl_get_state")
         return dict(tiles=tiles, frozen=frozen, hw=hw, pos=pos, counters=ctr)
 
     def pcgrl_set_state(self, tiles, frozen, hw, pos):
-        t = self._dev(tiles, torch.int8, (self.B, self.Hm, self.Wm), "tiles")
-        f = self._dev(frozen, torch.uint8, (self.B, self.Hm, self.Wm), "frozen", optional=True)
-        s = self._dev(hw, torch.int16, (self.B, 2), "hw")
-        q = self._dev(pos, torch.int16, (self.B, 2), "pos")
-        _check(self.L.pcgrl_set_state(self.h, t, f, s, q, self._st()), "pcgrl_set_state")
+        rc = self._env.set_state(tiles, frozen, hw, pos)
+        if rc == _LOOK:
+            t = self._dev(tiles, torch.int8, (self.B, self.Hm, self.Wm), "tiles")
+            f = self._dev(frozen, torch.uint8, (self.B, self.Hm, self.Wm), "frozen", optional=True)
+            s = self._dev(hw, torch.int16, (self.B, 2), "hw")
+            q = self._dev(pos, torch.int16, (self.B, 2), "pos")
+            rc = self.L.pcgrl_set_state(self.h, t, f, s, q, self._st())
+        if rc:
+            _check(rc, "pcgrl_set_state")
 
     def pcgrl_set_targets(self, targets):
         t = self._dev(targets, torch.int32, (self.B, self.M, 2), "targets")

@@ -1,4 +1,5 @@
-"""Compiles the HIP library for gfx950 in-tree (hipcc cross-compiles without a GPU)."""
+"""Compiles the HIP library for gfx950 in-tree (hipcc cross-compiles without a GPU), and the
+compiled part of the Python binding, which is host code only."""
 from __future__ import annotations
 
 import json
@@ -6,6 +7,7 @@ import os
 import re
 import shutil
 import subprocess
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +16,8 @@ DEPS = [SRC, os.path.join(HERE, "csrc", "pcgrl_kernels.hip.h"),
         os.path.join(os.path.dirname(HERE), "include", "pcgrl.h")]
 LIB_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIB_DIR, "libpcgrl.so")
+PY_SRC = os.path.join(HERE, "csrc", "pcgrl_py.cpp")
+PY_LIB = os.path.join(LIB_DIR, "pcgrl_py.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -28,7 +32,9 @@ HIPCC_FLAGS = [
 
 
 def is_stale() -> bool:
-    return (not os.path.exists(LIB)) or os.path.getmtime(LIB) < max(os.path.getmtime(d) for d in DEPS)
+    newest = lambda files: max(os.path.getmtime(f) for f in files)
+    return (not os.path.exists(LIB) or os.path.getmtime(LIB) < newest(DEPS) or not os.path.exists(PY_LIB) or
+            os.path.getmtime(PY_LIB) < newest([PY_SRC, DEPS[-1]]))
 
 
 SCAN_REPORT = os.path.join(LIB_DIR, "libpcgrl.scan.json")
@@ -100,7 +106,35 @@ def build(force: bool = True, verbose: bool = False) -> str:
             shutil.move(out, LIB)
         finally:
             shutil.rmtree(tmp, ignore_errors=True)
+        build_py(verbose)
     return LIB
+
+
+def build_py(verbose: bool = False) -> str:
+    """Compiles csrc/pcgrl_py.cpp against the installed torch and the library in-tree."""
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = tempfile.mkdtemp(prefix="pcgrl_build_")
+    try:
+        out = os.path.join(tmp, "pcgrl_py.so")
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+               "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+               "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+               "-I" + os.path.join(troot, "include"),
+               "-I" + os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+               "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"],
+               PY_SRC, "-o", out, "-L" + LIB_DIR, "-l:libpcgrl.so", "-L" + os.path.join(troot, "lib"),
+               "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("the Python binding's compiled part failed to build:\n" + res.stdout)
+        shutil.move(out, PY_LIB)
+    finally:
+        shutil.rmtree(tmp, ignore_errors=True)
+    return PY_LIB
 
 
 if __name__ == "__main__":

@@ -31,7 +31,7 @@ struct pcgrl_ctx {
   int store_step, store_roll;  // how a step / a rollout launch stores observations (kStore*)
   int store_step_auto;         // store_step follows the buffers the caller hands in (below)
   const uint8_t* recent_obs[32];  // observation pointers of the last 32 pcgrl_step calls
-  unsigned recent_n;
+  unsigned recent_n, recent_distinct;
   KArgs base;  // device pointers and configuration, copied into every launch
   void* d_planes;
   void* d_frozen;
@@ -278,14 +278,21 @@ int launch_init(pcgrl_ctx* ctx, int flags, uint64_t seed, uint8_t* obs, hipStrea
 // sees only pointers, so it remembers those of the last 32 calls and takes the bytes of the
 // distinct buffers among them as the working set.  Tuning only: results do not depend on it.
 int step_store_kind(pcgrl_ctx* ctx, const uint8_t* obs) {
-  ctx->recent_obs[ctx->recent_n++ & 31u] = obs;
-  const unsigned filled = ctx->recent_n < 32u ? ctx->recent_n : 32u;
-  unsigned distinct = 0;
-  for (unsigned i = 0; i < filled; ++i) {
-    bool seen = false;
-    for (unsigned j = 0; j < i; ++j) seen = seen || ctx->recent_obs[j] == ctx->recent_obs[i];
-    distinct += seen ? 0u : 1u;
+  // (the number of distinct pointers follows from the one that leaves the window and the one that
+  // enters it; counting them afresh took a tenth of a call)
+  const unsigned at = ctx->recent_n++ & 31u;
+  const uint8_t* const old = ctx->recent_obs[at];  // NULL while the window fills; obs never is
+  if (old != obs) {
+    ctx->recent_obs[at] = nullptr;
+    unsigned of_old = 0, of_new = 0;
+    for (int i = 0; i < 32; ++i) {
+      of_old += ctx->recent_obs[i] == old ? 1u : 0u;
+      of_new += ctx->recent_obs[i] == obs ? 1u : 0u;
+    }
+    ctx->recent_obs[at] = obs;
+    ctx->recent_distinct += (of_new == 0 ? 1u : 0u) - (old != nullptr && of_old == 0 ? 1u : 0u);
   }
+  const unsigned distinct = ctx->recent_distinct;
   const size_t step_bytes = (size_t)ctx->cfg.batch * ctx->obs_stride;
   if (distinct <= 1) return ctx->store_step;
   if ((size_t)distinct * step_bytes <= ((size_t)256 << 20)) return kStoreThrough;

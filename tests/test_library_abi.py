@@ -83,3 +83,18 @@ def test_built_library_passed_the_scan():
         build.build(force=True)
     rep = json.load(open(build.SCAN_REPORT))
     assert rep["findings"] == [] and rep["kernels"] >= 80
+
+
+def test_compiled_call_path_leaves_doubtful_arguments_to_the_python_checks():
+    """Arguments that are not device tensors of the right type and shape, missing ones and a closed
+    environment are answered with LOOK, before any library call (no GPU is touched)."""
+    import torch
+    py = binding._load_py()
+    env = py.Env(1, 0, 4, 16, 16, (3, 2, 31, 31), (3, 2, 31, 31))   # (the handle is never followed)
+    act, obs = torch.zeros(3, dtype=torch.int32), torch.zeros((3, 2, 31, 31), dtype=torch.uint8)
+    calls = lambda e: [e.step(act, None, None, None), e.step(None, obs, None, None), e.step(act), e.rollout(act, None, None, None),
+                       e.rollout(act[None], obs, None, None), e.reset("1", None), e.reset(1, obs), e.metrics(act),
+                       e.observe(obs), e.unpack_obs(obs, obs), e.exact_diameter(act), e.set_state(act, None, act, act)]
+    assert set(calls(env)) == {py.LOOK}
+    env.close()
+    assert set(calls(env) + [env.get_state(), env.reset(1, None)]) == {py.LOOK}
