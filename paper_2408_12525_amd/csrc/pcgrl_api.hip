@@ -159,6 +159,13 @@ template <int S, int PROBLEM> struct LaunchInit {
   }
 };
 
+template <int S, int PROBLEM> struct LaunchSetState {
+  static int run(const pcgrl_ctx* ctx, const KArgs& a, const LevelSource& src, hipStream_t st) {
+    hipLaunchKernelGGL((set_state_kernel<S, PROBLEM>), dim3(ctx->nwaves), dim3(64), 0, st, a, src);
+    return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
+  }
+};
+
 template <int S, int PROBLEM> struct LaunchExact {
   static int run(const pcgrl_ctx* ctx, const KArgs& a, int32_t* out, int parts_log2, hipStream_t st) {
     hipLaunchKernelGGL((exact_diameter_kernel<S, PROBLEM>), dim3((unsigned)ctx->nwaves << parts_log2), dim3(64),
@@ -727,14 +734,17 @@ int pcgrl_get_state(pcgrl_ctx* ctx, int8_t* tiles, uint8_t* frozen, int16_t* hw,
   if (!ctx) return PCGRL_E_NULL;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
-  const int n = ctx->cfg.batch * ctx->S;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  // a thread for every 16 cells (and at least one for every level's scalars)
+  const uint64_t cells = (uint64_t)ctx->cfg.batch * (uint64_t)(ctx->cfg.max_h * ctx->cfg.max_w);
+  const uint64_t threads = (tiles || frozen) && (cells + 15) / 16 > (uint64_t)ctx->cfg.batch ? (cells + 15) / 16 : (uint64_t)ctx->cfg.batch;
+  const dim3 grid((unsigned)((threads + kGetThreads - 1) / kGetThreads));
   if (ctx->S == 64)
-    hipLaunchKernelGGL(get_state_kernel<uint64_t>, dim3((n + 255) / 256), dim3(256), 0, st, ctx->base,
-                       ctx->S, ctx->P, tiles, frozen, hw, pos, counters);
+    hipLaunchKernelGGL(get_state_kernel<uint64_t>, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, ctx->P, tiles, frozen,
+                       hw, pos, counters);
   else
-    hipLaunchKernelGGL(get_state_kernel<uint32_t>, dim3((n + 255) / 256), dim3(256), 0, st, ctx->base,
-                       ctx->S, ctx->P, tiles, frozen, hw, pos, counters);
+    hipLaunchKernelGGL(get_state_kernel<uint32_t>, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, ctx->P, tiles, frozen,
+                       hw, pos, counters);
   return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
 }
 
@@ -743,17 +753,11 @@ int pcgrl_set_state(pcgrl_ctx* ctx, const int8_t* tiles, const uint8_t* frozen, 
   if (!ctx || !tiles || !hw || !pos) return PCGRL_E_NULL;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
-  const int n = ctx->cfg.batch * ctx->S;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (ctx->S == 64)
-    hipLaunchKernelGGL(set_state_kernel<uint64_t>, dim3((n + 255) / 256), dim3(256), 0, st, ctx->base,
-                       ctx->S, ctx->P, ctx->K, tiles, frozen, hw, pos);
-  else
-    hipLaunchKernelGGL(set_state_kernel<uint32_t>, dim3((n + 255) / 256), dim3(256), 0, st, ctx->base,
-                       ctx->S, ctx->P, ctx->K, tiles, frozen, hw, pos);
-  if (hipGetLastError() != hipSuccess) return PCGRL_E_HIP;
+  const LevelSource src = {tiles, frozen, hw, pos};
+  const int rc = dispatch<LaunchSetState>(ctx->S, ctx->cfg.problem, ctx, ctx->base, src, static_cast<hipStream_t>(stream));
+  if (rc != PCGRL_OK) return rc;
   if (frozen) ctx->base.use_frozen = ctx->cfg.obs_frozen_channel ? 3 : 1;  // from now on steps have to look pinpoints up
-  return launch_init(ctx, kInitMetrics, ctx->base.seed, nullptr, st);
+  return PCGRL_OK;
 }
 
 int pcgrl_set_targets(pcgrl_ctx* ctx, const int32_t* targets, void* stream) {

@@ -1133,11 +1133,6 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
     for (int i = 0; i < PR::P; ++i) p[i] = planes[(size_t)i * a.plane_stride + ridx];
     fz = 0;
     if ((a.flags & kInitObs) && a.obs_frozen_channel) fz = frozen[ridx];
-    if (a.flags & kInitMetrics) {  // a level was installed: its pinpoint flag has to be refreshed
-      fz = frozen[ridx];
-      er.cell_frozen = L.gany(L.y == py && ((fz >> px) & 1)) ? 1u : 0u;
-      if (wm.primary && L.y == 0) a.env[wm.env] = er;
-    }
   }
   const W inside = inside_row<W>(L.y, h, w);
   if (a.flags & kInitMetrics) {
@@ -1865,74 +1860,223 @@ __global__ __launch_bounds__(MODE == kModeRolloutSplit ? 320 : 64) void rollout_
 
 // ------------------------------------------------- plain-layout conversion
 
-// tiles int8 [B][max_h][max_w] <-> bit-planes; one thread per (env, row).
-template <typename W>
-__global__ void set_state_kernel(KArgs a, int S, int P, int K, const int8_t* tiles,
-                                 const uint8_t* fro, const int16_t* hw, const int16_t* pos) {
-  int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (idx >= a.B * S) return;
-  int env = idx / S, y = idx % S;
-  int h = min(max((int)hw[2 * env], 1), a.max_h), w = min(max((int)hw[2 * env + 1], 1), a.max_w);
-  W pl[3] = {0, 0, 0};
-  W fz = 0;
-  if (y < h) {
-    for (int x = 0; x < w; ++x) {
-      size_t ci = ((size_t)env * a.max_h + y) * a.max_w + x;
-      int t = tiles[ci];
-      if (t < 0 || t >= K) t = 0;
-      for (int i = 0; i < P; ++i) pl[i] |= (W)((t >> i) & 1) << x;
-      if (fro && fro[ci]) fz |= (W)1 << x;
+// Levels in the plain layout (bytes [B][max_h][max_w]) -> bit-planes, and the metrics of what was
+// installed, in one pass.  A wavefront takes the levels of its lane groups, whose cells are one
+// contiguous run of bytes in either array: it reads the run in 16-byte pieces, packs each piece to 16 bits per plane with a multiply per four cells, and
+// keeps the packed runs in LDS, out of which every lane then cuts its row.  Bound by latency and by
+// the from-scratch metrics that follow.  Reading the bytes one by one, a thread per row, took
+// 31 us for 5001 levels of 27x45 (12 MB) in a kernel of its own, and the metrics a second one
+// (16 us); both together now take 19.
+struct LevelSource {
+  const int8_t* tiles;
+  const uint8_t* frozen;  // or NULL: no pinpoints
+  const int16_t *hw, *pos;
+};
+// bit 0 of every byte that is not zero
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) {
+  return ((((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) >> 7) & 0x01010101u;
+}
+// bit 0 of the four bytes of v (whose other bits are zero), moved together
+__device__ __forceinline__ uint32_t gather_nibble(uint32_t v) { return (v * 0x01020408u) >> 24; }
+// The 16 bytes of an array from byte `at` on, for any address; what lies behind its `total` bytes
+// is not read and reads as zero.
+typedef u32x4 __attribute__((aligned(1))) unaligned_u32x4;
+__device__ __forceinline__ u32x4 load_piece(const uint8_t* array, size_t at, size_t total) {
+  if (at + 16 <= total) return *reinterpret_cast<const unaligned_u32x4*>(array + at);
+  uint64_t lo = 0, hi = 0;
+  if (total >= 16) {  // the last 16 bytes, moved down
+    const u32x4 v = *reinterpret_cast<const unaligned_u32x4*>(array + total - 16);
+    lo = (uint64_t)v.x | ((uint64_t)v.y << 32);
+    hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+    const int by = 8 * (int)(at + 16 - total);
+    lo = by < 64 ? (lo >> by) | (hi << 1 << (63 - by)) : hi >> (by - 64);
+    hi = by < 64 ? hi >> by : 0ull;
+  } else {
+#pragma unroll 1
+    for (size_t j = total; j > at; --j) {
+      hi = (hi << 8) | (lo >> 56);
+      lo = (lo << 8) | array[j - 1];
     }
   }
-  W* planes = reinterpret_cast<W*>(a.planes);
-  for (int i = 0; i < P; ++i) planes[(size_t)i * a.plane_stride + idx] = pl[i];
-  reinterpret_cast<W*>(a.frozen)[idx] = fz;
-  if (y == 0) {
-    EnvRec er = a.env[env];
-    er.h = (uint8_t)h;
-    er.w = (uint8_t)w;
-    er.py = (uint8_t)min(max((int)pos[2 * env], 0), h - 1);
-    er.px = (uint8_t)min(max((int)pos[2 * env + 1], 0), w - 1);
-    er.t = 0;
-    er.n_changes = 0;
-    a.env[env] = er;
+  const u32x4 r = {(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+  return r;
+}
+
+template <int S, int PROBLEM>
+__device__ __forceinline__ void load_plain_rows(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm, const LevelSource& src,
+                                                int h, int w, typename RowWord<S>::T (&p)[Prob<PROBLEM>::P],
+                                                typename RowWord<S>::T& fz) {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  constexpr int kHalves = 64 * S / 16 + 4;  // (a row is cut out of three words)
+  __shared__ __align__(4) uint16_t runs[PR::P + 1][kHalves];
+  const int cells = a.max_h * a.max_w, n = wm.nvalid * cells;
+  const size_t at0 = (size_t)wm.env0 * (size_t)cells, total = (size_t)a.B * (size_t)cells;
+  const uint8_t* tiles = reinterpret_cast<const uint8_t*>(src.tiles);
+  const bool with_fz = src.frozen != nullptr;
+  u32x4 t = {0, 0, 0, 0}, f = {0, 0, 0, 0};
+  auto request = [&](int q) {
+    if (16 * q < n) {
+      t = load_piece(tiles, at0 + 16 * q, total);
+      if (with_fz) f = load_piece(src.frozen, at0 + 16 * q, total);
+    }
+  };
+  request(L.lane);
+#pragma unroll 1
+  for (int q = L.lane; 16 * q < n; q += 64) {
+    const uint32_t tw[4] = {t.x, t.y, t.z, t.w}, fw[4] = {f.x, f.y, f.z, f.w};
+    request(q + 64);
+    uint32_t bits[PR::P] = {}, fbits = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      // a code that is no tile of the problem counts as tile 0
+      uint32_t bad = nonzero_bytes(tw[j] & (0x01010101u * (0xffu & ~((1u << PR::P) - 1u))));
+      if constexpr (PR::K == 7) bad |= tw[j] & (tw[j] >> 1) & (tw[j] >> 2) & 0x01010101u;
+#pragma unroll
+      for (int i = 0; i < PR::P; ++i) bits[i] |= gather_nibble((tw[j] >> i) & 0x01010101u & ~bad) << (4 * j);
+      fbits |= gather_nibble(nonzero_bytes(fw[j])) << (4 * j);
+    }
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) runs[i][q] = (uint16_t)bits[i];
+    runs[PR::P][q] = (uint16_t)fbits;
+  }
+  lds_sync();
+  const int bit = wm.sl.slot * cells + L.y * a.max_w, word = bit >> 5, sh = bit & 31;  // where this lane's row starts
+  const W mask = wm.valid ? inside_row<W>(L.y, h, w) : (W)0;
+  auto row = [&](int i) -> W {
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(runs[i]) + word;
+    uint64_t r = ((uint64_t)words[0] | ((uint64_t)words[1] << 32)) >> sh;
+    if constexpr (S == 64) r |= (uint64_t)words[2] << 1 << (63 - sh);
+    return (W)r & mask;
+  };
+  fz = 0;
+#pragma unroll
+  for (int i = 0; i < PR::P; ++i) p[i] = 0;
+  if (mask != 0) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) p[i] = row(i);
+    fz = row(PR::P);
   }
 }
 
-template <typename W>
-__global__ void get_state_kernel(KArgs a, int S, int P, int8_t* tiles, uint8_t* fro, int16_t* hw,
-                                 int16_t* pos, int32_t* counters) {
-  int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (idx >= a.B * S) return;
-  int env = idx / S, y = idx % S;
-  EnvRec er = a.env[env];
-  const W* planes = reinterpret_cast<const W*>(a.planes);
-  W pl[3] = {0, 0, 0};
-  for (int i = 0; i < P; ++i) pl[i] = planes[(size_t)i * a.plane_stride + idx];
-  W fz = reinterpret_cast<const W*>(a.frozen)[idx];
-  if (y < a.max_h) {
-    for (int x = 0; x < a.max_w; ++x) {
-      size_t ci = ((size_t)env * a.max_h + y) * a.max_w + x;
-      bool in = y < er.h && x < er.w;
-      int t = 0;
-      for (int i = 0; i < P; ++i) t |= (int)((pl[i] >> x) & 1) << i;
-      if (tiles) tiles[ci] = in ? (int8_t)t : (int8_t)-1;
-      if (fro) fro[ci] = (in && ((fz >> x) & 1)) ? 1 : 0;
-    }
+template <int S, int PROBLEM>
+__global__ __launch_bounds__(64) void set_state_kernel(KArgs a, LevelSource src) {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  Lanes<S> L;
+  WaveMap<S> wm;
+  wm.init(a, L, nullptr, (int)blockIdx.x, a.envs_per_wave_log2 & 0xff);
+  const int16_t* hwp = src.hw + 2 * (size_t)wm.envl;
+  const int16_t* qp = src.pos + 2 * (size_t)wm.envl;
+  // the episode and its key stay (read as words: a struct that is loaded whole and then changed field
+  // by field is kept in memory by the compiler, in LDS slots found through the dispatch packet, which
+  // lies in host memory: 13 us of a launch)
+  const uint4* erp = reinterpret_cast<const uint4*>(a.env + wm.envl);
+  const uint4 er0 = erp[0], er1 = erp[1];
+  const int h = min(max((int)hwp[0], 1), a.max_h), w = min(max((int)hwp[1], 1), a.max_w);
+  const int py = min(max((int)qp[0], 0), h - 1), px = min(max((int)qp[1], 0), w - 1);
+  W p[PR::P], fz;
+  load_plain_rows<S, PROBLEM>(a, L, wm, src, h, w, p, fz);
+  W* planes = reinterpret_cast<W*>(a.planes);
+  const size_t ridx = (size_t)wm.envl * S + L.y;
+  EnvRec er;
+  er.episode = (int32_t)er0.w;
+  er.key = (uint64_t)er1.x | ((uint64_t)er1.y << 32);
+  er.pad_ = 0;
+  er.h = (uint8_t)h;
+  er.w = (uint8_t)w;
+  er.py = (uint8_t)py;
+  er.px = (uint8_t)px;
+  er.t = 0;
+  er.n_changes = 0;
+  er.cell_frozen = L.gany(L.y == py && ((fz >> px) & 1)) ? 1u : 0u;
+  if (wm.primary) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) planes[(size_t)i * a.plane_stride + ridx] = p[i];
+    reinterpret_cast<W*>(a.frozen)[ridx] = fz;
+    if (L.y == 0) a.env[wm.env] = er;
   }
-  if (y == 0) {
+  int m[PR::M];
+  W comp;
+  full_metrics<S, PROBLEM>(L, p, inside_row<W>(L.y, h, w), wm.valid, m, comp);
+  if (wm.primary && L.y == 0) store_metrics<S, PROBLEM>(a.metrics + (size_t)wm.env * kMaxMetrics, m);
+  if constexpr (PROBLEM == kBinary) {  // (the plane after the tile planes)
+    if (wm.primary) planes[(size_t)PR::P * a.plane_stride + ridx] = comp;
+  }
+}
+
+// Bit-planes -> the plain layout.  A thread writes 16 consecutive bytes of the tile array and of
+// the pinpoint array, wherever rows and levels end in between: the bits of each row they touch
+// (one or two rows for most widths) are put together and widened with a multiply per four cells.
+// Bound by its stores: a thread per row that wrote byte after byte took 49 us for 5001 levels of
+// 27x45 (12 MB), this 7.
+constexpr int kGetThreads = 256;
+template <typename W>
+__global__ __launch_bounds__(kGetThreads) void get_state_kernel(KArgs a, int S, int P, int8_t* tiles, uint8_t* fro, int16_t* hw,
+                                                                int16_t* pos, int32_t* counters) {
+  const int cells = a.max_h * a.max_w;
+  const uint64_t total = (uint64_t)a.B * (uint64_t)cells;
+  const W* planes = reinterpret_cast<const W*>(a.planes);
+  const uint64_t block0 = (uint64_t)blockIdx.x * (16 * kGetThreads);
+  const uint64_t at = block0 + 16 * threadIdx.x;
+  if (at < total && (tiles || fro)) {
+    const int from = (int)(block0 % (uint32_t)cells) + 16 * (int)threadIdx.x;
+    int env = (int)(block0 / (uint32_t)cells) + from / cells;
+    int y = from % cells / a.max_w, x = from % cells % a.max_w;
+    const int n = (int)min((uint64_t)16, total - at);
+    uint32_t bits[3] = {0, 0, 0}, in = 0, fz = 0;
+    for (int got = 0; got < n;) {
+      const int run = min(n - got, a.max_w - x);
+      const EnvRec& er = a.env[env];
+      const size_t row = (size_t)env * S + y;
+      const uint32_t mask = (1u << run) - 1u;
+      for (int i = 0; i < P; ++i) bits[i] |= ((uint32_t)(planes[(size_t)i * a.plane_stride + row] >> x) & mask) << got;
+      fz |= ((uint32_t)(reinterpret_cast<const W*>(a.frozen)[row] >> x) & mask) << got;
+      in |= ((uint32_t)(inside_row<W>(y, er.h, er.w) >> x) & mask) << got;
+      got += run;
+      x = 0;
+      if (++y == a.max_h) {
+        y = 0;
+        ++env;
+      }
+    }
+    // (a nibble times 0x204081 puts bit k at bit 8 k)
+    auto widen = [](uint32_t b, int j) { return __umul24((b >> (4 * j)) & 15u, 0x00204081u) & 0x01010101u; };
+    uint32_t t[4], f[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t inj = widen(in, j), outj = inj ^ 0x01010101u;
+      t[j] = widen(bits[0] & in, j) | widen(bits[1] & in, j) << 1 | widen(bits[2] & in, j) << 2 | ((outj << 8) - outj);
+      f[j] = widen(fz & in, j);
+    }
+    auto store = [&](uint8_t* dst, const uint32_t (&v)[4]) {
+      dst += at;
+      if (n == 16 && ((uintptr_t)dst & 15u) == 0) {
+        *reinterpret_cast<uint4*>(dst) = make_uint4(v[0], v[1], v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (j < n) dst[j] = (uint8_t)(v[j >> 2] >> (8 * (j & 3)));
+      }
+    };
+    if (tiles) store(reinterpret_cast<uint8_t*>(tiles), t);
+    if (fro) store(fro, f);
+  }
+  const int e = (int)(blockIdx.x * kGetThreads + threadIdx.x);
+  if (e < a.B && (hw || pos || counters)) {
+    const EnvRec er = a.env[e];
     if (hw) {
-      hw[2 * env] = er.h;
-      hw[2 * env + 1] = er.w;
+      hw[2 * (size_t)e] = er.h;
+      hw[2 * (size_t)e + 1] = er.w;
     }
     if (pos) {
-      pos[2 * env] = er.py;
-      pos[2 * env + 1] = er.px;
+      pos[2 * (size_t)e] = er.py;
+      pos[2 * (size_t)e + 1] = er.px;
     }
     if (counters) {
-      counters[3 * env] = er.t;
-      counters[3 * env + 1] = er.n_changes;
-      counters[3 * env + 2] = er.episode;
+      counters[3 * (size_t)e] = er.t;
+      counters[3 * (size_t)e + 1] = er.n_changes;
+      counters[3 * (size_t)e + 2] = er.episode;
     }
   }
 }

@@ -1,0 +1,71 @@
+"""GPU kernels vs the oracle at the sizes where their splits can go wrong (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity import assert_same, compare_state
+from paper_2408_12525_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+
+def _plain_levels(problem, B, h, w, seed, p_wall=None):
+    """Random levels in the plain layout, some codes of them no tile of the problem, ragged shapes,
+    positions inside and outside."""
+    rng = np.random.default_rng(seed)
+    K = wl.NUM_TILES[problem]
+    if p_wall is None:
+        tiles = rng.integers(-2, K + 3, size=(B, h, w)).astype(np.int8)
+    else:
+        tiles = (rng.random((B, h, w)) < p_wall).astype(np.int8)
+    frozen = ((rng.random((B, h, w)) < 0.2) * rng.integers(1, 256, size=(B, h, w))).astype(np.uint8)
+    hw = np.stack([rng.integers(1, h + 1, B), rng.integers(1, w + 1, B)], 1).astype(np.int16)
+    hw[0] = (h, w)
+    pos = rng.integers(-1, 70, size=(B, 2)).astype(np.int16)
+    return tiles, frozen, hw, pos
+
+
+@pytest.mark.parametrize("problem,B,h,w", [
+    (wl.BINARY, 1, 1, 1), (wl.MAZE, 37, 16, 16), (wl.DUNGEON, 2051, 11, 3), (wl.BINARY, 65, 3, 32), (wl.MAZE, 4099, 31, 17),
+    (wl.DUNGEON, 19, 27, 45), (wl.BINARY, 9, 64, 64), (wl.DUNGEON, 5, 2, 64), (wl.MAZE, 7, 63, 5)])
+@pytest.mark.parametrize("with_frozen", [True, False])
+def test_plain_levels_in_and_out(problem, B, h, w, with_frozen):
+    """pcgrl_set_state and pcgrl_get_state where rows, levels and the 16-byte pieces they are read
+    and written in end at different places."""
+    cfg = wl.make_config(problem, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0)
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    gpu.pcgrl_reset(3)
+    cpu.reset(3)
+    tiles, frozen, hw, pos = _plain_levels(problem, B, h, w, B + h)
+    frozen = frozen if with_frozen else None
+    # arrays that do not start on a 16-byte boundary, with guard bytes behind them
+    def shifted(a, by):
+        buf = torch.full((a.size + 64,), 0x55, dtype=torch.uint8, device=DEV)
+        buf[by:by + a.size] = torch.from_numpy(a.reshape(-1).view(np.uint8)).to(DEV)
+        return buf[by:by + a.size].view(torch.int8 if a.dtype == np.int8 else torch.uint8).view(a.shape)
+    gpu.pcgrl_set_state(shifted(tiles, 7), None if frozen is None else shifted(frozen, 13),
+                        torch.from_numpy(hw).to(DEV), torch.from_numpy(pos).to(DEV))
+    # (what the library makes of it: unknown codes count as tile 0, positions are clamped)
+    known = np.where((tiles < 0) | (tiles >= wl.NUM_TILES[problem]), 0, tiles).astype(np.int8)
+    cpu.set_state(known, frozen, hw, np.clip(pos, 0, hw - 1).astype(np.int16))
+    compare_state(gpu, cpu, "after set_state")
+    assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "after set_state")
+    assert_same("obs", gpu.pcgrl_observe(), cpu.observe(), "after set_state")
+    n = B * h * w
+    for by in (0, 5):
+        t, f = (torch.full((n + 32,), 0x77, dtype=torch.uint8, device=DEV) for _ in range(2))
+        rc = gpu.L.pcgrl_get_state(gpu.h, t.data_ptr() + by, f.data_ptr() + by, None, None, None, gpu._st())
+        assert rc == 0
+        st = cpu.get_state()
+        assert_same("tiles", t[by:by + n].view(torch.int8).view(B, h, w), st["tiles"], f"offset {by}")
+        assert_same("frozen", f[by:by + n].view(B, h, w), st["frozen"], f"offset {by}")
+        for buf in (t, f):
+            assert bool((buf[by + n:] == 0x77).all()) and bool((buf[:by] == 0x77).all())
+    acts = wl.random_actions(cfg, 4, 12)
+    for t in range(12):
+        gpu.pcgrl_step(torch.from_numpy(acts[t]).to(DEV))
+        cpu.step(acts[t], want_obs=False)
+    assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "after edits")
+    gpu.close()
