@@ -5,7 +5,6 @@
 
 #include <cstdint>
 #include <cstring>
-#include <mutex>
 #include <new>
 
 #include "pcgrl_kernels.hip.h"
@@ -39,8 +38,7 @@ struct pcgrl_ctx {
   void* d_metrics;
   void* d_targets;
   void* d_bad;
-  void* d_exact;         // partial results of pcgrl_exact_diameter, [1 << exact_parts_log2][batch] ints (NULL for one part)
-  int exact_parts_log2;  // a level's sources are shared out over this many workgroups there
+  int exact_waves_log2;  // pcgrl_exact_diameter: wavefronts per workgroup
 };
 
 namespace {
@@ -167,45 +165,16 @@ template <int S, int PROBLEM> struct LaunchSetState {
 };
 
 template <int S, int PROBLEM> struct LaunchExact {
-  static int run(const pcgrl_ctx* ctx, const KArgs& a, int32_t* out, int parts_log2, hipStream_t st) {
-    hipLaunchKernelGGL((exact_diameter_kernel<S, PROBLEM>), dim3((unsigned)ctx->nwaves << parts_log2), dim3(64),
-                       ctx->lds_bytes, st, a, out, parts_log2);
+  static int run(const pcgrl_ctx* ctx, const KArgs& a, int32_t* out, int waves_log2, hipStream_t st) {
+    hipLaunchKernelGGL((exact_diameter_kernel<S, PROBLEM>), dim3((unsigned)ctx->nwaves), dim3(64u << waves_log2), 0, st, a, out,
+                       waves_log2);
     return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
   }
 };
 
-// Exact diameters into `out`, the sources of every level shared out over 1 << parts_log2
-// workgroups whose partial results go through `partial` ([parts][batch] ints, unused for one part).
-int exact_diameter_with(pcgrl_ctx* ctx, int32_t* out, int32_t* partial, int parts_log2, hipStream_t st) {
-  if (parts_log2 == 0) return dispatch<LaunchExact>(ctx->S, ctx->cfg.problem, ctx, ctx->base, out, 0, st);
-  int rc = dispatch<LaunchExact>(ctx->S, ctx->cfg.problem, ctx, ctx->base, partial, parts_log2, st);
-  if (rc != PCGRL_OK) return rc;
-  const int B = ctx->cfg.batch;
-  hipLaunchKernelGGL(max_over_parts_kernel, dim3((B + 255) / 256), dim3(256), 0, st, partial, out, B, 1 << parts_log2);
-  return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
-}
-
-// Partial results of pcgrl_exact_diameter_static, for callers that must not allocate: one array per
-// GPU the library runs on, held until the process ends.  The name is a host-side stand-in, not a
-// device address; host code uses only the address hipGetSymbolAddress gives for the current device.
-constexpr size_t kStaticScratchInts = (size_t)1 << 18;  // 1 MiB
-__device__ __align__(256) int32_t scratch[kStaticScratchInts];
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-int32_t* g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each GPU, once asked for
-
-// The device address of `scratch` on `device`, which must be the current device.
-int static_scratch(int device, int32_t** out) {
-  if (device < 0 || device >= kMaxDevices) return PCGRL_E_DEVICE;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[device]) {
-    void* ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return PCGRL_E_HIP;
-    g_scratch_ptr[device] = static_cast<int32_t*>(ptr);
-  }
-  *out = g_scratch_ptr[device];
-  return PCGRL_OK;
-}
+// pcgrl_exact_diameter_static takes at most this many levels times parts, if the caller chooses the
+// parts (see the header).
+constexpr size_t kStaticMostParts = (size_t)1 << 18;
 
 // ---- launch shapes.  Results never depend on them; every row below is a measurement on MI355X
 // (per-step launches replayed from a HIP graph, rollouts of 100 steps; the figures are in the
@@ -259,11 +228,18 @@ int levels_per_wave_for(int G, int batch, int min_groups) {
   return n;
 }
 
-// Into how many parts (a power of two, at most one per row) pcgrl_exact_diameter splits the
-// sources of a level: enough for about four thousand wavefronts.
-int exact_parts_for(int nwaves, int S) {
+// How many wavefronts (1 << the result) of pcgrl_exact_diameter share a level's components out among
+// them.  Two parts a level always (a copy of the level in a spare lane group is a part as well), more
+// while that takes no more than 4096 wavefronts, up to S / 4 parts and eight.  Measured, us for 1, 2,
+// 4, 8, 16 wavefronts a workgroup: 4096 64x64 levels 280 / 223 / 243 / 308 / 501, 1024 of them 147 /
+// 93 / 88 / 88 / 140, 256 143 / 73 / 45 / 41 / 53; 16 384 32x32 levels 199 / 178 / 203 / 276 / 442,
+// 1024 (two copies each) 39 / 27 / 27 / 35 / 54; 16 384 16x16 levels 62 / 53 / 62 / 82 / 126, 1024 (four
+// copies each) 16 / 21 / 21 / 23 / 28.
+constexpr int kMostExactWavesLog2 = 4;  // a workgroup of 1024 threads
+int exact_waves_for(int nwaves, int copies, int S) {
+  const int most = S / 4 < 8 ? S / 4 : 8;
   int lg = 0;
-  while ((1 << (lg + 1)) <= S && ((long long)nwaves << (lg + 1)) <= 4096) ++lg;
+  while ((copies << (lg + 1)) <= most && ((copies << lg) < 2 || ((long long)nwaves << (lg + 1)) <= 4096)) ++lg;
   return lg;
 }
 
@@ -498,7 +474,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
     }
   }
 
-  ctx->exact_parts_log2 = exact_parts_for(ctx->nwaves, ctx->S);
+  ctx->exact_waves_log2 = exact_waves_for(ctx->nwaves, ctx->G / ctx->epw, ctx->S);
   const size_t rows = (size_t)ctx->B_pad * ctx->S;
   struct { void** p; size_t n; } allocs[] = {
       // (the binary problem keeps one more plane: the component of the first walkable cell)
@@ -510,7 +486,6 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
       // through the one pointer it has at hand when it issues its loads)
       {&ctx->d_targets, ((size_t)ctx->B_pad + 1) * kMaxMetrics * sizeof(uint32_t)},
       {&ctx->d_bad, sizeof(unsigned long long)},
-      {&ctx->d_exact, ctx->exact_parts_log2 ? ((size_t)cfg->batch << ctx->exact_parts_log2) * sizeof(int32_t) : 0},
   };
   for (auto& al : allocs) *al.p = nullptr;
   for (auto& al : allocs) {
@@ -608,7 +583,7 @@ int pcgrl_destroy(pcgrl_ctx* ctx) {
   if (!ctx) return PCGRL_OK;
   DeviceGuard guard(ctx->device);  // (freed in any case)
   int rc = guard.ok && hipDeviceSynchronize() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
-  void* bufs[] = {ctx->d_planes, ctx->d_frozen, ctx->d_env, ctx->d_metrics, ctx->d_targets, ctx->d_bad, ctx->d_exact};
+  void* bufs[] = {ctx->d_planes, ctx->d_frozen, ctx->d_env, ctx->d_metrics, ctx->d_targets, ctx->d_bad};
   for (void* b : bufs)
     if (b && hipFree(b) != hipSuccess) rc = PCGRL_E_HIP;
   delete ctx;
@@ -702,24 +677,18 @@ int pcgrl_exact_diameter(pcgrl_ctx* ctx, int32_t* out, void* stream) {
   if (!ctx || !out) return PCGRL_E_NULL;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
-  return exact_diameter_with(ctx, out, static_cast<int32_t*>(ctx->d_exact), ctx->exact_parts_log2,
-                             static_cast<hipStream_t>(stream));
+  return dispatch<LaunchExact>(ctx->S, ctx->cfg.problem, ctx, ctx->base, out, ctx->exact_waves_log2, static_cast<hipStream_t>(stream));
 }
 
 int pcgrl_exact_diameter_static(pcgrl_ctx* ctx, int32_t* out, int32_t parts_log2, void* stream) {
   if (!ctx || !out) return PCGRL_E_NULL;
   if (parts_log2 < -1 || (parts_log2 >= 0 && (1 << parts_log2) > ctx->S)) return PCGRL_E_CONFIG;
-  const int lg = parts_log2 < 0 ? ctx->exact_parts_log2 : parts_log2;
-  const size_t need = lg ? ((size_t)ctx->cfg.batch << lg) : 0;  // ints of partial results
-  if (need > kStaticScratchInts) return PCGRL_E_SCRATCH;
+  const int lg = parts_log2 < 0 ? ctx->exact_waves_log2 : parts_log2;
+  if (parts_log2 > 0 && ((size_t)ctx->cfg.batch << lg) > kStaticMostParts) return PCGRL_E_SCRATCH;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
-  int32_t* partial = nullptr;
-  if (lg) {
-    const int rc = static_scratch(ctx->device, &partial);
-    if (rc != PCGRL_OK) return rc;
-  }
-  return exact_diameter_with(ctx, out, partial, lg, static_cast<hipStream_t>(stream));
+  return dispatch<LaunchExact>(ctx->S, ctx->cfg.problem, ctx, ctx->base, out, lg < kMostExactWavesLog2 ? lg : kMostExactWavesLog2,
+                               static_cast<hipStream_t>(stream));
 }
 
 int pcgrl_observe(pcgrl_ctx* ctx, uint8_t* obs, void* stream) {

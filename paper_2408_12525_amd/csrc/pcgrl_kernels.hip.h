@@ -1153,47 +1153,197 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
     observe<S, PROBLEM>(a, L, wm, obs_plan(a, L.lane, wm.sl, a.obs, wm.env0, wm.nvalid), p, fz, inside, py, px);
 }
 
-// Exact diameter: a sweep from every walkable cell, the largest eccentricity found.  The sources
-// of a level are shared out over 1 << parts_log2 workgroups by their row (row y goes to part
-// y mod parts); each writes the largest eccentricity among its sources to out[part][env], and
-// max_over_parts_kernel folds the parts (with one part, out is the result itself).  Cells are
-// taken in row-major order, each group at its own pace; the loop ends when no group has a cell
-// left (every sweep ends because its visited set can only grow).
+// The cells within r edges of a seed (r the same in every lane of a group), and in `ring` those
+// exactly r edges away.
+template <int S>
+__device__ __forceinline__ typename RowWord<S>::T ball(const Lanes<S>& L, typename RowWord<S>::T seed, typename RowWord<S>::T pass,
+                                                       int r, typename RowWord<S>::T& ring) {
+  using W = typename RowWord<S>::T;
+  W V = seed, inner = 0;
+  for (int i = 0; wave_any<S>(i < r && seed != 0); ++i) {
+    const W grown = L.grow(V, pass);
+    inner = i < r ? V : inner;
+    V = i < r ? grown : V;
+  }
+  ring = V & ~inner;
+  return V;
+}
+
+// A cell of a set near the middle of its rows, and of the columns of that row.
+template <int S>
+__device__ __forceinline__ typename RowWord<S>::T middle_cell(const Lanes<S>& L, typename RowWord<S>::T set) {
+  using W = typename RowWord<S>::T;
+  // the highest set bit at or below the middle between the lowest and the highest one
+  auto middle = [](uint64_t v) { return 63 - __builtin_clzll(v & (~0ull >> (63 - (__builtin_ctzll(v) + 63 - __builtin_clzll(v)) / 2))); };
+  const uint64_t rows = L.gbits(__builtin_amdgcn_ballot_w64(set != 0));
+  if (rows == 0 || L.y != middle(rows)) return 0;
+  return (W)1 << middle((uint64_t)set);
+}
+
+// The side n of the largest square that no shortest path of more than `best` edges fits into.  Such a
+// path never fills a 2 x 2 square, so that an n x n square holds at most 3 n^2 / 4 of its cells for
+// even n, and for odd n as many as the square of side n - 1 and the 2 n - 1 cells around it.
+__device__ __forceinline__ int square_below(int best) {
+  constexpr int kEdges[] = {2, 7, 11, 20, 26, 39, 47, 64, 74, 95, 107, 132, 146, 175, 191};  // n = 2, 3, ... 16
+  int n = 1;
+#pragma unroll
+  for (int i = 0; i < 15; ++i) n += best >= kEdges[i] ? 1 : 0;
+  return n;
+}
+
+// The cells of `todo`, a union of whole components, whose components fit into a square of side n
+// (n > 1) of the grid moved by (my, mx): those that a flood from the cells next to a grid line which
+// their component crosses does not reach.
+template <int S>
+__device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>& L, typename RowWord<S>::T todo, int n, int my, int mx) {
+  using W = typename RowWord<S>::T;
+  uint64_t lines = 0;
+  for (int x = 0; x < S; x += n) lines |= 1ull << x;
+  W down = todo & L.from_above(todo);  // (not inside a condition: a lane shift reads active lanes only)
+  if (((lines << my) >> L.y & 1) == 0) down = 0;
+  const W across = todo & (W)(todo << 1) & (W)(lines << mx);
+  W last, reached;
+  sweep<S>(L, down | across, todo, last, reached);
+  return todo & ~reached;
+}
+
+// Exact diameter: the longest shortest path between two cells of a level.  Components are taken one
+// after the other, and of a component's cells only those that a longer path than the best so far
+// could start from are swept:
+//  * a sweep from any cell (eccentricity e) finishes a component with 2 e <= best;
+//  * otherwise two sweeps find the two ends of a long path and a third one starts from its middle c:
+//    two cells further apart than `best` are not both within best / 2 of c, so that only the cells
+//    outside that ball are left, a few at the rim;
+//  * a sweep from a cell v of eccentricity e(v) rules out every cell u with d(u, v) + e(v) <= best.
+// The first component a wavefront takes is the one in which a flood from a row arrives last, most
+// often a large one; with `best` that large nearly all others end after their first sweep, or, being
+// small, before it (inside_squares).
+// A workgroup is 1 << waves_log2 wavefronts on the same levels, each with a part of their rows (as has
+// each copy of a level inside a wavefront), which take components from their own rows first and then
+// from all.  What is left to do, and the best so far, they share through LDS: a component belongs to
+// the part that takes its first cell out of the shared set.  Lane groups work at their own pace (a
+// group that has nothing to do in a sweep has no seed); every loop ends because each turn takes cells
+// out of a finite set.
+// Bound by the latency of one flood layer after the other, some 1400 of them for a random 64x64 level
+// of 50 % walls: a sweep from each of its 2000 open cells instead took 1268 us for 1024 levels
+// (a launch of 4096 wavefronts and one that folded their results); this takes 84.
 template <int S, int PROBLEM>
-__global__ __launch_bounds__(64) void exact_diameter_kernel(KArgs a, int32_t* out, int parts_log2) {
+__global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* out, int waves_log2) {
   using W = typename RowWord<S>::T;
   using PR = Prob<PROBLEM>;
-  extern __shared__ __align__(16) uint32_t lds_all[];
+  constexpr int kWords = sizeof(W) / 4;
+  __shared__ uint32_t left[kWords][64];  // [slot * S + y]: the cells of the components nobody has taken yet
+  __shared__ int shared_best[64 / S];
   Lanes<S> L;
   WaveMap<S> wm;
-  const int part = (int)blockIdx.x & ((1 << parts_log2) - 1);
-  wm.init(a, L, lds_all, (int)blockIdx.x >> parts_log2, a.envs_per_wave_log2 & 0xff);
+  wm.init(a, L, nullptr, (int)blockIdx.x, a.envs_per_wave_log2 & 0xff);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int part = (wave << wm.sl.copies_log2) + wm.sl.copy, parts_log2 = waves_log2 + wm.sl.copies_log2;
   const W* planes = reinterpret_cast<const W*>(a.planes);
   const size_t ridx = (size_t)wm.envl * S + L.y;
   W p[PR::P];
 #pragma unroll
   for (int i = 0; i < PR::P; ++i) p[i] = planes[(size_t)i * a.plane_stride + ridx];
-  const EnvRec er = a.env[wm.envl];
-  const W inside = wm.valid ? inside_row<W>(L.y, er.h, er.w) : (W)0;
+  const uint32_t hw = *reinterpret_cast<const uint32_t*>(a.env + wm.envl);
+  const int h = (int)(hw & 0xffu), w = (int)((hw >> 8) & 0xffu);
+  const W inside = wm.valid ? inside_row<W>(L.y, h, w) : (W)0;
   const W pass = inside & ~channel_row<PROBLEM, W>(p, inside, 1);
-  W todo = (L.y & ((1 << parts_log2) - 1)) == part ? pass : (W)0;
-  int best = 0;
-  for (;;) {
-    const W src = first_cell<S>(L, todo);
-    if (!wave_any<S>(src != 0)) break;
-    todo &= ~src;
-    best = max(best, eccentricity<S>(L, src, pass));
+  // (a cell on its own is the end of no path)
+  W todo = pass & ((W)(pass << 1) | (W)(pass >> 1) | L.from_above(pass) | L.from_below(pass));
+  const int row = wm.sl.slot * S + L.y;
+  if (wave == 0 && wm.sl.copy == 0) {
+    left[0][row] = (uint32_t)todo;
+    if constexpr (kWords == 2) left[1][row] = (uint32_t)((uint64_t)todo >> 32);
+    if (L.y == 0) shared_best[wm.sl.slot] = 0;
   }
-  if (wm.primary && L.y == 0) out[(size_t)part * (size_t)a.B + wm.env] = best;
-}
-
-// out[env] = max over parts of partial[part][env]
-__global__ void max_over_parts_kernel(const int32_t* partial, int32_t* out, int B, int parts) {
-  const int env = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (env >= B) return;
-  int best = 0;
-  for (int q = 0; q < parts; ++q) best = max(best, partial[(size_t)q * B + env]);
-  out[env] = best;
+  __syncthreads();
+  auto take = [&](W cells) -> W {  // out of the shared set; returns what it held of them
+    W had = (W)atomicAnd(&left[0][row], ~(uint32_t)cells);
+    if constexpr (kWords == 2) had |= (W)atomicAnd(&left[1][row], ~(uint32_t)((uint64_t)cells >> 32)) << 32;
+    return had & cells;
+  };
+  auto look = [&]() -> W {
+    W v = (W)__hip_atomic_load(&left[0][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if constexpr (kWords == 2)
+      v |= (W)__hip_atomic_load(&left[1][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) << 32;
+    return v;
+  };
+  const int row_lo = part * h >> parts_log2, row_mid = (2 * part + 1) * h >> (parts_log2 + 1);
+  int best = 0, side = 1;
+  W none, comp;
+  W src;
+  {
+    W cross = L.y == row_mid ? todo : (W)0;
+    if (parts_log2 == 0) cross |= todo & ((W)1 << (w / 2));
+    sweep<S>(L, cross, todo, src, comp);
+    src = first_cell<S>(L, src);
+  }
+  for (bool first = true;; first = false) {
+    todo = look();
+    best = max(best, __hip_atomic_load(&shared_best[wm.sl.slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (!first) {
+      const int n = square_below(best);
+      if (wave_any<S>(n > side)) {  // (once, and again should `best` grow by much later on)
+        for (int turn = 0; turn < max(4 >> parts_log2, 1); ++turn) {  // (four grids at least)
+          const int t = part + (turn << parts_log2);
+          const int half = n >> 1, quarter = (t >> 2) & 1 ? n >> 2 : 0;
+          const W small = inside_squares<S>(L, n > side ? todo : (W)0, max(n, 2), ((t & 1) ? half : 0) + quarter,
+                                            (((t ^ (t >> 1)) & 1) ? half : 0) + quarter);
+          take(small);
+          todo &= ~small;
+        }
+        side = max(side, n);
+      }
+    }
+    if (!first || !L.gany(src != 0)) {
+      const W mine = first_cell<S>(L, L.y >= row_lo ? todo : (W)0), any = first_cell<S>(L, todo);
+      src = L.gany(mine != 0) ? mine : any;
+    }
+    if (!wave_any<S>(src != 0)) break;
+    W far;
+    const int e1 = sweep<S>(L, src, pass, far, comp);
+    // (the first cell decides, before the others go: a part that looks while they do sees a piece of
+    // the component, which it may take for a small one but no longer for its own)
+    const bool ours = L.gany(take(first_cell<S>(L, comp)) != 0);
+    take(comp);
+    best = max(best, e1);
+    bool open = ours && 2 * e1 > best;
+    if (wave_any<S>(open)) {
+      W end_a = first_cell<S>(L, far);
+      if (!open) end_a = 0;
+      const int e2 = sweep<S>(L, end_a, pass, far, none);
+      best = max(best, e2);
+      open = open && 2 * e1 > best;
+      if (wave_any<S>(open)) {
+        W ring_a, ring_b;
+        W end_b = first_cell<S>(L, far);
+        if (!open) end_a = end_b = 0;
+        ball<S>(L, end_a, pass, e2 >> 1, ring_a);
+        ball<S>(L, end_b, pass, e2 - (e2 >> 1), ring_b);
+        const W centre = middle_cell<S>(L, ring_a & ring_b);
+        const int ec = sweep<S>(L, centre, pass, far, none);
+        best = max(best, ec);
+        open = open && 2 * ec > best;
+        const W core = open ? centre : (W)0;
+        const W near = ball<S>(L, core, pass, best >> 1, none);
+        W rim = open ? comp & ~near : (W)0;
+        for (;;) {
+          const W v = first_cell<S>(L, rim);
+          if (!wave_any<S>(v != 0)) break;
+          rim &= ~v;
+          const int e = sweep<S>(L, v, pass, far, none);
+          const bool longer = e > best;
+          best = max(best, e);
+          // (a new best widens the ball around the centre; otherwise v's own ball goes)
+          rim &= ~ball<S>(L, longer ? core : v, pass, longer ? best >> 1 : best - e, none);
+        }
+      }
+      if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], best);
+    }
+  }
+  if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], best);
+  __syncthreads();
+  if (wave == 0 && wm.primary && L.y == 0) out[wm.env] = shared_best[wm.sl.slot];
 }
 
 // The observation wavefront of the split kernel: loads the level, applies the edit in registers

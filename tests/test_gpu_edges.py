@@ -69,3 +69,33 @@ def test_plain_levels_in_and_out(problem, B, h, w, with_frozen):
         cpu.step(acts[t], want_obs=False)
     assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "after edits")
     gpu.close()
+
+
+@pytest.mark.parametrize("h,w", [(16, 16), (13, 7), (32, 32), (5, 32), (64, 64), (64, 33)])
+def test_exact_diameter_prunes_no_longest_path(h, w):
+    """The exact diameter on maps of every density (one huge component to none), rooms, corridors
+    and rings, for one and several parts per level."""
+    rng = np.random.default_rng(h * 100 + w)
+    maps = [(rng.random((h, w)) < d).astype(np.int8) for d in (0, .05, .2, .3, .35, .4, .42, .45, .5, .5, .6, .8, 1)]
+    y, x = np.mgrid[:h, :w]
+    maps += [((y % 2 == 1) & (x != np.where(y % 4 == 1, w - 1, 0))).astype(np.int8),         # a serpentine
+             (np.minimum(np.minimum(y, h - 1 - y), np.minimum(x, w - 1 - x)) % 2).astype(np.int8),  # nested rings
+             ((y % 4 == 0) & (x % 7 != 3)).astype(np.int8),                                  # rooms with doors
+             ((x % 2 == 1) & (y > 0)).astype(np.int8),                                       # a comb
+             ((y + x) % 2).astype(np.int8)]                                                  # single cells
+    maps += [(rng.random((h, w)) < .5).astype(np.int8) for _ in range(400)]
+    tiles = np.stack(maps)
+    B = len(tiles)
+    hw = np.full((B, 2), (h, w), np.int16)
+    cfg = wl.make_config(wl.BINARY, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0)
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    gpu.pcgrl_reset(1)
+    cpu.reset(1)
+    gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, torch.from_numpy(hw).to(DEV), torch.zeros_like(torch.from_numpy(hw)).to(DEV))
+    cpu.set_state(tiles, None, hw, np.zeros_like(hw))
+    want = cpu.exact_diameters()
+    assert_same("exact diameters", gpu.pcgrl_exact_diameter(), want, (h, w))
+    for parts_log2 in (0, 1, 4):
+        got = gpu.pcgrl_exact_diameter_static(torch.empty(B, dtype=torch.int32, device=DEV), parts_log2)
+        assert_same("exact diameters", got, want, (h, w, parts_log2))
+    gpu.close()
