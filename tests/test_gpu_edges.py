@@ -99,3 +99,24 @@ def test_exact_diameter_prunes_no_longest_path(h, w):
         got = gpu.pcgrl_exact_diameter_static(torch.empty(B, dtype=torch.int32, device=DEV), parts_log2)
         assert_same("exact diameters", got, want, (h, w, parts_log2))
     gpu.close()
+
+
+@pytest.mark.parametrize("problem", [wl.BINARY, wl.MAZE, wl.DUNGEON])
+@pytest.mark.parametrize("B,h,w", [(5, 1, 1), (37, 16, 15), (9, 3, 31), (33, 32, 32), (7, 5, 33), (6, 64, 63), (5, 64, 64)])
+def test_drawn_levels(problem, B, h, w):
+    """First levels of pcgrl_reset where the 32 columns that are drawn together end at different
+    places, with tiles that never or always come up (equal, lowest and highest thresholds)."""
+    K = wl.NUM_TILES[problem]
+    rng = np.random.default_rng(B + w)
+    odds = [[1 / K] * K, [1.] + [0.] * (K - 1), [0.] * (K - 1) + [1.]]
+    some = rng.random(K) * (rng.random(K) < .6)
+    some[rng.integers(K)] += .1
+    odds.append(list(some / some.sum()))
+    for probs in odds:
+        cfg = wl.make_config(problem, B, h, 5, max_w=w, min_size=1, min_w=1, probs=probs)
+        gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+        gpu.pcgrl_reset(11)
+        cpu.reset(11)
+        compare_state(gpu, cpu, f"after reset, {probs}")
+        assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"after reset, {probs}")
+        gpu.close()
