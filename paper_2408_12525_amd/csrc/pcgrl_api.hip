@@ -787,14 +787,23 @@ int pcgrl_unpack_obs(const pcgrl_ctx* ctx, const uint8_t* packed, void* out, int
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
   const int32_t cells = ctx->C * ctx->cfg.obs_w * ctx->cfg.obs_w;
-  const dim3 grid((unsigned)ctx->cfg.batch), block(64);
+  // Four wavefronts a level from 32 KiB of output on, where one spends long on a level.  Measured, us
+  // for 1 / 2 / 4: 1024 levels of 36 kB 9.2 / 7.2 / 7.0, of 71 kB 15.7 / 11.6 / 11.3; 8192 of 4.8 kB
+  // 8.1 / 8.1 / 9.0; 65 536 of 75 bytes 26 / 39 / 64.
+  const dim3 grid((unsigned)ctx->cfg.batch), block(cells * es >= 32768 ? 256 : 64);
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* o = static_cast<uint8_t*>(out);
   const int64_t stride = (int64_t)ctx->obs_stride;
-  if (out_type == PCGRL_UNPACK_U8) hipLaunchKernelGGL(unpack_obs_kernel<1>, grid, block, 0, st, packed, stride, o, cells, 1u);
-  else if (out_type == PCGRL_UNPACK_F16) hipLaunchKernelGGL(unpack_obs_kernel<2>, grid, block, 0, st, packed, stride, o, cells, 0x3C00u);
-  else if (out_type == PCGRL_UNPACK_BF16) hipLaunchKernelGGL(unpack_obs_kernel<2>, grid, block, 0, st, packed, stride, o, cells, 0x3F80u);
-  else hipLaunchKernelGGL(unpack_obs_kernel<4>, grid, block, 0, st, packed, stride, o, cells, 0x3F800000u);
+  // Rows of less than 64 bytes are read where they lie: the way through LDS costs a level more than its
+  // few loads there (65 536 rows of 10 bytes 17 us without LDS, 25 with it; 16 384 of 85 bytes 6.7
+  // and 6.6; 4096 of 2209 bytes 18 and 13).
+  const bool staged = cells >= 64 * 8;
+  auto launch = [&](auto plain, auto through_lds, uint32_t one) {
+    hipLaunchKernelGGL(staged ? through_lds : plain, grid, block, 0, st, packed, stride, o, cells, one);
+  };
+  if (es == 1) launch(unpack_obs_kernel<1, false>, unpack_obs_kernel<1, true>, 1u);
+  else if (es == 2) launch(unpack_obs_kernel<2, false>, unpack_obs_kernel<2, true>, out_type == PCGRL_UNPACK_F16 ? 0x3C00u : 0x3F80u);
+  else launch(unpack_obs_kernel<4, false>, unpack_obs_kernel<4, true>, 0x3F800000u);
   return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
 }
 

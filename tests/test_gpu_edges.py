@@ -120,3 +120,26 @@ def test_drawn_levels(problem, B, h, w):
         compare_state(gpu, cpu, f"after reset, {probs}")
         assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"after reset, {probs}")
         gpu.close()
+
+
+@pytest.mark.parametrize("problem,size,obs_w,frozen", [
+    (wl.BINARY, 16, 1, 0), (wl.BINARY, 16, 6, 0), (wl.BINARY, 16, 13, 0), (wl.DUNGEON, 16, 8, 0), (wl.MAZE, 16, 5, 0), (wl.DUNGEON, 16, 4, 0), (wl.DUNGEON, 16, 63, 3)])
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.bfloat16, torch.float32])
+def test_unpack_row_lengths(problem, size, obs_w, frozen, dtype):
+    """pcgrl_unpack_obs on packed rows of less than 16 bytes, of about 16, and of the most there can
+    be, at an odd address, into an array that starts off a 16-byte boundary; guards stay as they are."""
+    B = 11
+    cfg = wl.make_config(problem, B, size, obs_w, obs_format=1, n_frozen=frozen, obs_frozen_channel=1 if frozen else 0)
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    obs = gpu.new_obs()
+    gpu.pcgrl_reset(5, obs)
+    want = torch.from_numpy(cpu.reset(5)).to(dtype)
+    for by in (0, 1, 7):
+        src = torch.full((obs.numel() + 32,), 0xff, dtype=torch.uint8, device=DEV)
+        src[by:by + obs.numel()] = obs.reshape(-1)
+        buf = torch.full((want.numel() + 32,), 7, dtype=dtype, device=DEV)
+        out = buf[by:by + want.numel()].view(want.shape)
+        gpu.pcgrl_unpack_obs(src[by:by + obs.numel()].view(obs.shape), out=out)
+        assert torch.equal(out.cpu(), want), by
+        assert bool((buf[:by] == 7).all()) and bool((buf[by + want.numel():] == 7).all()), by
+    gpu.close()
