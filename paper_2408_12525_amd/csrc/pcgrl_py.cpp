@@ -6,8 +6,9 @@
 // kernel of 4.5 us for 64 levels of 16x16.
 //
 // Only what is plainly right is handled here.  Anything else -- a wrong type, shape, device or
-// layout, an argument that is missing -- makes the call return kLook, and the Python method then
-// goes through the arguments one by one and says what is wrong.
+// layout, an argument that is missing, a tensor that torch itself refuses to look into (one without
+// storage, say) -- makes the call return kLook, and the Python method then goes through the arguments
+// one by one and says what is wrong.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -223,12 +224,28 @@ PyObject* env_new(PyTypeObject* type, PyObject* args, PyObject*) {
   return reinterpret_cast<PyObject*>(e);
 }
 
-#define PCGRL_FAST(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+// The tensor accessors and the stream lookup throw, and no C++ exception may reach the interpreter's
+// frames: the process would end.  The Python checks make the same accesses and raise what torch says.
+// (Nothing throws while the interpreter lock is released: the library's C entry points do not.)
+template <auto F, typename... A> PyObject* guarded(PyObject* self, A... args) noexcept {
+  try {
+    return F(self, args...);
+  } catch (...) {
+    PyErr_Clear();  // (a tensor type written in Python leaves its exception behind)
+    return look();
+  }
+}
+
+template <auto F> PyCFunction one() { return guarded<F, PyObject*>; }
+template <auto F> PyCFunction fast() {
+  return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&guarded<F, PyObject* const*, Py_ssize_t>));
+}
 PyMethodDef env_methods[] = {
-    PCGRL_FAST("step", env_step), PCGRL_FAST("rollout", env_rollout), PCGRL_FAST("reset", env_reset),
-    PCGRL_FAST("unpack_obs", env_unpack_obs), PCGRL_FAST("set_state", env_set_state),
-    {"metrics", env_metrics, METH_O, nullptr}, {"exact_diameter", env_exact_diameter, METH_O, nullptr},
-    {"observe", env_observe, METH_O, nullptr}, {"get_state", env_get_state, METH_NOARGS, nullptr},
+    {"step", fast<env_step>(), METH_FASTCALL, nullptr}, {"rollout", fast<env_rollout>(), METH_FASTCALL, nullptr},
+    {"reset", fast<env_reset>(), METH_FASTCALL, nullptr}, {"unpack_obs", fast<env_unpack_obs>(), METH_FASTCALL, nullptr},
+    {"set_state", fast<env_set_state>(), METH_FASTCALL, nullptr},
+    {"metrics", one<env_metrics>(), METH_O, nullptr}, {"exact_diameter", one<env_exact_diameter>(), METH_O, nullptr},
+    {"observe", one<env_observe>(), METH_O, nullptr}, {"get_state", env_get_state, METH_NOARGS, nullptr},
     {"close", env_close, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr},
 };
 

@@ -98,3 +98,39 @@ def test_compiled_call_path_leaves_doubtful_arguments_to_the_python_checks():
     assert set(calls(env)) == {py.LOOK}
     env.close()
     assert set(calls(env) + [env.get_state(), env.reset(1, None)]) == {py.LOOK}
+
+
+WRAPPED = """
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2408_12525_amd import binding
+py = binding._load_py()
+env = py.Env(1, 0, 4, 16, 16, (3, 2, 31, 31), (3, 2, 31, 31))   # (the handle is never followed)
+shapes = dict(env=((3,), torch.int32), two=((5, 3), torch.int32), obs=((3, 2, 31, 31), torch.uint8), met=((3, 4), torch.int32),
+              grid=((3, 16, 16), torch.int8), pair=((3, 2), torch.int16))
+asked = []
+def inside(env_, two, obs, met, grid, pair):
+    try:
+        env_.data_ptr()
+        raise SystemExit("the wrapped tensor has storage after all")
+    except RuntimeError:
+        pass
+    asked.extend([env.step(env_, None, None, None), env.rollout(two, None, None, None), env.reset(1, obs), env.metrics(met),
+                  env.exact_diameter(env_), env.observe(obs), env.unpack_obs(obs, obs), env.set_state(grid, None, pair, pair)])
+    return env_
+with FakeTensorMode():
+    torch.vmap(inside)(*[torch.empty((2,) + s, dtype=d, device="cuda:0") for s, d in shapes.values()])
+assert asked == [py.LOOK] * 8, asked
+print("asked")
+"""
+
+
+def test_compiled_call_path_outlives_tensors_without_storage():
+    """A tensor of the right device, type and shape whose accessors throw inside torch (a batched
+    tensor of torch.vmap without storage) is answered with LOOK by every entry point that takes
+    tensors: the exception ends neither the call nor the process.  In a process of its own, which is
+    what an escaping exception would end."""
+    import subprocess
+    import sys
+    res = subprocess.run([sys.executable, "-c", WRAPPED], cwd=ROOT, capture_output=True, text=True)
+    assert res.returncode == 0 and res.stdout.split() == ["asked"], res.stderr[-2000:]
