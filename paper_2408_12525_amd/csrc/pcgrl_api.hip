@@ -704,10 +704,8 @@ int pcgrl_get_state(pcgrl_ctx* ctx, int8_t* tiles, uint8_t* frozen, int16_t* hw,
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // a thread for every 16 cells (and at least one for every level's scalars)
-  const uint64_t cells = (uint64_t)ctx->cfg.batch * (uint64_t)(ctx->cfg.max_h * ctx->cfg.max_w);
-  const uint64_t threads = (tiles || frozen) && (cells + 15) / 16 > (uint64_t)ctx->cfg.batch ? (cells + 15) / 16 : (uint64_t)ctx->cfg.batch;
-  const dim3 grid((unsigned)((threads + kGetThreads - 1) / kGetThreads));
+  const GetGrid g = get_grid((uint32_t)ctx->cfg.batch, (uint32_t)(ctx->cfg.max_h * ctx->cfg.max_w), tiles || frozen);
+  const dim3 grid(g.x, g.y);
   if (ctx->S == 64)
     hipLaunchKernelGGL(get_state_kernel<uint64_t>, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, ctx->P, tiles, frozen,
                        hw, pos, counters);

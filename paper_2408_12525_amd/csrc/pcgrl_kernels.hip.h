@@ -15,6 +15,8 @@
 
 #include <type_traits>
 
+#include "pcgrl_index.h"
+
 namespace pcgrl {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -2195,20 +2197,15 @@ __global__ __launch_bounds__(64) void set_state_kernel(KArgs a, LevelSource src)
 // (one or two rows for most widths) are put together and widened with a multiply per four cells.
 // Bound by its stores: a thread per row that wrote byte after byte took 49 us for 5001 levels of
 // 27x45 (12 MB), this 7.
-constexpr int kGetThreads = 256;
 template <typename W>
 __global__ __launch_bounds__(kGetThreads) void get_state_kernel(KArgs a, int S, int P, int8_t* tiles, uint8_t* fro, int16_t* hw,
                                                                 int16_t* pos, int32_t* counters) {
   const int cells = a.max_h * a.max_w;
-  const uint64_t total = (uint64_t)a.B * (uint64_t)cells;
   const W* planes = reinterpret_cast<const W*>(a.planes);
-  const uint64_t block0 = (uint64_t)blockIdx.x * (16 * kGetThreads);
-  const uint64_t at = block0 + 16 * threadIdx.x;
-  if (at < total && (tiles || fro)) {
-    const int from = (int)(block0 % (uint32_t)cells) + 16 * (int)threadIdx.x;
-    int env = (int)(block0 / (uint32_t)cells) + from / cells;
-    int y = from % cells / a.max_w, x = from % cells % a.max_w;
-    const int n = (int)min((uint64_t)16, total - at);
+  const GetPiece pc = get_piece(blockIdx.x, blockIdx.y, (int)threadIdx.x, (uint32_t)a.B, cells, a.max_w);
+  if (pc.n > 0 && (tiles || fro)) {
+    const int n = pc.n;
+    int env = pc.env, y = pc.y, x = pc.x;
     uint32_t bits[3] = {0, 0, 0}, in = 0, fz = 0;
     for (int got = 0; got < n;) {
       const int run = min(n - got, a.max_w - x);
@@ -2235,20 +2232,20 @@ __global__ __launch_bounds__(kGetThreads) void get_state_kernel(KArgs a, int S, 
       f[j] = widen(fz & in, j);
     }
     auto store = [&](uint8_t* dst, const uint32_t (&v)[4]) {
-      dst += at;
-      if (n == 16 && ((uintptr_t)dst & 15u) == 0) {
+      dst += pc.at;
+      if (n == kGetBytes && ((uintptr_t)dst & 15u) == 0) {
         *reinterpret_cast<uint4*>(dst) = make_uint4(v[0], v[1], v[2], v[3]);
       } else {
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
+        for (int j = 0; j < kGetBytes; ++j)
           if (j < n) dst[j] = (uint8_t)(v[j >> 2] >> (8 * (j & 3)));
       }
     };
     if (tiles) store(reinterpret_cast<uint8_t*>(tiles), t);
     if (fro) store(fro, f);
   }
-  const int e = (int)(blockIdx.x * kGetThreads + threadIdx.x);
-  if (e < a.B && (hw || pos || counters)) {
+  const uint64_t e = get_level(blockIdx.x, blockIdx.y, (int)threadIdx.x);
+  if (e < (uint64_t)a.B && (hw || pos || counters)) {
     const EnvRec er = a.env[e];
     if (hw) {
       hw[2 * (size_t)e] = er.h;

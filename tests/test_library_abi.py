@@ -134,3 +134,54 @@ def test_compiled_call_path_outlives_tensors_without_storage():
     import sys
     res = subprocess.run([sys.executable, "-c", WRAPPED], cwd=ROOT, capture_output=True, text=True)
     assert res.returncode == 0 and res.stdout.split() == ["asked"], res.stderr[-2000:]
+
+
+INDEX = """
+#include "pcgrl_index.h"
+extern "C" void grid(uint32_t batch, uint32_t cells, int with_cells, uint32_t* out) {
+  const pcgrl::GetGrid g = pcgrl::get_grid(batch, cells, with_cells != 0);
+  out[0] = g.x; out[1] = g.y;
+}
+extern "C" void piece(uint32_t bx, uint32_t by, int thread, uint32_t batch, int cells, int max_w, int64_t* out) {
+  const pcgrl::GetPiece p = pcgrl::get_piece(bx, by, thread, batch, cells, max_w);
+  out[0] = (int64_t)p.at; out[1] = p.n; out[2] = p.env; out[3] = p.y; out[4] = p.x;
+  out[5] = (int64_t)pcgrl::get_level(bx, by, thread);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def index(tmp_path_factory):
+    import subprocess
+    d = tmp_path_factory.mktemp("index")
+    (d / "index.cpp").write_text(INDEX)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2408_12525_amd", "csrc"),
+                    str(d / "index.cpp"), "-o", str(d / "index.so")], check=True)
+    lib = C.CDLL(str(d / "index.so"))
+    u32, p64 = C.c_uint32, C.POINTER(C.c_int64 * 6)
+    lib.grid.argtypes, lib.grid.restype = [u32, u32, C.c_int, C.POINTER(u32 * 2)], None
+    lib.piece.argtypes, lib.piece.restype = [u32, u32, C.c_int, u32, C.c_int, C.c_int, p64], None
+    return lib
+
+
+@pytest.mark.parametrize("batch,h,w", [(1, 1, 1), (300, 1, 1), (5, 3, 7), (1, 64, 64), (37, 27, 45), (2051, 2, 64), (8388608, 64, 64), (8388609, 64, 64),
+                                       (8388613, 63, 61), (1 << 24, 64, 64), ((1 << 24) - 1, 64, 63), (1 << 24, 16, 16), (1 << 24, 1, 1)])
+def test_get_state_indices_at_every_batch(index, batch, h, w):
+    """What the threads of the plain-layout kernel address, from one cell to the largest batch there
+    can be: a launch below 2^32 threads either way, workgroups numbered without a gap, every piece
+    inside the arrays and where it belongs, and every level's scalars written by the one thread of
+    that number (from 2^31 threads on the numbers are no 32-bit integers any more)."""
+    cells, total = h * w, batch * h * w
+    g, out = (C.c_uint32 * 2)(), (C.c_int64 * 6)()
+    for with_cells in (1, 0):
+        index.grid(batch, cells, with_cells, C.byref(g))
+        gx, gy = g
+        want = -(-max(-(-total // 16) if with_cells else 0, batch) // 256)
+        assert gx * 256 < 1 << 31 and 1 <= gy < 1 << 16 and gx * gy >= want > gx * (gy - 1)
+        for b in sorted({b for b in (0, 1, want // 3, batch // 256, 1 << 22, (1 << 23) - 1, 1 << 23, want - 1, gx * gy - 1) if b < gx * gy}):
+            for t in range(256):
+                index.piece(b % gx, b // gx, t, batch, cells, w, C.byref(out))
+                at, n, env, y, x, level = out
+                assert level == b * 256 + t and at == 16 * level and n == max(0, min(16, total - at))
+                if n:
+                    assert (env, y, x) == (at // cells, at % cells // w, at % cells % w) and env < batch
