@@ -1317,6 +1317,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   }
   for (bool first = true;; first = false) {
     todo = look();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");  // (with the release below)
     best = max(best, __hip_atomic_load(&shared_best[wm.sl.slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
     if (!first) {
       const int n = square_below(best);
@@ -1340,8 +1341,11 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     W far;
     const int e1 = sweep<S>(L, src, pass, far, comp);
     // (the first cell decides, before the others go: a part that looks while they do sees a piece of
-    // the component, which it may take for a small one but no longer for its own)
+    // the component, which it may take for a small one but no longer for its own.  The words of a row
+    // and the rows are atomics of their own, hence the fence: were the others seen to go first, a piece
+    // that still holds the first cell could be dropped as a small component and belong to nobody)
     const bool ours = L.gany(take(first_cell<S>(L, comp)) != 0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     take(comp);
     best = max(best, e1);
     bool open = ours && 2 * e1 > best;

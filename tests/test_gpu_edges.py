@@ -101,6 +101,37 @@ def test_exact_diameter_prunes_no_longest_path(h, w):
     gpu.close()
 
 
+@pytest.mark.parametrize("parts_log2", [0, 1, 2, 3, 4])
+def test_exact_diameter_components_in_both_words_of_a_row(parts_log2):
+    """64-column levels of hooks and zigzags whose first cell lies in the upper half of its row and
+    the others in the lower half (two words of the set that the wavefronts of a workgroup take
+    components from), some of them small enough to be dropped unswept once a longer one is known."""
+    rng = np.random.default_rng(parts_log2)
+    B, n = 300, 64
+    tiles = np.ones((B, n, n), np.int8)
+    for b in range(B):
+        y = 0
+        while y < n - 1:
+            rows = int(rng.integers(2, min(6, n - y + 1)))
+            for k in range(rows):
+                lo, hi = ((32, 33 + rng.integers(0, 20)) if k == 0 else (33 - rng.integers(1, 30), 33))
+                tiles[b, y + k, int(lo):int(hi)] = 0
+            tiles[b, y:y + rows, 32] = 0
+            y += rows + 1
+    hw = np.full((B, 2), n, np.int16)
+    cfg = wl.make_config(wl.BINARY, B, n, 5, min_size=1, autoreset=0)
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    gpu.pcgrl_reset(1)
+    cpu.reset(1)
+    gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, torch.from_numpy(hw).to(DEV), torch.zeros((B, 2), dtype=torch.int16, device=DEV))
+    cpu.set_state(tiles, None, hw, np.zeros_like(hw))
+    want = cpu.exact_diameters()
+    for _ in range(5):
+        got = gpu.pcgrl_exact_diameter_static(torch.empty(B, dtype=torch.int32, device=DEV), parts_log2)
+        assert_same("exact diameters", got, want, parts_log2)
+    gpu.close()
+
+
 @pytest.mark.parametrize("problem", [wl.BINARY, wl.MAZE, wl.DUNGEON])
 @pytest.mark.parametrize("B,h,w", [(5, 1, 1), (37, 16, 15), (9, 3, 31), (33, 32, 32), (7, 5, 33), (6, 64, 63), (5, 64, 64)])
 def test_drawn_levels(problem, B, h, w):
