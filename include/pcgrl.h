@@ -218,8 +218,10 @@ int pcgrl_metrics(pcgrl_ctx* ctx, int32_t* out, void* stream);
  * walkable cells (the graph diameter that the two-sweep estimate of Task / Binary domain stands
  * for).  A diagnostic for the error of the two-sweep estimate, not part of a step.  Breadth-first
  * sweeps, from those cells only that an upper bound on their distances does not rule out; the
- * components of a level are shared out over the wavefronts of a workgroup.  out: device, int32
- * [batch]. */
+ * components of a level, and what cells such bounds leave of them, are shared out over the wavefronts
+ * of a workgroup.  The cost is that of a few sweeps for most levels (a thousand random 64x64 levels
+ * 0.08 ms); on a loop, where nothing is ruled out, half of its cells are swept (one to 256 64x64 levels
+ * with a loop of 2080 cells 7 ms).  out: device, int32 [batch]. */
 int pcgrl_exact_diameter(pcgrl_ctx* ctx, int32_t* out, void* stream);
 
 /* pcgrl_exact_diameter with the number of wavefronts chosen by the caller.  Neither call allocates

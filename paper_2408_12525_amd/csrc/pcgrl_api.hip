@@ -228,16 +228,21 @@ int levels_per_wave_for(int G, int batch, int min_groups) {
   return n;
 }
 
-// How many wavefronts (1 << the result) of pcgrl_exact_diameter share a level's components out among
-// them.  Two parts a level always (a copy of the level in a spare lane group is a part as well), more
-// while that takes no more than 4096 wavefronts, up to S / 4 parts and eight.  Measured, us for 1, 2,
-// 4, 8, 16 wavefronts a workgroup: 4096 64x64 levels 280 / 223 / 243 / 308 / 501, 1024 of them 147 /
-// 93 / 88 / 88 / 140, 256 143 / 73 / 45 / 41 / 53; 16 384 32x32 levels 199 / 178 / 203 / 276 / 442,
-// 1024 (two copies each) 39 / 27 / 27 / 35 / 54; 16 384 16x16 levels 62 / 53 / 62 / 82 / 126, 1024 (four
-// copies each) 16 / 21 / 21 / 23 / 28.
+// How many wavefronts (1 << the result) of pcgrl_exact_diameter share a level's work out among them.
+// Two parts a level always (a copy of the level in a spare lane group is a part as well), more while
+// that takes no more than 4096 wavefronts, up to 8 parts of a 64-row level, 16 or 8 of a 32-row one and
+// 16 or 4 of a 16-row one, the larger number where there is no more than about a workgroup for every
+// other compute unit (32 rows) or two for each (16).  Measured on random levels, us for 1, 2, 4, 8, 16
+// wavefronts a workgroup: 4096 64x64 levels 257 / 222 / 236 / 301 / 495, 1024 of them 147 / 86 / 80 /
+// 88 / 137, 256 147 / 76 / 42 / 38 / 48, 64 119 / 80 / 41 / 34 / 44; 16 384 32x32 levels 194 / 178 /
+// 204 / 281 / 448, 1024 (two copies each) 39 / 25 / 29 / 37 / 54, 128 35 / 22 / 18 / 18 / 21; 16 384
+// 16x16 levels 58 / 53 / 60 / 80 / 126, 1024 (four copies each) 17 / 17 / 19 / 21 / 29, 512 14 / 14 /
+// 13 / 14 / 16.  Levels of one long loop, whose cost is the sweeps of half of its cells, gain from
+// every part: 16 of 32x32 332 with 8 parts, 238 with 16; 64 of 16x16 59 with 4, 34 with 16; 64x64 37
+// 800 with 1, 6700 with 8, 6200 with 16.
 constexpr int kMostExactWavesLog2 = 4;  // a workgroup of 1024 threads
 int exact_waves_for(int nwaves, int copies, int S) {
-  const int most = S / 4 < 8 ? S / 4 : 8;
+  const int most = S == 64 ? 8 : S == 32 ? (nwaves <= 128 ? 16 : 8) : nwaves <= 512 ? 16 : 4;
   int lg = 0;
   while ((copies << (lg + 1)) <= most && ((copies << lg) < 2 || ((long long)nwaves << (lg + 1)) <= 4096)) ++lg;
   return lg;

@@ -1250,7 +1250,7 @@ __device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>&
 //  * a sweep from any cell (eccentricity e) finishes a component with 2 e <= best;
 //  * otherwise two sweeps find the two ends of a long path and a third one starts from its middle c:
 //    two cells further apart than `best` are not both within best / 2 of c, so that only the cells
-//    outside that ball are left, a few at the rim;
+//    outside that ball are left, the rim: a few on random maps, half of the cells on a long loop;
 //  * a sweep from a cell v of eccentricity e(v) rules out every cell u with d(u, v) + e(v) <= best.
 // The first component a wavefront takes is the one in which a flood from a row arrives last, most
 // often a large one; with `best` that large nearly all others end after their first sweep, or, being
@@ -1258,19 +1258,29 @@ __device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>&
 // A workgroup is 1 << waves_log2 wavefronts on the same levels, each with a part of their rows (as has
 // each copy of a level inside a wavefront), which take components from their own rows first and then
 // from all.  What is left to do, and the best so far, they share through LDS: a component belongs to
-// the part that takes its first cell out of the shared set.  Lane groups work at their own pace (a
-// group that has nothing to do in a sweep has no seed); every loop ends because each turn takes cells
-// out of a finite set.
+// the part that takes its first cell out of the shared set.  Its owner sweeps a few rim cells itself
+// (each rules out many of the others, so that all parts together would sweep in vain), and what is left
+// of all rims is shared out cell by cell once nobody has a component left.  Lane groups work at their
+// own pace (a group that has nothing to do in a sweep has no seed); every loop ends because each turn
+// takes cells out of a finite set.
 // Bound by the latency of one flood layer after the other, some 1400 of them for a random 64x64 level
 // of 50 % walls: a sweep from each of its 2000 open cells instead took 1268 us for 1024 levels
-// (a launch of 4096 wavefronts and one that folded their results); this takes 84.
+// (a launch of 4096 wavefronts and one that folded their results); this takes 80.  A loop of 2080 cells
+// is the worst there is, 1040 sweeps of 1040 layers and bound by instructions: 64 such levels 6.7 ms
+// (37.8 while the owner swept the whole rim, 6.5 from each cell on 4096 wavefronts; one level alone takes
+// as long here, and took 2.0 there), 1024 of them 26.7 ms (38.0, 104).
+// (Of 0, 2, 4, 8 and 16 own rim cells: 1024 levels of rooms 68, 67, 57, 57, 57 us, of a grid of corridors 63,
+// 78, 77, 107, 114.)
+constexpr int kOwnRimCells = 4;
 template <int S, int PROBLEM>
 __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* out, int waves_log2) {
   using W = typename RowWord<S>::T;
   using PR = Prob<PROBLEM>;
   constexpr int kWords = sizeof(W) / 4;
-  __shared__ uint32_t left[kWords][64];  // [slot * S + y]: the cells of the components nobody has taken yet
-  __shared__ int shared_best[64 / S];
+  // sets of cells that the wavefronts share, [slot * S + y]: those of the components nobody has taken
+  // yet, those still to be swept, and the middles of the components these lie in
+  __shared__ uint32_t left[kWords][64], rim[kWords][64], middles[kWords][64];
+  __shared__ int shared_best[64 / S], any_rim;
   Lanes<S> L;
   WaveMap<S> wm;
   wm.init(a, L, nullptr, (int)blockIdx.x, a.envs_per_wave_log2 & 0xff);
@@ -1289,25 +1299,49 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   W todo = pass & ((W)(pass << 1) | (W)(pass >> 1) | L.from_above(pass) | L.from_below(pass));
   const int row = wm.sl.slot * S + L.y;
   if (wave == 0 && wm.sl.copy == 0) {
-    left[0][row] = (uint32_t)todo;
-    if constexpr (kWords == 2) left[1][row] = (uint32_t)((uint64_t)todo >> 32);
-    if (L.y == 0) shared_best[wm.sl.slot] = 0;
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) {
+      left[k][row] = (uint32_t)((uint64_t)todo >> (32 * k));
+      rim[k][row] = middles[k][row] = 0;
+    }
+    if (L.y == 0) shared_best[wm.sl.slot] = any_rim = 0;
   }
   __syncthreads();
-  auto take = [&](W cells) -> W {  // out of the shared set; returns what it held of them
-    W had = (W)atomicAnd(&left[0][row], ~(uint32_t)cells);
-    if constexpr (kWords == 2) had |= (W)atomicAnd(&left[1][row], ~(uint32_t)((uint64_t)cells >> 32)) << 32;
+  using Shared = uint32_t (&)[kWords][64];
+  auto take = [&](Shared set, W cells) -> W {  // out of a shared set; returns what it held of them
+    W had = (W)atomicAnd(&set[0][row], ~(uint32_t)cells);
+    if constexpr (kWords == 2) had |= (W)atomicAnd(&set[1][row], ~(uint32_t)((uint64_t)cells >> 32)) << 32;
     return had & cells;
   };
-  auto look = [&]() -> W {
-    W v = (W)__hip_atomic_load(&left[0][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  auto put = [&](Shared set, W cells) {
+    atomicOr(&set[0][row], (uint32_t)cells);
+    if constexpr (kWords == 2) atomicOr(&set[1][row], (uint32_t)((uint64_t)cells >> 32));
+  };
+  auto look = [&](Shared set) -> W {
+    W v = (W)__hip_atomic_load(&set[0][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if constexpr (kWords == 2)
-      v |= (W)__hip_atomic_load(&left[1][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) << 32;
+      v |= (W)__hip_atomic_load(&set[1][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) << 32;
     return v;
   };
+  auto best_so_far = [&]() {
+    return __hip_atomic_load(&shared_best[wm.sl.slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
   const int row_lo = part * h >> parts_log2, row_mid = (2 * part + 1) * h >> (parts_log2 + 1);
+  auto choose = [&](W set) -> W {  // a cell, from this part's rows on if there is one
+    const W mine = first_cell<S>(L, L.y >= row_lo ? set : (W)0), any = first_cell<S>(L, set);
+    return L.gany(mine != 0) ? mine : any;
+  };
   int best = 0, side = 1;
   W none, comp;
+  // Sweeps a rim cell and returns the cells that no longer path than the best starts from by what it
+  // found: a new best widens the ball around the middle of the component, otherwise v's own ball goes.
+  auto rule_out = [&](W v, W middle) -> W {
+    W far, all;
+    const int e = sweep<S>(L, v, pass, far, all);
+    const bool longer = e > best;
+    best = max(best, e);
+    return ball<S>(L, longer ? middle & all : v, pass, longer ? best >> 1 : best - e, none);
+  };
   W src;
   {
     W cross = L.y == row_mid ? todo : (W)0;
@@ -1316,9 +1350,9 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     src = first_cell<S>(L, src);
   }
   for (bool first = true;; first = false) {
-    todo = look();
+    todo = look(left);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");  // (with the release below)
-    best = max(best, __hip_atomic_load(&shared_best[wm.sl.slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    best = max(best, best_so_far());
     if (!first) {
       const int n = square_below(best);
       if (wave_any<S>(n > side)) {  // (once, and again should `best` grow by much later on)
@@ -1327,16 +1361,13 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
           const int half = n >> 1, quarter = (t >> 2) & 1 ? n >> 2 : 0;
           const W small = inside_squares<S>(L, n > side ? todo : (W)0, max(n, 2), ((t & 1) ? half : 0) + quarter,
                                             (((t ^ (t >> 1)) & 1) ? half : 0) + quarter);
-          take(small);
+          take(left, small);
           todo &= ~small;
         }
         side = max(side, n);
       }
     }
-    if (!first || !L.gany(src != 0)) {
-      const W mine = first_cell<S>(L, L.y >= row_lo ? todo : (W)0), any = first_cell<S>(L, todo);
-      src = L.gany(mine != 0) ? mine : any;
-    }
+    if (!first || !L.gany(src != 0)) src = choose(todo);
     if (!wave_any<S>(src != 0)) break;
     W far;
     const int e1 = sweep<S>(L, src, pass, far, comp);
@@ -1344,9 +1375,9 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     // the component, which it may take for a small one but no longer for its own.  The words of a row
     // and the rows are atomics of their own, hence the fence: were the others seen to go first, a piece
     // that still holds the first cell could be dropped as a small component and belong to nobody)
-    const bool ours = L.gany(take(first_cell<S>(L, comp)) != 0);
+    const bool ours = L.gany(take(left, first_cell<S>(L, comp)) != 0);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    take(comp);
+    take(left, comp);
     best = max(best, e1);
     bool open = ours && 2 * e1 > best;
     if (wave_any<S>(open)) {
@@ -1367,16 +1398,17 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
         open = open && 2 * ec > best;
         const W core = open ? centre : (W)0;
         const W near = ball<S>(L, core, pass, best >> 1, none);
-        W rim = open ? comp & ~near : (W)0;
-        for (;;) {
-          const W v = first_cell<S>(L, rim);
+        W mine = open ? comp & ~near : (W)0;
+        for (int turn = 0; turn < kOwnRimCells; ++turn) {
+          const W v = first_cell<S>(L, mine);
           if (!wave_any<S>(v != 0)) break;
-          rim &= ~v;
-          const int e = sweep<S>(L, v, pass, far, none);
-          const bool longer = e > best;
-          best = max(best, e);
-          // (a new best widens the ball around the centre; otherwise v's own ball goes)
-          rim &= ~ball<S>(L, longer ? core : v, pass, longer ? best >> 1 : best - e, none);
+          mine &= ~v;
+          mine &= ~rule_out(v, core);
+        }
+        if (wave_any<S>(mine != 0)) {
+          put(rim, mine);
+          put(middles, core);
+          any_rim = 1;
         }
       }
       if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], best);
@@ -1384,6 +1416,24 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   }
   if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], best);
   __syncthreads();
+  // What is left of the rims, shared out cell by cell: on a level with a long loop, all of whose cells
+  // are equally far from their farthest one, that is half of its cells, each with a sweep of its own.
+  if (any_rim) {
+    for (;;) {
+      W v = 0;
+      for (;;) {  // (another part may be quicker; each turn some part gets a cell)
+        const W c = choose(L.gany(v != 0) ? (W)0 : look(rim));
+        if (!wave_any<S>(c != 0)) break;
+        v |= take(rim, c);
+      }
+      if (!wave_any<S>(v != 0)) break;
+      best = max(best, best_so_far());
+      const int before = best;
+      take(rim, rule_out(v, look(middles)));
+      if (best > before && L.y == 0) atomicMax(&shared_best[wm.sl.slot], best);
+    }
+    __syncthreads();
+  }
   if (wave == 0 && wm.primary && L.y == 0) out[wm.env] = shared_best[wm.sl.slot];
 }
 

@@ -71,6 +71,19 @@ def test_plain_levels_in_and_out(problem, B, h, w, with_frozen):
     gpu.close()
 
 
+def _loop(h, w):
+    """A serpentine closed to one loop by a way back along the first column."""
+    n = (h + 1) // 4 * 2
+    t = np.ones((h, w), np.int8)
+    for i in range(n):
+        t[2 * i, 2:] = 0
+        if i < n - 1:
+            t[2 * i + 1, w - 1 if i % 2 == 0 else 2] = 0
+    t[0, :2] = t[2 * n - 2, :2] = 0
+    t[:2 * n - 1, 0] = 0
+    return t
+
+
 @pytest.mark.parametrize("h,w", [(16, 16), (13, 7), (32, 32), (5, 32), (64, 64), (64, 33)])
 def test_exact_diameter_prunes_no_longest_path(h, w):
     """The exact diameter on maps of every density (one huge component to none), rooms, corridors
@@ -98,6 +111,30 @@ def test_exact_diameter_prunes_no_longest_path(h, w):
     for parts_log2 in (0, 1, 4):
         got = gpu.pcgrl_exact_diameter_static(torch.empty(B, dtype=torch.int32, device=DEV), parts_log2)
         assert_same("exact diameters", got, want, (h, w, parts_log2))
+    gpu.close()
+
+
+def test_exact_diameter_shares_out_a_loop():
+    """The cells of one long loop are all equally far from their farthest one, so that half of them
+    are swept, each on its own: with 16 wavefronts at that, a level takes less than a quarter of the
+    time of one."""
+    n = 64
+    tiles = _loop(n, n)[None]
+    hw = torch.full((1, 2), n, dtype=torch.int16, device=DEV)
+    gpu = binding.Pcgrl(wl.make_config(wl.BINARY, 1, n, 5, min_size=1, autoreset=0), 0)
+    gpu.pcgrl_reset(1)
+    gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, hw, torch.zeros_like(hw))
+    out = torch.empty(1, dtype=torch.int32, device=DEV)
+    took = {}
+    for parts_log2 in (4, 0, 4, 0):
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        begin.record()
+        gpu.pcgrl_exact_diameter_static(out, parts_log2)
+        end.record()
+        torch.cuda.synchronize()
+        assert int(out[0]) == 1040  # half of the loop's 2080 cells
+        took[parts_log2] = begin.elapsed_time(end)
+    assert took[4] < took[0] / 4, took
     gpu.close()
 
 
