@@ -119,14 +119,18 @@ def _load_py():
     global _py
     if _py is None:
         load()
-        if not os.path.exists(_build.PY_LIB):
+        path = _build.py_lib()
+        if not os.path.exists(path):
             try:
                 _build.build_py()
             except Exception as e:
-                raise PcgrlError(f"{_build.PY_LIB} is missing and could not be built ({e})") from e
-        spec = importlib.util.spec_from_file_location("pcgrl_py", _build.PY_LIB)
-        mod = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(mod)
+                raise PcgrlError(f"{path} is missing and could not be built ({e})") from e
+        try:
+            spec = importlib.util.spec_from_file_location("pcgrl_py", path)
+            mod = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(mod)
+        except ImportError as e:
+            raise PcgrlError(f"{path} cannot be loaded ({e})") from e
         assert mod.LOOK == _LOOK
         _py = mod
     return _py

@@ -17,7 +17,6 @@ DEPS = [SRC, os.path.join(HERE, "csrc", "pcgrl_kernels.hip.h"), os.path.join(HER
 LIB_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIB_DIR, "libpcgrl.so")
 PY_SRC = os.path.join(HERE, "csrc", "pcgrl_py.cpp")
-PY_LIB = os.path.join(LIB_DIR, "pcgrl_py.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -31,10 +30,18 @@ HIPCC_FLAGS = [
 ]
 
 
+def py_lib() -> str:
+    """Path of the binding's compiled part.  Unlike the library it is good for one interpreter and one
+    torch only (it reads torch's C++ objects), so its name carries both, and after a change of either
+    it counts as not built."""
+    import torch
+    return os.path.join(LIB_DIR, "pcgrl_py.%s.torch-%s.so" % (sysconfig.get_config_var("SOABI"), torch.__version__))
+
+
 def is_stale() -> bool:
     newest = lambda files: max(os.path.getmtime(f) for f in files)
-    return (not os.path.exists(LIB) or os.path.getmtime(LIB) < newest(DEPS) or not os.path.exists(PY_LIB) or
-            os.path.getmtime(PY_LIB) < newest([PY_SRC, DEPS[-1]]))
+    return (not os.path.exists(LIB) or os.path.getmtime(LIB) < newest(DEPS) or not os.path.exists(py_lib()) or
+            os.path.getmtime(py_lib()) < newest([PY_SRC, DEPS[-1]]))
 
 
 SCAN_REPORT = os.path.join(LIB_DIR, "libpcgrl.scan.json")
@@ -131,10 +138,10 @@ def build_py(verbose: bool = False) -> str:
         res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         if res.returncode != 0:
             raise RuntimeError("the Python binding's compiled part failed to build:\n" + res.stdout)
-        shutil.move(out, PY_LIB)
+        shutil.move(out, py_lib())
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
-    return PY_LIB
+    return py_lib()
 
 
 if __name__ == "__main__":

@@ -136,6 +136,38 @@ def test_compiled_call_path_outlives_tensors_without_storage():
     assert res.returncode == 0 and res.stdout.split() == ["asked"], res.stderr[-2000:]
 
 
+def test_compiled_call_path_belongs_to_one_torch_and_one_interpreter(monkeypatch, tmp_path):
+    """The compiled part of the binding is looked for under a name that changes with torch and with
+    the interpreter, is built where that one is missing, and a file that cannot be loaded is
+    reported as the binding reports everything else."""
+    import shutil
+    import sysconfig
+    import torch
+    here = binding._load_py().__file__
+    monkeypatch.setattr(build, "LIB_DIR", str(tmp_path))
+    built = []
+    monkeypatch.setattr(build, "build_py", lambda: built.append(shutil.copy(here, build.py_lib())))
+    monkeypatch.setattr(binding, "_py", None)
+    binding._load_py()
+    assert len(built) == 1
+    monkeypatch.setattr(binding, "_py", None)
+    binding._load_py()
+    assert len(built) == 1                          # (there now)
+    monkeypatch.setattr(torch, "__version__", "0.0.1")
+    monkeypatch.setattr(binding, "_py", None)
+    binding._load_py()
+    assert len(built) == 2 and "0.0.1" in built[1]
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda name: "other-" + name)
+    monkeypatch.setattr(binding, "_py", None)
+    binding._load_py()
+    assert len(built) == 3 and "other-SOABI" in built[2]
+    monkeypatch.setattr(torch, "__version__", "0.0.2")
+    open(build.py_lib(), "wb").write(b"no module")
+    monkeypatch.setattr(binding, "_py", None)
+    with pytest.raises(binding.PcgrlError, match="cannot be loaded"):
+        binding._load_py()
+
+
 INDEX = """
 #include "pcgrl_index.h"
 extern "C" void grid(uint32_t batch, uint32_t cells, int with_cells, uint32_t* out) {
