@@ -27,14 +27,17 @@ def _plain_levels(problem, B, h, w, seed, p_wall=None):
     return tiles, frozen, hw, pos
 
 
-@pytest.mark.parametrize("problem,B,h,w", [
-    (wl.BINARY, 1, 1, 1), (wl.MAZE, 37, 16, 16), (wl.DUNGEON, 2051, 11, 3), (wl.BINARY, 65, 3, 32), (wl.MAZE, 4099, 31, 17),
-    (wl.DUNGEON, 19, 27, 45), (wl.BINARY, 9, 64, 64), (wl.DUNGEON, 5, 2, 64), (wl.MAZE, 7, 63, 5)])
+@pytest.mark.parametrize("problem,B,h,w,per_wave", [
+    (wl.BINARY, 1, 1, 1, 0), (wl.MAZE, 37, 16, 16, 0), (wl.DUNGEON, 2051, 11, 3, 0), (wl.BINARY, 65, 3, 32, 0), (wl.MAZE, 4099, 31, 17, 0),
+    (wl.DUNGEON, 19, 27, 45, 0), (wl.BINARY, 9, 64, 64, 0), (wl.DUNGEON, 5, 2, 64, 0), (wl.MAZE, 7, 63, 5, 0),
+    # several levels a wavefront, the last one partly filled, rows that start at odd bits of the run
+    (wl.DUNGEON, 37, 11, 3, 2), (wl.DUNGEON, 37, 11, 3, 4), (wl.BINARY, 419, 13, 7, 2), (wl.BINARY, 419, 13, 7, 4), (wl.MAZE, 38, 16, 16, 4),
+    (wl.MAZE, 3, 16, 16, 4), (wl.BINARY, 2, 1, 1, 4), (wl.MAZE, 37, 31, 17, 2), (wl.DUNGEON, 5, 32, 32, 2)])
 @pytest.mark.parametrize("with_frozen", [True, False])
-def test_plain_levels_in_and_out(problem, B, h, w, with_frozen):
+def test_plain_levels_in_and_out(problem, B, h, w, per_wave, with_frozen):
     """pcgrl_set_state and pcgrl_get_state where rows, levels and the 16-byte pieces they are read
-    and written in end at different places."""
-    cfg = wl.make_config(problem, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0)
+    and written in end at different places, with one and several levels in a wavefront."""
+    cfg = wl.make_config(problem, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0, levels_per_wave=per_wave)
     gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
     gpu.pcgrl_reset(3)
     cpu.reset(3)
@@ -84,10 +87,13 @@ def _loop(h, w):
     return t
 
 
-@pytest.mark.parametrize("h,w", [(16, 16), (13, 7), (32, 32), (5, 32), (64, 64), (64, 33)])
-def test_exact_diameter_prunes_no_longest_path(h, w):
-    """The exact diameter on maps of every density (one huge component to none), rooms, corridors
-    and rings, for one and several parts per level."""
+@pytest.mark.parametrize("h,w,per_wave", [
+    (16, 16, 0), (13, 7, 0), (32, 32, 0), (5, 32, 0), (64, 64, 0), (64, 33, 0),
+    (16, 16, 2), (16, 16, 4), (13, 7, 2), (13, 7, 4), (32, 32, 2), (5, 32, 2)])
+def test_exact_diameter_prunes_no_longest_path(h, w, per_wave):
+    """The exact diameter on maps of every density (one huge component to none), rooms, corridors,
+    rings and loops, for one and several parts per level, each level in a wavefront of its own (or
+    in all of its lane groups) and together with different ones, the last wavefront partly filled."""
     rng = np.random.default_rng(h * 100 + w)
     maps = [(rng.random((h, w)) < d).astype(np.int8) for d in (0, .05, .2, .3, .35, .4, .42, .45, .5, .5, .6, .8, 1)]
     y, x = np.mgrid[:h, :w]
@@ -96,11 +102,14 @@ def test_exact_diameter_prunes_no_longest_path(h, w):
              ((y % 4 == 0) & (x % 7 != 3)).astype(np.int8),                                  # rooms with doors
              ((x % 2 == 1) & (y > 0)).astype(np.int8),                                       # a comb
              ((y + x) % 2).astype(np.int8)]                                                  # single cells
-    maps += [(rng.random((h, w)) < .5).astype(np.int8) for _ in range(400)]
+    # loops beside levels of nothing, a few cells and another loop
+    maps += [_loop(h, w), np.ones((h, w), np.int8), np.ascontiguousarray(_loop(h, w)[::-1]), (rng.random((h, w)) < .9).astype(np.int8),
+             ((y % 4 != 0) & (x % 4 != 0)).astype(np.int8)]                                  # corridors all round blocks
+    maps += [(rng.random((h, w)) < .5).astype(np.int8) for _ in range(396)]
     tiles = np.stack(maps)
     B = len(tiles)
     hw = np.full((B, 2), (h, w), np.int16)
-    cfg = wl.make_config(wl.BINARY, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0)
+    cfg = wl.make_config(wl.BINARY, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0, levels_per_wave=per_wave)
     gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
     gpu.pcgrl_reset(1)
     cpu.reset(1)
@@ -210,4 +219,61 @@ def test_unpack_row_lengths(problem, size, obs_w, frozen, dtype):
         gpu.pcgrl_unpack_obs(src[by:by + obs.numel()].view(obs.shape), out=out)
         assert torch.equal(out.cpu(), want), by
         assert bool((buf[:by] == 7).all()) and bool((buf[by + want.numel():] == 7).all()), by
+    gpu.close()
+
+
+def _spoilt(t, wrong):
+    """A tensor like t with one property that is not t's."""
+    if wrong == "type":
+        return torch.zeros(t.shape, dtype=torch.int64, device=DEV)
+    if wrong == "size":
+        return torch.zeros(t.shape[:-1] + (t.shape[-1] + 1,), dtype=t.dtype, device=DEV)
+    if wrong == "first size":
+        return torch.zeros((t.shape[0] + 1,) + t.shape[1:], dtype=t.dtype, device=DEV)
+    if wrong == "stride":
+        return torch.zeros(t.shape[:-1] + (2 * t.shape[-1],), dtype=t.dtype, device=DEV)[..., ::2]
+    if wrong == "one more dimension":
+        return torch.zeros((1,) + t.shape, dtype=t.dtype, device=DEV)
+    if wrong == "one dimension less":
+        return torch.zeros(t.shape[1:], dtype=t.dtype, device=DEV)
+    return torch.zeros(t.shape, dtype=t.dtype)  # "device"
+
+
+@pytest.mark.parametrize("wrong", ["type", "size", "first size", "stride", "one more dimension", "one dimension less", "device"])
+@pytest.mark.parametrize("packed", [False, True])
+def test_every_argument_of_every_call_is_checked(wrong, packed):
+    """Device tensors with one property wrong, one at a time, in every place of every call that goes
+    through the compiled path: answered with LOOK there and with PcgrlError by the binding; what
+    is right is taken."""
+    B, T = 5, 4
+    cfg = wl.make_config(wl.MAZE, B, 9, 6, max_w=11, min_size=1, min_w=1, obs_format=int(packed))
+    gpu = binding.Pcgrl(cfg, 0)
+    z = lambda shape, dtype: torch.zeros(tuple(shape), dtype=dtype, device=DEV)
+    i8, u8, i16, i32, f32 = torch.int8, torch.uint8, torch.int16, torch.int32, torch.float32
+    obs, grid, pair = tuple(gpu.obs_shape), (B, 9, 11), (B, 2)
+    calls = dict(
+        step=[z((B,), i32), z(obs, u8), z((B,), f32), z((B,), u8)],
+        rollout=[z((T, B), i32), z((T,) + obs, u8), z((T, B), f32), z((T, B), u8)],
+        reset=[7, z(obs, u8)], metrics=[z((B, gpu.M), i32)], exact_diameter=[z((B,), i32)], observe=[z(obs, u8)],
+        set_state=[z(grid, i8), z(grid, u8), torch.full(pair, 3, dtype=i16, device=DEV), z(pair, i16)])
+    if packed:
+        calls["unpack_obs"] = [z(obs, u8), z(gpu.onehot_shape, f32)]
+    gpu.pcgrl_reset(1)
+    for name, args in calls.items():
+        fast, method = getattr(gpu._env, name), getattr(gpu, "pcgrl_" + name)
+        # (those of one argument take it alone, like every other caller of them)
+        assert fast(*args) == 0, name
+        method(*args)
+        for i, t in enumerate(args):
+            if not isinstance(t, torch.Tensor):
+                continue
+            if wrong == "first size" and name == "rollout" and i == 0:
+                continue  # (another number of steps; then the others are wrong)
+            bad = args[:i] + [_spoilt(t, wrong)] + args[i + 1:]
+            rc = fast(*bad)
+            # (more slots than steps is for the library to refuse)
+            assert rc == (-2 if wrong == "first size" and name == "rollout" and i == 1 else binding._LOOK), (name, i)
+            with pytest.raises(binding.PcgrlError):
+                method(*bad)
+    torch.cuda.synchronize()
     gpu.close()

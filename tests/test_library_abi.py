@@ -86,8 +86,9 @@ def test_built_library_passed_the_scan():
 
 
 def test_compiled_call_path_leaves_doubtful_arguments_to_the_python_checks():
-    """Arguments that are not device tensors of the right type and shape, missing ones and a closed
-    environment are answered with LOOK, before any library call (no GPU is touched)."""
+    """Tensors that are not on the device, arguments that are missing or no tensors, and a closed
+    environment are answered with LOOK, before any library call (no GPU is touched; device tensors of
+    a wrong type or shape are tested on the GPU)."""
     import torch
     py = binding._load_py()
     env = py.Env(1, 0, 4, 16, 16, (3, 2, 31, 31), (3, 2, 31, 31))   # (the handle is never followed)

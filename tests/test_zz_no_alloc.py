@@ -1,6 +1,6 @@
-"""The entry point that allocates nothing (pcgrl_exact_diameter_static) against the entry point it
-is a variant of, through the C ABI: same results, on two calls in a row that share the library's
-static scratch array, the second on a smaller batch (needs an MI355X)."""
+"""pcgrl_exact_diameter_static, whose caller chooses how many wavefronts share a level, against
+pcgrl_exact_diameter, through the C ABI: same results for every choice, on calls in a row of
+different sizes (needs an MI355X)."""
 import ctypes as C
 
 import numpy as np
@@ -28,9 +28,9 @@ def _diameters(gpu, static, parts_log2=-1):
 
 def test_static_scratch_variant_equals_the_allocating_entry_point():
     dev = torch.device("cuda", 0)
-    # first call: 700 levels, sources of a level shared out over 4 workgroups (2800 partial results);
-    # second call: 45 larger levels over 32 workgroups each (1440): its partial results land on
-    # words that still hold the first call's
+    # 700 levels with the wavefronts the other entry point takes, 45 larger ones with 32 wavefronts
+    # each asked for (16 are used), 3 with 64, and 9000 with one: each workgroup leaves its sets of
+    # cells in LDS for the next one, which has to start from its own
     cases = [("binary16", 700, -1), ("dungeon32", 45, 5), ("maze64", 3, 6), ("binary16", 9000, 0)]
     envs = []
     for name, batch, lg in cases:
@@ -67,10 +67,10 @@ def test_static_scratch_variant_rejects_what_does_not_fit():
     out = torch.empty((gpu.B,), dtype=torch.int32, device=dev)
     st = C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
     call = lambda lg: gpu.L.pcgrl_exact_diameter_static(gpu.h, C.c_void_p(out.data_ptr()), lg, st)
-    assert call(3) == -6                       # 40 000 levels x 8 parts = 320 000 > 262 144 partial results
-    assert call(2) == 0                        # 160 000 fit
+    assert call(3) == -6                       # 40 000 levels x 8 parts = 320 000 > 262 144
+    assert call(2) == 0                        # 160 000 are accepted
     assert call(5) == -2 and call(-2) == -2    # more parts than rows / no such code
     assert gpu.L.pcgrl_exact_diameter_static(None, C.c_void_p(out.data_ptr()), 0, st) == -1
-    assert b"static scratch" in gpu.L.pcgrl_strerror(-6)
+    assert b"static scratch" in gpu.L.pcgrl_strerror(-6) and b"262 144" in gpu.L.pcgrl_strerror(-6)
     torch.cuda.synchronize()
     gpu.close()
