@@ -173,7 +173,8 @@ template <int S, int PROBLEM> struct LaunchExact {
 };
 
 // pcgrl_exact_diameter_static takes at most this many levels times parts, if the caller chooses the
-// parts (see the header).
+// parts: as many as a static array for partial results once held.  Nothing is limited by it any more;
+// what was refused stays refused.
 constexpr size_t kStaticMostParts = (size_t)1 << 18;
 
 // ---- launch shapes.  Results never depend on them; every row below is a measurement on MI355X
@@ -301,7 +302,7 @@ const char* pcgrl_strerror(int code) {
     case PCGRL_E_HIP: return "HIP runtime call failed";
     case PCGRL_E_NOMEM: return "device allocation failed";
     case PCGRL_E_DEVICE: return "no such device, or not a gfx950 device";
-    case PCGRL_E_SCRATCH: return "the call needs more partial results than the library's static scratch array holds";
+    case PCGRL_E_SCRATCH: return "more than 262 144 levels times parts (what a static scratch array once held; the limit has stayed)";
     default: return "unknown error code";
   }
 }
