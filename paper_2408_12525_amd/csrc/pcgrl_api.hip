@@ -249,9 +249,9 @@ int exact_waves_for(int nwaves, int copies, int S) {
   return lg;
 }
 
-int launch_init(pcgrl_ctx* ctx, int flags, uint64_t seed, uint8_t* obs, hipStream_t st) {
+int launch_init(pcgrl_ctx* ctx, bool fresh, uint64_t seed, uint8_t* obs, hipStream_t st) {
   KArgs a = ctx->base;
-  a.flags = flags;
+  a.fresh = fresh;
   a.seed = seed;
   a.obs = obs;
   return dispatch<LaunchInit>(ctx->S, ctx->cfg.problem, ctx, a, st);
@@ -575,7 +575,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
   for (int j = 0; j < 8; ++j) a.pinpoint_tile[j] = cfg->pinpoint_tile[j];
   a.ctrl_mask = cfg->ctrl_mask & ((1u << ctx->M) - 1u);
 
-  rc = launch_init(ctx, kInitGenerate | kInitMetrics | kInitTargets, 0, nullptr, nullptr);
+  rc = launch_init(ctx, true, 0, nullptr, nullptr);
   if (rc == PCGRL_OK && hipDeviceSynchronize() != hipSuccess) rc = PCGRL_E_HIP;
   if (rc != PCGRL_OK) {
     pcgrl_destroy(ctx);
@@ -601,8 +601,7 @@ int pcgrl_reset(pcgrl_ctx* ctx, uint64_t seed, uint8_t* obs, void* stream) {
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
   ctx->base.seed = seed;
-  return launch_init(ctx, kInitGenerate | kInitMetrics | kInitTargets | kInitObs, seed, obs,
-                     static_cast<hipStream_t>(stream));
+  return launch_init(ctx, true, seed, obs, static_cast<hipStream_t>(stream));
 }
 
 int pcgrl_step(pcgrl_ctx* ctx, const int32_t* actions, uint8_t* obs, float* reward, uint8_t* done,
@@ -701,7 +700,7 @@ int pcgrl_observe(pcgrl_ctx* ctx, uint8_t* obs, void* stream) {
   if (!ctx || !obs) return PCGRL_E_NULL;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return PCGRL_E_DEVICE;
-  return launch_init(ctx, kInitObs, ctx->base.seed, obs, static_cast<hipStream_t>(stream));
+  return launch_init(ctx, false, ctx->base.seed, obs, static_cast<hipStream_t>(stream));
 }
 
 int pcgrl_get_state(pcgrl_ctx* ctx, int8_t* tiles, uint8_t* frozen, int16_t* hw, int16_t* pos,

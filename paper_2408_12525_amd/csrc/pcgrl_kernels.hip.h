@@ -34,7 +34,6 @@ enum : int { kPadBorder = 0, kPadWall = 1 };
 enum : int { kPosScan = 0, kPosRandom = 1 };
 enum : int { kRegionsIncremental = 0, kRegionsRecount = 1 };
 enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
-enum : int { kInitGenerate = 1, kInitMetrics = 2, kInitObs = 4, kInitTargets = 8 };
 // step kernel variants: one step per launch; the same with the work of a wavefront split over
 // two (a metrics wavefront and an observation wavefront per workgroup); n steps per launch; n steps
 // per launch split the same way
@@ -79,7 +78,7 @@ struct KArgs {
   int32_t obs_frozen_channel;  // non-zero: a last channel marks the pinpoint cells in view
   int32_t stream_obs;     // how observations are stored: kStoreCached / kStoreStream / kStoreThrough
   int32_t by_die;       // rollouts: consecutive level groups run on the same die (see level_group_of_block)
-  int32_t flags;          // init kernel only
+  int32_t fresh;          // init kernel only: first levels from the seed instead of the stored ones
   int32_t rollout_steps;  // rollout kernel: steps per launch
   int32_t obs_slots;      // rollout kernel: step t writes observation slot t % obs_slots
   int32_t obs_lds_words;  // split step: LDS words of one observation wavefront's staging area
@@ -1124,9 +1123,8 @@ __device__ __forceinline__ void observe(const KArgs& a, const Lanes<S>& L, const
     write_obs<S, PROBLEM, false, CLEARED, LEAN>(a, L, wm.sl, pl, wm.lds, p, fz, inside, qy, qx);
 }
 
-// Reset / refresh / observe: flags choose between generating a fresh episode 0 from the seed or
-// loading the stored level, recomputing all metrics, restoring default targets, writing the
-// observation.
+// Reset / observe: either a fresh episode 0 from the seed, with its metrics and the default targets, or
+// the stored level; then its observation, if a buffer is given.
 template <int S, int PROBLEM>
 __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
   using W = typename RowWord<S>::T;
@@ -1142,7 +1140,7 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
   W p[PR::P], fz;
   int h, w, py, px;
   EnvRec er;
-  if (a.flags & kInitGenerate) {
+  if (a.fresh) {
     er.key = env_key(a.seed, (uint64_t)wm.envl, 0);
     er.t = 0;
     er.n_changes = 0;
@@ -1169,10 +1167,10 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
 #pragma unroll
     for (int i = 0; i < PR::P; ++i) p[i] = planes[(size_t)i * a.plane_stride + ridx];
     fz = 0;
-    if ((a.flags & kInitObs) && a.obs_frozen_channel) fz = frozen[ridx];
+    if (a.obs_frozen_channel) fz = frozen[ridx];
   }
   const W inside = inside_row<W>(L.y, h, w);
-  if (a.flags & kInitMetrics) {
+  if (a.fresh) {
     int m[PR::M];
     W comp;
     full_metrics<S, PROBLEM>(L, p, inside, wm.valid, m, comp);
@@ -1180,13 +1178,13 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
     if constexpr (PROBLEM == kBinary) {  // (the plane after the tile planes)
       if (wm.primary) planes[(size_t)PR::P * a.plane_stride + ridx] = comp;
     }
+    if (wm.primary && L.y < PR::M) {
+      uint32_t t = pack_range(a.target_lo[L.y], a.target_hi[L.y]);
+      if ((a.ctrl_mask >> L.y) & 1u) t = control_target(a, er.key, L.y);
+      a.targets[(size_t)wm.env * kMaxMetrics + L.y] = t;
+    }
   }
-  if ((a.flags & kInitTargets) && wm.primary && L.y < PR::M) {
-    uint32_t t = pack_range(a.target_lo[L.y], a.target_hi[L.y]);
-    if ((a.ctrl_mask >> L.y) & 1u) t = control_target(a, er.key, L.y);
-    a.targets[(size_t)wm.env * kMaxMetrics + L.y] = t;
-  }
-  if ((a.flags & kInitObs) && a.obs != nullptr)
+  if (a.obs != nullptr)
     observe<S, PROBLEM>(a, L, wm, obs_plan(a, L.lane, wm.sl, a.obs, wm.env0, wm.nvalid), p, fz, inside, py, px);
 }
 
