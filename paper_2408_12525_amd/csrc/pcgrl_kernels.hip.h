@@ -1261,9 +1261,10 @@ __device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>&
 // of all rims is shared out cell by cell once nobody has a component left.  Lane groups work at their
 // own pace (a group that has nothing to do in a sweep has no seed); every loop ends because each turn
 // takes cells out of a finite set.
-// Bound by the latency of one flood layer after the other, some 1400 of them for a random 64x64 level
-// of 50 % walls: a sweep from each of its 2000 open cells instead took 1268 us for 1024 levels
-// (a launch of 4096 wavefronts and one that folded their results); this takes 80.  A loop of 2080 cells
+// Some 1400 flood layers for a random 64x64 level of 50 % walls, bound by the latency of one after the
+// other in small batches and by vector instructions (73 % of the issue slots) from 1024 levels on: a
+// sweep from each of its 2000 open cells instead took 1350 us for 1024 levels (a launch of 4096
+// wavefronts and one that folded their results); this takes 80.  A loop of 2080 cells
 // is the worst there is, 1040 sweeps of 1040 layers and bound by instructions: 64 such levels 6.7 ms
 // (37.8 while the owner swept the whole rim, 6.5 from each cell on 4096 wavefronts; one level alone takes
 // as long here, and took 2.0 there), 1024 of them 26.7 ms (38.0, 104).
@@ -2105,7 +2106,7 @@ __global__ __launch_bounds__(MODE == kModeRolloutSplit ? 320 : 64) void rollout_
 // keeps the packed runs in LDS, out of which every lane then cuts its row.  Bound by latency and by
 // the from-scratch metrics that follow.  Reading the bytes one by one, a thread per row, took
 // 31 us for 5001 levels of 27x45 (12 MB) in a kernel of its own, and the metrics a second one
-// (16 us); both together now take 19.
+// (16 us); both together now take 18.
 struct LevelSource {
   const int8_t* tiles;
   const uint8_t* frozen;  // or NULL: no pinpoints
