@@ -520,9 +520,12 @@ __device__ __forceinline__ int regions_full(const Lanes<S>& L, typename RowWord<
 }
 
 // Number of distinct components of `passw` (the level with the edited cell walled off) among the
-// walkable four-neighbours `nbr` of that cell.  Floods start from the neighbours one after the
-// other and stop as soon as every remaining neighbour is reached or the flood stalls; the last
-// unreached neighbour needs no flood of its own.
+// walkable four-neighbours `nbr` of that cell.  A flood starts from the first neighbour; most of the
+// time it has reached all the others within a few layers, round the corner.  If it has not, a second
+// flood starts from those it has not reached, and the two go on side by side until they meet (the
+// first neighbour then hangs together with one of the others and adds nothing to the count) or
+// either of them stalls (then it is a component of its own); either way it is done with, and what is
+// left are the others.
 template <int S>
 __device__ __forceinline__ int neighbour_components(const Lanes<S>& L, typename RowWord<S>::T nbr,
                                                     typename RowWord<S>::T passw) {
@@ -543,44 +546,38 @@ __device__ __forceinline__ int neighbour_components(const Lanes<S>& L, typename 
       U = 0;
     }
     if (!wave_any<S>(go)) break;
-    W V = go ? first_cell<S>(L, U) : (W)0;
+    W A = go ? first_cell<S>(L, U) : (W)0;
     W pw = go ? passw : (W)0;
-    k += go ? 1 : 0;
     // A group whose neighbours are all reached is finished for good: whatever its flood still
     // adds while other groups go on changes nothing below.
     bool more = true;
     for (int n = 0; n < kShortTrips && more; ++n) {
-      W V1 = L.grow(V, pw);
-      W Vn = L.grow(V1, pw);
-      bool ch = Vn != V1;  // a last layer that adds nothing means the flood is complete
-      V = Vn;
-      bool open = L.gany((U & ~V) != 0);
+      W A1 = L.grow(A, pw);
+      W An = L.grow(A1, pw);
+      bool ch = An != A1;  // a last layer that adds nothing means the flood is complete
+      A = An;
+      bool open = L.gany((U & ~A) != 0);
       more = wave_any<S>(ch && open);
     }
-    // (64-row levels, whose components can wind for hundreds of layers, go on to eight layers a
-    // trip after two trips of four: measured -1.5 % on the 64x64 maze; for the smaller sizes the
-    // third stage costs more in code than it saves)
-    for (int n = 0; (S < 64 || n < 2) && more; ++n) {
-      W V1 = L.grow(L.grow(L.grow(V, pw), pw), pw);
-      W Vn = L.grow(V1, pw);
-      bool ch = Vn != V1;
-      V = Vn;
-      bool open = L.gany((U & ~V) != 0);
-      more = wave_any<S>(ch && open);
-    }
-    if constexpr (S == 64) {
-      while (more) {
-        W V1 = V;
+    U &= ~A;
+    bool meet = false;
+    if (more) {
+      W B = U;
+      do {
+        W A1 = A, B1 = B;
 #pragma unroll
-        for (int l = 0; l < 7; ++l) V1 = L.grow(V1, pw);
-        W Vn = L.grow(V1, pw);
-        bool ch = Vn != V1;
-        V = Vn;
-        bool open = L.gany((U & ~V) != 0);
-        more = wave_any<S>(ch && open);
-      }
+        for (int l = 0; l < 3; ++l) {
+          A1 = L.grow(A1, pw);
+          B1 = L.grow(B1, pw);
+        }
+        A = L.grow(A1, pw);
+        B = L.grow(B1, pw);
+        const bool grew_a = L.gany(A != A1), grew_b = L.gany(B != B1);
+        meet = L.gany((A & B) != 0);
+        more = wave_any<S>(grew_a & grew_b & !meet);
+      } while (more);
     }
-    U &= ~V;
+    k += go && !meet ? 1 : 0;
     left = count(U);
   }
   return k;
