@@ -157,6 +157,53 @@ template <int CTRL> __device__ __forceinline__ uint32_t dpp_zero_fill(uint32_t v
 }
 constexpr int kRowShr1 = 0x111, kRowShl1 = 0x101, kWaveShr1 = 0x138, kWaveShl1 = 0x130;
 
+// Flood layers written out.  A lane-shifted (DPP) read has to come two instructions after the write of
+// any register the instruction uses, and the compiler neither looks into an assembly block for that
+// nor lets anything read a block's result without a wait; so whole groups of layers are one block, in
+// an order that leaves few waits.  Measured, clocks a layer of one wavefront alone: 32 / 43 for 16 / 32
+// rows (41 / 65 layer by layer as the compiler arranges it), 54 / 78 for two sets together.  Each is the
+// variant with the fewest vector instructions; one more per set and no waits at all was slower where
+// the batch fills the machine (32x32 binary levels at 16 384: 13.9 against 13.5 us per step).  Every
+// lane shift rides on a two-operand OR.  bitop3:0xa8 is (first | second) & third.
+#define PCGRL_DPP(D, F, ACC, SHIFT, ROWS) "v_or_b32_dpp " D ", " F ", " ACC " " SHIFT ":1 row_mask:" ROWS " bank_mask:0xf bound_ctrl:1\n\t"
+// one layer of the set F inside R, to D; scratch %2, %3
+#define PCGRL_LAYER16(F, D, R)                                             \
+  "v_lshrrev_b32 %2, 1, " F "\n\tv_lshl_or_b32 %2, " F ", 1, %2\n\t"       \
+  PCGRL_DPP("%3", F, F, "row_shr", "0xf") "s_nop 0\n\t"                    \
+  PCGRL_DPP("%2", F, "%2", "row_shl", "0xf")                               \
+  "v_bitop3_b32 " D ", %2, %3, " R " bitop3:0xa8\n\t"
+// (32 rows: a shift inside each row of 16 lanes, then the step across the middle of each level only:
+// rows 1 and 3 take from below them, rows 0 and 2 from above them; what the second step repeats does
+// no harm)
+#define PCGRL_LAYER32(F, D, R)                                             \
+  "v_lshrrev_b32 %2, 1, " F "\n\tv_lshl_or_b32 %2, " F ", 1, %2\n\t"       \
+  PCGRL_DPP("%3", F, F, "row_shr", "0xf") "s_nop 0\n\t"                    \
+  PCGRL_DPP("%2", F, "%2", "row_shl", "0xf")                               \
+  PCGRL_DPP("%3", F, "%3", "wave_shr", "0xa") "s_nop 0\n\t"                \
+  PCGRL_DPP("%2", F, "%2", "wave_shl", "0x5")                              \
+  "v_bitop3_b32 " D ", %2, %3, " R " bitop3:0xa8\n\t"
+// one layer of king's moves of two sets, %2 and %3, inside %8, to DA and DB; scratch %4 to %7
+#define PCGRL_KINGS16(DA, DB)                                                               \
+  PCGRL_DPP("%4", "%2", "%2", "row_shr", "0xf") "s_nop 0\n\t"                               \
+  PCGRL_DPP("%6", "%3", "%3", "row_shr", "0xf") PCGRL_DPP("%4", "%2", "%4", "row_shl", "0xf") \
+  "v_lshrrev_b32 %5, 1, %4\n\t"                                                             \
+  PCGRL_DPP("%6", "%3", "%6", "row_shl", "0xf")                                             \
+  "v_lshl_or_b32 %5, %4, 1, %5\n\tv_bitop3_b32 " DA ", %5, %4, %8 bitop3:0xa8\n\t"          \
+  "v_lshrrev_b32 %7, 1, %6\n\tv_lshl_or_b32 %7, %6, 1, %7\n\t"                              \
+  "v_bitop3_b32 " DB ", %7, %6, %8 bitop3:0xa8\n\t"
+#define PCGRL_KINGS32(DA, DB)                                                               \
+  PCGRL_DPP("%4", "%2", "%2", "row_shr", "0xf") "s_nop 0\n\t"                               \
+  PCGRL_DPP("%6", "%3", "%3", "row_shr", "0xf") PCGRL_DPP("%4", "%2", "%4", "row_shl", "0xf") \
+  "s_nop 0\n\t"                                                                             \
+  PCGRL_DPP("%6", "%3", "%6", "row_shl", "0xf") PCGRL_DPP("%4", "%2", "%4", "wave_shr", "0xa") \
+  "s_nop 0\n\t"                                                                             \
+  PCGRL_DPP("%6", "%3", "%6", "wave_shr", "0xa") PCGRL_DPP("%4", "%2", "%4", "wave_shl", "0x5") \
+  "v_lshrrev_b32 %5, 1, %4\n\t"                                                             \
+  PCGRL_DPP("%6", "%3", "%6", "wave_shl", "0x5")                                            \
+  "v_lshl_or_b32 %5, %4, 1, %5\n\tv_bitop3_b32 " DA ", %5, %4, %8 bitop3:0xa8\n\t"          \
+  "v_lshrrev_b32 %7, 1, %6\n\tv_lshl_or_b32 %7, %6, 1, %7\n\t"                              \
+  "v_bitop3_b32 " DB ", %7, %6, %8 bitop3:0xa8\n\t"
+
 template <int S> struct Lanes {
   using W = typename RowWord<S>::T;
   static constexpr int G = 64 / S;
@@ -202,50 +249,83 @@ template <int S> struct Lanes {
     const uint32_t r = S == 16 ? dpp_zero_fill<kRowShl1>(v) : dpp_zero_fill<kWaveShl1>(v);
     return S == 32 && y == S - 1 ? 0u : r;
   }
-  // The four-neighbour dilation of a cell set (the set itself included), not yet masked.
-  // Written out instruction by instruction so that every lane shift rides on an OR (the compiler's
-  // three-operand ORs cannot take a lane-shifted operand and need a separate move for each, and it
-  // masks the group boundary of 32-row levels with two selects).  A lane-shifted read must come at
-  // least two instructions after the write of any register the instruction uses: f is written
-  // before the block, the accumulators two instructions before they are used again.
-  __device__ __forceinline__ W dilate(W f) const {
+  // acc | the value of `v` a lane shift away, as one instruction.  (The compiler folds a lane shift
+  // into an OR that is the only use of it, but would first gather a chain of ORs into three-operand
+  // ones, which cannot take a shifted operand; the empty statement keeps the chain as it is written.)
+  template <int CTRL, int ROWS = 0xf> static __device__ __forceinline__ uint32_t or_shifted(uint32_t acc, uint32_t v) {
+    uint32_t r = acc | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, ROWS == 0xf);
+    asm("" : "+v"(r));
+    return r;
+  }
+  // a cell set with the cells above and below it
+  __device__ __forceinline__ W with_above_below(W f) const {
     if constexpr (S == 16) {
-      uint32_t t, u;
-      asm("v_lshrrev_b32 %0, 1, %2\n\t"
-          "v_lshl_or_b32 %0, %2, 1, %0\n\t"
-          "v_or_b32_dpp %1, %2, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-          "s_nop 0\n\t"
-          "v_or_b32_dpp %0, %2, %0 row_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-          : "=&v"(t), "=&v"(u)
-          : "v"(f));
-      return t | u;
+      return or_shifted<kRowShl1>(or_shifted<kRowShr1>(f, f), f);
     } else if constexpr (S == 32) {
       // a shift inside each row of 16 lanes, then the step across the boundary between the two
       // rows of one level only (rows 1 and 3 take from below them, rows 0 and 2 from above them);
       // the second step repeats values the first has already ORed in, which does no harm
-      uint32_t t, u;
-      asm("v_lshrrev_b32 %0, 1, %2\n\t"
-          "v_lshl_or_b32 %0, %2, 1, %0\n\t"
-          "v_or_b32_dpp %1, %2, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-          "s_nop 0\n\t"
-          "v_or_b32_dpp %0, %2, %0 row_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-          "v_or_b32_dpp %1, %2, %1 wave_shr:1 row_mask:0xa bank_mask:0xf bound_ctrl:1\n\t"
-          "s_nop 0\n\t"
-          "v_or_b32_dpp %0, %2, %0 wave_shl:1 row_mask:0x5 bank_mask:0xf bound_ctrl:1"
-          : "=&v"(t), "=&v"(u)
-          : "v"(f));
-      return t | u;
+      const uint32_t u = or_shifted<kWaveShr1, 0xa>(or_shifted<kRowShr1>(f, f), f);
+      return or_shifted<kWaveShl1, 0x5>(or_shifted<kRowShl1>(u, f), f);
     } else {
-      // (for 64-row levels the same treatment was measured and is slower than the compiler's code)
-      return f | (W)(f << 1) | (W)(f >> 1) | from_above(f) | from_below(f);
+      const uint32_t lo = (uint32_t)f, hi = (uint32_t)(f >> 32);
+      return ((uint64_t)or_shifted<kWaveShl1>(or_shifted<kWaveShr1>(hi, hi), hi) << 32) |
+             or_shifted<kWaveShl1>(or_shifted<kWaveShr1>(lo, lo), lo);
     }
   }
   // one breadth-first layer inside the cell set r
   __device__ __forceinline__ W grow(W f, W r) const { return dilate(f) & r; }
+  // the four-neighbour dilation of a cell set (the set itself included), not masked
+  __device__ __forceinline__ W dilate(W f) const { return with_above_below(f) | (W)(f << 1) | (W)(f >> 1); }
   // one layer of king's moves inside the cell set r
   __device__ __forceinline__ W grow8(W f, W r) const {
-    const W v = f | from_above(f) | from_below(f);
+    const W v = with_above_below(f);
     return (v | (W)(v << 1) | (W)(v >> 1)) & r;
+  }
+  // Two breadth-first layers: `one` after the first, the result after the second.
+  __device__ __forceinline__ W grow_twice(W f, W r, W& one) const {
+    if constexpr (S == 64) {
+      one = grow(f, r);
+      return grow(one, r);
+    } else {
+      uint32_t two, t, u;
+      if constexpr (S == 16)
+        asm(PCGRL_LAYER16("%4", "%0", "%5") PCGRL_LAYER16("%0", "%1", "%5")
+            : "=&v"(one), "=&v"(two), "=&v"(t), "=&v"(u) : "v"(f), "v"(r));
+      else
+        asm(PCGRL_LAYER32("%4", "%0", "%5") PCGRL_LAYER32("%0", "%1", "%5")
+            : "=&v"(one), "=&v"(two), "=&v"(t), "=&v"(u) : "v"(f), "v"(r));
+      return two;
+    }
+  }
+  // N layers of king's moves of two sets side by side; a1 and b1 are what they were one layer earlier.
+  template <int N> __device__ __forceinline__ void grow8_both(W& a, W& b, W& a1, W& b1, W r) const {
+    static_assert(N == 2 || N == 4, "written out for two and for four layers");
+    a1 = a;
+    b1 = b;
+    if constexpr (S == 64) {
+#pragma unroll
+      for (int l = 0; l < N - 1; ++l) {
+        a1 = grow8(a1, r);
+        b1 = grow8(b1, r);
+      }
+      a = grow8(a1, r);
+      b = grow8(b1, r);
+    } else {
+      uint32_t u, v, x, y;
+#define PCGRL_OPERANDS : "=&v"(a), "=&v"(b), "+&v"(a1), "+&v"(b1), "=&v"(u), "=&v"(v), "=&v"(x), "=&v"(y) : "v"(r)
+      if constexpr (S == 16 && N == 2)
+        asm("s_nop 1\n\t" PCGRL_KINGS16("%2", "%3") PCGRL_KINGS16("%0", "%1") PCGRL_OPERANDS);
+      else if constexpr (S == 16)
+        asm("s_nop 1\n\t" PCGRL_KINGS16("%2", "%3") PCGRL_KINGS16("%2", "%3") PCGRL_KINGS16("%2", "%3")
+            PCGRL_KINGS16("%0", "%1") PCGRL_OPERANDS);
+      else if constexpr (N == 2)
+        asm("s_nop 1\n\t" PCGRL_KINGS32("%2", "%3") PCGRL_KINGS32("%0", "%1") PCGRL_OPERANDS);
+      else
+        asm("s_nop 1\n\t" PCGRL_KINGS32("%2", "%3") PCGRL_KINGS32("%2", "%3") PCGRL_KINGS32("%2", "%3")
+            PCGRL_KINGS32("%0", "%1") PCGRL_OPERANDS);
+#undef PCGRL_OPERANDS
+    }
   }
   // bits of a wave ballot that belong to this lane's group, moved down to bit 0
   __device__ __forceinline__ uint64_t gbits(uint64_t ballot) const {
@@ -333,8 +413,8 @@ __device__ __forceinline__ int sweep(const Lanes<S>& L, typename RowWord<S>::T s
   W V = seed, added = seed;
   int k = 0, k_last = 0;  // pairs done; the pair that last added cells in this lane
   auto pair_of_layers = [&]() {
-    W V1 = L.grow(V, pass);
-    W V2 = L.grow(V1, pass);
+    W V1;
+    const W V2 = L.grow_twice(V, pass, V1);
     k += 1;
     if (V2 != V) {
       added = V2 ^ V;
@@ -368,8 +448,8 @@ __device__ __forceinline__ int eccentricity(const Lanes<S>& L, typename RowWord<
   W V = seed;
   int k = 0, k1 = 0, k2 = 0;  // pairs done; the pairs whose first / second layer last reached this lane
   auto pair_of_layers = [&]() {
-    W V1 = L.grow(V, pass);
-    W V2 = L.grow(V1, pass);
+    W V1;
+    const W V2 = L.grow_twice(V, pass, V1);
     k += 1;
     if (V1 != V) k1 = k;
     const bool grew = V2 != V1;
@@ -436,7 +516,7 @@ __device__ __forceinline__ int nearest(const Lanes<S>& L, typename RowWord<S>::T
     constexpr int N = decltype(n_tag)::value;
     W layer[N];
 #pragma unroll
-    for (int l = 0; l < N; ++l) layer[l] = L.grow(l == 0 ? V : layer[l - 1], pass);
+    for (int l = 0; l < N; l += 2) layer[l + 1] = L.grow_twice(l == 0 ? V : layer[l - 1], pass, layer[l]);
     const bool ch = layer[N - 1] != layer[N - 2];
     V = layer[N - 1];
     const bool hit = d < 0 && L.gany((V & tgt) != 0);
@@ -478,7 +558,7 @@ __device__ __forceinline__ void nearest_two(const Lanes<S>& L, typename RowWord<
     constexpr int N = decltype(n_tag)::value;
     W layer[N];
 #pragma unroll
-    for (int l = 0; l < N; ++l) layer[l] = L.grow(l == 0 ? V : layer[l - 1], pass);
+    for (int l = 0; l < N; l += 2) layer[l + 1] = L.grow_twice(l == 0 ? V : layer[l - 1], pass, layer[l]);
     const bool ch = layer[N - 1] != layer[N - 2];
     V = layer[N - 1];
     const bool hit_a = d_a < 0 && L.gany((V & tgt_a) != 0);
@@ -586,14 +666,8 @@ __device__ __forceinline__ int components_around(const Lanes<S>& L, typename Row
       bool meet;
       auto trip = [&](auto n_tag) {
         constexpr int N = decltype(n_tag)::value;
-        W A1 = A, B1 = B;
-#pragma unroll
-        for (int l = 0; l < N - 1; ++l) {
-          A1 = L.grow8(A1, walls);
-          B1 = L.grow8(B1, walls);
-        }
-        A = L.grow8(A1, walls);
-        B = L.grow8(B1, walls);
+        W A1, B1;
+        L.template grow8_both<N>(A, B, A1, B1, walls);
         if (L.gany((A & edge) != 0)) A |= edge;
         if (L.gany((B & edge) != 0)) B |= edge;
         const bool grew_a = L.gany(A != A1), grew_b = L.gany(B != B1);
