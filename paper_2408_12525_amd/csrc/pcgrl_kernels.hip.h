@@ -588,26 +588,71 @@ __device__ __forceinline__ void nearest_two(const Lanes<S>& L, typename RowWord<
   while (more) more = trip(std::integral_constant<int, 4>{});
 }
 
-// Number of 4-connected components of `pass`, by parallel shrinking (Levialdi's algorithm in its
-// 4-connectivity form).  One step, on every cell at once: a cell stays if its left or its lower
-// neighbour is set, and an empty cell is filled if its left, lower and lower-left neighbours all
-// are; this moves every component towards the lower left corner of its bounding box without ever
-// joining two or splitting one, until it is a single cell with no neighbour, which the next step
-// deletes.  The count is the number of such cells met on the way.  A level of h x w cells is empty
-// after h + w - 1 steps, whatever its components look like, where a flood needs one layer per edge
-// of the longest shortest path.  Steps on an empty level do nothing, so they run four to a trip.
+// The cells of a level that lie on its border (next to nothing on some side).
 template <int S>
-__device__ __forceinline__ int regions_full(const Lanes<S>& L, typename RowWord<S>::T pass) {
+__device__ __forceinline__ typename RowWord<S>::T border_cells(const Lanes<S>& L, typename RowWord<S>::T inside) {
   using W = typename RowWord<S>::T;
+  return inside & ~(L.from_above(inside) & L.from_below(inside) & (W)(inside << 1) & (W)(inside >> 1));
+}
+
+// Number of 4-connected components of `pass`, the walkable cells of a level.
+//
+// In the plane it is the Euler number - cells less neighbouring pairs plus 2 x 2 squares, which every
+// lane counts for its row - plus the number of holes, i.e. of components of the walls, diagonal steps
+// included, that do not reach the outside.  A flood of king's moves from the border through the walls
+// leaves the walls of the holes; those are counted by parallel shrinking (Levialdi's algorithm): in one
+// step, on every cell at once, a cell stays if its left, lower or lower-left neighbour is set, and an
+// empty cell is filled if its left and its lower neighbour are; this moves every component towards the
+// lower left corner of its bounding box without joining two or splitting one, until it is a single
+// cell with no neighbour, which the next step deletes: the count is the number of such cells met on
+// the way.  Holes are few and small where the walkable region itself, shrunk the same way (in the
+// 4-connected form: a cell stays if its left or its lower neighbour is set, an empty one is filled if
+// left, lower and lower-left all are), takes up to h + w - 1 steps: on generated 64x64 levels with 45 %
+// walls 43 layers of 10 vector instructions and 11 steps of 23 against 67 steps of 20, with 25 % 13 and
+// 22 against 126.  Shrinking the walkable cells remains for levels of mostly walls (`open` false), whose
+// components are small, and for those whose walls wind so much that the flood takes more than 2 S
+// layers; it needs no more than 2 S steps whatever the level looks like.  8192 generated 64x64 maze levels,
+// reset with observations: 59.0 -> 47.6 us against shrinking the walkable cells throughout.
+template <int S>
+__device__ __forceinline__ int regions_full(const Lanes<S>& L, typename RowWord<S>::T pass, typename RowWord<S>::T inside,
+                                            bool open) {
+  using W = typename RowWord<S>::T;
+  if (wave_any<S>(open)) {
+    const W walls = inside & ~pass;
+    W out = walls & border_cells<S>(L, inside);
+    bool more = true;
+    for (int trip = 0; trip < S / 2 && more; ++trip) {
+      W before = out;
+#pragma unroll
+      for (int n = 0; n < 3; ++n) before = L.grow8(before, walls);
+      out = L.grow8(before, walls);
+      more = wave_any<S>(out != before);
+    }
+    if (!more) {
+      const W down = pass & L.from_above(pass);
+      int count = popc(pass) - popc((W)(pass & (W)(pass >> 1))) - popc(down) + popc((W)(down & (W)(down >> 1)));
+      W p = walls & ~out;
+      while (wave_any<S>(p != 0)) {  // (at most 2 S steps)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const W left = (W)(p << 1), below = L.from_below(p);
+          const W beside = left | (W)(p >> 1), three = beside | p;
+          count += popc((W)(p & ~(beside | L.from_above(three) | L.from_below(three))));
+          p = (p & (left | below | (W)(below << 1))) | (left & below);
+        }
+      }
+      return L.gsum(count);
+    }
+  }
   W p = pass;
   int vanished = 0;  // this row's share of the count
   for (int trip = 0; trip < S / 2 && wave_any<S>(p != 0); ++trip) {  // (2 S steps: more than any level needs)
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
       const W left = (W)(p << 1), below = L.from_below(p);
-      const W alone = p & ~(left | (W)(p >> 1) | below | L.from_above(p));
-      vanished += popc(alone);
-      p = (p & (left | below)) | (left & below & (W)(below << 1));
+      const W keep = p & (left | below);
+      vanished += popc((W)(p & ~(keep | (W)(p >> 1) | L.from_above(p))));
+      p = keep | (below & (W)((W)(p & below) << 1));
     }
   }
   return L.gsum(vanished);
@@ -652,7 +697,7 @@ __device__ __forceinline__ int components_around(const Lanes<S>& L, typename Row
     const uint32_t seed = mid | L.from_below32(wall_starts & 7u) | L.from_above32((__brev(wall_starts) >> 25) & 7u);
     const W walls = go ? inside & ~(pass | cell) : (W)0;
     W U = (px > 0 ? (W)seed << (px - 1) : (W)(seed >> 1)) & walls;
-    const W edge = walls & ~(L.from_above(inside) & L.from_below(inside) & (W)(inside << 1) & (W)(inside >> 1));
+    const W edge = walls & border_cells<S>(L, inside);
     // wall arcs still to be taken: those of which U holds a cell, and all that lie outside as one
     const uint32_t off_map = (py == 0 ? 0x07u : 0u) | (py == h - 1 ? 0x70u : 0u) | (px == 0 ? 0xc1u : 0u) | (px == w - 1 ? 0x1cu : 0u);
     bool out = go && (all & off_map & 0xffu) != 0;
@@ -700,7 +745,10 @@ __device__ __forceinline__ void full_metrics(const Lanes<S>& L,
   W pass = in & ~wall;
 #pragma unroll
   for (int k = 0; k < PR::K; ++k) m[PR::CNT + k] = L.gsum(popc(channel_row<PROBLEM, W>(p, in, k)));
-  m[0] = regions_full<S>(L, pass);
+  int cells = 0;
+#pragma unroll
+  for (int k = 0; k < PR::K; ++k) cells += m[PR::CNT + k];
+  m[0] = regions_full<S>(L, pass, in, 5 * m[PR::CNT + 1] <= 3 * cells);
   if constexpr (PROBLEM == kBinary) {
     m[1] = two_sweep_diameter<S>(L, pass, comp);
   } else if constexpr (PROBLEM == kMaze) {
@@ -730,6 +778,11 @@ __device__ __forceinline__ uint32_t control_target(const KArgs& a, uint64_t key,
   return pack_range(v, v);
 }
 
+template <typename W> __device__ __forceinline__ W inside_row(int y, int h, int w) {
+  W full = w >= (int)(8 * sizeof(W)) ? (W)~(W)0 : (W)(((W)1 << w) - 1);
+  return y < h ? full : (W)0;
+}
+
 // ---------------------------------------------------------------- episodes
 
 // Start of an episode: shape, tiles, pinpoints, first position, all from the env's key.
@@ -749,19 +802,51 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
   for (int k = 0; k < 8; ++k) empty_start = empty_start && a.cdf[k] == 0;
 #pragma unroll
   for (int i = 0; i < PR::P; ++i) p[i] = 0;
-  auto cells = [&](uint64_t k, int x0, int x1, int dx, W (&out)[PR::P]) {  // this row's cells x0, x0+dx, ... < x1
-    for (int x = x0; x < x1; x += dx) {
-      uint32_t r = (uint32_t)(draw(k, 1, (uint32_t)(L.y * a.max_w + x)) >> 32);
-      int tile = 0;  // thresholds are non-decreasing: the first one above r = how many are <= r
+  // Bits x0 .. x0 + n - 1 of this row (n <= 32 and the same in all lanes), as they would be in a level
+  // of any size.  Bound by vector instructions, seven of the 22 or so a cell being 32-bit multiplications
+  // of the hash.  The rest is kept short: the counter goes down by one constant, so that a cell's bits
+  // are shifted into 32-bit words from the right, as the carry of an addition, and end up in place,
+  // and the thresholds, which are non-decreasing, are searched instead of counted (8192 64x64 maze levels,
+  // reset with observations: 65.1 -> 57.1 us when this loop was brought in, 47.6 -> 46.3 with the carries).
+  auto draw_cells = [&](uint64_t k, int x0, int n, uint32_t (&acc)[PR::P]) {
 #pragma unroll
-      for (int k2 = 0; k2 < PR::K - 1; ++k2) tile += r >= a.cdf[k2] ? 1 : 0;
-#pragma unroll
-      for (int i = 0; i < PR::P; ++i) out[i] |= (W)((tile >> i) & 1) << x;
+    for (int i = 0; i < PR::P; ++i) acc[i] = 0;
+    uint64_t z = k + kGolden * ((1ull << 32) + (uint64_t)(uint32_t)(L.y * a.max_w + x0 + n));
+    auto cell = [&](uint64_t zc) {
+      const uint32_t r = (uint32_t)(mix64(zc) >> 32);
+      // acc = 2 acc + bit, the bits of a cell in one block: as the carry of an addition a bit takes one
+      // instruction (a select and a shift otherwise); a comparison's result may be read two instructions
+      // after it, which the compiler does not see to inside the block
+      auto bits = [](bool c) { return __builtin_amdgcn_ballot_w64(c); };
+      uint64_t none;
+      if constexpr (PROBLEM == kBinary) {
+        asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(acc[0]), "=&s"(none) : "s"(bits(r >= a.cdf[0])));
+      } else if constexpr (PROBLEM == kMaze) {
+        const bool b1 = r >= a.cdf[1];
+        asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %2, %0, %0, %3\n\tv_addc_co_u32_e64 %1, %2, %1, %1, %4"
+            : "+v"(acc[0]), "+v"(acc[1]), "=&s"(none) : "s"(bits(r >= (b1 ? a.cdf[2] : a.cdf[0]))), "s"(bits(b1)));
+      } else {  // (tile 7 does not exist)
+        const bool b2 = r >= a.cdf[3];
+        const bool b1 = r >= (b2 ? a.cdf[5] : a.cdf[1]);
+        const bool b0 = r >= (b1 ? a.cdf[2] : b2 ? a.cdf[4] : a.cdf[0]);
+        asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %3, %0, %0, %4\n\tv_addc_co_u32_e64 %1, %3, %1, %1, %5\n\t"
+            "v_addc_co_u32_e64 %2, %3, %2, %2, %6"
+            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "=&s"(none)
+            : "s"(bits(b0) & ~(bits(b1) & bits(b2))), "s"(bits(b1)), "s"(bits(b2)));
+      }
+    };
+    int j = n;
+    for (; j >= 4; j -= 4, z -= 4 * kGolden) {  // (four hashes side by side)
+      cell(z);
+      cell(z - kGolden);
+      cell(z - 2 * kGolden);
+      cell(z - 3 * kGolden);
     }
+    for (; j > 0; --j, z -= kGolden) cell(z);
   };
   if constexpr (SHARED && (64 / S) > 1) {
     // Inside a step few levels of a wavefront restart at the same time, and the draws are what a
-    // restart costs: every lane group takes every G-th column of a restarting level, whichever
+    // restart costs: every lane group takes a G-th of the columns of a restarting level, whichever
     // group holds it, and the rows are put together across the groups afterwards.  Levels that
     // restart together take turns; copies of one level are served by the same turn.
     constexpr int G = 64 / S;
@@ -770,57 +855,38 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
       const int src = (int)__builtin_ctzll(todo);  // a lane of the first level still to do
       const uint64_t k = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), src) << 32) |
                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
-      const int kh = __builtin_amdgcn_readlane(h, src), kw = __builtin_amdgcn_readlane(w, src);
-      const int kenv = __builtin_amdgcn_readlane(envl, src);
-      W part[PR::P];
-#pragma unroll
-      for (int i = 0; i < PR::P; ++i) part[i] = 0;
-      if (L.y < kh) cells(k, L.g, kw, G, part);
+      const int kw = __builtin_amdgcn_readlane(w, src), kenv = __builtin_amdgcn_readlane(envl, src);
+      const int n = (kw + G - 1) / G;
+      uint32_t part[PR::P];
+      draw_cells(k, L.g * n, n, part);
       const bool mine = restart && envl == kenv;
 #pragma unroll
       for (int i = 0; i < PR::P; ++i) {
-        uint32_t v = (uint32_t)part[i];
+        uint32_t v = part[i] << (L.g * n);
         if constexpr (S == 16) v |= (uint32_t)Lanes<S>::xor16((int)v);
         v |= (uint32_t)__shfl_xor((int)v, 32);
         if (mine) p[i] = (W)v;
       }
       todo &= ~__builtin_amdgcn_ballot_w64(mine);
     }
-  } else {
-    // Bound by vector instructions, seven of the 25 or so a cell being 32-bit multiplications of the
-    // hash.  The rest is kept short: the counter goes down by one constant, so that a cell's bits are
-    // shifted into 32-bit words from the right and end up in place, and the thresholds, which are
-    // non-decreasing, are searched instead of counted (8192 64x64 maze levels, reset with
-    // observations: 65.1 -> 57.08 us).
-    if (!empty_start && L.y < h) {
+  } else if (!empty_start) {
+    int widest = __builtin_amdgcn_readfirstlane(w);
 #pragma unroll
-      for (int x0 = 0; x0 < S; x0 += 32) {
-        const int n = min(w - x0, 32);
-        if (n <= 0) break;
-        uint32_t acc[PR::P] = {};
-        uint64_t z = key + kGolden * ((1ull << 32) + (uint64_t)(uint32_t)(L.y * a.max_w + x0 + n));
-#pragma unroll 4
-        for (int j = 0; j < n; ++j, z -= kGolden) {
-          const uint32_t r = (uint32_t)(mix64(z) >> 32);
-          auto put = [&](int i, bool bit) { acc[i] = acc[i] + acc[i] + (bit ? 1u : 0u); };
-          if constexpr (PROBLEM == kBinary) {
-            put(0, r >= a.cdf[0]);
-          } else if constexpr (PROBLEM == kMaze) {
-            const bool b1 = r >= a.cdf[1];
-            put(0, r >= (b1 ? a.cdf[2] : a.cdf[0]));
-            put(1, b1);
-          } else {  // (tile 7 does not exist)
-            const bool b2 = r >= a.cdf[3];
-            const bool b1 = r >= (b2 ? a.cdf[5] : a.cdf[1]);
-            put(0, r >= (b1 ? a.cdf[2] : b2 ? a.cdf[4] : a.cdf[0]) && !(b2 && b1));
-            put(1, b1);
-            put(2, b2);
-          }
-        }
+    for (int g = 1; g < 64 / S; ++g) widest = max(widest, __builtin_amdgcn_readlane(w, g * S));
 #pragma unroll
-        for (int i = 0; i < PR::P; ++i) p[i] |= (W)acc[i] << x0;
-      }
+    for (int x0 = 0; x0 < S; x0 += 32) {
+      const int n = min(widest - x0, 32);
+      if (n <= 0) break;
+      uint32_t acc[PR::P];
+      draw_cells(key, x0, n, acc);
+#pragma unroll
+      for (int i = 0; i < PR::P; ++i) p[i] |= (W)acc[i] << x0;
     }
+  }
+  {
+    const W in = inside_row<W>(L.y, h, w);
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) p[i] &= in;
   }
   fz = 0;
   int placed = 0;
@@ -850,11 +916,6 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
     py = below((uint32_t)(u >> 32), h);
     px = below((uint32_t)u, w);
   }
-}
-
-template <typename W> __device__ __forceinline__ W inside_row(int y, int h, int w) {
-  W full = w >= (int)(8 * sizeof(W)) ? (W)~(W)0 : (W)(((W)1 << w) - 1);
-  return y < h ? full : (W)0;
 }
 
 // -------------------------------------------------------------- observation
@@ -1959,7 +2020,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
       const bool was_pass = old_code != 1, now_pass = act != 1;
       // regions
       if (a.regions_mode == kRegionsRecount) {
-        int rc = regions_full<S>(L, pass);
+        int rc = regions_full<S>(L, pass, in, true);
         if (changed) regions_new = rc;
       } else {
         const bool flip = changed && was_pass != now_pass;

@@ -178,6 +178,94 @@ def test_exact_diameter_components_in_both_words_of_a_row(parts_log2):
     gpu.close()
 
 
+@pytest.mark.parametrize("problem,h,w,per_wave", [
+    (wl.BINARY, 16, 16, 0), (wl.MAZE, 16, 16, 1), (wl.DUNGEON, 5, 3, 4), (wl.BINARY, 3, 3, 2), (wl.BINARY, 1, 7, 4), (wl.MAZE, 9, 2, 0),
+    (wl.BINARY, 32, 32, 2), (wl.DUNGEON, 32, 9, 1), (wl.MAZE, 17, 31, 2), (wl.BINARY, 64, 64, 0), (wl.DUNGEON, 2, 64, 0), (wl.MAZE, 64, 33, 0),
+    (wl.BINARY, 64, 1, 0)])
+def test_every_ring_around_the_edited_cell(problem, h, w, per_wave):
+    """The region update after one edit, for all 256 patterns of walls around the cell, in the middle
+    of a map, on each side and in each corner of it (where the ring is partly outside), in random
+    surroundings from open to dense; the cell walled up and opened."""
+    rng = np.random.default_rng(10 * h + w)
+    ys, xs = sorted({0, h // 2, h - 1}), sorted({0, w // 2, w - 1})
+    places = [(y, x) for y in ys for x in xs]
+    ring = [(-1, -1), (-1, 0), (-1, 1), (0, 1), (1, 1), (1, 0), (1, -1), (0, -1)]
+    levels, pos, acts = [], [], []
+    for y, x in places:
+        for pattern in range(256):
+            t = (rng.random((h, w)) < rng.choice([.2, .4, .5])).astype(np.int8)
+            for b, (dy, dx) in enumerate(ring):
+                if 0 <= y + dy < h and 0 <= x + dx < w:
+                    t[y + dy, x + dx] = pattern >> b & 1
+            t[y, x] = pattern & 1 ^ (y + x) & 1
+            levels.append(t)
+            pos.append((y, x))
+            acts.append(1 - t[y, x])
+    B = len(levels)
+    cfg = wl.make_config(problem, B, h, 5, max_w=w, min_size=1, min_w=1, autoreset=0, levels_per_wave=per_wave)
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    gpu.pcgrl_reset(3)
+    cpu.reset(3)
+    tiles, hw = np.stack(levels), np.tile(np.array([h, w], np.int16), (B, 1))
+    pos, acts = np.array(pos, np.int16), np.array(acts, np.int32)
+    gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, torch.from_numpy(hw).to(DEV), torch.from_numpy(pos).to(DEV))
+    cpu.set_state(tiles, None, hw, pos)
+    assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "before the edit")
+    gpu.pcgrl_step(torch.from_numpy(acts).to(DEV))
+    cpu.step(acts, want_obs=False)
+    assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "after the edit")
+    gpu.close()
+
+
+def _spiral(n):
+    """A corridor that winds inwards and the wall beside it, each one cell wide."""
+    t = np.ones((n, n), np.int8)
+    y, x, dy, dx = 0, 0, 0, 1
+    t[0, 0] = 0
+    while True:
+        for _ in range(2):  # straight on, or round the corner once
+            a, b, c, d = y + dy, x + dx, y + 2 * dy, x + 2 * dx
+            if 0 <= a < n and 0 <= b < n and t[a, b] == 1 and not (0 <= c < n and 0 <= d < n and t[c, d] == 0):
+                break
+            dy, dx = dx, -dy
+        else:
+            return t
+        y, x = y + dy, x + dx
+        t[y, x] = 0
+
+
+@pytest.mark.parametrize("n", [16, 31, 64])
+def test_regions_of_winding_walls(n):
+    """The from-scratch region count where a flood through the walls takes longer than it is allowed
+    to (next to levels where it does not, some in the same wavefront), and edits along such walls."""
+    spiral = _spiral(n)
+    cut = spiral.copy()
+    cut[n // 2] = 1
+    wall_only = 1 - spiral
+    comb = np.ones((n, n), np.int8)
+    comb[1::2, 1:] = 0
+    few = np.zeros((n, n), np.int8)
+    few[n // 3, n // 4:n // 2] = 1
+    levels = [spiral, few, cut, wall_only, comb, spiral.T.copy(), np.ones_like(few), np.zeros_like(few), spiral[::-1, ::-1].copy()]
+    tiles = np.stack(levels * 3)
+    B = len(tiles)
+    hw, pos = np.full((B, 2), n, np.int16), np.random.default_rng(n).integers(0, n, (B, 2)).astype(np.int16)
+    for mode in (wl.REGIONS_INCREMENTAL, wl.REGIONS_RECOUNT):
+        cfg = wl.make_config(wl.BINARY, B, n, 5, autoreset=0, pos_mode=wl.POS_RANDOM, levels_per_wave=4, regions_mode=mode)
+        gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+        gpu.pcgrl_reset(3)
+        cpu.reset(3)
+        gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, torch.from_numpy(hw).to(DEV), torch.from_numpy(pos).to(DEV))
+        cpu.set_state(tiles, None, hw, pos)
+        assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), "set_state")
+        acts = wl.random_actions(cfg, 5, 40)
+        for t in range(40):
+            gpu.pcgrl_step(torch.from_numpy(acts[t]).to(DEV))
+            cpu.step(acts[t], want_obs=False)
+            assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"step {t}")
+        gpu.close()
+
+
 @pytest.mark.parametrize("problem", [wl.BINARY, wl.MAZE, wl.DUNGEON])
 @pytest.mark.parametrize("B,h,w", [(5, 1, 1), (37, 16, 15), (9, 3, 31), (33, 32, 32), (7, 5, 33), (6, 64, 63), (5, 64, 64)])
 def test_drawn_levels(problem, B, h, w):
