@@ -144,7 +144,8 @@ typedef struct {
                            (each keeps its own copy of the levels and writes the observation of
                            every n-th step).  Pays where the batch leaves most of the chip idle:
                            the automatic choice takes turns only while every wavefront still has
-                           a SIMD to itself; a workgroup holds at most four observation wavefronts */
+                           a SIMD to itself, and for small batches shares the searches for the metrics
+                           out in the same way; a workgroup holds at most four observation wavefronts */
 } pcgrl_config;
 
 #define PCGRL_OBS_PITCH_LINES (-1)

@@ -37,7 +37,8 @@ enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
 // step kernel variants: one step per launch; the same with the work of a wavefront split over
 // two (a metrics wavefront and an observation wavefront per workgroup); n steps per launch; n steps
 // per launch split the same way
-// (split variants: a metrics wavefront and observation wavefronts per workgroup)
+// (split variants: a metrics wavefront and observation wavefronts per workgroup); and n steps with the
+// metrics searched by several wavefronts in turn (see rollout_relay_kernel)
 enum : int { kModeStep = 0, kModeSplit = 1, kModeRollout = 2, kModeRolloutSplit = 3 };
 
 // Per-environment scalars, 32 bytes, read and written as two 16-byte words.
@@ -64,7 +65,7 @@ struct KArgs {
   int32_t envs_per_wave_log2;  // bits 0-7: log2 of the distinct levels per wavefront (at most 64 / S);
                                // bits 8-15, split step only: the same for an observation wavefront;
                                // bits 16-23, split rollout only: log2 of the observation wavefronts
-                               // that take the steps in turn
+                               // that take the steps in turn; bits 24-30: of the searching wavefronts
   int32_t use_frozen;     // 0: no level of this context has a pinpoint cell; bit 1: a step needs the pinpoint rows (they are shown in the observation)
   uint8_t* obs;
   float* reward;
@@ -1597,6 +1598,77 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   if (wave == 0 && wm.primary && L.y == 0) out[wm.env] = shared_best[wm.sl.slot];
 }
 
+// What a modifying edit does to the metrics that have to be searched for.  `regions`: by how much the
+// region count changes, or the new count in recount mode; `searched`: whether path (and enemy) are the
+// new values, otherwise they are as before.  Binary problem: `comp`, the component of the first
+// walkable cell before the edit if `comp_known`, becomes that after it.  (p, inside: the level after the
+// edit; nothing is asked of a level that did not change.)
+struct Moved {
+  int regions, path, enemy;
+  bool searched;
+};
+template <int S, int PROBLEM>
+__device__ __forceinline__ Moved after_edit(bool recount, const Lanes<S>& L, const typename RowWord<S>::T (&p)[Prob<PROBLEM>::P],
+                                            typename RowWord<S>::T inside, bool changed, int old_code, int act, int h, int w,
+                                            int py, int px, typename RowWord<S>::T& comp, bool comp_known) {
+  using W = typename RowWord<S>::T;
+  Moved mv = {0, 0, 0, false};
+  const bool at_row = L.y == py;
+  const W in = changed ? inside : (W)0;  // unchanged levels look empty: their loops end at once
+  const W wall = channel_row<PROBLEM, W>(p, in, 1);
+  const W pass = in & ~wall;
+  const bool was_pass = old_code != 1, now_pass = act != 1;
+  // regions
+  if (recount) {
+    mv.regions = regions_full<S>(L, pass, in, true);
+  } else {
+    const bool flip = changed && was_pass != now_pass;
+    if (wave_any<S>(flip)) {
+      const W cell = (flip && at_row) ? (W)1 << px : (W)0;
+      const int k = components_around<S>(L, flip ? (W)(pass & ~cell) : (W)0, inside, cell, h, w, py, px);
+      if (flip) mv.regions = now_pass ? 1 - k : k - 1;
+    }
+  }
+  // paths
+  if constexpr (PROBLEM == kBinary) {
+    // (every modifying edit of a binary level flips the walkability of its cell)
+    const W cell = (changed && at_row) ? (W)1 << px : (W)0;
+    const bool untouched = diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, now_pass);
+    const bool need = changed && !(comp_known && untouched);
+    if (wave_any<S>(need)) {
+      W ncomp;
+      const int dm = two_sweep_diameter<S>(L, need ? pass : (W)0, ncomp);
+      if (need) {
+        comp = ncomp;
+        mv.path = dm;
+      }
+    }
+    mv.searched = need;
+  } else if constexpr (PROBLEM == kMaze) {
+    W r;
+    const int dd = nearest<S>(L, channel_row<PROBLEM, W>(p, in, 2), channel_row<PROBLEM, W>(p, in, 3), pass, r);
+    mv.path = dd < 0 ? 0 : dd;
+    mv.searched = changed;
+  } else {
+    // swapping empty and chest changes neither the graph nor any source or target set
+    const bool plain = (old_code == 0 || old_code == 6) && (act == 0 || act == 6);
+    const bool need = changed && !plain;
+    if (wave_any<S>(need)) {
+      const W inn = need ? in : (W)0;
+      const W passn = need ? pass : (W)0;
+      W k1, r;
+      int d1, de;
+      nearest_two<S>(L, channel_row<PROBLEM, W>(p, inn, 2), channel_row<PROBLEM, W>(p, inn, 3),
+                     channel_row<PROBLEM, W>(p, inn, 5), passn, d1, k1, de);
+      const int d2 = nearest<S>(L, k1, channel_row<PROBLEM, W>(p, inn, 4), passn, r);
+      mv.path = (d1 >= 0 && d2 >= 0) ? d1 + d2 : 0;
+      mv.enemy = de < 0 ? 0 : de;
+    }
+    mv.searched = need;
+  }
+  return mv;
+}
+
 // The observation wavefront of the split kernel: loads the level, applies the edit in registers
 // (it stores nothing but the observation), finds the agent's next cell and writes the window
 // around it.  It reads what the metrics wavefront of the same workgroup reads, and the workgroup
@@ -1692,6 +1764,23 @@ __device__ __forceinline__ void obs_wave_step(KArgs& a, const Lanes<S>& L, WaveM
   observe<S, PROBLEM, true, true, WIDTH>(a, L, wm, pl, p, fz, inside, qy, qx);
 }
 
+// Says that values have arrived: whatever loads them is waited for here and not, as the compiler would
+// have it, at their first use inside a loop, where the wait would be one for everything that the
+// loop's own stores have not finished yet, in every iteration.
+template <typename T> __device__ __forceinline__ void arrived(T& v) {
+  if constexpr (sizeof(T) == 8) {
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)((uint64_t)v >> 32);
+    asm volatile("" : "+v"(lo), "+v"(hi));
+    v = (T)(((uint64_t)hi << 32) | lo);
+  } else {
+    asm volatile("" : "+v"(v));
+  }
+}
+template <typename T, typename... R> __device__ __forceinline__ void arrived(T& v, R&... rest) {
+  arrived(v);
+  arrived(rest...);
+}
+
 // The observation wavefront of a split rollout.  It needs nothing from the metrics wavefront: what
 // an observation shows -- the edited level, the agent's next cell, a restarted episode -- follows
 // from the loaded state, the seeds and the action stream alone, so this wavefront carries its own
@@ -1716,7 +1805,7 @@ __device__ __forceinline__ void obs_wave_rollout(const KArgs& a, const Lanes<S>&
   for (int i = 0; i < PR::P; ++i) p[i] = planes[(size_t)i * a.plane_stride + ridx];
   W fz = reinterpret_cast<const W*>(a.frozen)[ridx];
   const uint4* erp = reinterpret_cast<const uint4*>(a.env + wm.envl);
-  const uint4 er0 = erp[0], er1 = erp[1];
+  uint4 er0 = erp[0], er1 = erp[1];
   int act = a.actions[wm.envl];
   __builtin_amdgcn_sched_barrier(0);
   // (the metrics wavefront stores the final state only after this barrier, and the barrier comes
@@ -1724,6 +1813,9 @@ __device__ __forceinline__ void obs_wave_rollout(const KArgs& a, const Lanes<S>&
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < PR::P; ++i) arrived(p[i]);
+  arrived(fz, er0.x, er0.y, er0.z, er0.w, er1.x, er1.y, act);
 
   int h = (int)(er0.x & 0xffu), w = (int)((er0.x >> 8) & 0xffu);
   int py = (int)((er0.x >> 16) & 0xffu), px = (int)(er0.x >> 24);
@@ -1806,6 +1898,459 @@ __device__ __forceinline__ void obs_wave_rollout(const KArgs& a, const Lanes<S>&
     px = qx;
     act = act_next;
   }
+}
+
+// The sum over metrics, in index order, of weight * (old loss - new loss), in lane M - 1 of a lane group
+// whose lane k holds metric k, its range and its weight: every lane its own term; then M-1 times every
+// lane adds its term to what the lane before it holds, so that lane k ends with
+// ((t[k-M+1] + ...) + t[k-1]) + t[k], terms before the first lane counting as zero.
+template <int M> __device__ __forceinline__ float reward_of(int before, int after, uint32_t range, float weight) {
+  const int lo = (int)(range & 0xffffu), hi = (int)(range >> 16);
+  const int dl = loss(before, lo, hi) - loss(after, lo, hi);
+  const float term = __fmul_rn(weight, (float)dl);
+  float acc = __fadd_rn(0.0f, term);
+#pragma unroll
+  for (int j = 1; j < M; ++j) acc = __fadd_rn(__int_as_float((int)dpp_zero_fill<kRowShr1>((uint32_t)__float_as_int(acc))), term);
+  return acc;
+}
+
+// ---- Relay: a rollout of a small batch.
+// Its time is that of one dependent chain per step, and most of the machine is idle.  What the levels go
+// through (edits, restarts, where the agent goes) does not depend on the metrics, and the searches of
+// one step do not depend on those of another, so the wavefronts of a workgroup pass the steps of their
+// levels on to each other, kRelaySteps at a time through LDS:
+//   the leader    follows edits, counters, restarts and positions and writes them down;
+//   the searchers apply the edits of all steps and work the metrics out for every n-th;
+//   the observers do the same for the observations;
+//   the adder     sums the rewards up from what the searchers found and keeps the metric vectors.
+// While the leader is at one piece of the rollout, searchers and observers are at the piece before it and
+// the adder at the one before that; one barrier a piece.  256-step rollouts of 64 levels, us per step,
+// against one metrics wavefront and observation wavefronts that take turns: 16x16 binary 1.11 -> 0.62, 16x16
+// maze 0.88 -> 0.53, 32x32 dungeon 1.22 -> 0.48, 64x64 maze 1.08 -> 0.56.  What is left is the observers'
+// chain (without it 0.45 to 0.5) and the other wavefronts', none of which does much less.  Pieces of 8 steps
+// keep the three stages short for rollouts of a few steps (4 steps of 64 dungeon levels 2.56 -> 2.12 us each),
+// and give every searcher and observer two turns or more to even out.
+constexpr int kRelaySteps = 8;
+template <int S, int PROBLEM> struct RelayTables {
+  static constexpr int kLevels = 64 / S;  // of a workgroup, at most
+  // what the leader wrote down of a step: x bits 0-2 the action, 3-5 the tile it replaced, 6 the level
+  // changed, 7 the episode is done, 8 a new one begins; y the cell and the next one, a byte a number
+  uint2 trace[3][kRelaySteps][kLevels];
+  // what a searcher found (see Moved): x bit 0 path and enemy are new, bits 16-31 regions; y path | enemy << 16
+  uint2 found[2][kRelaySteps][kLevels];
+  // a new episode: its level (planes, pinpoints, height | width << 8) and its metrics; one a piece, since a
+  // relay is run only for episodes of kRelaySteps steps or more
+  typename RowWord<S>::T rows[3][kLevels][Prob<PROBLEM>::P + 1][S];
+  int32_t hw[3][kLevels];
+  int32_t metrics[2][kLevels][kMaxMetrics];
+};
+constexpr uint32_t kTraceChanged = 1u << 6, kTraceDone = 1u << 7, kTraceRestart = 1u << 8;
+__device__ __forceinline__ int relay_pieces(int nsteps) { return (nsteps + kRelaySteps - 1) / kRelaySteps; }
+// (LDS traffic of the pieces only: what a wavefront has stored to memory need not have arrived)
+__device__ __forceinline__ void relay_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The leader.  Lane y of a level's lane group prepares step y of a piece: the action, and (random
+// positions) the cell the agent goes to after it, one hash for all the steps of all the levels.  The
+// lane of the edited row alone knows the old tile, and writes the step down.
+template <int S, int PROBLEM>
+__device__ __forceinline__ void relay_leader(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm, RelayTables<S, PROBLEM>& tables) {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  static_assert(kRelaySteps <= 16, "a lane for every step of a piece");
+  W* planes = reinterpret_cast<W*>(a.planes);
+  W* frozen = reinterpret_cast<W*>(a.frozen);
+  const size_t ridx = (size_t)wm.envl * S + L.y;
+  W p[PR::P];
+#pragma unroll
+  for (int i = 0; i < PR::P; ++i) p[i] = planes[(size_t)i * a.plane_stride + ridx];
+  W fz = frozen[ridx];
+  const uint4* erp = reinterpret_cast<const uint4*>(a.env + wm.envl);
+  uint4 er0 = erp[0], er1 = erp[1];
+  const int nsteps = a.rollout_steps, pieces = relay_pieces(nsteps);
+  auto action_of = [&](int piece) { return a.actions[(size_t)min(piece * kRelaySteps + (L.y & (kRelaySteps - 1)), nsteps - 1) * a.B + wm.envl]; };
+  int act_next = action_of(0);
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the final state is stored after the barrier)
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < PR::P; ++i) arrived(p[i]);
+  arrived(fz, er0.x, er0.y, er0.z, er0.w, er1.x, er1.y, act_next);
+  EnvRec er;
+  er.t = (int32_t)er0.y;
+  er.n_changes = (int32_t)er0.z;
+  er.episode = (int32_t)er0.w;
+  er.key = (uint64_t)er1.x | ((uint64_t)er1.y << 32);
+  er.pad_ = 0;
+  int h = (int)(er0.x & 0xffu), w = (int)((er0.x >> 8) & 0xffu), py = (int)((er0.x >> 16) & 0xffu), px = (int)(er0.x >> 24);
+  const bool random = a.pos_mode == kPosRandom;
+  int max_steps = a.max_steps, max_changes = a.max_changes, autoreset = a.autoreset;
+  asm volatile("" : "+s"(max_steps), "+s"(max_changes), "+s"(autoreset));
+  int buf = 0, row_changes = 0;
+  for (int piece = 0; piece < pieces; ++piece) {
+    const int n = min(kRelaySteps, nsteps - piece * kRelaySteps);
+    const int act_y = act_next;
+    act_next = action_of(piece + 1);  // (wanted a piece later)
+    const bool in_range_y = act_y >= 0 && act_y < PR::K;
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(wm.primary && L.y < n && !in_range_y);
+    if (bad != 0 && L.lane == 0) atomicAdd(a.bad_actions, (unsigned long long)__popcll(bad));
+    const uint32_t what_y = (uint32_t)(act_y & 7) << 16 | (in_range_y ? 1u << 19 : 0u);
+    auto prepared = [&](int i) {  // lane y: step y, the next one being step i
+      uint32_t v = what_y;
+      if (random) {
+        const uint64_t u = draw(er.key, 3, (uint32_t)(er.t + 1 + L.y - i));
+        v |= (uint32_t)below((uint32_t)(u >> 32), h) | (uint32_t)below((uint32_t)u, w) << 8;
+      }
+      return (int)v;
+    };
+    int steps_y = prepared(0);
+    uint32_t step_v = (uint32_t)L.gread_i(steps_y, 0);
+    for (int i = 0; i < n; ++i) {
+      const uint32_t v = step_v;
+      step_v = (uint32_t)L.gread_i(steps_y, i + 1);
+      const W cell = wm.valid && L.y == py ? (W)1 << px : (W)0;
+      const int act = (int)((v >> 16) & 7u);
+      int old_code = 0;
+#pragma unroll
+      for (int k = 0; k < PR::P; ++k) old_code |= (p[k] & cell) != 0 ? 1 << k : 0;
+      const bool changed = cell != 0 && (v >> 19 & 1u) != 0 && (fz & cell) == 0 && act != old_code;  // in the row's lane
+      if (changed) {
+#pragma unroll
+        for (int k = 0; k < PR::P; ++k) p[k] = (p[k] & ~cell) | ((act >> k) & 1 ? cell : (W)0);
+      }
+      er.t += 1;
+      bool done = er.t >= max_steps;
+      if (max_changes > 0) {
+        er.n_changes += L.gany(changed) ? 1 : 0;
+        done = done || er.n_changes >= max_changes;
+      } else {
+        row_changes += changed ? 1 : 0;  // (put together at the end)
+      }
+      const bool restart = wm.valid && done && autoreset != 0;
+      int qy = (int)(v & 0xffu), qx = (int)((v >> 8) & 0xffu);
+      if (!random) {
+        qy = py;
+        qx = px + 1;
+        if (qx >= w) {
+          qx = 0;
+          qy += 1;
+          if (qy >= h) qy = 0;
+        }
+      }
+      uint2 r;
+      r.x = (uint32_t)act | (uint32_t)old_code << 3 | (changed ? kTraceChanged : 0u) | (done ? kTraceDone : 0u) | (restart ? kTraceRestart : 0u);
+      const uint32_t here = (uint32_t)py | (uint32_t)px << 8;
+      const bool writer = wm.primary && L.y == py;
+      if (wave_any<S>(restart)) {
+        const KArgs& ra = cold_args<true>();
+        W np[PR::P], nfz;
+        int nh, nw, npy, npx;
+        const uint64_t nkey = env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)(er.episode + 1));
+        begin_episode<S, PROBLEM, true>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
+        if (restart) {
+#pragma unroll
+          for (int k = 0; k < PR::P; ++k) p[k] = np[k];
+          fz = nfz;
+          h = nh;
+          w = nw;
+          qy = npy;
+          qx = npx;
+          if (wm.primary) {
+#pragma unroll
+            for (int k = 0; k < PR::P; ++k) tables.rows[buf][wm.sl.slot][k][L.y] = np[k];
+            tables.rows[buf][wm.sl.slot][PR::P][L.y] = nfz;
+            if (L.y == 0) tables.hw[buf][wm.sl.slot] = nh | nw << 8;
+          }
+          er.key = nkey;
+          er.episode += 1;
+          er.t = 0;
+          er.n_changes = 0;
+          row_changes = 0;
+        }
+        steps_y = prepared(i + 1);
+        step_v = (uint32_t)L.gread_i(steps_y, i + 1);
+      }
+      r.y = here | (uint32_t)qy << 16 | (uint32_t)qx << 24;
+      if (writer) tables.trace[buf][i][wm.sl.slot] = r;
+      py = qy;
+      px = qx;
+    }
+    buf = buf == 2 ? 0 : buf + 1;
+    relay_barrier();
+  }
+  relay_barrier();
+  er.n_changes += L.gsum(row_changes);
+  if (wm.primary) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) planes[(size_t)i * a.plane_stride + ridx] = p[i];
+    frozen[ridx] = fz;
+  }
+  er.cell_frozen = L.gany(L.y == py && ((fz >> px) & 1)) ? 1u : 0u;
+  if (wm.primary && L.y == 0) {
+    er.h = (uint8_t)h;
+    er.w = (uint8_t)w;
+    er.py = (uint8_t)py;
+    er.px = (uint8_t)px;
+    a.env[wm.env] = er;
+  }
+}
+
+// What searchers and observers have in common: their own copy of the levels, taken through the traced
+// steps.
+template <int S, int PROBLEM> struct RelayFollower {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  W p[PR::P], fz, inside;
+  int h, w;
+  __device__ __forceinline__ void load(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm) {
+    const size_t ridx = (size_t)wm.envl * S + L.y;
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) p[i] = reinterpret_cast<const W*>(a.planes)[(size_t)i * a.plane_stride + ridx];
+    fz = reinterpret_cast<const W*>(a.frozen)[ridx];
+    const uint32_t hw = *reinterpret_cast<const uint32_t*>(a.env + wm.envl);
+    h = (int)(hw & 0xffu);
+    w = (int)((hw >> 8) & 0xffu);
+  }
+  __device__ __forceinline__ void loaded(const Lanes<S>& L) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) arrived(p[i]);
+    arrived(fz, h, w);
+    inside = inside_row<W>(L.y, h, w);
+  }
+  // (the lane of the row alone has a cell)
+  __device__ __forceinline__ void edit(W cell, int act) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) p[i] = (p[i] & ~cell) | ((act >> i) & 1 ? cell : (W)0);
+  }
+  __device__ __forceinline__ void restart(const Lanes<S>& L, const RelayTables<S, PROBLEM>& tables, int buf, int level) {
+#pragma unroll
+    for (int i = 0; i < PR::P; ++i) p[i] = tables.rows[buf][level][i][L.y];
+    fz = tables.rows[buf][level][PR::P][L.y];
+    const int hw = tables.hw[buf][level];
+    h = hw & 0xff;
+    w = hw >> 8;
+    inside = inside_row<W>(L.y, h, w);
+  }
+};
+
+// A searcher.  The change of the region count and the paths depend on the level before and after the
+// edit alone, and path values that an edit leaves as they are need not be known.  Binary problem: the
+// component of the first walkable cell is kept until an edit touches it, at whoever's turn, and searched
+// for again at the next own turn that needs it.
+template <int S, int PROBLEM>
+__device__ __forceinline__ void relay_searcher(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm, int turn, int turn_mask,
+                                               RelayTables<S, PROBLEM>& tables) {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  RelayFollower<S, PROBLEM> f;
+  f.load(a, L, wm);
+  W comp = 0;
+  if constexpr (PROBLEM == kBinary)
+    comp = reinterpret_cast<const W*>(a.planes)[(size_t)PR::P * a.plane_stride + (size_t)wm.envl * S + L.y];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  f.loaded(L);
+  arrived(comp);
+  bool comp_known = true;
+  int mode = a.regions_mode;
+  asm volatile("" : "+s"(mode));
+  const int nsteps = a.rollout_steps, pieces = relay_pieces(nsteps);
+  int buf = 0;
+  relay_barrier();
+  for (int piece = 0; piece < pieces; ++piece) {
+    const int n = min(kRelaySteps, nsteps - piece * kRelaySteps), half = piece & 1;
+    uint2 next = tables.trace[buf][0][wm.sl.slot];
+    for (int i = 0; i < n; ++i) {
+      const uint2 r = next;
+      next = tables.trace[buf][min(i + 1, n - 1)][wm.sl.slot];
+      const bool mine = ((piece * kRelaySteps + i) & turn_mask) == turn;
+      const int act = (int)(r.x & 7u), py = (int)(r.y & 0xffu), px = (int)((r.y >> 8) & 0xffu);
+      const bool changed = wm.valid && (r.x & kTraceChanged) != 0, restart = wm.valid && (r.x & kTraceRestart) != 0;
+      const W cell = changed && L.y == py ? (W)1 << px : (W)0;
+      f.edit(cell, act);
+      if (mine) {
+        Moved mv = {0, 0, 0, false};
+        if (wave_any<S>(changed)) {
+          mv = after_edit<S, PROBLEM>(mode == kRegionsRecount, L, f.p, f.inside, changed, (int)(r.x >> 3 & 7u), act, f.h, f.w, py, px, comp, comp_known);
+          comp_known = comp_known || mv.searched;
+        }
+        if (wm.primary && L.y == 0)
+          tables.found[half][i][wm.sl.slot] = make_uint2((mv.searched ? 1u : 0u) | (uint32_t)mv.regions << 16, (uint32_t)mv.path | (uint32_t)mv.enemy << 16);
+      } else if constexpr (PROBLEM == kBinary) {
+        if (wave_any<S>(changed && comp_known)) {
+          const bool untouched = diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, act != 1);
+          comp_known = comp_known && (!changed || untouched);
+        }
+      }
+      if (wave_any<S>(restart)) {
+        if (restart) f.restart(L, tables, buf, wm.sl.slot);
+        W ncomp = 0;
+        if (mine) {
+          int nm[PR::M];
+          full_metrics<S, PROBLEM>(L, f.p, f.inside, restart, nm, ncomp);
+          int v = 0;
+#pragma unroll
+          for (int k = 0; k < PR::M; ++k) v = L.y == k ? nm[k] : v;
+          if (restart && wm.primary && L.y < kMaxMetrics) tables.metrics[half][wm.sl.slot][L.y] = v;
+        }
+        if (restart) {
+          comp = ncomp;
+          comp_known = mine;
+        }
+      }
+    }
+    buf = buf == 2 ? 0 : buf + 1;
+    relay_barrier();
+  }
+  if constexpr (PROBLEM == kBinary) {  // the last turn's wavefront leaves the component behind
+    if (((nsteps - 1) & turn_mask) == turn) {
+      if (wave_any<S>(!comp_known)) {
+        const W pass = comp_known ? (W)0 : (W)(f.inside & ~channel_row<PROBLEM, W>(f.p, f.inside, 1));
+        W far, all;
+        sweep<S>(L, first_cell<S>(L, pass), pass, far, all);
+        comp = comp_known ? comp : all;
+      }
+      if (wm.primary) reinterpret_cast<W*>(a.planes)[(size_t)PR::P * a.plane_stride + (size_t)wm.envl * S + L.y] = comp;
+    }
+  }
+}
+
+// An observer.
+template <int S, int PROBLEM>
+__device__ __forceinline__ void relay_observer(KArgs a, const Lanes<S>& L, const WaveMap<S>& wm, int turn, int turn_mask,
+                                               int level0, const RelayTables<S, PROBLEM>& tables) {
+  using W = typename RowWord<S>::T;
+  const int nsteps = a.rollout_steps, pieces = relay_pieces(nsteps);
+  if (wm.env0 >= a.B) {  // the batch ends inside this workgroup: only the barriers are owed
+    __syncthreads();
+    for (int piece = 0; piece < pieces + 1; ++piece) relay_barrier();
+    return;
+  }
+  RelayFollower<S, PROBLEM> f;
+  f.load(a, L, wm);
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  f.loaded(L);
+  // (each a register of its own: the compiler would otherwise hold on to the whole pieces of the argument
+  // block they come in, and set stack space aside for those)
+  asm volatile("" : "+s"(a.env_obs_bytes), "+s"(a.obs_packed), "+s"(a.obs_frozen_channel), "+s"(a.stream_obs));
+  int slot = 0, buf = 0;
+  relay_barrier();
+  for (int piece = 0; piece < pieces; ++piece) {
+    const int n = min(kRelaySteps, nsteps - piece * kRelaySteps);
+    uint2 next = tables.trace[buf][0][level0 + wm.sl.slot];
+    for (int i = 0; i < n; ++i) {
+      const uint2 r = next;
+      next = tables.trace[buf][min(i + 1, n - 1)][level0 + wm.sl.slot];
+      const bool changed = wm.valid && (r.x & kTraceChanged) != 0, restart = wm.valid && (r.x & kTraceRestart) != 0;
+      f.edit(changed && L.y == (int)(r.y & 0xffu) ? (W)1 << (r.y >> 8 & 0xffu) : (W)0, (int)(r.x & 7u));
+      if (restart) f.restart(L, tables, buf, level0 + wm.sl.slot);
+      if (((piece * kRelaySteps + i) & turn_mask) == turn) {
+        // (the plan anew: kept from step to step it ties up scalar registers that this wavefront lacks)
+        const ObsPlan pl = obs_plan(a, L.lane, wm.sl, a.obs + (size_t)slot * ((size_t)a.B * (size_t)a.env_obs_bytes), wm.env0, wm.nvalid);
+        observe<S, PROBLEM, false, true>(a, L, wm, pl, f.p, f.fz, f.inside, (int)(r.y >> 16 & 0xffu), (int)(r.y >> 24));
+      }
+      slot = slot + 1 == a.obs_slots ? 0 : slot + 1;  // (step t writes slot t mod obs_slots)
+    }
+    buf = buf == 2 ? 0 : buf + 1;
+    relay_barrier();
+  }
+}
+
+// The adder.
+template <int S, int PROBLEM>
+__device__ __forceinline__ void relay_adder(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm, const RelayTables<S, PROBLEM>& tables) {
+  using PR = Prob<PROBLEM>;
+  const int yi = L.y & (kMaxMetrics - 1);
+  const size_t mrow = (size_t)wm.envl * kMaxMetrics;
+  int m_l = a.metrics[mrow + yi];
+  uint32_t tg_l = a.targets[mrow + yi];
+  float w_l = __uint_as_float((a.targets - kMaxMetrics)[yi]);  // (the row in front of the ranges)
+  int episode = a.env[wm.envl].episode;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  arrived(m_l, tg_l, w_l, episode);
+  const int nsteps = a.rollout_steps, pieces = relay_pieces(nsteps);
+  bool targets_dirty = false;
+  int buf = 0;
+  relay_barrier();
+  relay_barrier();
+  for (int piece = 0; piece < pieces; ++piece) {
+    const int n = min(kRelaySteps, nsteps - piece * kRelaySteps), half = piece & 1;
+    uint2 next = tables.trace[buf][0][wm.sl.slot], next_found = tables.found[half][0][wm.sl.slot];
+    for (int i = 0; i < n; ++i) {
+      const uint2 r = next, fd = next_found;
+      next = tables.trace[buf][min(i + 1, n - 1)][wm.sl.slot];
+      next_found = tables.found[half][min(i + 1, n - 1)][wm.sl.slot];
+      const bool changed = wm.valid && (r.x & kTraceChanged) != 0, searched = changed && (fd.x & 1u) != 0;
+      const int act = (int)(r.x & 7u), old_code = (int)(r.x >> 3 & 7u), regions = (int)fd.x >> 16;
+      const int k = yi - PR::CNT;
+      int mn_l = m_l + (changed && act == k ? 1 : 0) - (changed && old_code == k ? 1 : 0);
+      if (changed && yi == 0) mn_l = a.regions_mode == kRegionsRecount ? regions : m_l + regions;
+      if (searched && yi == 1) mn_l = (int)(fd.y & 0xffffu);
+      if (PROBLEM == kDungeon && searched && yi == 2) mn_l = (int)(fd.y >> 16);
+      const float acc = reward_of<PR::M>(m_l, mn_l, tg_l, w_l);
+      const size_t out = (size_t)(piece * kRelaySteps + i) * a.B + wm.env;
+      if (wm.primary && L.y == PR::M - 1 && a.reward) a.reward[out] = changed ? acc : 0.0f;
+      if (wm.primary && L.y == 0 && a.done) a.done[out] = (r.x & kTraceDone) != 0 ? 1 : 0;
+      const bool restart = wm.valid && (r.x & kTraceRestart) != 0;
+      if (wave_any<S>(restart)) {
+        if (restart) mn_l = tables.metrics[half][wm.sl.slot][yi];
+        const KArgs& ra = cold_args<true>();
+        if (restart && ra.ctrl_mask != 0) {
+          if ((ra.ctrl_mask >> yi) & 1u)
+            tg_l = control_target(ra, env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)(episode + 1)), yi);
+          targets_dirty = true;
+        }
+        episode += restart ? 1 : 0;
+      }
+      m_l = mn_l;
+    }
+    buf = buf == 2 ? 0 : buf + 1;
+    if (piece + 1 < pieces) relay_barrier();
+  }
+  if (wm.primary && L.y < PR::M) {
+    a.metrics[(size_t)wm.env * kMaxMetrics + L.y] = m_l;
+    if (targets_dirty) a.targets[(size_t)wm.env * kMaxMetrics + L.y] = tg_l;
+  }
+}
+
+template <int S, int PROBLEM>
+__global__ __launch_bounds__(640) void rollout_relay_kernel(KArgs a) {
+  extern __shared__ __align__(16) uint32_t lds_all[];
+  __shared__ RelayTables<S, PROBLEM> tables;
+  Lanes<S> L;
+  WaveMap<S> wm;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lg = a.envs_per_wave_log2 & 0xff, lgo = (a.envs_per_wave_log2 >> 8) & 0xff;
+  const int searchers = 1 << ((a.envs_per_wave_log2 >> 24) & 0x7f);
+  const int group = level_group_of_block<true>(a.by_die);
+  if (wid >= 2 + searchers) {
+    const int o = wid - 2 - searchers, share = o & ((1 << (lg - lgo)) - 1);
+    wm.init(a, L, lds_all + o * a.obs_lds_words, (group << (lg - lgo)) + share, lgo);
+    relay_observer<S, PROBLEM>(a, L, wm, o >> (lg - lgo), (1 << ((a.envs_per_wave_log2 >> 16) & 0xff)) - 1, share << lgo, tables);
+    __builtin_amdgcn_endpgm();
+  }
+  wm.init(a, L, lds_all, group, lg);
+  if (wid >= 2) {
+    relay_searcher<S, PROBLEM>(a, L, wm, wid - 2, searchers - 1, tables);
+    __builtin_amdgcn_endpgm();
+  }
+  if (wid == 1) {
+    relay_adder<S, PROBLEM>(a, L, wm, tables);
+    __builtin_amdgcn_endpgm();
+  }
+  relay_leader<S, PROBLEM>(a, L, wm, tables);
 }
 
 // The body of the two kernels below.  On entry `a` holds what a step needs to request its loads
@@ -2009,79 +2554,25 @@ __device__ __forceinline__ void step_body(KArgs& a) {
     int regions_new = regions_now;
     float reward = 0.0f;          // (ends up in lane M-1 of the group)
     if (wave_any<S>(changed)) {
-      const W in = changed ? inside : (W)0;  // unchanged levels look empty: their loops end at once
-      const W wall = channel_row<PROBLEM, W>(p, in, 1);
-      const W pass = in & ~wall;
       // tile counts: one cell moved from one tile type to another
       {
         const int k = yi - PR::CNT;  // the tile type whose count this lane keeps, if any
         mn_l += (changed && act == k ? 1 : 0) - (changed && old_code == k ? 1 : 0);
       }
-      const bool was_pass = old_code != 1, now_pass = act != 1;
-      // regions
-      if (a.regions_mode == kRegionsRecount) {
-        int rc = regions_full<S>(L, pass, in, true);
-        if (changed) regions_new = rc;
-      } else {
-        const bool flip = changed && was_pass != now_pass;
-        if (wave_any<S>(flip)) {
-          const W cell = (flip && at_row) ? (W)1 << px : (W)0;
-          const int k = components_around<S>(L, flip ? (W)(pass & ~cell) : (W)0, inside, cell, h, w, py, px);
-          if (flip) regions_new = regions_now + (now_pass ? 1 - k : k - 1);
-        }
-      }
+      const Moved mv = after_edit<S, PROBLEM>(a.regions_mode == kRegionsRecount, L, p, inside, changed, old_code, act, h, w, py, px, comp, true);
+      if (a.regions_mode == kRegionsRecount) regions_new = changed ? mv.regions : regions_now;
+      else regions_new = regions_now + mv.regions;
       if (yi == 0) mn_l = regions_new;
-      // paths
+      if (mv.searched && yi == 1) mn_l = mv.path;
+      if (PROBLEM == kDungeon && mv.searched && yi == 2) mn_l = mv.enemy;
       if constexpr (PROBLEM == kBinary) {
-        // (every modifying edit of a binary level flips the walkability of its cell)
-        const W cell = (changed && at_row) ? (W)1 << px : (W)0;
-        const bool need = changed && !diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, now_pass);
-        if (wave_any<S>(need)) {
-          W ncomp;
-          int dm = two_sweep_diameter<S>(L, need ? pass : (W)0, ncomp);
-          if (need) {
-            comp = ncomp;
-            comp_dirty = true;
-            if (yi == 1) mn_l = dm;
-            if constexpr (!ROLL) {
-              if (wm.primary) planes[(size_t)PR::P * a.plane_stride + ridx] = ncomp;
-            }
-          }
-        }
-      } else if constexpr (PROBLEM == kMaze) {
-        W r;
-        int dd = nearest<S>(L, channel_row<PROBLEM, W>(p, in, 2), channel_row<PROBLEM, W>(p, in, 3), pass, r);
-        if (changed && yi == 1) mn_l = dd < 0 ? 0 : dd;
-      } else {
-        // swapping empty and chest changes neither the graph nor any source or target set
-        const bool plain = (old_code == 0 || old_code == 6) && (act == 0 || act == 6);
-        const bool need = changed && !plain;
-        if (wave_any<S>(need)) {
-          const W inn = need ? in : (W)0;
-          const W passn = need ? pass : (W)0;
-          W k1, r;
-          int d1, de;
-          nearest_two<S>(L, channel_row<PROBLEM, W>(p, inn, 2), channel_row<PROBLEM, W>(p, inn, 3),
-                         channel_row<PROBLEM, W>(p, inn, 5), passn, d1, k1, de);
-          int d2 = nearest<S>(L, k1, channel_row<PROBLEM, W>(p, inn, 4), passn, r);
-          if (need && yi == 1) mn_l = (d1 >= 0 && d2 >= 0) ? d1 + d2 : 0;
-          if (need && yi == 2) mn_l = de < 0 ? 0 : de;
+        comp_dirty = comp_dirty || mv.searched;
+        if constexpr (!ROLL) {
+          if (mv.searched && wm.primary) planes[(size_t)PR::P * a.plane_stride + ridx] = comp;
         }
       }
-      // reward = sum over metrics, in index order, of weight * (old loss - new loss): every lane
-      // its own term; then M-1 times every lane adds its term to what the lane before it holds, so
-      // that lane k ends with ((t[k-M+1] + ...) + t[k-1]) + t[k], terms before the first lane
-      // counting as zero: in lane M-1 that is the sum in index order
-      {
-        const int lo = (int)(tg_l & 0xffffu), hi = (int)(tg_l >> 16);
-        const int dl = loss(m_l, lo, hi) - loss(mn_l, lo, hi);
-        const float term = __fmul_rn(w_l, (float)dl);
-        float acc = __fadd_rn(0.0f, term);
-#pragma unroll
-        for (int j = 1; j < PR::M; ++j)
-          acc = __fadd_rn(__int_as_float((int)dpp_zero_fill<kRowShr1>((uint32_t)__float_as_int(acc))), term);
-        if (changed) reward = acc;
-      }
+      const float acc = reward_of<PR::M>(m_l, mn_l, tg_l, w_l);
+      if (changed) reward = acc;
     }
     // ---- auto-reset: fresh seeded episode for the finished levels; the others keep their registers
     if (any_restart) {

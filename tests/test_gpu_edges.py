@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from parity import assert_same, compare_state
+from parity import assert_same, check_obs, compare_state
 from paper_2408_12525_amd import binding, workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -364,4 +364,43 @@ def test_every_argument_of_every_call_is_checked(wrong, packed):
             with pytest.raises(binding.PcgrlError):
                 method(*bad)
     torch.cuda.synchronize()
+    gpu.close()
+
+
+@pytest.mark.parametrize("problem,h,w,T,more", [
+    (wl.BINARY, 16, 16, 1, {}), (wl.BINARY, 16, 16, 7, dict(max_steps=8)), (wl.MAZE, 16, 16, 8, dict(max_steps=8)),
+    (wl.DUNGEON, 11, 16, 9, dict(max_steps=9, n_frozen=2)), (wl.BINARY, 32, 20, 17, dict(max_steps=11, min_size=5, min_w=5)),
+    (wl.MAZE, 32, 32, 16, dict(max_changes=8, obs_format=1)), (wl.DUNGEON, 32, 32, 33, dict(max_steps=8, max_changes=8, pos_mode=wl.POS_SCAN)),
+    (wl.BINARY, 64, 64, 24, dict(max_steps=13, n_frozen=3, min_size=20)), (wl.MAZE, 64, 40, 15, dict(autoreset=0, max_steps=4)),
+    (wl.DUNGEON, 64, 64, 25, dict(max_steps=10, regions_mode=wl.REGIONS_RECOUNT)),
+    # episodes that end twice within a piece of a relay
+    (wl.BINARY, 16, 16, 20, dict(max_steps=3)), (wl.MAZE, 32, 32, 20, dict(max_changes=2))])
+@pytest.mark.parametrize("slots", ["all", "two"])
+def test_rollouts_in_pieces(problem, h, w, T, more, slots):
+    """Rollouts of a small batch around the sizes of the pieces that their wavefronts hand on to each
+    other, episodes that end in every one of them, three in a row and single steps in between: what
+    they leave behind is what the next one starts from."""
+    B = 21
+    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=50, pos_mode=wl.POS_RANDOM), **more))
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    gpu.pcgrl_reset(5)
+    cpu.reset(5)
+    S = T if slots == "all" else min(2, T)
+    for turn in range(3):
+        acts = wl.random_actions(cfg, 30 + turn, T + 2, bad_fraction=0.05)
+        obs = torch.zeros((S,) + tuple(gpu.obs_shape), dtype=torch.uint8, device=DEV)
+        rew, done = torch.empty((T, B), dtype=torch.float32, device=DEV), torch.empty((T, B), dtype=torch.uint8, device=DEV)
+        gpu.pcgrl_rollout(torch.from_numpy(acts[:T].copy()).to(DEV), obs, rew, done)
+        for t in range(T):
+            o, r, d = cpu.step(acts[t])
+            assert np.array_equal(rew[t].cpu().numpy(), r) and np.array_equal(done[t].cpu().numpy(), d), f"turn {turn} step {t}"
+            if t >= T - S:
+                check_obs(gpu, obs[t % S], o, f"turn {turn} step {t}")
+        assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"turn {turn}")
+        assert_same("targets", gpu.pcgrl_get_targets(), cpu.get_targets(), f"turn {turn}")
+        compare_state(gpu, cpu, f"turn {turn}")
+        for t in range(T, T + 2):
+            gpu.pcgrl_step(torch.from_numpy(acts[t]).to(DEV))
+            cpu.step(acts[t], want_obs=False)
+        assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"turn {turn}, single steps")
     gpu.close()
