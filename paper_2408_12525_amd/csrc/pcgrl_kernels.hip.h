@@ -732,6 +732,66 @@ __device__ __forceinline__ int components_around(const Lanes<S>& L, typename Row
   return k;
 }
 
+// The same number searched for among the walkable cells: of distinct components of `passw` (the level with
+// the edited cell walled off) among the walkable neighbours `nbr` of that cell.  A flood starts from the
+// first neighbour; if it has not reached the others within a few layers, a second one starts from those
+// and the two go on side by side until they meet or either stalls.  For 16-row binary levels, whose
+// components are small: four of them to a wavefront, what the ring costs every edit is more than the
+// searches through their walls save (262 144 levels, steps without observations 34.8 against 37.3 us,
+// 256-step rollouts of 64 levels 152 against 155); other problems and sizes are faster through the walls (16x16
+// dungeons at 65 536 18.4 against 18.8, at 4096 4.58 against 4.73).
+template <int S>
+__device__ __forceinline__ int neighbour_components(const Lanes<S>& L, typename RowWord<S>::T nbr,
+                                                    typename RowWord<S>::T passw) {
+  using W = typename RowWord<S>::T;
+  W U = nbr;
+  // at most four cells in three rows; a row holds two of them only for the left/right pair
+  auto count = [&](W u) {
+    int rows = popc(L.gbits(__builtin_amdgcn_ballot_w64(u != 0)));
+    return rows + (L.gany((u & (u - 1)) != 0) ? 1 : 0);
+  };
+  int left = count(U);
+  int k = 0;
+  for (;;) {
+    bool go = left >= 2;
+    if (!go && left == 1) {
+      k += 1;
+      left = 0;
+      U = 0;
+    }
+    if (!wave_any<S>(go)) break;
+    W A = go ? first_cell<S>(L, U) : (W)0;
+    W pw = go ? passw : (W)0;
+    // A group whose neighbours are all reached is finished for good: whatever its flood still
+    // adds while other groups go on changes nothing below.
+    bool more = true;
+    for (int n = 0; n < kShortTrips && more; ++n) {
+      W A1;
+      const W An = L.grow_twice(A, pw, A1);
+      bool ch = An != A1;  // a last layer that adds nothing means the flood is complete
+      A = An;
+      bool open = L.gany((U & ~A) != 0);
+      more = wave_any<S>(ch && open);
+    }
+    U &= ~A;
+    bool meet = false;
+    if (more) {
+      W B = U;
+      do {
+        W A1, B1;
+        A = L.grow_twice(L.grow_twice(A, pw, A1), pw, A1);
+        B = L.grow_twice(L.grow_twice(B, pw, B1), pw, B1);
+        const bool grew_a = L.gany(A != A1), grew_b = L.gany(B != B1);
+        meet = L.gany((A & B) != 0);
+        more = wave_any<S>(grew_a & grew_b & !meet);
+      } while (more);
+    }
+    k += go && !meet ? 1 : 0;
+    left = count(U);
+  }
+  return k;
+}
+
 // Full metric vector of the level held by a group (all M entries).
 template <int S, int PROBLEM>
 __device__ __forceinline__ void full_metrics(const Lanes<S>& L,
@@ -1625,7 +1685,13 @@ __device__ __forceinline__ Moved after_edit(bool recount, const Lanes<S>& L, con
     const bool flip = changed && was_pass != now_pass;
     if (wave_any<S>(flip)) {
       const W cell = (flip && at_row) ? (W)1 << px : (W)0;
-      const int k = components_around<S>(L, flip ? (W)(pass & ~cell) : (W)0, inside, cell, h, w, py, px);
+      int k;
+      if constexpr (S == 16 && PROBLEM == kBinary) {  // (see neighbour_components)
+        const W passw = flip ? (W)(pass & ~cell) : (W)0;
+        k = neighbour_components<S>(L, (L.dilate(cell) & ~cell) & passw, passw);
+      } else {
+        k = components_around<S>(L, flip ? (W)(pass & ~cell) : (W)0, inside, cell, h, w, py, px);
+      }
       if (flip) mv.regions = now_pass ? 1 - k : k - 1;
     }
   }
@@ -1633,8 +1699,7 @@ __device__ __forceinline__ Moved after_edit(bool recount, const Lanes<S>& L, con
   if constexpr (PROBLEM == kBinary) {
     // (every modifying edit of a binary level flips the walkability of its cell)
     const W cell = (changed && at_row) ? (W)1 << px : (W)0;
-    const bool untouched = diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, now_pass);
-    const bool need = changed && !(comp_known && untouched);
+    const bool need = changed && !(comp_known && diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, now_pass));
     if (wave_any<S>(need)) {
       W ncomp;
       const int dm = two_sweep_diameter<S>(L, need ? pass : (W)0, ncomp);
