@@ -213,8 +213,10 @@ const SplitRule kStepSplit[] = {
     {16, 8193, kMax, 3072, kMax, 256 * kMB + 1, 448 * kMB, -1, 0},  // stored through the cache: +17 %
     {16, 8193, kMax, 1536, kMax, 0, kMax, -1, 1},     // maze16 -13 % at 12 288, -2...-4 % from 32 768; binary16 -3 % at 262 144
     {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // dungeon32 -16 % at 256, -7 % at 4096
-    {32, 4097, 16384, 8192, kMax, 0, kMax, -1, 1},    // 63-cell window (12 KB a level): -7 % at 16 384
+    {32, 4097, 16384, 2560, kMax, 0, kMax, -1, 1},    // us one / two, observation: maze 8192 10.2 / 9.7 (4.8 KB), 7.8 / 7.9 (2.2 KB),
+                                                      // 16 384 17.2 / 16.3, 11.9 / 12.3; dungeon 16 384 14.3 / 13.6 (3.5 KB); binary 8192 11.0 / 10.6 (2.9 KB)
     {64, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // maze64 -12 % at 256, -4 % at 4096; none from 8192 on
+    {64, 4097, 12288, 6000, kMax, 0, kMax, -1, 1},    // dungeon 8192 16.3 / 15.5 (7.7 KB), 13.2 / 13.9 (3.5 KB); binary 13.6 / 13.2 (6.1 KB)
     {0, 1, kMax, 0, kMax, 0, kMax, -1, 0},
 };
 // pcgrl_rollout (each wavefront keeps its own copy of the level for all the steps).
