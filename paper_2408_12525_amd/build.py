@@ -84,6 +84,31 @@ def scan_shift_amounts(asm_text: str):
     return len(alloc), found
 
 
+def kernel_resources(asm_text: str):
+    """What each kernel of the device assembly takes: vector registers, bytes of scratch memory, and the
+    vector loads from memory that stand in its code.  Returns {kernel: {"vgprs", "scratch", "loads"}}."""
+    out, loads, cur, kern, scratch, vgprs = {}, {}, None, None, 0, 0
+    for line in asm_text.splitlines():
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            cur = m.group(1)
+            loads[cur] = 0
+        elif cur and re.match(r"\s+(global|flat|scratch|buffer)_load_", line):
+            loads[cur] += 1
+        m = re.match(r"\s*\.(end_amdhsa_kernel|amdhsa_kernel|amdhsa_next_free_vgpr|amdhsa_private_segment_fixed_size)\b\s*(\w*)", line)
+        if not m:
+            continue
+        if m.group(1) == "amdhsa_kernel":
+            kern = m.group(2)
+        elif m.group(1) == "amdhsa_next_free_vgpr":
+            vgprs = int(m.group(2))
+        elif m.group(1) == "amdhsa_private_segment_fixed_size":
+            scratch = int(m.group(2))
+        else:
+            out[kern] = {"vgprs": vgprs, "scratch": scratch, "loads": loads.get(kern, 0)}
+    return out
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     """Runs hipcc; with force=False only when the library is missing or older than its sources.
     The device assembly the compiler leaves behind is checked by scan_shift_amounts(); a finding
@@ -104,9 +129,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
             if len(asm) != 1:
                 raise RuntimeError("device assembly not found among the compiler's temporaries: %s" % os.listdir(tmp))
             with open(os.path.join(tmp, asm[0])) as f:
-                n_kernels, found = scan_shift_amounts(f.read())
+                text = f.read()
+            n_kernels, found = scan_shift_amounts(text)
             with open(SCAN_REPORT, "w") as f:
-                json.dump({"kernels": n_kernels, "findings": found}, f)
+                json.dump({"kernels": n_kernels, "findings": found, "resources": kernel_resources(text)}, f)
             if found:
                 raise RuntimeError("64-bit shifts with their amount in the highest allocated vector register:\n" +
                                    "\n".join("  %s (allocation %d): %s" % t for t in found))

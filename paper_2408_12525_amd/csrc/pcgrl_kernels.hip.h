@@ -846,8 +846,18 @@ template <typename W> __device__ __forceinline__ W inside_row(int y, int h, int 
 
 // ---------------------------------------------------------------- episodes
 
-// Start of an episode: shape, tiles, pinpoints, first position, all from the env's key.
-template <int S, int PROBLEM, bool SHARED = false>
+// Cells drawn side by side by a level that restarts inside a step or a rollout.  What a draw waits for
+// counts where the launch lasts as long as its slowest wavefront (4096 64x64 dungeon levels with a
+// change limit, four / two / one: 13.7 / 14.2 / 15.3 us a step), and registers where wavefronts are not in step:
+// in a rollout the constants of four hashes are scalar registers that its loop then lacks (8192 64x64
+// dungeon levels with a 15-cell window 6.9 / 6.6 / 6.6 us a step).  32x32 dungeons: with four the step
+// kernel for wide windows takes 97 vector registers (17 000 levels with a 33-cell window 27.4 us a step, 25.6
+// with two).
+template <int S, int PROBLEM, bool ROLL> constexpr int kDrawsAbreast = ROLL ? 1 : S == 32 && PROBLEM == kDungeon ? 2 : 4;
+
+// Start of an episode: shape, tiles, pinpoints, first position, all from the env's key.  SHARED: inside a
+// step, where few levels of a wavefront begin one.  ABREAST: how many cells are drawn side by side.
+template <int S, int PROBLEM, bool SHARED = false, int ABREAST = 4>
 __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L, uint64_t key,
                                               typename RowWord<S>::T (&p)[Prob<PROBLEM>::P],
                                               typename RowWord<S>::T& fz, int& h, int& w, int& py,
@@ -864,11 +874,24 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
 #pragma unroll
   for (int i = 0; i < PR::P; ++i) p[i] = 0;
   // Bits x0 .. x0 + n - 1 of this row (n <= 32 and the same in all lanes), as they would be in a level
-  // of any size.  Bound by vector instructions, seven of the 22 or so a cell being 32-bit multiplications
+  // of any size.  Bound by vector instructions, six of the 22 or so a cell being 32-bit multiplications
   // of the hash.  The rest is kept short: the counter goes down by one constant, so that a cell's bits
   // are shifted into 32-bit words from the right, as the carry of an addition, and end up in place,
   // and the thresholds, which are non-decreasing, are searched instead of counted (8192 64x64 maze levels,
   // reset with observations: 65.1 -> 57.1 us when this loop was brought in, 47.6 -> 46.3 with the carries).
+  // The thresholds are fetched once and chosen among as values.  A choice between two of them written on
+  // the argument block, or on an array, is a choice between two addresses: inside a step, where the block
+  // is read through a pointer, each was a vector load per cell, two in a row for a draw, and each waited
+  // for every observation store the wavefront still had under way.  Steps with a change limit of 100, us:
+  // 8192 16x16 dungeon levels 13.1 -> 10.8, 4096 32x32 ones with three pinpoints 13.6 -> 10.8, 8192 64x64
+  // ones 27.8 -> 22.1, 8192 16x16 maze levels 8.5 -> 7.7.
+  uint32_t cdf[PR::K - 1];
+#pragma unroll
+  for (int i = 0; i < PR::K - 1; ++i) {
+    cdf[i] = a.cdf[i];
+    asm("" : "+v"(cdf[i]));  // (scalar registers are what the loops around a restart are short of)
+  }
+  auto either = [](bool c, uint32_t x, uint32_t y) { return c ? x : y; };
   auto draw_cells = [&](uint64_t k, int x0, int n, uint32_t (&acc)[PR::P]) {
 #pragma unroll
     for (int i = 0; i < PR::P; ++i) acc[i] = 0;
@@ -881,15 +904,15 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
       auto bits = [](bool c) { return __builtin_amdgcn_ballot_w64(c); };
       uint64_t none;
       if constexpr (PROBLEM == kBinary) {
-        asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(acc[0]), "=&s"(none) : "s"(bits(r >= a.cdf[0])));
+        asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(acc[0]), "=&s"(none) : "s"(bits(r >= cdf[0])));
       } else if constexpr (PROBLEM == kMaze) {
-        const bool b1 = r >= a.cdf[1];
+        const bool b1 = r >= cdf[1];
         asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %2, %0, %0, %3\n\tv_addc_co_u32_e64 %1, %2, %1, %1, %4"
-            : "+v"(acc[0]), "+v"(acc[1]), "=&s"(none) : "s"(bits(r >= (b1 ? a.cdf[2] : a.cdf[0]))), "s"(bits(b1)));
+            : "+v"(acc[0]), "+v"(acc[1]), "=&s"(none) : "s"(bits(r >= either(b1, cdf[2], cdf[0]))), "s"(bits(b1)));
       } else {  // (tile 7 does not exist)
-        const bool b2 = r >= a.cdf[3];
-        const bool b1 = r >= (b2 ? a.cdf[5] : a.cdf[1]);
-        const bool b0 = r >= (b1 ? a.cdf[2] : b2 ? a.cdf[4] : a.cdf[0]);
+        const bool b2 = r >= cdf[3];
+        const bool b1 = r >= either(b2, cdf[5], cdf[1]);
+        const bool b0 = r >= either(b1, cdf[2], either(b2, cdf[4], cdf[0]));
         asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %3, %0, %0, %4\n\tv_addc_co_u32_e64 %1, %3, %1, %1, %5\n\t"
             "v_addc_co_u32_e64 %2, %3, %2, %2, %6"
             : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "=&s"(none)
@@ -897,12 +920,13 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
       }
     };
     int j = n;
-    for (; j >= 4; j -= 4, z -= 4 * kGolden) {  // (four hashes side by side)
-      cell(z);
-      cell(z - kGolden);
-      cell(z - 2 * kGolden);
-      cell(z - 3 * kGolden);
+    if constexpr (ABREAST > 1) {
+      for (; j >= ABREAST; j -= ABREAST, z -= ABREAST * kGolden) {
+#pragma unroll
+        for (int i = 0; i < ABREAST; ++i) cell(z - i * kGolden);
+      }
     }
+#pragma unroll 1
     for (; j > 0; --j, z -= kGolden) cell(z);
   };
   if constexpr (SHARED && (64 / S) > 1) {
@@ -1819,7 +1843,7 @@ __device__ __forceinline__ void obs_wave_step(KArgs& a, const Lanes<S>& L, WaveM
     W np[PR::P], nfz;
     int nh, nw, npy, npx;
     uint64_t nkey = env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)((int)er0.w + 1));
-    begin_episode<S, PROBLEM, true>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
+    begin_episode<S, PROBLEM, true, kDrawsAbreast<S, PROBLEM, false>>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
     if (restart) {
 #pragma unroll
       for (int i = 0; i < PR::P; ++i) p[i] = np[i];
@@ -1939,7 +1963,7 @@ __device__ __forceinline__ void obs_wave_rollout(const KArgs& a, const Lanes<S>&
       W np[PR::P], nfz;
       int nh, nw, npy, npx;
       uint64_t nkey = env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)(episode + 1));
-      begin_episode<S, PROBLEM, true>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
+      begin_episode<S, PROBLEM, true, kDrawsAbreast<S, PROBLEM, true>>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
       if (restart) {
 #pragma unroll
         for (int i = 0; i < PR::P; ++i) p[i] = np[i];
@@ -2118,7 +2142,7 @@ __device__ __forceinline__ void relay_leader(const KArgs& a, const Lanes<S>& L, 
         W np[PR::P], nfz;
         int nh, nw, npy, npx;
         const uint64_t nkey = env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)(er.episode + 1));
-        begin_episode<S, PROBLEM, true>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
+        begin_episode<S, PROBLEM, true, kDrawsAbreast<S, PROBLEM, false>>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
         if (restart) {
 #pragma unroll
           for (int k = 0; k < PR::P; ++k) p[k] = np[k];
@@ -2708,7 +2732,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
       W np[PR::P], nfz;
       int nh, nw, npy, npx;
       uint64_t nkey = env_key(ra.seed, (uint64_t)wm.envl, (uint64_t)(er.episode + 1));
-      begin_episode<S, PROBLEM, true>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
+      begin_episode<S, PROBLEM, true, kDrawsAbreast<S, PROBLEM, ROLL>>(ra, L, nkey, np, nfz, nh, nw, npy, npx, restart, wm.envl);
       W ninside = inside_row<W>(L.y, nh, nw);
       int nm[PR::M];
       W ncomp;

@@ -85,6 +85,38 @@ def test_built_library_passed_the_scan():
     assert rep["findings"] == [] and rep["kernels"] >= 80
 
 
+def _resources(kernel):
+    """What the build noted of the instances of a kernel, by their template arguments."""
+    import json
+    binding.load()
+    rep = json.load(open(build.SCAN_REPORT)) if os.path.exists(build.SCAN_REPORT) else {}
+    if "resources" not in rep:                     # a library from before the note: build again
+        build.build(force=True)
+        rep = json.load(open(build.SCAN_REPORT))
+    out = {}
+    for name, res in rep["resources"].items():
+        m = re.match(r"_ZN5pcgrl\d+%sI((?:L[ib]\d+E)+)E" % kernel, name)
+        if m:
+            out[tuple(int(v) for v in re.findall(r"L[ib](\d+)E", m.group(1)))] = res
+    return out
+
+
+PLANES = {0: 1, 1: 2, 2: 3}   # bit-planes of binary, maze and dungeon levels
+
+
+def test_single_steps_load_their_state_and_nothing_else():
+    """A step asks memory for the level, its record, action, metrics, ranges and weights: beside the
+    planes twelve loads at most, and three for the observation wavefront, which loads the planes
+    again.  More of them are configuration read as if it differed from lane to lane, in the middle of a
+    chain and behind the wavefront's own stores (as the draws of a restart once were).  Nor does a step
+    use scratch memory."""
+    steps = _resources("step_kernel")
+    assert len(steps) == 54
+    for (S, problem, split, pin, wide), res in steps.items():
+        assert res["loads"] <= (1 + split) * PLANES[problem] + 12 + 3 * split, (S, problem, split, pin, wide, res)
+        assert res["scratch"] == 0, (S, problem, split, pin, wide, res)
+
+
 def test_compiled_call_path_leaves_doubtful_arguments_to_the_python_checks():
     """Tensors that are not on the device, arguments that are missing or no tensors, and a closed
     environment are answered with LOOK, before any library call (no GPU is touched; device tensors of
