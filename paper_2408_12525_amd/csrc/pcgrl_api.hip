@@ -140,8 +140,11 @@ template <int S, int PROBLEM> struct LaunchSplit {  // a metrics wavefront and i
 template <int S, int PROBLEM> struct LaunchRolloutSplit {
   static int run(const pcgrl_ctx* ctx, const KArgs& a, hipStream_t st) {
     const int obs_waves = (ctx->roll_m / ctx->roll_o) << ((a.envs_per_wave_log2 >> 16) & 0xff);
-    hipLaunchKernelGGL((rollout_kernel<S, PROBLEM, kModeRolloutSplit>), dim3(ctx->roll_groups),
-                       dim3(64 * (1 + obs_waves)), obs_waves * ctx->roll_lds_wave, st, a);
+    const dim3 grid(ctx->roll_groups), block(64 * (1 + obs_waves));
+    if (((a.envs_per_wave_log2 >> 16) & 0xff) != 0)
+      hipLaunchKernelGGL((rollout_kernel<S, PROBLEM, kModeRolloutTurns>), grid, block, obs_waves * ctx->roll_lds_wave, st, a);
+    else
+      hipLaunchKernelGGL((rollout_kernel<S, PROBLEM, kModeRolloutSplit>), grid, block, obs_waves * ctx->roll_lds_wave, st, a);
     return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
   }
 };

@@ -34,12 +34,11 @@ enum : int { kPadBorder = 0, kPadWall = 1 };
 enum : int { kPosScan = 0, kPosRandom = 1 };
 enum : int { kRegionsIncremental = 0, kRegionsRecount = 1 };
 enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
-// step kernel variants: one step per launch; the same with the work of a wavefront split over
-// two (a metrics wavefront and an observation wavefront per workgroup); n steps per launch; n steps
-// per launch split the same way
-// (split variants: a metrics wavefront and observation wavefronts per workgroup); and n steps with the
-// metrics searched by several wavefronts in turn (see rollout_relay_kernel)
-enum : int { kModeStep = 0, kModeSplit = 1, kModeRollout = 2, kModeRolloutSplit = 3 };
+// step kernel variants: one step per launch; the same with the work of a wavefront split over a metrics
+// wavefront and observation wavefronts of one workgroup; n steps per launch; n steps per launch split the
+// same way; and that with observation wavefronts that take the steps in turn.  (A relay, see
+// rollout_relay_kernel, is a kernel of its own.)
+enum : int { kModeStep = 0, kModeSplit = 1, kModeRollout = 2, kModeRolloutSplit = 3, kModeRolloutTurns = 4 };
 
 // Per-environment scalars, 32 bytes, read and written as two 16-byte words.
 struct __attribute__((aligned(16))) EnvRec {
@@ -735,11 +734,13 @@ __device__ __forceinline__ int components_around(const Lanes<S>& L, typename Row
 // The same number searched for among the walkable cells: of distinct components of `passw` (the level with
 // the edited cell walled off) among the walkable neighbours `nbr` of that cell.  A flood starts from the
 // first neighbour; if it has not reached the others within a few layers, a second one starts from those
-// and the two go on side by side until they meet or either stalls.  For 16-row binary levels, whose
-// components are small: four of them to a wavefront, what the ring costs every edit is more than the
-// searches through their walls save (262 144 levels, steps without observations 34.8 against 37.3 us,
-// 256-step rollouts of 64 levels 152 against 155); other problems and sizes are faster through the walls (16x16
-// dungeons at 65 536 18.4 against 18.8, at 4096 4.58 against 4.73).
+// and the two go on side by side until they meet or either stalls.  For binary levels of 16 rows, and of 32
+// in rollouts, whose components are small: with two or four of them to a wavefront, what the ring costs every
+// edit is more than the searches through their walls save (262 144 16x16 levels, steps without observations
+// 34.8 against 37.3 us, 256-step rollouts of 64 of them 152 against 155; 65 536 32x32 levels with a 3-cell
+// window, rollouts 19.8 against 20.3 us a step, 16 384 of them 6.26 against 6.45).  A single step of 32-row levels
+// lasts as long as its slowest search, which is shorter through the walls, and other problems are faster so
+// as well (16x16 dungeons at 65 536 18.4 against 18.8, at 4096 4.58 against 4.73).
 template <int S>
 __device__ __forceinline__ int neighbour_components(const Lanes<S>& L, typename RowWord<S>::T nbr,
                                                     typename RowWord<S>::T passw) {
@@ -1879,8 +1880,9 @@ template <typename T, typename... R> __device__ __forceinline__ void arrived(T& 
 // copy of the level through all the steps and only writes observations.  Where the batch leaves
 // SIMDs idle, several such wavefronts take the steps in turn: this one writes the observations of
 // the steps t with (t & turn_mask) == turn and only follows the level through the others.
-// (TURNS = false is the same code for the launches in which every such wavefront writes every step:
-// the test per step costs the large batches 7 % through the registers it ties up.)
+// (TURNS = false is the same code for the launches in which every such wavefront writes every step: the
+// test per step costs the large batches 7 % through the registers it ties up.  Each form has a kernel of
+// its own: both in one, 65 536 32x32 binary levels with a 3-cell window took 22.2 us a step against 20.9.)
 template <int S, int PROBLEM, bool TURNS>
 __device__ __forceinline__ void obs_wave_rollout(const KArgs& a, const Lanes<S>& L, const WaveMap<S>& wm, int turn,
                                                  int turn_mask) {
@@ -2456,8 +2458,15 @@ template <int S, int PROBLEM, int MODE, bool PIN, int WIDTH>
 __device__ __forceinline__ void step_body(KArgs& a) {
   using W = typename RowWord<S>::T;
   using PR = Prob<PROBLEM>;
-  constexpr bool ROLL = MODE == kModeRollout || MODE == kModeRolloutSplit;
-  constexpr bool SPLIT = MODE == kModeSplit || MODE == kModeRolloutSplit;
+  constexpr bool ROLL = MODE >= kModeRollout;
+  constexpr bool SPLIT = MODE != kModeStep && MODE != kModeRollout;
+  // Whether what a rollout needs rarely or at its end is looked up in the argument block again instead of
+  // being kept in scalar registers, of which the step loop has too few: it spills them to vector
+  // registers and reads them back in every step.  Us a step without / with: 8192 32x32 maze levels 4.08 / 3.68,
+  // 64x64 dungeons 7.10 / 6.92, 65 536 32x32 binary levels 20.9 / 20.5, 8192 16x16 dungeons without
+  // observations 2.10 / 2.04.  Not for split rollouts of 16-row levels (8192 binary levels 4.85 / 4.91, 2048 maze
+  // levels 2.42 / 2.49) and, one wavefront a level, 64-row binary and maze levels (12 288 maze levels 12.7 / 12.9).
+  constexpr bool LOOK_UP = ROLL && (SPLIT ? S > 16 : S < 64 || PROBLEM == kDungeon);
   extern __shared__ __align__(16) uint32_t lds_all[];
   Lanes<S> L;
   WaveMap<S> wm;
@@ -2478,8 +2487,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
       if constexpr (ROLL) {
         wm.lds = lds_all + (wid - 1) * a.obs_lds_words;
         const int turn_mask = (1 << ((a.envs_per_wave_log2 >> 16) & 0xff)) - 1;
-        if (turn_mask == 0) obs_wave_rollout<S, PROBLEM, false>(a, L, wm, 0, 0);
-        else obs_wave_rollout<S, PROBLEM, true>(a, L, wm, (wid - 1) >> (lg - lgo), turn_mask);
+        obs_wave_rollout<S, PROBLEM, MODE == kModeRolloutTurns>(a, L, wm, (wid - 1) >> (lg - lgo), turn_mask);
       } else {
         obs_wave_step<S, PROBLEM, PIN, WIDTH>(a, L, wm, lds_all, wid);
       }
@@ -2594,7 +2602,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
     const bool changed = valid && in_range && !is_frozen && act != old_code;
     if (__builtin_amdgcn_ballot_w64((uint32_t)act >= (uint32_t)PR::K) != 0) {  // rare: count them
       const uint64_t bad = __builtin_amdgcn_ballot_w64(wm.primary && !in_range && L.y == 0);
-      if (bad != 0 && L.lane == 0) atomicAdd(a.bad_actions, (unsigned long long)__popcll(bad));
+      if (bad != 0 && L.lane == 0) atomicAdd(LOOK_UP ? cold_args<ROLL>().bad_actions : a.bad_actions, (unsigned long long)__popcll(bad));
     }
     if (changed && at_row) {
 #pragma unroll
@@ -2664,7 +2672,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
         if (wave_any<S>(flip)) {
           const W cell = (flip && at_row) ? (W)1 << px : (W)0;
           int k;
-          if constexpr (S == 16 && PROBLEM == kBinary) {
+          if constexpr ((S == 16 || (S == 32 && ROLL)) && PROBLEM == kBinary) {  // (see neighbour_components)
             const W passw = flip ? (W)(pass & ~cell) : (W)0;
             k = neighbour_components<S>(L, (L.dilate(cell) & ~cell) & passw, passw);
           } else {
@@ -2808,15 +2816,20 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   }
 
   // ---- store the level's scalars (and, after a rollout, everything that changed)
+  const KArgs& fin = [&]() -> const KArgs& {
+    if constexpr (LOOK_UP) return cold_args<ROLL>();
+    else return a;
+  }();
   if constexpr (ROLL) {
+    planes = reinterpret_cast<W*>(fin.planes);
     if (wm.primary) {
       if (planes_dirty) {
 #pragma unroll
-        for (int i = 0; i < PR::P; ++i) planes[(size_t)i * a.plane_stride + ridx] = p[i];
+        for (int i = 0; i < PR::P; ++i) planes[(size_t)i * fin.plane_stride + ridx] = p[i];
       }
-      if (fz_dirty) frozen[ridx] = fz;
+      if (fz_dirty) reinterpret_cast<W*>(fin.frozen)[ridx] = fz;
       if constexpr (PROBLEM == kBinary) {
-        if (comp_dirty) planes[(size_t)PR::P * a.plane_stride + ridx] = comp;
+        if (comp_dirty) planes[(size_t)PR::P * fin.plane_stride + ridx] = comp;
       }
     }
     next_fz_row = L.gread(fz, py);
@@ -2827,11 +2840,11 @@ __device__ __forceinline__ void step_body(KArgs& a) {
     er.py = (uint8_t)py;
     er.px = (uint8_t)px;
     er.cell_frozen = ROLL ? (uint32_t)((next_fz_row >> px) & 1) : next_cell_frozen;
-    a.env[wm.env] = er;
+    fin.env[wm.env] = er;
   }
   if (wm.primary && L.y < PR::M) {
-    if (metrics_dirty) a.metrics[(size_t)wm.env * kMaxMetrics + L.y] = m_l;
-    if (targets_dirty) a.targets[(size_t)wm.env * kMaxMetrics + L.y] = tg_l;
+    if (metrics_dirty) fin.metrics[(size_t)wm.env * kMaxMetrics + L.y] = m_l;
+    if (targets_dirty) fin.targets[(size_t)wm.env * kMaxMetrics + L.y] = tg_l;
   }
   if constexpr (SPLIT) __builtin_amdgcn_endpgm();  // see the observation wavefront's exit above
 }
@@ -2895,8 +2908,8 @@ __global__ __launch_bounds__(MODE == kModeSplit ? 320 : 64) void step_kernel(
 // leave the registers: per step only the action is read and the observation, reward and done
 // flag are written.  A launch per hundred steps has nothing to gain from preloaded arguments.
 template <int S, int PROBLEM, int MODE>
-__global__ __launch_bounds__(MODE == kModeRolloutSplit ? 320 : 64) void rollout_kernel(KArgs a) {
-  static_assert(MODE == kModeRollout || MODE == kModeRolloutSplit, "rollouts only");
+__global__ __launch_bounds__(MODE == kModeRollout ? 64 : 320) void rollout_kernel(KArgs a) {
+  static_assert(MODE >= kModeRollout, "rollouts only");
   step_body<S, PROBLEM, MODE, true, kWidthAny>(a);
 }
 

@@ -117,6 +117,21 @@ def test_single_steps_load_their_state_and_nothing_else():
         assert res["scratch"] == 0, (S, problem, split, pin, wide, res)
 
 
+# wavefronts that a SIMD's 512 vector registers hold of a rollout with observation wavefronts; a lost one
+# showed as 11 % on 32-row binary levels
+ROLLOUT_WAVEFRONTS = {(16, 0): 6, (16, 1): 5, (16, 2): 4, (32, 0): 6, (32, 1): 5, (32, 2): 4, (64, 0): 8, (64, 1): 7, (64, 2): 6}
+
+
+def test_rollouts_of_large_batches_keep_their_wavefronts():
+    rollouts = _resources("rollout_kernel")
+    assert {(S, p) for S, p, mode in rollouts if mode == 3} == set(ROLLOUT_WAVEFRONTS)
+    for (S, problem, mode), res in rollouts.items():
+        assert res["scratch"] == 0, (S, problem, mode, res)
+        if mode == 3:
+            held = min(8, 512 // (-(-res["vgprs"] // 8) * 8))
+            assert held >= ROLLOUT_WAVEFRONTS[S, problem], (S, problem, res)
+
+
 def test_compiled_call_path_leaves_doubtful_arguments_to_the_python_checks():
     """Tensors that are not on the device, arguments that are missing or no tensors, and a closed
     environment are answered with LOOK, before any library call (no GPU is touched; device tensors of
