@@ -142,10 +142,11 @@ typedef struct {
   int32_t rollout_turns; /* tuning only, results do not depend on it: 0 = automatic; 1, 2 or 4 = how
                            many observation wavefronts take the steps of a pcgrl_rollout in turn
                            (each keeps its own copy of the levels and writes the observation of
-                           every n-th step).  Pays where the batch leaves most of the chip idle:
-                           the automatic choice takes turns only while every wavefront still has
-                           a SIMD to itself, and for small batches shares the searches for the metrics
-                           out in the same way; a workgroup holds at most four observation wavefronts */
+                           every n-th step).  Pays where the batch leaves most of the chip idle.
+                           The automatic choice shares the searches for the metrics out in the same
+                           way while a compute unit has few workgroups, by what was measured for each size
+                           class, and otherwise takes turns while the launch stays at two or three
+                           wavefronts a SIMD; a workgroup holds at most four observation wavefronts */
 } pcgrl_config;
 
 #define PCGRL_OBS_PITCH_LINES (-1)

@@ -13,6 +13,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "pcgrl_api.hip")
 DEPS = [SRC, os.path.join(HERE, "csrc", "pcgrl_kernels.hip.h"), os.path.join(HERE, "csrc", "pcgrl_index.h"),
+        os.path.join(HERE, "csrc", "pcgrl_relay.h"),
         os.path.join(os.path.dirname(HERE), "include", "pcgrl.h")]
 LIB_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIB_DIR, "libpcgrl.so")
@@ -85,9 +86,11 @@ def scan_shift_amounts(asm_text: str):
 
 
 def kernel_resources(asm_text: str):
-    """What each kernel of the device assembly takes: vector registers, bytes of scratch memory, and the
-    vector loads from memory that stand in its code.  Returns {kernel: {"vgprs", "scratch", "loads"}}."""
-    out, loads, cur, kern, scratch, vgprs = {}, {}, None, None, 0, 0
+    """What each kernel of the device assembly takes: vector registers, bytes of scratch memory and of LDS (without
+    what a launch adds), and the vector loads from memory that stand in its code.  Returns
+    {kernel: {"vgprs", "scratch", "lds", "loads"}}."""
+    fields = {"amdhsa_next_free_vgpr": "vgprs", "amdhsa_private_segment_fixed_size": "scratch", "amdhsa_group_segment_fixed_size": "lds"}
+    out, loads, cur, kern = {}, {}, None, None
     for line in asm_text.splitlines():
         m = re.match(r"^(_Z\w+):", line)
         if m:
@@ -95,17 +98,12 @@ def kernel_resources(asm_text: str):
             loads[cur] = 0
         elif cur and re.match(r"\s+(global|flat|scratch|buffer)_load_", line):
             loads[cur] += 1
-        m = re.match(r"\s*\.(end_amdhsa_kernel|amdhsa_kernel|amdhsa_next_free_vgpr|amdhsa_private_segment_fixed_size)\b\s*(\w*)", line)
-        if not m:
-            continue
-        if m.group(1) == "amdhsa_kernel":
+        m = re.match(r"\s*\.(amdhsa_\w+)\s+(\w+)", line)
+        if m and m.group(1) == "amdhsa_kernel":
             kern = m.group(2)
-        elif m.group(1) == "amdhsa_next_free_vgpr":
-            vgprs = int(m.group(2))
-        elif m.group(1) == "amdhsa_private_segment_fixed_size":
-            scratch = int(m.group(2))
-        else:
-            out[kern] = {"vgprs": vgprs, "scratch": scratch, "loads": loads.get(kern, 0)}
+            out[kern] = {"loads": loads.get(kern, 0)}
+        elif m and m.group(1) in fields:
+            out[kern][fields[m.group(1)]] = int(m.group(2))
     return out
 
 

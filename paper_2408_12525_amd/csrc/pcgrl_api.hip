@@ -21,7 +21,8 @@ struct pcgrl_ctx {
   size_t lds_bytes;  // per wavefront
   int split_roll;    // pcgrl_rollout with observations does the same, with its own shape:
   int roll_m, roll_o, roll_groups, roll_turns;
-  int relay_searchers, relay_turns;  // pcgrl_rollout runs as a relay, with this many wavefronts of either kind (0: it does not)
+  bool may_relay;    // pcgrl_rollout may run as a relay (relay_shape says when): what the rule needs of this context,
+  RelayCase relay;   // all but the steps and slots of a call
   size_t roll_lds_wave;
   int split;         // pcgrl_step with an observation uses the metrics | observation kernel, with
   int split_m, split_o, split_groups;  // this many levels per metrics / observation wavefront and workgroups
@@ -269,41 +270,27 @@ int exact_waves_for(int nwaves, int copies, int S) {
   return lg;
 }
 
-// Whether, and with how many searchers and observers, a pcgrl_rollout runs as a relay.  It pays while all
-// its workgroups are on the machine at once: searchers and observers share a chain of one wavefront per
-// step out among them, at the price of following the levels in each.  How many workgroups a compute unit
-// takes follows from the kernel's registers (512 a SIMD, handed out in eights; three wavefront places are
-// left over, since a workgroup's wavefronts do not always spread evenly over the four SIMDs: 1024
-// workgroups of 5 wavefronts with 88 registers each took twice the time of those with 80).  Measured, us
-// per step of 32-step rollouts, without a relay / as one with 4 searchers and 4 observers, 4 and 2, 2
-// and 2, 2 and 1: 16x16 binary levels, 64 of them 1.52 / 0.94 / 0.99 / 1.09 / 1.44, 512 2.08 / 1.25 /
-// 1.28 / 1.47 / 1.67, 1024 2.22 / 2.40 / 2.08 / 2.28 / 1.87; 32x32 dungeons, 64 1.43 / 0.72 / 0.85 / 0.88 /
-// 1.23, 512 1.67 / 1.35 / 1.11 / 1.09 / 1.37, 1024 1.77 / 2.44 / 1.93 / 2.02 / 2.47; 64x64 maze, 64 1.28 /
-// 0.83 / 0.99 / 0.99 / 1.41, 512 1.56 / 1.16 / 1.29 / 1.26 / 1.57, 1024 1.76 / 2.45 / 2.03 / 2.00 / 1.80.  The last
-// shape is for the binary problem alone, whose searches are the longer half of a step (32x32, 2048 levels
-// 2.90 -> 2.22); on 64-row levels it gains nothing.  Episodes shorter than a piece of the relay would end
-// twice in one, for which it has no room.
-struct RelayShape { int searchers, turns; };
-const RelayShape kRelayShapes[] = {{4, 4}, {4, 2}, {2, 2}, {2, 1}};
-int choose_relay(pcgrl_ctx* ctx, int compute_units) {
+// Episodes shorter than a piece of a relay would end twice in one, for which it has no room.
+int prepare_relay(pcgrl_ctx* ctx, int compute_units) {
   const pcgrl_config& cfg = ctx->cfg;
-  ctx->relay_searchers = ctx->relay_turns = 0;
   const bool long_episodes = !cfg.autoreset || (cfg.max_steps >= kRelaySteps && (cfg.max_changes == 0 || cfg.max_changes >= kRelaySteps));
-  if (!ctx->split_roll || cfg.rollout_turns != 0 || !long_episodes) return PCGRL_OK;
+  ctx->may_relay = ctx->split_roll && cfg.rollout_turns == 0 && long_episodes;
+  if (!ctx->may_relay) return PCGRL_OK;
   hipFuncAttributes fa;
   const int rc = dispatch<RelayAttributes>(ctx->S, cfg.problem, &fa);
   if (rc != PCGRL_OK) return rc;
-  const int registers = (fa.numRegs + 7) / 8 * 8, per_simd = registers <= 64 ? 8 : 512 / registers;
-  const int per_step = ctx->roll_m / ctx->roll_o;
-  for (const RelayShape& r : kRelayShapes) {
-    const int observers = per_step * r.turns, waves = 2 + r.searchers + observers;
-    if (r.turns == 1 && (cfg.problem != PCGRL_BINARY || ctx->S == 64)) continue;
-    if (observers > 4 || fa.sharedSizeBytes + ctx->roll_lds_wave * (size_t)observers > 64 * 1024) continue;
-    if ((long long)ctx->roll_groups > (long long)compute_units * ((4 * per_simd - 3) / waves)) continue;
-    ctx->relay_searchers = r.searchers;
-    ctx->relay_turns = r.turns;
-    break;
-  }
+  const int registers = (fa.numRegs + 7) / 8 * 8;  // (512 a SIMD, handed out in eights)
+  RelayCase& c = ctx->relay;
+  c.rows = ctx->S;
+  c.binary = cfg.problem == PCGRL_BINARY;
+  c.per_simd = registers <= 64 ? 8 : 512 / registers;
+  c.compute_units = compute_units;
+  c.workgroups = ctx->roll_groups;
+  c.observers = ctx->roll_m / ctx->roll_o;
+  c.obs_bytes = (int64_t)ctx->obs_bytes;
+  c.step_bytes = (int64_t)(ctx->obs_stride * (size_t)cfg.batch);
+  c.lds_tables = (int64_t)fa.sharedSizeBytes;
+  c.lds_observer = (int64_t)ctx->roll_lds_wave;
   return PCGRL_OK;
 }
 
@@ -537,7 +524,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
         ctx->roll_turns *= 2;
     }
   }
-  rc = choose_relay(ctx, prop.multiProcessorCount);
+  rc = prepare_relay(ctx, prop.multiProcessorCount);
   if (rc != PCGRL_OK) {
     delete ctx;
     return rc;
@@ -718,18 +705,19 @@ int pcgrl_rollout(pcgrl_ctx* ctx, const int32_t* actions, int32_t n_steps, uint8
   a.by_die = (a.stream_obs == kStoreCached && (ctx->obs_stride & 127) != 0) ? 1 : 0;
   if (obs && ctx->split_roll) {
     auto lg2 = [](int v) { return v == 4 ? 2 : v == 2 ? 1 : 0; };
-    // Wavefronts that take turns are not ordered among each other: a slot that is written more than
-    // once in this rollout must be written by the same wavefront every time, i.e. the number of
-    // turns has to divide the number of slots.
-    int turns = ctx->roll_turns;
-    if (ctx->relay_searchers > 0) turns = ctx->relay_turns;
-    while (turns > 1 && a.obs_slots != n_steps && a.obs_slots % turns != 0) turns /= 2;
-    a.envs_per_wave_log2 = lg2(ctx->roll_m) | (lg2(ctx->roll_o) << 8) | (lg2(turns) << 16);
-    a.obs_lds_words = (int32_t)(ctx->roll_lds_wave / 4);
-    if (ctx->relay_searchers > 0) {
-      a.envs_per_wave_log2 |= lg2(ctx->relay_searchers) << 24;
-      return dispatch<LaunchRolloutRelay>(ctx->S, ctx->cfg.problem, ctx, a, static_cast<hipStream_t>(stream));
+    RelayShape relay = {0, 0};
+    if (ctx->may_relay) {
+      RelayCase c = ctx->relay;
+      c.steps = n_steps;
+      c.slots = a.obs_slots;
+      relay = relay_shape(c);
     }
+    // (the number of turns has to divide the number of slots, see relay_shape)
+    int turns = relay.searchers > 0 ? relay.turns : ctx->roll_turns;
+    while (turns > 1 && a.obs_slots != n_steps && a.obs_slots % turns != 0) turns /= 2;
+    a.envs_per_wave_log2 = lg2(ctx->roll_m) | (lg2(ctx->roll_o) << 8) | (lg2(turns) << 16) | (lg2(relay.searchers) << 24);
+    a.obs_lds_words = (int32_t)(ctx->roll_lds_wave / 4);
+    if (relay.searchers > 0) return dispatch<LaunchRolloutRelay>(ctx->S, ctx->cfg.problem, ctx, a, static_cast<hipStream_t>(stream));
     return dispatch<LaunchRolloutSplit>(ctx->S, ctx->cfg.problem, ctx, a, static_cast<hipStream_t>(stream));
   }
   return dispatch<LaunchRollout>(ctx->S, ctx->cfg.problem, ctx, a, static_cast<hipStream_t>(stream));

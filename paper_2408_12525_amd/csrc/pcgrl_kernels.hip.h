@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "pcgrl_index.h"
+#include "pcgrl_relay.h"
 
 namespace pcgrl {
 
@@ -2024,7 +2025,6 @@ template <int M> __device__ __forceinline__ float reward_of(int before, int afte
 // chain (without it 0.45 to 0.5) and the other wavefronts', none of which does much less.  Pieces of 8 steps
 // keep the three stages short for rollouts of a few steps (4 steps of 64 dungeon levels 2.56 -> 2.12 us each),
 // and give every searcher and observer two turns or more to even out.
-constexpr int kRelaySteps = 8;
 template <int S, int PROBLEM> struct RelayTables {
   static constexpr int kLevels = 64 / S;  // of a workgroup, at most
   // what the leader wrote down of a step: x bits 0-2 the action, 3-5 the tile it replaced, 6 the level

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import oracle
+import relay_rule
 from parity import assert_same, check_obs, compare_state
 from paper_2408_12525_amd import binding, workloads as wl
 
@@ -367,25 +368,12 @@ def test_every_argument_of_every_call_is_checked(wrong, packed):
     gpu.close()
 
 
-@pytest.mark.parametrize("problem,h,w,T,more", [
-    (wl.BINARY, 16, 16, 1, {}), (wl.BINARY, 16, 16, 7, dict(max_steps=8)), (wl.MAZE, 16, 16, 8, dict(max_steps=8)),
-    (wl.DUNGEON, 11, 16, 9, dict(max_steps=9, n_frozen=2)), (wl.BINARY, 32, 20, 17, dict(max_steps=11, min_size=5, min_w=5)),
-    (wl.MAZE, 32, 32, 16, dict(max_changes=8, obs_format=1)), (wl.DUNGEON, 32, 32, 33, dict(max_steps=8, max_changes=8, pos_mode=wl.POS_SCAN)),
-    (wl.BINARY, 64, 64, 24, dict(max_steps=13, n_frozen=3, min_size=20)), (wl.MAZE, 64, 40, 15, dict(autoreset=0, max_steps=4)),
-    (wl.DUNGEON, 64, 64, 25, dict(max_steps=10, regions_mode=wl.REGIONS_RECOUNT)),
-    # episodes that end twice within a piece of a relay
-    (wl.BINARY, 16, 16, 20, dict(max_steps=3)), (wl.MAZE, 32, 32, 20, dict(max_changes=2))])
-@pytest.mark.parametrize("slots", ["all", "two"])
-def test_rollouts_in_pieces(problem, h, w, T, more, slots):
-    """Rollouts of a small batch around the sizes of the pieces that their wavefronts hand on to each
-    other, episodes that end in every one of them, three in a row and single steps in between: what
-    they leave behind is what the next one starts from."""
-    B = 21
-    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=50, pos_mode=wl.POS_RANDOM), **more))
+def _rollouts_against_steps(cfg, T, S):
+    """Three rollouts of T steps into S slots, two single steps after each, against the oracle's steps."""
+    B = cfg["batch"]
     gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
     gpu.pcgrl_reset(5)
     cpu.reset(5)
-    S = T if slots == "all" else min(2, T)
     for turn in range(3):
         acts = wl.random_actions(cfg, 30 + turn, T + 2, bad_fraction=0.05)
         obs = torch.zeros((S,) + tuple(gpu.obs_shape), dtype=torch.uint8, device=DEV)
@@ -404,3 +392,48 @@ def test_rollouts_in_pieces(problem, h, w, T, more, slots):
             cpu.step(acts[t], want_obs=False)
         assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"turn {turn}, single steps")
     gpu.close()
+
+
+@pytest.mark.parametrize("problem,h,w,T,more", [
+    (wl.BINARY, 16, 16, 1, {}), (wl.BINARY, 16, 16, 7, dict(max_steps=8)), (wl.MAZE, 16, 16, 8, dict(max_steps=8)),
+    (wl.DUNGEON, 11, 16, 9, dict(max_steps=9, n_frozen=2)), (wl.BINARY, 32, 20, 17, dict(max_steps=11, min_size=5, min_w=5)),
+    (wl.MAZE, 32, 32, 16, dict(max_changes=8, obs_format=1)), (wl.DUNGEON, 32, 32, 33, dict(max_steps=8, max_changes=8, pos_mode=wl.POS_SCAN)),
+    (wl.BINARY, 64, 64, 24, dict(max_steps=13, n_frozen=3, min_size=20)), (wl.MAZE, 64, 40, 15, dict(autoreset=0, max_steps=4)),
+    (wl.DUNGEON, 64, 64, 25, dict(max_steps=10, regions_mode=wl.REGIONS_RECOUNT)),
+    # episodes that end twice within a piece of a relay
+    (wl.BINARY, 16, 16, 20, dict(max_steps=3)), (wl.MAZE, 32, 32, 20, dict(max_changes=2))])
+@pytest.mark.parametrize("slots", ["all", "two"])
+def test_rollouts_in_pieces(problem, h, w, T, more, slots):
+    """Rollouts of a small batch around the sizes of the pieces that their wavefronts hand on to each
+    other, episodes that end in every one of them, three in a row and single steps in between: what
+    they leave behind is what the next one starts from."""
+    B = 21
+    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=50, pos_mode=wl.POS_RANDOM), **more))
+    _rollouts_against_steps(cfg, T, T if slots == "all" else min(2, T))
+
+
+@pytest.mark.parametrize("problem,B,h,T,slots,shape,more", [
+    # several levels to a workgroup, of which some restart while the others go on
+    (wl.BINARY, 21, 16, 25, 25, (4, 4), dict(levels_per_wave=4)), (wl.MAZE, 37, 16, 20, 20, (4, 4), dict(levels_per_wave=2, n_frozen=2)),
+    (wl.DUNGEON, 38, 16, 33, 33, (4, 4), dict(levels_per_wave=4)), (wl.BINARY, 21, 32, 24, 24, (4, 4), dict(levels_per_wave=2, min_size=7)),
+    (wl.DUNGEON, 9, 32, 19, 19, (4, 4), dict(levels_per_wave=2)), (wl.MAZE, 15, 32, 17, 6, (4, 2), dict(levels_per_wave=2)),
+    # several observers to a step; some of the last workgroup have no level at all
+    (wl.BINARY, 21, 16, 25, 25, (4, 2), dict(levels_per_wave=4, split_obs_levels=2)), (wl.DUNGEON, 21, 16, 18, 18, (4, 1), dict(levels_per_wave=4, split_obs_levels=1)),
+    (wl.MAZE, 37, 16, 27, 3, (4, 1), dict(levels_per_wave=2, split_obs_levels=1)), (wl.BINARY, 7, 32, 22, 2, (4, 2), dict(levels_per_wave=2, split_obs_levels=1)),
+    # one slot, an odd ring, a ring of two
+    (wl.MAZE, 21, 16, 20, 1, (4, 1), {}), (wl.DUNGEON, 21, 64, 17, 3, (4, 1), {}), (wl.BINARY, 33, 64, 20, 2, (4, 2), {}),
+    # the shapes of larger batches
+    (wl.MAZE, 300, 16, 18, 18, (4, 2), {}), (wl.DUNGEON, 300, 16, 17, 17, (2, 2), dict(obs_w=31, n_frozen=1)), (wl.DUNGEON, 511, 32, 12, 12, (2, 2), dict(obs_w=21)),
+    (wl.BINARY, 513, 16, 19, 19, (4, 2), {}), (wl.MAZE, 700, 64, 10, 10, (4, 2), {}), (wl.BINARY, 769, 16, 25, 25, (2, 1), {}),
+    (wl.MAZE, 800, 32, 18, 18, (2, 1), {}), (wl.DUNGEON, 770, 64, 10, 5, (2, 1), {}), (wl.BINARY, 2047, 32, 18, 18, (2, 1), {}),
+    (wl.BINARY, 1100, 16, 17, 17, (4, 2), {}), (wl.BINARY, 1030, 32, 9, 9, (4, 2), {}),
+    # ... with several observers, and without a relay
+    (wl.MAZE, 601, 16, 11, 11, (4, 2), dict(levels_per_wave=2, split_obs_levels=1)), (wl.BINARY, 1100, 16, 17, 3, (0, 0), {}),
+    (wl.MAZE, 37, 32, 2, 2, (0, 0), {}), (wl.DUNGEON, 300, 16, 8, 8, (0, 0), {}), (wl.BINARY, 21, 16, 1, 1, (0, 0), {})])
+def test_every_shape_of_a_relay(problem, B, h, T, slots, shape, more):
+    """Rollouts in every shape that the rule for them gives out, in levels whose episodes end at different
+    steps (a change limit)."""
+    more = dict(dict(max_steps=60, max_changes=9, obs_w=9, pos_mode=wl.POS_RANDOM, split_step=2), **more)
+    cfg = wl.make_config(problem, B, h, more.pop("obs_w"), **more)
+    assert relay_rule.shape(**relay_rule.case_of(cfg, T, slots)) == shape
+    _rollouts_against_steps(cfg, T, slots)

@@ -442,8 +442,8 @@ ROLLOUTS = [
 ]
 
 
-@pytest.mark.parametrize("split,olv,turns", [(1, 0, 0), (2, 0, 1), (2, 0, 0), (2, 1, 2)],
-                         ids=["one-wavefront", "split-one-turn", "split", "split-obs1-two-turns"])
+@pytest.mark.parametrize("split,olv,turns", [(1, 0, 0), (2, 0, 1), (2, 0, 0), (2, 1, 2), (2, 0, 2), (2, 0, 4)],
+                         ids=["one-wavefront", "split-one-turn", "split", "split-obs1-two-turns", "split-two-turns", "split-four-turns"])
 @pytest.mark.parametrize("label,cfg,T,slots", ROLLOUTS, ids=[r[0] for r in ROLLOUTS])
 def test_rollout_equals_the_same_steps_one_by_one(label, cfg, T, slots, split, olv, turns):
     """pcgrl_rollout against the oracle stepped T times (every observation slot that survives,
@@ -451,7 +451,7 @@ def test_rollout_equals_the_same_steps_one_by_one(label, cfg, T, slots, split, o
     against T calls of pcgrl_step.  split: the levels stay in one wavefront for the whole rollout,
     or in a metrics wavefront and observation wavefronts that each carry their own copy; turns:
     how many observation wavefronts take the steps in turn (0: the library's choice, which at
-    these batches is as many as a workgroup holds)."""
+    these batches is a relay, whose searches are shared out as well)."""
     cfg = dict(cfg, split_step=split, split_obs_levels=olv, rollout_turns=turns)
     print(f"[rollout] {label} T={T} slots={slots} split={split} obs levels={olv} turns={turns}", flush=True)
     dev = torch.device("cuda", 0)
