@@ -220,7 +220,8 @@ const SplitRule kStepSplit[] = {
     {32, 4097, 16384, 2560, kMax, 0, kMax, -1, 1},    // us one / two, observation: maze 8192 10.2 / 9.7 (4.8 KB), 7.8 / 7.9 (2.2 KB),
                                                       // 16 384 17.2 / 16.3, 11.9 / 12.3; dungeon 16 384 14.3 / 13.6 (3.5 KB); binary 8192 11.0 / 10.6 (2.9 KB)
     {64, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // maze64 -12 % at 256, -4 % at 4096; none from 8192 on
-    {64, 4097, 12288, 6000, kMax, 0, kMax, -1, 1},    // dungeon 8192 16.3 / 15.5 (7.7 KB), 13.2 / 13.9 (3.5 KB); binary 13.6 / 13.2 (6.1 KB)
+    {64, 4097, 12288, 6000, kMax, 0, kMax, -1, 1},    // dungeon (7.7 KB) 4097 10.5 / 10.1, 8192 16.0 / 15.0, 12 288 20.7 / 19.5, binary (6.1 KB)
+                                                      // 10.3 / 9.9, 13.5 / 13.4, 17.4 / 16.8; maze (4.8 KB) 8.8 / 8.6, 12.1 / 12.3, 15.0 / 15.7
     {0, 1, kMax, 0, kMax, 0, kMax, -1, 0},
 };
 // pcgrl_rollout (each wavefront keeps its own copy of the level for all the steps).

@@ -2719,20 +2719,8 @@ __device__ __forceinline__ void step_body(KArgs& a) {
           if (need && yi == 2) mn_l = de < 0 ? 0 : de;
         }
       }
-      // reward = sum over metrics, in index order, of weight * (old loss - new loss): every lane
-      // its own term; then M-1 times every lane adds its term to what the lane before it holds, so
-      // that lane k ends with ((t[k-M+1] + ...) + t[k-1]) + t[k], terms before the first lane
-      // counting as zero: in lane M-1 that is the sum in index order
-      {
-        const int lo = (int)(tg_l & 0xffffu), hi = (int)(tg_l >> 16);
-        const int dl = loss(m_l, lo, hi) - loss(mn_l, lo, hi);
-        const float term = __fmul_rn(w_l, (float)dl);
-        float acc = __fadd_rn(0.0f, term);
-#pragma unroll
-        for (int j = 1; j < PR::M; ++j)
-          acc = __fadd_rn(__int_as_float((int)dpp_zero_fill<kRowShr1>((uint32_t)__float_as_int(acc))), term);
-        if (changed) reward = acc;
-      }
+      const float sum = reward_of<PR::M>(m_l, mn_l, tg_l, w_l);
+      if (changed) reward = sum;
     }
     // ---- auto-reset: fresh seeded episode for the finished levels; the others keep their registers
     if (any_restart) {
