@@ -891,7 +891,8 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
 #pragma unroll
   for (int i = 0; i < PR::K - 1; ++i) {
     cdf[i] = a.cdf[i];
-    asm("" : "+v"(cdf[i]));  // (scalar registers are what the loops around a restart are short of)
+    // (scalar registers are what the loops around a restart are short of; one threshold is no burden)
+    if constexpr (PROBLEM != kBinary) asm("" : "+v"(cdf[i]));
   }
   auto either = [](bool c, uint32_t x, uint32_t y) { return c ? x : y; };
   auto draw_cells = [&](uint64_t k, int x0, int n, uint32_t (&acc)[PR::P]) {
