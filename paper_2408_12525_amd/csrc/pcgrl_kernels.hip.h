@@ -849,13 +849,14 @@ template <typename W> __device__ __forceinline__ W inside_row(int y, int h, int 
 // ---------------------------------------------------------------- episodes
 
 // Cells drawn side by side by a level that restarts inside a step or a rollout.  What a draw waits for
-// counts where the launch lasts as long as its slowest wavefront (4096 64x64 dungeon levels with a
-// change limit, four / two / one: 13.7 / 14.2 / 15.3 us a step), and registers where wavefronts are not in step:
-// in a rollout the constants of four hashes are scalar registers that its loop then lacks (8192 64x64
-// dungeon levels with a 15-cell window 6.9 / 6.6 / 6.6 us a step).  32x32 dungeons: with four the step
-// kernel for wide windows takes 97 vector registers (17 000 levels with a 33-cell window 27.4 us a step, 25.6
-// with two).
-template <int S, int PROBLEM, bool ROLL> constexpr int kDrawsAbreast = ROLL ? 1 : S == 32 && PROBLEM == kDungeon ? 2 : 4;
+// counts where a launch lasts as long as its slowest wavefront (steps of 4096 64x64 maze levels with a change limit,
+// four / two / one: 12.9 / 13.6 / 13.9 us), registers and length of code where none restarts: 8192 64x64
+// maze levels 11.92 / 11.63 / 11.64 us a step, 16 384 16x16 dungeon levels 8.61 / 8.43 / 8.46 (with a limit 10.93 /
+// 10.91 / 10.95), and 97 instead of 96 vector registers for 32x32 dungeons with wide windows (17 000 levels with 33
+// cells 27.4 us with four, 25.6 with two).  In a rollout wavefronts are not in step, and the constants of several
+// hashes are scalar registers that its loop lacks (8192 64x64 dungeon levels 6.9 / 6.6 / 6.6 us a step).
+template <int S, int PROBLEM, bool ROLL>
+constexpr int kDrawsAbreast = ROLL ? 1 : PROBLEM == kDungeon || (S == 64 && PROBLEM == kMaze) ? 2 : 4;
 
 // Start of an episode: shape, tiles, pinpoints, first position, all from the env's key.  SHARED: inside a
 // step, where few levels of a wavefront begin one.  ABREAST: how many cells are drawn side by side.
