@@ -886,8 +886,8 @@ __device__ __forceinline__ void begin_episode(const KArgs& a, const Lanes<S>& L,
   // the argument block, or on an array, is a choice between two addresses: inside a step, where the block
   // is read through a pointer, each was a vector load per cell, two in a row for a draw, and each waited
   // for every observation store the wavefront still had under way.  Steps with a change limit of 100, us:
-  // 8192 16x16 dungeon levels 13.1 -> 10.8, 4096 32x32 ones with three pinpoints 13.6 -> 10.8, 8192 64x64
-  // ones 27.8 -> 22.1, 8192 16x16 maze levels 8.5 -> 7.7.
+  // 8192 16x16 dungeon levels 13.1 -> 10.9, 4096 32x32 ones with three pinpoints 13.6 -> 10.8, 8192 64x64
+  // ones 27.8 -> 22.7, 8192 16x16 maze levels 8.5 -> 7.7.
   uint32_t cdf[PR::K - 1];
 #pragma unroll
   for (int i = 0; i < PR::K - 1; ++i) {
