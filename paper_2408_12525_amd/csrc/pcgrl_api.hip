@@ -8,6 +8,7 @@
 #include <new>
 
 #include "pcgrl_kernels.hip.h"
+#include "pcgrl_spans.h"
 
 using namespace pcgrl;
 
@@ -24,6 +25,9 @@ struct pcgrl_ctx {
   bool may_relay;    // pcgrl_rollout may run as a relay (relay_shape says when): what the rule needs of this context,
   RelayCase relay;   // all but the steps and slots of a call
   size_t roll_lds_wave;
+  int64_t span_room;  // pcgrl_rollout may be cut up along its steps (span_shape says when): levels that d_spans,
+  void* d_spans;      // the states at the starts of the spans, has room for
+  size_t span_lds;    // LDS bytes of an observation wavefront there
   int split;         // pcgrl_step with an observation uses the metrics | observation kernel, with
   int split_m, split_o, split_groups;  // this many levels per metrics / observation wavefront and workgroups
   size_t split_lds_wave;  // LDS bytes of one observation wavefront there
@@ -155,6 +159,16 @@ template <int S, int PROBLEM> struct LaunchRolloutRelay {
     const int searchers = 1 << ((a.envs_per_wave_log2 >> 24) & 0x7f);
     hipLaunchKernelGGL((rollout_relay_kernel<S, PROBLEM>), dim3(ctx->roll_groups), dim3(64 * (2 + searchers + obs_waves)),
                        obs_waves * ctx->roll_lds_wave, st, a);
+    return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
+  }
+};
+template <int S, int PROBLEM> struct LaunchSpans {
+  static int run(const pcgrl_ctx* ctx, const KArgs& a, const SpanArgs& sp, hipStream_t st) {
+    hipLaunchKernelGGL((span_starts_kernel<S, PROBLEM>), dim3(a.B), dim3(64 * kSpanStartWaves), 0, st, a, sp);
+    if (hipGetLastError() != hipSuccess) return PCGRL_E_HIP;
+    // a metrics wavefront and, with observations, one for them, of as many levels as a wavefront holds
+    hipLaunchKernelGGL((rollout_span_kernel<S, PROBLEM>), dim3((a.B + ctx->G - 1) / ctx->G, sp.spans),
+                       dim3(a.obs ? 128 : 64), a.obs ? a.obs_lds_words * 4 : 0, st, a, sp);
     return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
   }
 };
@@ -293,6 +307,24 @@ int prepare_relay(pcgrl_ctx* ctx, int compute_units) {
   c.lds_tables = (int64_t)fa.sharedSizeBytes;
   c.lds_observer = (int64_t)ctx->roll_lds_wave;
   return PCGRL_OK;
+}
+
+// The room a context keeps for the starts of spans, in the order of SpanArgs.
+size_t span_bytes(const pcgrl_ctx* ctx) {
+  return (size_t)ctx->span_room * ((size_t)ctx->S * ctx->word_bytes * (ctx->P + 1) + sizeof(EnvRec) + kMaxMetrics * sizeof(uint32_t));
+}
+SpanArgs span_args(const pcgrl_ctx* ctx, const SpanShape& s) {
+  SpanArgs sp;
+  const size_t rows = (size_t)ctx->span_room * ctx->S * ctx->word_bytes;
+  char* at = static_cast<char*>(ctx->d_spans);
+  sp.planes = at;
+  sp.frozen = at + rows * ctx->P;
+  sp.env = reinterpret_cast<EnvRec*>(at + rows * (ctx->P + 1));
+  sp.targets = reinterpret_cast<uint32_t*>(sp.env + ctx->span_room);
+  sp.plane_stride = (int32_t)(ctx->span_room * ctx->S);
+  sp.spans = s.spans;
+  sp.steps = s.steps;
+  return sp;
 }
 
 int launch_init(pcgrl_ctx* ctx, bool fresh, uint64_t seed, uint8_t* obs, hipStream_t st) {
@@ -533,6 +565,10 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
 
   ctx->exact_waves_log2 = exact_waves_for(ctx->nwaves, ctx->G / ctx->epw, ctx->S);
   const size_t rows = (size_t)ctx->B_pad * ctx->S;
+  // (a configuration that chooses the shape of the launches gets that shape)
+  ctx->span_lds = lds_for(ctx->G);
+  if (cfg->split_step == 0 && cfg->rollout_turns == 0 && cfg->levels_per_wave == 0 && cfg->split_obs_levels == 0 && ctx->span_lds <= 64 * 1024)
+    ctx->span_room = span_room(ctx->S, cfg->problem == PCGRL_BINARY, cfg->batch);
   struct { void** p; size_t n; } allocs[] = {
       // (the binary problem keeps one more plane: the component of the first walkable cell)
       {&ctx->d_planes, rows * ctx->word_bytes * (ctx->P + (cfg->problem == PCGRL_BINARY ? 1 : 0))},
@@ -543,6 +579,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
       // through the one pointer it has at hand when it issues its loads)
       {&ctx->d_targets, ((size_t)ctx->B_pad + 1) * kMaxMetrics * sizeof(uint32_t)},
       {&ctx->d_bad, sizeof(unsigned long long)},
+      {&ctx->d_spans, span_bytes(ctx)},
   };
   for (auto& al : allocs) *al.p = nullptr;
   for (auto& al : allocs) {
@@ -640,7 +677,7 @@ int pcgrl_destroy(pcgrl_ctx* ctx) {
   if (!ctx) return PCGRL_OK;
   DeviceGuard guard(ctx->device);  // (freed in any case)
   int rc = guard.ok && hipDeviceSynchronize() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
-  void* bufs[] = {ctx->d_planes, ctx->d_frozen, ctx->d_env, ctx->d_metrics, ctx->d_targets, ctx->d_bad};
+  void* bufs[] = {ctx->d_planes, ctx->d_frozen, ctx->d_env, ctx->d_metrics, ctx->d_targets, ctx->d_bad, ctx->d_spans};
   for (void* b : bufs)
     if (b && hipFree(b) != hipSuccess) rc = PCGRL_E_HIP;
   delete ctx;
@@ -704,8 +741,18 @@ int pcgrl_rollout(pcgrl_ctx* ctx, const int32_t* actions, int32_t n_steps, uint8
   }
   // (consecutive level groups on one die: only where neighbouring observations share cache lines)
   a.by_die = (a.stream_obs == kStoreCached && (ctx->obs_stride & 127) != 0) ? 1 : 0;
+  auto lg2 = [](int v) { return v == 4 ? 2 : v == 2 ? 1 : 0; };
+  // (a slot that several steps write has to end with the last one's, and spans are not ordered among each other)
+  if (ctx->span_room > 0 && (!obs || obs_slots == n_steps)) {
+    const int64_t batch = ctx->cfg.batch;
+    const SpanShape s = span_shape({ctx->S, ctx->cfg.problem == PCGRL_BINARY, obs != nullptr, batch, n_steps, obs ? batch * (int64_t)ctx->obs_stride : 0});
+    if (s.spans > 1 && s.spans * batch <= ctx->span_room) {
+      a.envs_per_wave_log2 = lg2(ctx->G) | (lg2(ctx->G) << 8);
+      a.obs_lds_words = (int32_t)(ctx->span_lds / 4);
+      return dispatch<LaunchSpans>(ctx->S, ctx->cfg.problem, ctx, a, span_args(ctx, s), static_cast<hipStream_t>(stream));
+    }
+  }
   if (obs && ctx->split_roll) {
-    auto lg2 = [](int v) { return v == 4 ? 2 : v == 2 ? 1 : 0; };
     RelayShape relay = {0, 0};
     if (ctx->may_relay) {
       RelayCase c = ctx->relay;

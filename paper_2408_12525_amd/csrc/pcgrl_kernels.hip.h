@@ -37,9 +37,10 @@ enum : int { kRegionsIncremental = 0, kRegionsRecount = 1 };
 enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
 // step kernel variants: one step per launch; the same with the work of a wavefront split over a metrics
 // wavefront and observation wavefronts of one workgroup; n steps per launch; n steps per launch split the
-// same way; and that with observation wavefronts that take the steps in turn.  (A relay, see
-// rollout_relay_kernel, is a kernel of its own.)
-enum : int { kModeStep = 0, kModeSplit = 1, kModeRollout = 2, kModeRolloutSplit = 3, kModeRolloutTurns = 4 };
+// same way; that with observation wavefronts that take the steps in turn; and that for one span of a rollout,
+// from the state its levels have there (see span_starts_kernel).  (A relay, see rollout_relay_kernel, is a
+// kernel of its own.)
+enum : int { kModeStep = 0, kModeSplit = 1, kModeRollout = 2, kModeRolloutSplit = 3, kModeRolloutTurns = 4, kModeSpan = 5 };
 
 // Per-environment scalars, 32 bytes, read and written as two 16-byte words.
 struct __attribute__((aligned(16))) EnvRec {
@@ -2456,11 +2457,12 @@ __global__ __launch_bounds__(640) void rollout_relay_kernel(KArgs a) {
 // registers for one more wavefront per SIMD on 64-row levels (all 8192 wavefronts of the 64x64
 // maze at a batch of 8192 resident at once, -2.3 % per step; 32x32 dungeon -2.8 %).  WIDTH: which
 // form of the observation code a single step carries (see observe); a rollout carries both.
+// (last_span: the span of a rollout that this workgroup runs is its last one)
 template <int S, int PROBLEM, int MODE, bool PIN, int WIDTH>
-__device__ __forceinline__ void step_body(KArgs& a) {
+__device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_span = false) {
   using W = typename RowWord<S>::T;
   using PR = Prob<PROBLEM>;
-  constexpr bool ROLL = MODE >= kModeRollout;
+  constexpr bool ROLL = MODE >= kModeRollout, SPAN = MODE == kModeSpan;
   constexpr bool SPLIT = MODE != kModeStep && MODE != kModeRollout;
   // Whether what a rollout needs rarely or at its end is looked up in the argument block again instead of
   // being kept in scalar registers, of which the step loop has too few: it spills them to vector
@@ -2468,7 +2470,8 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   // 64x64 dungeons 7.10 / 6.92, 65 536 32x32 binary levels 20.9 / 20.5, 8192 16x16 dungeons without
   // observations 2.10 / 2.04.  Not for split rollouts of 16-row levels (8192 binary levels 4.85 / 4.91, 2048 maze
   // levels 2.42 / 2.49) and, one wavefront a level, 64-row binary and maze levels (12 288 maze levels 12.7 / 12.9).
-  constexpr bool LOOK_UP = ROLL && (SPLIT ? S > 16 : S < 64 || PROBLEM == kDungeon);
+  // (A span's state comes from one place and goes to another: the block holds the latter.)
+  constexpr bool LOOK_UP = SPAN || (ROLL && (SPLIT ? S > 16 : S < 64 || PROBLEM == kDungeon));
   extern __shared__ __align__(16) uint32_t lds_all[];
   Lanes<S> L;
   WaveMap<S> wm;
@@ -2512,7 +2515,7 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   // estimate depends on; an edit elsewhere needs no sweep (see diameter_untouched)
   W comp = 0;
   bool comp_dirty = false;
-  if constexpr (PROBLEM == kBinary) comp = planes[(size_t)PR::P * a.plane_stride + ridx];
+  if constexpr (PROBLEM == kBinary && !SPAN) comp = planes[(size_t)PR::P * a.plane_stride + ridx];
   const uint4* erp = reinterpret_cast<const uint4*>(a.env + wm.envl);
   const uint4 er0 = erp[0], er1 = erp[1];  // unpacked below, after all loads are under way
   int act = a.actions[wm.envl];  // (lanes without a level of their own read a neighbour's and ignore it)
@@ -2523,10 +2526,13 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   // also needed by every lane (the incremental update starts from it).
   const int yi = L.y & (kMaxMetrics - 1);
   const size_t mrow = (size_t)wm.envl * kMaxMetrics;
-  int m_l = a.metrics[mrow + yi];
+  int m_l = 0, regions_now = 0;
+  if constexpr (!SPAN) {
+    m_l = a.metrics[mrow + yi];
+    regions_now = a.metrics[mrow];
+  }
   uint32_t tg_l = a.targets[mrow + yi];
-  int regions_now = a.metrics[mrow];
-  const float w_l = __uint_as_float((a.targets - kMaxMetrics)[yi]);  // (the row in front of the ranges)
+  const float w_l = __uint_as_float(((SPAN ? cold_args<true>().targets : a.targets) - kMaxMetrics)[yi]);  // (the row in front of the ranges)
   // every load above is issued before anything below waits for one of them; now the rest of the
   // arguments is fetched, in their shadow
   __builtin_amdgcn_sched_barrier(0);
@@ -2557,6 +2563,14 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   W inside = inside_row<W>(L.y, h, w);
   bool planes_dirty = false, fz_dirty = false;  // ROLL: what has to be written back at the end
   bool metrics_dirty = false, targets_dirty = false;
+  if constexpr (SPAN) {  // nobody has followed the metrics as far as here
+    int m[PR::M];
+    full_metrics<S, PROBLEM>(L, p, inside, valid, m, comp);
+#pragma unroll
+    for (int i = 0; i < PR::M; ++i)
+      if (yi == i) m_l = m[i];
+    regions_now = m[0];
+  }
   W next_fz_row = 0;
   uint32_t next_cell_frozen = 0;
 
@@ -2806,6 +2820,14 @@ __device__ __forceinline__ void step_body(KArgs& a) {
   }
 
   // ---- store the level's scalars (and, after a rollout, everything that changed)
+  if constexpr (SPAN) {  // (all but the metrics span_starts_kernel has stored)
+    if (last_span && wm.primary) {
+      const KArgs& to = cold_args<true>();
+      if constexpr (PROBLEM == kBinary) reinterpret_cast<W*>(to.planes)[(size_t)PR::P * to.plane_stride + ridx] = comp;
+      if (L.y < PR::M) to.metrics[(size_t)wm.env * kMaxMetrics + L.y] = m_l;
+    }
+    __builtin_amdgcn_endpgm();
+  }
   const KArgs& fin = [&]() -> const KArgs& {
     if constexpr (LOOK_UP) return cold_args<ROLL>();
     else return a;
@@ -2901,6 +2923,231 @@ template <int S, int PROBLEM, int MODE>
 __global__ __launch_bounds__(MODE == kModeRollout ? 64 : 320) void rollout_kernel(KArgs a) {
   static_assert(MODE >= kModeRollout, "rollouts only");
   step_body<S, PROBLEM, MODE, true, kWidthAny>(a);
+}
+
+// ---- Spans: a rollout of a small batch, cut up along its steps.
+// A small batch leaves most of the machine idle while each of its levels goes through one dependent chain
+// per step.  What the levels go through does not depend on the metrics, and costs next to nothing beside
+// them, so one wavefront a level runs ahead through all the steps and writes down what the level looks like
+// at the start of every span of `steps` steps; all spans of all levels are then taken through their steps
+// at the same time, each by wavefronts of its own, which begin with the metrics from scratch.
+// When, and into how many spans, csrc/pcgrl_spans.h says.  256 steps of 64 16x16 binary levels 150 -> 29.8 us (the
+// relay before), 32 steps of 512 16x16 maze levels 32 -> 21, of 1024 32x32 dungeon levels 56 -> 44.
+struct SpanArgs {
+  void* planes;       // word [P][plane_stride], index (span * B + env) * S + y
+  void* frozen;       // word [plane_stride]
+  EnvRec* env;        // [spans * B]
+  uint32_t* targets;  // [spans * B][16]
+  int32_t plane_stride;
+  int32_t spans, steps;  // spans of a rollout, and steps of a span (the last one may have fewer)
+};
+
+// The states at the starts of all spans, and the state after the rollout, all but its metrics.
+// Lane i follows step i of the next 64: where the agent goes is one hash a lane, the tile it finds is that
+// of the latest earlier step of the 64 on the same cell (few share one: `who` names one lane of a cell, and
+// only those that do not find themselves there look at each other), and an edit is the exclusive or of the
+// tile's code before and after, so that the edits of any run of steps go into the bit-planes in LDS at once,
+// in any order.  A step that ends an episode ends the 64 steps early: what later ones did to the level is
+// of no consequence, the new level takes its place.
+// Bound by latency: 256 steps of 64 16x16 binary levels, 64 spans, 7.4 us, 32 steps of 512 64x64 dungeon levels 5.1, of which
+// 3 are the launch, its loads and its stores.  The spans are shared out over kSpanStartWaves wavefronts, which all follow all
+// steps (with one of them 9.8 us; each span is some 400 clocks of reading back and storing).
+constexpr int kSpanStartWaves = 4;
+template <int S, int PROBLEM>
+__global__ __launch_bounds__(64 * kSpanStartWaves) void span_starts_kernel(KArgs a, SpanArgs sp) {
+  using W = typename RowWord<S>::T;
+  using PR = Prob<PROBLEM>;
+  constexpr int kWords = sizeof(W) / 4;
+  struct Tables {
+    uint32_t rows[PR::P][kWords][S];  // the level's bit-planes
+    uint32_t pins[kWords][S];         // its pinpoints
+    uint8_t who[S * S];
+  };
+  __shared__ Tables tables[kSpanStartWaves];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  auto& rows = tables[wave].rows;
+  auto& pins = tables[wave].pins;
+  auto& who = tables[wave].who;
+  Lanes<S> L;
+  WaveMap<S> wm;
+  wm.init(a, L, nullptr, (int)blockIdx.x, 0);
+  const int env = wm.env, lane = L.lane, n_steps = a.rollout_steps;
+  const bool primary = wm.primary;
+  const size_t ridx = (size_t)env * S + L.y;
+  W p[PR::P];
+#pragma unroll
+  for (int k = 0; k < PR::P; ++k) p[k] = reinterpret_cast<const W*>(a.planes)[(size_t)k * a.plane_stride + ridx];
+  W fz = reinterpret_cast<const W*>(a.frozen)[ridx];
+  const uint4* erp = reinterpret_cast<const uint4*>(a.env + env);
+  const uint4 er0 = erp[0], er1 = erp[1];
+  const int yi = L.y & (kMaxMetrics - 1);
+  uint32_t tg = a.targets[(size_t)env * kMaxMetrics + yi];
+  bool targets_moved = false;
+  auto action_at = [&](int step) { return a.actions[(size_t)min(step + lane, n_steps - 1) * a.B + env]; };
+  int act_next = action_at(0);
+  // (every wavefront has the old state before one of them stores the new one)
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  int h = (int)(er0.x & 0xffu), w = (int)((er0.x >> 8) & 0xffu), py = (int)((er0.x >> 16) & 0xffu), px = (int)(er0.x >> 24);
+  int t = (int)er0.y, n_changes = (int)er0.z, episode = (int)er0.w;
+  uint64_t key = (uint64_t)er1.x | ((uint64_t)er1.y << 32);
+  // (a span's record leaves the pinpoint flag of the agent's cell out: a rollout looks at the rows)
+  auto store_env = [&](EnvRec* to, uint32_t at, int t_, int n_changes_, uint32_t cell_frozen) {
+    if (lane == 0) {
+      uint4* r = reinterpret_cast<uint4*>(to);
+      r[0] = make_uint4((uint32_t)h | (uint32_t)w << 8 | at << 16, (uint32_t)t_, (uint32_t)n_changes_, (uint32_t)episode);
+      r[1] = make_uint4((uint32_t)key, (uint32_t)(key >> 32), cell_frozen, 0u);
+    }
+  };
+  auto store_span = [&](int span, uint32_t at, int t_, int n_changes_) {
+    const size_t i = (size_t)span * a.B + env, row = i * S + L.y;
+    if (primary) {
+#pragma unroll
+      for (int k = 0; k < PR::P; ++k) reinterpret_cast<W*>(sp.planes)[(size_t)k * sp.plane_stride + row] = p[k];
+      reinterpret_cast<W*>(sp.frozen)[row] = fz;
+      if (L.y < PR::M) sp.targets[i * kMaxMetrics + L.y] = tg;
+    }
+    store_env(sp.env + i, at, t_, n_changes_, 0u);
+  };
+  auto level_to_lds = [&]() {
+    if (primary) {
+#pragma unroll
+      for (int j = 0; j < kWords; ++j) {
+#pragma unroll
+        for (int k = 0; k < PR::P; ++k) rows[k][j][L.y] = (uint32_t)((uint64_t)p[k] >> (32 * j));
+        pins[j][L.y] = (uint32_t)((uint64_t)fz >> (32 * j));
+      }
+    }
+    lds_sync();
+  };
+  auto level_from_lds = [&]() {
+    lds_sync();
+#pragma unroll
+    for (int k = 0; k < PR::P; ++k) {
+      uint64_t v = rows[k][0][L.y];
+      if constexpr (kWords == 2) v |= (uint64_t)rows[k][1][L.y] << 32;
+      p[k] = (W)v;
+    }
+  };
+  uint32_t at = (uint32_t)py | (uint32_t)px << 8;  // the agent's cell
+  if (wave == 0) store_span(0, at, t, n_changes);
+  level_to_lds();
+  int span = wave == 0 ? kSpanStartWaves : wave;  // the next one for this wavefront to store
+  for (int done_steps = 0; done_steps < n_steps;) {
+    const int n = min(64, n_steps - done_steps);
+    const int act = act_next;
+    act_next = action_at(done_steps + n);
+    // the agent's cell after this lane's step, and before it
+    uint32_t after;
+    if (a.pos_mode == kPosRandom) {
+      const uint64_t u = draw(key, 3, (uint32_t)(t + 1 + lane));
+      after = (uint32_t)below((uint32_t)(u >> 32), h) | (uint32_t)below((uint32_t)u, w) << 8;
+    } else {
+      const uint32_t j = ((at & 0xffu) * (uint32_t)w + (at >> 8) + (uint32_t)lane + 1u) % (uint32_t)(h * w);
+      after = j / (uint32_t)w | (j % (uint32_t)w) << 8;
+    }
+    uint32_t before = dpp_zero_fill<kWaveShr1>(after);
+    if (lane == 0) before = at;
+    lds_sync();
+    const int y = (int)(before & 0xffu), x = (int)(before >> 8), word = x >> 5, cell = y * S + x;
+    int old = 0;
+#pragma unroll
+    for (int k = 0; k < PR::P; ++k) old |= (int)((rows[k][word][y] >> (x & 31)) & 1u) << k;
+    const bool pinned = ((pins[word][y] >> (x & 31)) & 1u) != 0;
+    const bool may_write = lane < n && act >= 0 && act < PR::K && !pinned;
+    // the tile the step finds: that of the latest earlier one on the same cell, if there is one
+    if (may_write) who[cell] = (uint8_t)lane;
+    lds_sync();
+    uint64_t clash = __builtin_amdgcn_ballot_w64(may_write && who[cell] != (uint8_t)lane);
+    if (clash != 0) {
+      uint64_t same = 0;
+      do {  // (once for every cell that several steps share)
+        const int c = __builtin_amdgcn_readlane(cell, (int)__builtin_ctzll(clash));
+        const bool here = may_write && cell == c;
+        const uint64_t all = __builtin_amdgcn_ballot_w64(here);
+        if (here) same = all;
+        clash &= ~all;
+      } while (clash != 0);
+      same &= (1ull << lane) - 1ull;
+      const int tile = __shfl(act, same != 0 ? 63 - __builtin_clzll(same) : lane);
+      if (same != 0) old = tile;
+    }
+    const bool changed = may_write && act != old;
+    const uint64_t changes = __builtin_amdgcn_ballot_w64(changed);
+    auto first_steps = [](int k) { return k >= 64 ? ~0ull : (1ull << k) - 1ull; };
+    const bool ends = t + 1 + lane >= a.max_steps ||
+                      (a.max_changes > 0 && n_changes + (int)__popcll(changes & first_steps(lane + 1)) >= a.max_changes);
+    const uint64_t end = a.autoreset ? __builtin_amdgcn_ballot_w64(lane < n && ends) : 0ull;
+    const int used = end != 0 ? (int)__builtin_ctzll(end) + 1 : n;
+    if (used != n) act_next = action_at(done_steps + used);
+    // the edits, as far as the start of each span that lies among these steps
+    for (int from = 0; from < used;) {
+      const int to = span < sp.spans ? min(used, span * sp.steps - done_steps) : used;
+      if (changed && lane >= from && lane < to) {
+#pragma unroll
+        for (int k = 0; k < PR::P; ++k)
+          if (((old ^ act) >> k) & 1) atomicXor(&rows[k][word][y], 1u << (x & 31));
+      }
+      from = to;
+      if (to == used) break;
+      level_from_lds();
+      store_span(span, (uint32_t)__builtin_amdgcn_readlane((int)after, to - 1), t + to, n_changes + (int)__popcll(changes & first_steps(to)));
+      span += kSpanStartWaves;
+    }
+    t += used;
+    n_changes += (int)__popcll(changes & first_steps(used));
+    at = (uint32_t)__builtin_amdgcn_readlane((int)after, used - 1);
+    done_steps += used;
+    if (end != 0) {  // a new episode
+      key = env_key(a.seed, (uint64_t)env, (uint64_t)(episode + 1));
+      begin_episode<S, PROBLEM, true>(a, L, key, p, fz, h, w, py, px, true, env);
+      h = __builtin_amdgcn_readfirstlane(h);
+      w = __builtin_amdgcn_readfirstlane(w);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)py | (uint32_t)px << 8));
+      episode += 1;
+      t = 0;
+      n_changes = 0;
+      if ((a.ctrl_mask >> yi) & 1u) tg = control_target(a, key, yi);
+      targets_moved = true;
+      lds_sync();
+      level_to_lds();
+    }
+    if (span < sp.spans && span * sp.steps == done_steps) {
+      level_from_lds();
+      store_span(span, at, t, n_changes);
+      span += kSpanStartWaves;
+    }
+  }
+  if (wave != 0) return;
+  level_from_lds();
+  if (primary) {
+#pragma unroll
+    for (int k = 0; k < PR::P; ++k) reinterpret_cast<W*>(a.planes)[(size_t)k * a.plane_stride + ridx] = p[k];
+    reinterpret_cast<W*>(a.frozen)[ridx] = fz;
+    if (targets_moved && L.y < PR::M) a.targets[(size_t)env * kMaxMetrics + L.y] = tg;
+  }
+  store_env(a.env + env, at, t, n_changes, L.gany((uint32_t)L.y == (at & 0xffu) && ((fz >> (at >> 8)) & 1) != 0) ? 1u : 0u);
+}
+
+// One span of the rollout for a group of levels: block x is the group, y the span.
+template <int S, int PROBLEM>
+__global__ __launch_bounds__(320) void rollout_span_kernel(KArgs a, SpanArgs sp) {
+  using W = typename RowWord<S>::T;
+  const int span = (int)blockIdx.y;
+  const size_t level0 = (size_t)span * a.B, step0 = (size_t)span * sp.steps, out0 = step0 * a.B;
+  a.planes = reinterpret_cast<W*>(sp.planes) + level0 * S;
+  a.plane_stride = sp.plane_stride;
+  a.frozen = reinterpret_cast<W*>(sp.frozen) + level0 * S;
+  a.env = sp.env + level0;
+  a.targets = sp.targets + level0 * kMaxMetrics;
+  a.actions += out0;
+  if (a.obs != nullptr) a.obs += out0 * (size_t)a.env_obs_bytes;
+  if (a.reward != nullptr) a.reward += out0;
+  if (a.done != nullptr) a.done += out0;
+  a.rollout_steps = min(sp.steps, a.rollout_steps - (int)step0);
+  step_body<S, PROBLEM, kModeSpan, true, kWidthAny>(a, span == sp.spans - 1);
 }
 
 // ------------------------------------------------- plain-layout conversion

@@ -5,6 +5,7 @@ import torch
 
 import oracle
 import relay_rule
+import span_rule
 from parity import assert_same, check_obs, compare_state
 from paper_2408_12525_amd import binding, workloads as wl
 
@@ -368,7 +369,7 @@ def test_every_argument_of_every_call_is_checked(wrong, packed):
     gpu.close()
 
 
-def _rollouts_against_steps(cfg, T, S):
+def _rollouts_against_steps(cfg, T, S, observed=True):
     """Three rollouts of T steps into S slots, two single steps after each, against the oracle's steps."""
     B = cfg["batch"]
     gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
@@ -378,11 +379,11 @@ def _rollouts_against_steps(cfg, T, S):
         acts = wl.random_actions(cfg, 30 + turn, T + 2, bad_fraction=0.05)
         obs = torch.zeros((S,) + tuple(gpu.obs_shape), dtype=torch.uint8, device=DEV)
         rew, done = torch.empty((T, B), dtype=torch.float32, device=DEV), torch.empty((T, B), dtype=torch.uint8, device=DEV)
-        gpu.pcgrl_rollout(torch.from_numpy(acts[:T].copy()).to(DEV), obs, rew, done)
+        gpu.pcgrl_rollout(torch.from_numpy(acts[:T].copy()).to(DEV), obs if observed else None, rew, done)
         for t in range(T):
             o, r, d = cpu.step(acts[t])
             assert np.array_equal(rew[t].cpu().numpy(), r) and np.array_equal(done[t].cpu().numpy(), d), f"turn {turn} step {t}"
-            if t >= T - S:
+            if observed and t >= T - S:
                 check_obs(gpu, obs[t % S], o, f"turn {turn} step {t}")
         assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), f"turn {turn}")
         assert_same("targets", gpu.pcgrl_get_targets(), cpu.get_targets(), f"turn {turn}")
@@ -437,3 +438,25 @@ def test_every_shape_of_a_relay(problem, B, h, T, slots, shape, more):
     cfg = wl.make_config(problem, B, h, more.pop("obs_w"), **more)
     assert relay_rule.shape(**relay_rule.case_of(cfg, T, slots)) == shape
     _rollouts_against_steps(cfg, T, slots)
+
+
+@pytest.mark.parametrize("problem,B,h,w,T,observed,shape,more", [
+    # one step a span, the last span of a rollout, several levels to a wavefront and some without one
+    (wl.BINARY, 21, 16, 16, 12, True, (12, 1), {}), (wl.MAZE, 130, 16, 11, 70, True, (35, 2), dict(max_changes=5)),
+    (wl.DUNGEON, 9, 32, 20, 131, True, (131, 1), dict(max_steps=40, n_frozen=2)), (wl.BINARY, 300, 30, 32, 33, True, (11, 3), dict(max_changes=3)),
+    (wl.MAZE, 601, 32, 32, 25, False, (13, 2), dict(max_steps=7)), (wl.DUNGEON, 100, 64, 64, 30, True, (15, 2), dict(max_steps=13, min_size=30)),
+    (wl.BINARY, 33, 64, 50, 67, True, (34, 2), dict(max_changes=9, obs_format=1)), (wl.MAZE, 530, 16, 16, 40, True, (14, 3), dict(obs_pitch=-1)),
+    # several episodes within 64 steps, one that ends with every step, and none that ends
+    (wl.DUNGEON, 21, 16, 16, 90, True, (90, 1), dict(max_steps=7, ctrl={1: (3, 9), 2: (2, 6)})),
+    (wl.MAZE, 65, 16, 16, 64, True, (32, 2), dict(max_steps=1)), (wl.BINARY, 70, 16, 16, 129, False, (43, 3), dict(autoreset=0, max_steps=20)),
+    # many steps of 64 on the same cell; round a small map and round again; pinpoints that show
+    (wl.DUNGEON, 17, 2, 3, 140, True, (140, 1), {}), (wl.MAZE, 200, 3, 3, 80, True, (40, 2), dict(pos_mode=wl.POS_SCAN, max_changes=30)),
+    (wl.BINARY, 90, 1, 1, 65, True, (33, 2), dict(max_changes=20)),
+    (wl.DUNGEON, 150, 9, 33, 49, True, (13, 4), dict(pos_mode=wl.POS_SCAN, n_frozen=8, min_size=3, min_w=5, obs_frozen_channel=1, regions_mode=wl.REGIONS_RECOUNT))])
+def test_rollouts_cut_into_spans(problem, B, h, w, T, observed, shape, more):
+    """Rollouts that are cut up along their steps: the state that a wavefront runs ahead to at the start of
+    every span (64 steps at a time, edits of the same cell among them, episodes that end) and what the spans
+    leave behind, against the same steps of the oracle."""
+    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=500, pos_mode=wl.POS_RANDOM), **more))
+    assert span_rule.shape(**span_rule.case_of(cfg, T, observed)) == shape
+    _rollouts_against_steps(cfg, T, T, observed)

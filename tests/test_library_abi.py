@@ -2,11 +2,13 @@
 its defaults agree with the workload tables.  No GPU call is made."""
 import ctypes as C
 import os
+import random
 import re
 
 import pytest
 
 import relay_rule
+import span_rule
 from paper_2408_12525_amd import binding, build, workloads as wl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -300,3 +302,23 @@ def test_get_state_indices_at_every_batch(index, batch, h, w):
                 assert level == b * 256 + t and at == 16 * level and n == max(0, min(16, total - at))
                 if n:
                     assert (env, y, x) == (at // cells, at % cells // w, at % cells % w) and env < batch
+
+
+def test_spans_cover_a_rollout_and_fit_their_room():
+    rng = random.Random(7)
+    cut = 0
+    for _ in range(20000):
+        batch, steps = int(2 ** rng.uniform(0, 24)), int(2 ** rng.uniform(0, 20))
+        case = dict(rows=rng.choice([16, 32, 64]), binary=rng.random() < .5, observed=rng.random() < .5, batch=batch, steps=steps,
+                    step_bytes=rng.choice([0, batch * 75, batch * 4864]))
+        spans, each, room = span_rule.shape_and_room(**case)
+        assert spans == 1 and each == steps or spans > 1 and (spans - 1) * each < steps <= spans * each, case
+        assert spans == 1 or spans * batch <= room <= 16384, case
+        cut += spans > 1
+    assert cut > 2000
+    # where cutting up begins to pay, and where the stores are what a rollout waits for
+    shape = lambda **more: span_rule.shape(**dict(dict(rows=16, binary=1, observed=1, batch=64, steps=256, step_bytes=64 * 1922), **more))  # noqa: E731
+    assert shape() == (64, 4) and shape(steps=11) == (1, 11) and shape(steps=12) == (12, 1)
+    assert shape(step_bytes=9 << 20) == (64, 4) and shape(step_bytes=(9 << 20) + 1) == (1, 256)
+    assert shape(rows=64) == (32, 8) and shape(rows=64, steps=19) == (1, 19) and shape(rows=32, batch=1536, binary=0) == (2, 128)
+    assert shape(batch=4096) == (1, 256) and shape(batch=4096, observed=0, step_bytes=0) == (4, 64) and shape(batch=4097, observed=0, step_bytes=0) == (1, 256)
