@@ -270,11 +270,10 @@ int levels_per_wave_for(int G, int batch, int min_groups) {
 // that takes no more than 4096 wavefronts, up to 8 parts of a 64-row level, 16 or 8 of a 32-row one and
 // 16 or 4 of a 16-row one, the larger number where there is no more than about a workgroup for every
 // other compute unit (32 rows) or two for each (16).  Measured on random levels, us for 1, 2, 4, 8, 16
-// wavefronts a workgroup: 4096 64x64 levels 257 / 222 / 236 / 301 / 495, 1024 of them 147 / 86 / 80 /
-// 88 / 137, 256 147 / 76 / 42 / 38 / 48, 64 119 / 80 / 41 / 34 / 44; 16 384 32x32 levels 194 / 178 /
-// 204 / 281 / 448, 1024 (two copies each) 39 / 25 / 29 / 37 / 54, 128 35 / 22 / 18 / 18 / 21; 16 384
-// 16x16 levels 58 / 53 / 60 / 80 / 126, 1024 (four copies each) 17 / 17 / 19 / 21 / 29, 512 14 / 14 /
-// 13 / 14 / 16.  Levels of one long loop, whose cost is the sweeps of half of its cells, gain from
+// wavefronts a workgroup: 4096 64x64 levels 198 / 144 / 142 / 180 / 284, 1024 of them 113 / 62 / 50 /
+// 61 / 86, 256 110 / 55 / 31 / 32 / 32, 64 92 / 60 / 32 / 34 / 42; 16 384 32x32 levels 199 / 162 /
+// 171 / 228 / 362, 1024 (two copies each) 41 / 26 / 29 / 35 / 49, 128 34 / 20 / 23 / 23 / 24; 16 384
+// 16x16 levels 62 / 50 / 54 / 71 / 112, 1024 (four copies each) 17 / 17 / 16 / 19 / 27.  Levels of one long loop, whose cost is the sweeps of half of its cells, gain from
 // every part: 16 of 32x32 332 with 8 parts, 238 with 16; 64 of 16x16 59 with 4, 34 with 16; 64x64 37
 // 800 with 1, 6700 with 8, 6200 with 16.
 constexpr int kMostExactWavesLog2 = 4;  // a workgroup of 1024 threads

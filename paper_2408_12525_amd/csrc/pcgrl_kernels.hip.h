@@ -1439,6 +1439,51 @@ __global__ __launch_bounds__(64) void init_kernel(KArgs a) {
     observe<S, PROBLEM>(a, L, wm, obs_plan(a, L.lane, wm.sl, a.obs, wm.env0, wm.nvalid), p, fz, inside, py, px);
 }
 
+// The sweep above where a wavefront has one level only: all its lanes are at the same layer, so that nothing
+// but the last layers has to be kept: a layer is its own 10 vector instructions and a quarter of a comparison, where
+// the other form adds some 8 to it (exact diameter of 1024 random 64x64 levels 66.9 -> 50.8 us, with the ball's).
+// A step, which sweeps seldom and not far, is no faster with it (4096 64x64 binary levels 8.70 / 8.96 us).
+__device__ __forceinline__ int sweep_alone(const Lanes<64>& L, uint64_t seed, uint64_t pass, uint64_t& last, uint64_t& comp) {
+  constexpr int S = 64;
+  uint64_t V = seed, before = seed;  // the last layer, and the one before it
+  int k = 0;
+  for (int n = 0; n < kShortTrips; ++n) {
+    const uint64_t one = L.grow(V, pass), two = L.grow(one, pass);
+    if (!wave_any<S>(two != one)) {  // a second layer that adds nothing means the flood is complete
+      const bool odd = wave_any<S>(one != V);
+      comp = one;
+      last = odd ? one & ~V : k == 0 ? seed : V & ~before;
+      return odd ? k + 1 : k;
+    }
+    before = one;
+    V = two;
+    k += 2;
+  }
+  for (;; k += 4) {
+    const uint64_t one = L.grow(V, pass), two = L.grow(one, pass), three = L.grow(two, pass), four = L.grow(three, pass);
+    if (!wave_any<S>(four != three)) {
+      comp = three;
+      last = three & ~two;
+      if (wave_any<S>(last != 0)) return k + 3;
+      last = two & ~one;
+      if (wave_any<S>(last != 0)) return k + 2;
+      last = one & ~V;
+      if (wave_any<S>(last != 0)) return k + 1;
+      last = V & ~before;
+      return k;
+    }
+    before = three;
+    V = four;
+  }
+}
+
+template <int S>
+__device__ __forceinline__ int exact_sweep(const Lanes<S>& L, typename RowWord<S>::T seed, typename RowWord<S>::T pass,
+                                           typename RowWord<S>::T& last, typename RowWord<S>::T& comp) {
+  if constexpr (S == 64) return sweep_alone(L, seed, pass, last, comp);
+  else return sweep<S>(L, seed, pass, last, comp);
+}
+
 // The cells within r edges of a seed (r the same in every lane of a group), and in `ring` those
 // exactly r edges away.
 template <int S>
@@ -1446,6 +1491,15 @@ __device__ __forceinline__ typename RowWord<S>::T ball(const Lanes<S>& L, typena
                                                        int r, typename RowWord<S>::T& ring) {
   using W = typename RowWord<S>::T;
   W V = seed, inner = 0;
+  if constexpr (S == 64) {  // (one level to a wavefront: all lanes are at the same layer)
+    const int n = wave_any<S>(seed != 0) ? __builtin_amdgcn_readfirstlane(r) : 0;
+    for (int i = 0; i < n; ++i) {
+      inner = V;
+      V = L.grow(V, pass);
+    }
+    ring = V & ~inner;
+    return V;
+  }
   for (int i = 0; wave_any<S>(i < r && seed != 0); ++i) {
     const W grown = L.grow(V, pass);
     inner = i < r ? V : inner;
@@ -1489,8 +1543,33 @@ __device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>&
   if (((lines << my) >> L.y & 1) == 0) down = 0;
   const W across = todo & (W)(todo << 1) & (W)(lines << mx);
   W last, reached;
-  sweep<S>(L, down | across, todo, last, reached);
+  exact_sweep<S>(L, down | across, todo, last, reached);
   return todo & ~reached;
+}
+
+// The cells of `todo`, a union of whole components, whose components fit into a square of side 16 of the grid
+// moved by (my, mx), each 0 or 8, that holds no more than best + 1 cells of such components: no path in it has
+// more than `best` edges.  (A square that the move cuts in two counts as one.)
+template <int S>
+__device__ __forceinline__ typename RowWord<S>::T inside_few(const Lanes<S>& L, typename RowWord<S>::T todo, int best, int my, int mx) {
+  using W = typename RowWord<S>::T;
+  static_assert(S >= 32, "a square is a row of 16 lanes");
+  const W in = inside_squares<S>(L, todo, 16, my, mx);
+  // rows and columns moved so that squares are whole lane rows and whole pieces of a word, and back
+  auto turned = [](W r, int by) -> W { return (W)((W)(r >> by) | (W)((W)(r << 1) << (S - 1 - by))); };
+  const W v = turned(L.gread(in, (L.y + my) & (S - 1)), mx);
+  W keep = 0;
+#pragma unroll
+  for (int q = 0; q < S; q += 32) {
+    const uint32_t two = (uint32_t)(v >> q);  // rows of two squares
+    int c = popc(two & 0xffffu) | popc(two >> 16) << 16;
+    c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xf, 0xf, false);  // sums over 2, 4, 8 and 16 lanes
+    c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xf, 0xf, false);
+    c += __builtin_amdgcn_update_dpp(0, c, 0x141, 0xf, 0xf, false);
+    c += __builtin_amdgcn_update_dpp(0, c, 0x140, 0xf, 0xf, false);
+    keep |= (W)(((c & 0xffff) <= best + 1 ? 0xffffu : 0u) | ((c >> 16) <= best + 1 ? 0xffff0000u : 0u)) << q;
+  }
+  return in & L.gread(turned(keep, (S - mx) & (S - 1)), (L.y - my) & (S - 1));
 }
 
 // Exact diameter: the longest shortest path between two cells of a level.  Components are taken one
@@ -1512,13 +1591,14 @@ __device__ __forceinline__ typename RowWord<S>::T inside_squares(const Lanes<S>&
 // of all rims is shared out cell by cell once nobody has a component left.  Lane groups work at their
 // own pace (a group that has nothing to do in a sweep has no seed); every loop ends because each turn
 // takes cells out of a finite set.
-// Some 1400 flood layers for a random 64x64 level of 50 % walls, bound by the latency of one after the
-// other in small batches and by vector instructions (73 % of the issue slots) from 1024 levels on: a
-// sweep from each of its 2000 open cells instead took 1350 us for 1024 levels (a launch of 4096
-// wavefronts and one that folded their results); this takes 80.  A loop of 2080 cells
-// is the worst there is, 1040 sweeps of 1040 layers and bound by instructions: 64 such levels 6.7 ms
+// Some 1400 flood layers for a random 64x64 level of 50 % walls (540 of them the first sweeps of 22 components; 1800
+// and 50 components before inside_few, and while a part told the others its finds only once it was done with
+// a component), bound by the latency of one after the other in small batches and by vector instructions from
+// 1024 levels on: a sweep from each of its 2000 open cells instead took 1350 us for 1024 levels (a launch of 4096
+// wavefronts and one that folded their results); this takes 51 (76.9 before inside_few and sweep_alone).  A loop of 2080 cells
+// is the worst there is, 1040 sweeps of 1040 layers and bound by instructions: 64 such levels 5.9 ms
 // (37.8 while the owner swept the whole rim, 6.5 from each cell on 4096 wavefronts; one level alone takes
-// as long here, and took 2.0 there), 1024 of them 26.7 ms (38.0, 104).
+// as long here, and took 2.0 there), 1024 of them 22.5 ms (38.0, 104).
 // (Of 0, 2, 4, 8 and 16 own rim cells: 1024 levels of rooms 68, 67, 57, 57, 57 us, of a grid of corridors 63,
 // 78, 77, 107, 114.)
 constexpr int kOwnRimCells = 4;
@@ -1587,7 +1667,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   // found: a new best widens the ball around the middle of the component, otherwise v's own ball goes.
   auto rule_out = [&](W v, W middle) -> W {
     W far, all;
-    const int e = sweep<S>(L, v, pass, far, all);
+    const int e = exact_sweep<S>(L, v, pass, far, all);
     const bool longer = e > best;
     best = max(best, e);
     return ball<S>(L, longer ? middle & all : v, pass, longer ? best >> 1 : best - e, none);
@@ -1596,7 +1676,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   {
     W cross = L.y == row_mid ? todo : (W)0;
     if (parts_log2 == 0) cross |= todo & ((W)1 << (w / 2));
-    sweep<S>(L, cross, todo, src, comp);
+    exact_sweep<S>(L, cross, todo, src, comp);
     src = first_cell<S>(L, src);
   }
   for (bool first = true;; first = false) {
@@ -1609,10 +1689,15 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
         for (int turn = 0; turn < max(4 >> parts_log2, 1); ++turn) {  // (four grids at least)
           const int t = part + (turn << parts_log2);
           const int half = n >> 1, quarter = (t >> 2) & 1 ? n >> 2 : 0;
-          const W small = inside_squares<S>(L, n > side ? todo : (W)0, max(n, 2), ((t & 1) ? half : 0) + quarter,
+          W small = inside_squares<S>(L, n > side ? todo : (W)0, max(n, 2), ((t & 1) ? half : 0) + quarter,
                                             (((t ^ (t >> 1)) & 1) ? half : 0) + quarter);
           take(left, small);
-          todo &= ~small;
+          todo &= look(left);
+          if constexpr (S > 16) {
+            small = inside_few<S>(L, n > side ? todo : (W)0, best, (t & 1) ? 8 : 0, ((t ^ (t >> 1)) & 1) ? 8 : 0);
+            take(left, small);
+            todo &= look(left);
+          }
         }
         side = max(side, n);
       }
@@ -1620,7 +1705,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     if (!first || !L.gany(src != 0)) src = choose(todo);
     if (!wave_any<S>(src != 0)) break;
     W far;
-    const int e1 = sweep<S>(L, src, pass, far, comp);
+    const int e1 = exact_sweep<S>(L, src, pass, far, comp);
     // (the first cell decides, before the others go: a part that looks while they do sees a piece of
     // the component, which it may take for a small one but no longer for its own.  The words of a row
     // and the rows are atomics of their own, hence the fence: were the others seen to go first, a piece
@@ -1628,13 +1713,16 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     const bool ours = L.gany(take(left, first_cell<S>(L, comp)) != 0);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     take(left, comp);
-    best = max(best, e1);
+    // (told to the others at once: a component no more than half as deep as another is done with)
+    if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], e1);
+    best = max(best, best_so_far());
     bool open = ours && 2 * e1 > best;
     if (wave_any<S>(open)) {
       W end_a = first_cell<S>(L, far);
       if (!open) end_a = 0;
-      const int e2 = sweep<S>(L, end_a, pass, far, none);
-      best = max(best, e2);
+      const int e2 = exact_sweep<S>(L, end_a, pass, far, none);
+      if (L.y == 0) atomicMax(&shared_best[wm.sl.slot], e2);
+      best = max(best, best_so_far());
       open = open && 2 * e1 > best;
       if (wave_any<S>(open)) {
         W ring_a, ring_b;
@@ -1643,7 +1731,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
         ball<S>(L, end_a, pass, e2 >> 1, ring_a);
         ball<S>(L, end_b, pass, e2 - (e2 >> 1), ring_b);
         const W centre = middle_cell<S>(L, ring_a & ring_b);
-        const int ec = sweep<S>(L, centre, pass, far, none);
+        const int ec = exact_sweep<S>(L, centre, pass, far, none);
         best = max(best, ec);
         open = open && 2 * ec > best;
         const W core = open ? centre : (W)0;
@@ -2526,12 +2614,10 @@ __device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_s
   // also needed by every lane (the incremental update starts from it).
   const int yi = L.y & (kMaxMetrics - 1);
   const size_t mrow = (size_t)wm.envl * kMaxMetrics;
-  int m_l = 0, regions_now = 0;
-  if constexpr (!SPAN) {
-    m_l = a.metrics[mrow + yi];
-    regions_now = a.metrics[mrow];
-  }
+  int m_l = 0, regions_now = 0;  // (a span has them from scratch, below)
+  if constexpr (!SPAN) m_l = a.metrics[mrow + yi];
   uint32_t tg_l = a.targets[mrow + yi];
+  if constexpr (!SPAN) regions_now = a.metrics[mrow];
   const float w_l = __uint_as_float(((SPAN ? cold_args<true>().targets : a.targets) - kMaxMetrics)[yi]);  // (the row in front of the ranges)
   // every load above is issued before anything below waits for one of them; now the rest of the
   // arguments is fetched, in their shadow

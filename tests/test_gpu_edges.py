@@ -460,3 +460,31 @@ def test_rollouts_cut_into_spans(problem, B, h, w, T, observed, shape, more):
     cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=500, pos_mode=wl.POS_RANDOM), **more))
     assert span_rule.shape(**span_rule.case_of(cfg, T, observed)) == shape
     _rollouts_against_steps(cfg, T, T, observed)
+
+
+@pytest.mark.parametrize("n,corridor", [(64, 40), (32, 25)])
+def test_exact_diameter_of_snakes_beside_a_corridor(n, corridor):
+    """A corridor and a snake in a square of side 16, of a few cells less or more than the corridor has: squares with
+    no more cells than the longest path so far are dropped unswept, wherever they lie against the grid."""
+    snake = [(2 * r + k, c) for r in range(8) for k, c in
+             [(0, c) for c in (range(14) if r % 2 == 0 else range(13, -1, -1))] + [(1, 13 if r % 2 == 0 else 0)]]
+    maps, want = [], []
+    for oy in range(2, n - 15, 5):
+        for ox in range(0, n - 13, 3):
+            for cells in range(corridor - 1, corridor + 4):
+                t = np.ones((n, n), np.int8)
+                t[0, :corridor] = 0
+                for y, x in snake[:cells]:
+                    t[oy + y, ox + x] = 0
+                maps.append(t)
+                want.append(max(corridor, cells) - 1)  # (both are paths: one edge less than cells)
+    B = len(maps)
+    hw = torch.full((B, 2), n, dtype=torch.int16, device=DEV)
+    gpu = binding.Pcgrl(wl.make_config(wl.BINARY, B, n, 5, min_size=1, autoreset=0), 0)
+    gpu.pcgrl_reset(1)
+    for tiles in (np.stack(maps), np.stack(maps)[:, ::-1].copy(), np.stack(maps)[:, :, ::-1].copy()):
+        gpu.pcgrl_set_state(torch.from_numpy(tiles).to(DEV), None, hw, torch.zeros_like(hw))
+        for parts_log2 in (-1, 0, 3):
+            got = gpu.pcgrl_exact_diameter_static(torch.empty(B, dtype=torch.int32, device=DEV), parts_log2)
+            assert_same("exact diameters", got, np.array(want, np.int32), parts_log2)
+    gpu.close()
