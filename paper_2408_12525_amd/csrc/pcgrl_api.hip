@@ -814,12 +814,19 @@ int pcgrl_get_state(pcgrl_ctx* ctx, int8_t* tiles, uint8_t* frozen, int16_t* hw,
   hipStream_t st = static_cast<hipStream_t>(stream);
   const GetGrid g = get_grid((uint32_t)ctx->cfg.batch, (uint32_t)(ctx->cfg.max_h * ctx->cfg.max_w), tiles || frozen);
   const dim3 grid(g.x, g.y);
-  if (ctx->S == 64)
-    hipLaunchKernelGGL(get_state_kernel<uint64_t>, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, ctx->P, tiles, frozen,
-                       hw, pos, counters);
-  else
-    hipLaunchKernelGGL(get_state_kernel<uint32_t>, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, ctx->P, tiles, frozen,
-                       hw, pos, counters);
+  const GetSizes sizes = get_sizes((uint32_t)ctx->cfg.batch, ctx->cfg.max_h * ctx->cfg.max_w, ctx->cfg.max_w);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kGetThreads), 0, st, ctx->base, ctx->S, sizes, tiles, frozen, hw, pos, counters);
+  };
+  if (ctx->S == 64) {
+    if (ctx->P == 1) launch(get_state_kernel<uint64_t, 1>);
+    else if (ctx->P == 2) launch(get_state_kernel<uint64_t, 2>);
+    else launch(get_state_kernel<uint64_t, 3>);
+  } else {
+    if (ctx->P == 1) launch(get_state_kernel<uint32_t, 1>);
+    else if (ctx->P == 2) launch(get_state_kernel<uint32_t, 2>);
+    else launch(get_state_kernel<uint32_t, 3>);
+  }
   return hipGetLastError() == hipSuccess ? PCGRL_OK : PCGRL_E_HIP;
 }
 

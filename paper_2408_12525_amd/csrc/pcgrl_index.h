@@ -30,19 +30,49 @@ struct GetPiece {
   int env, y, x;     // the level, row and column of the first one
 };
 
+// The sizes of the arrays, with what stands for a division by each on the device, where one takes some twenty
+// vector instructions, and a 64-bit one hundreds: the largest 32-bit number over the divisor, times which the
+// upper half of a product is the quotient or up to two less.
+struct GetSizes {
+  uint64_t total;                     // cells of all levels
+  uint32_t cells, max_w;              // of a level, of its rows
+  uint32_t per_level, per_row;        // see above
+};
+constexpr GetSizes get_sizes(uint32_t batch, int cells, int max_w) {
+  return {(uint64_t)batch * (uint64_t)cells, (uint32_t)cells, (uint32_t)max_w, 0xffffffffu / (uint32_t)cells, 0xffffffffu / (uint32_t)max_w};
+}
+constexpr uint32_t divided(uint32_t n, uint32_t by, uint32_t reciprocal, uint32_t& rest) {
+  uint32_t q = (uint32_t)(((uint64_t)n * reciprocal) >> 32);
+  rest = n - q * by;
+  for (int k = 0; k < 2; ++k) {
+    const uint32_t more = rest >= by ? 1u : 0u;
+    q += more;
+    rest -= more != 0 ? by : 0u;
+  }
+  return q;
+}
+
 // The piece of thread `thread` of workgroup (bx, by).
-constexpr GetPiece get_piece(uint32_t bx, uint32_t by, int thread, uint32_t batch, int cells, int max_w) {
-  const uint64_t total = (uint64_t)batch * (uint64_t)cells;
+constexpr GetPiece get_piece(uint32_t bx, uint32_t by, int thread, const GetSizes& s) {
   const uint64_t first = ((uint64_t)by * kGetRow + bx) * (uint64_t)(kGetThreads * kGetBytes);
   GetPiece p = {first + (uint64_t)(kGetBytes * thread), 0, 0, 0, 0};
-  if (p.at < total) {
-    const int from = (int)(first % (uint32_t)cells) + kGetBytes * thread;  // (the 64-bit division is the whole workgroup's)
-    p.n = total - p.at < (uint64_t)kGetBytes ? (int)(total - p.at) : kGetBytes;
-    p.env = (int)(first / (uint32_t)cells) + from / cells;
-    p.y = from % cells / max_w;
-    p.x = from % cells % max_w;
+  if (p.at < s.total) {
+    uint32_t level = 0, rest = 0, x = 0;  // (the first cell's: the whole workgroup's)
+    if (s.total <= 0xffffffffu) {
+      level = divided((uint32_t)first, s.cells, s.per_level, rest);
+    } else {
+      level = (uint32_t)(first / s.cells);
+      rest = (uint32_t)(first % s.cells);
+    }
+    p.n = s.total - p.at < (uint64_t)kGetBytes ? (int)(s.total - p.at) : kGetBytes;
+    p.env = (int)(level + divided(rest + (uint32_t)(kGetBytes * thread), s.cells, s.per_level, rest));
+    p.y = (int)divided(rest, s.max_w, s.per_row, x);
+    p.x = (int)x;
   }
   return p;
+}
+constexpr GetPiece get_piece(uint32_t bx, uint32_t by, int thread, uint32_t batch, int cells, int max_w) {
+  return get_piece(bx, by, thread, get_sizes(batch, cells, max_w));
 }
 
 // The level whose scalars a thread writes, if there is one of that number.
