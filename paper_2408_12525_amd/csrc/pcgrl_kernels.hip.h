@@ -401,17 +401,62 @@ __device__ __forceinline__ W channel_row(const W (&p)[Prob<PROBLEM>::P], W insid
 // back cost about as much as three layers, which long floods need not pay every time.
 constexpr int kShortTrips = 2;
 
+// Floods all levels of a wavefront of several until none grows any more, keeping of each what its last layers
+// are worked out from afterwards: the cells at the end of its last trip that still grew (`base`), those one
+// layer before (`before`), and how many layers that is.  Kept once a trip and for the level as a whole, where a lane
+// for itself would have to be looked at after every second layer: for 32-row levels, whose floods are long.  Us without / with:
+// steps of 16 384 32x32 binary levels 12.4 / 12.1, of 4096 8.3 / 8.15, 4096 exact diameters 61.5 / 60.1, 16 384
+// levels installed and read back 31.6 / 30.8; 16-row levels, four to a wavefront, are faster where a batch is small (8192 with 15 cells 6.9 / 6.7) and
+// slower where it is large (65 536 19.1 / 19.7), and their rollouts would lose a wavefront a SIMD to the registers.  Nor for
+// rollouts of large batches (65 536 32x32 levels 19.5 / 19.7 us a step).
+template <int S>
+__device__ __forceinline__ int flood_to_end(const Lanes<S>& L, typename RowWord<S>::T seed, typename RowWord<S>::T pass,
+                                            typename RowWord<S>::T& base, typename RowWord<S>::T& before) {
+  using W = typename RowWord<S>::T;
+  W V = seed;
+  int k = 0;
+  base = seed;
+  before = 0;
+  auto trip = [&](auto n_tag) {
+    constexpr int N = decltype(n_tag)::value;
+    W one = V, two = V;
+#pragma unroll
+    for (int l = 0; l < N; l += 2) two = L.grow_twice(two, pass, one);
+    const uint64_t grew = __builtin_amdgcn_ballot_w64(two != one);
+    const bool mine = L.gbits(grew) != 0;
+    base = mine ? two : base;
+    before = mine ? one : before;
+    k += mine ? N : 0;
+    V = two;
+    return grew != 0;
+  };
+  bool more = true;
+  for (int n = 0; n < kShortTrips && more; ++n) more = trip(std::integral_constant<int, 2>{});
+  while (more) more = trip(std::integral_constant<int, 4>{});
+  return k;
+}
+
 // One sweep of the two-sweep diameter estimate: breadth-first layers from `seed` inside `pass`.
 // Returns the eccentricity of the seed and leaves in `last` the cells of the last layer
 // (the seed itself when nothing else is reachable) and in `comp` all the cells reached.  The loop advances two layers per trip and
 // only remembers, per lane, what the last pair of layers that reached the lane added; which of the
 // two layers was the last one is worked out after the loop with one more layer from the cells
 // known before that pair.
-template <int S>
+template <int S, bool TRIPS = S == 32>
 __device__ __forceinline__ int sweep(const Lanes<S>& L, typename RowWord<S>::T seed,
                                      typename RowWord<S>::T pass, typename RowWord<S>::T& last,
                                      typename RowWord<S>::T& comp) {
   using W = typename RowWord<S>::T;
+  if constexpr (TRIPS) {  // (see flood_to_end)
+    W base, before, one;
+    const int k = flood_to_end<S>(L, seed, pass, base, before);
+    const W two = L.grow_twice(base, pass, one), three = L.grow(two, pass);
+    const W l3 = three & ~two, l2 = two & ~one, l1 = one & ~base;
+    const bool a3 = L.gany(l3 != 0), a2 = L.gany(l2 != 0), a1 = L.gany(l1 != 0);
+    last = a3 ? l3 : a2 ? l2 : a1 ? l1 : (W)(base & ~before);
+    comp = three;
+    return k + (a3 ? 3 : a2 ? 2 : a1 ? 1 : 0);
+  }
   W V = seed, added = seed;
   int k = 0, k_last = 0;  // pairs done; the pair that last added cells in this lane
   auto pair_of_layers = [&]() {
@@ -443,10 +488,16 @@ __device__ __forceinline__ int sweep(const Lanes<S>& L, typename RowWord<S>::T s
 }
 
 // The eccentricity alone.
-template <int S>
+template <int S, bool TRIPS = S == 32>
 __device__ __forceinline__ int eccentricity(const Lanes<S>& L, typename RowWord<S>::T seed,
                                             typename RowWord<S>::T pass) {
   using W = typename RowWord<S>::T;
+  if constexpr (TRIPS) {  // (see flood_to_end)
+    W base, before, one;
+    const int k = flood_to_end<S>(L, seed, pass, base, before);
+    const W two = L.grow_twice(base, pass, one), three = L.grow(two, pass);
+    return k + (L.gany(three != two) ? 3 : L.gany(two != one) ? 2 : L.gany(one != base) ? 1 : 0);
+  }
   W V = seed;
   int k = 0, k1 = 0, k2 = 0;  // pairs done; the pairs whose first / second layer last reached this lane
   auto pair_of_layers = [&]() {
@@ -472,15 +523,15 @@ __device__ __forceinline__ int eccentricity(const Lanes<S>& L, typename RowWord<
 // longest shortest path out of x (lowest row-major index among equally far cells).
 // `comp` receives the component of x: the estimate depends on nothing else (see
 // diameter_untouched).
-template <int S>
+template <int S, bool TRIPS = S == 32>
 __device__ __forceinline__ int two_sweep_diameter(const Lanes<S>& L, typename RowWord<S>::T pass,
                                                   typename RowWord<S>::T& comp) {
   using W = typename RowWord<S>::T;
   W x = first_cell<S>(L, pass);
   W far;
-  sweep<S>(L, x, pass, far, comp);
+  sweep<S, TRIPS>(L, x, pass, far, comp);
   W y = first_cell<S>(L, far);
-  return eccentricity<S>(L, y, pass);
+  return eccentricity<S, TRIPS>(L, y, pass);
 }
 
 // Whether an edit leaves the two-sweep estimate as it is.  The estimate is a function of x, the
@@ -796,7 +847,7 @@ __device__ __forceinline__ int neighbour_components(const Lanes<S>& L, typename 
 }
 
 // Full metric vector of the level held by a group (all M entries).
-template <int S, int PROBLEM>
+template <int S, int PROBLEM, bool TRIPS = S == 32>
 __device__ __forceinline__ void full_metrics(const Lanes<S>& L,
                                              const typename RowWord<S>::T (&p)[Prob<PROBLEM>::P],
                                              typename RowWord<S>::T inside, bool active,
@@ -814,7 +865,7 @@ __device__ __forceinline__ void full_metrics(const Lanes<S>& L,
   for (int k = 0; k < PR::K; ++k) cells += m[PR::CNT + k];
   m[0] = regions_full<S>(L, pass, in, 5 * m[PR::CNT + 1] <= 3 * cells);
   if constexpr (PROBLEM == kBinary) {
-    m[1] = two_sweep_diameter<S>(L, pass, comp);
+    m[1] = two_sweep_diameter<S, TRIPS>(L, pass, comp);
   } else if constexpr (PROBLEM == kMaze) {
     W r;
     int d = nearest<S>(L, channel_row<PROBLEM, W>(p, in, 2), channel_row<PROBLEM, W>(p, in, 3), pass, r);
@@ -2551,6 +2602,7 @@ __device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_s
   using W = typename RowWord<S>::T;
   using PR = Prob<PROBLEM>;
   constexpr bool ROLL = MODE >= kModeRollout, SPAN = MODE == kModeSpan;
+  constexpr bool TRIPS = S == 32 && (!ROLL || SPAN);  // (see flood_to_end)
   constexpr bool SPLIT = MODE != kModeStep && MODE != kModeRollout;
   // Whether what a rollout needs rarely or at its end is looked up in the argument block again instead of
   // being kept in scalar registers, of which the step loop has too few: it spills them to vector
@@ -2651,7 +2703,7 @@ __device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_s
   bool metrics_dirty = false, targets_dirty = false;
   if constexpr (SPAN) {  // nobody has followed the metrics as far as here
     int m[PR::M];
-    full_metrics<S, PROBLEM>(L, p, inside, valid, m, comp);
+    full_metrics<S, PROBLEM, TRIPS>(L, p, inside, valid, m, comp);
 #pragma unroll
     for (int i = 0; i < PR::M; ++i)
       if (yi == i) m_l = m[i];
@@ -2791,7 +2843,7 @@ __device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_s
         const bool need = changed && !diameter_untouched<S>(L, comp, cell, L.dilate(cell), py, px, now_pass);
         if (wave_any<S>(need)) {
           W ncomp;
-          int dm = two_sweep_diameter<S>(L, need ? pass : (W)0, ncomp);
+          int dm = two_sweep_diameter<S, TRIPS>(L, need ? pass : (W)0, ncomp);
           if (need) {
             comp = ncomp;
             comp_dirty = true;
@@ -2834,7 +2886,7 @@ __device__ __forceinline__ void step_body(KArgs& a, [[maybe_unused]] bool last_s
       W ninside = inside_row<W>(L.y, nh, nw);
       int nm[PR::M];
       W ncomp;
-      full_metrics<S, PROBLEM>(L, np, ninside, restart, nm, ncomp);
+      full_metrics<S, PROBLEM, TRIPS>(L, np, ninside, restart, nm, ncomp);
       if (restart) {
 #pragma unroll
         for (int i = 0; i < PR::P; ++i) {
