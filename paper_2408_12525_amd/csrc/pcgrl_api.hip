@@ -231,8 +231,14 @@ const SplitRule kStepSplit[] = {
     {16, 8193, kMax, 3072, kMax, 256 * kMB + 1, 448 * kMB, -1, 0},  // stored through the cache: +17 %
     {16, 8193, kMax, 1536, kMax, 0, kMax, -1, 1},     // maze16 -13 % at 12 288, -2...-4 % from 32 768; binary16 -3 % at 262 144
     {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // dungeon32 -16 % at 256, -7 % at 4096
+    {32, 4097, 4608, 0, kMax, 0, kMax, -1, 1},        // us one / two at 4097: maze 6.18 / 5.96 (9 cells), binary 8.61 / 8.45, dungeon 6.84 / 6.54
+    {32, 4609, 6144, 1024, kMax, 0, kMax, -1, 1},     // at 5000 and 6000: maze (15 cells) 6.93 / 6.79, 7.24 / 7.08, (21) 7.30 / 6.91, 7.61 / 7.23; with
+                                                      // 9 cells dungeon 7.26 / 7.33, 7.64 / 7.64
     {32, 4097, 16384, 2560, kMax, 0, kMax, -1, 1},    // us one / two, observation: maze 8192 10.2 / 9.7 (4.8 KB), 7.8 / 7.9 (2.2 KB),
                                                       // 16 384 17.2 / 16.3, 11.9 / 12.3; dungeon 16 384 14.3 / 13.6 (3.5 KB); binary 8192 11.0 / 10.6 (2.9 KB)
+    {32, 16385, kMax, 2560, kMax, 0, 168 * kMB, -1, 1},  // us one / two: maze (31 cells) 16 385 17.2 / 15.9, 20 000 20.2 / 19.1, 32 768 32.1 / 31.0,
+                                                      // binary 20 000 15.7 / 15.5, 50 000 29.8 / 27.7, dungeon (21) 16 385 14.6 / 13.8, 32 768 24.1 /
+                                                      // 23.7, but 50 000 (179 MB a step) 38.7 / 44.6; smaller windows 16 385 maze (21 cells) 11.9 / 12.3
     {64, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // maze64 -12 % at 256, -4 % at 4096; none from 8192 on
     {64, 4097, 12288, 6000, kMax, 0, kMax, -1, 1},    // dungeon (7.7 KB) 4097 10.5 / 10.1, 8192 16.0 / 15.0, 12 288 20.7 / 19.5, binary (6.1 KB)
                                                       // 10.3 / 9.9, 13.5 / 13.4, 17.4 / 16.8; maze (4.8 KB) 8.8 / 8.6, 12.1 / 12.3, 15.0 / 15.7
