@@ -229,6 +229,8 @@ struct SplitRule {
 const SplitRule kStepSplit[] = {
     {16, 1, 8192, 0, kMax, 0, kMax, -1, 1},           // -10...-25 % per step at batches of 512...8192
     {16, 8193, kMax, 3072, kMax, 256 * kMB + 1, 448 * kMB, -1, 0},  // stored through the cache: +17 %
+    {16, 8193, 12288, 0, kMax, 0, kMax, -1, 1},       // us one / two at 8193, 12 288, 20 000: binary (15 cells) 7.7 / 7.4, 8.3 / 8.2, 10.0 / 10.1, maze (15)
+                                                      // 6.3 / 5.6, 7.0 / 6.5, 8.5 / 8.6, dungeon (7) 6.4 / 5.9, 7.2 / 6.9, 8.8 / 9.0
     {16, 8193, kMax, 1536, kMax, 0, kMax, -1, 1},     // maze16 -13 % at 12 288, -2...-4 % from 32 768; binary16 -3 % at 262 144
     {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // dungeon32 -16 % at 256, -7 % at 4096
     {32, 4097, 4608, 0, kMax, 0, kMax, -1, 1},        // us one / two at 4097: maze 6.18 / 5.96 (9 cells), binary 8.61 / 8.45, dungeon 6.84 / 6.54
@@ -252,8 +254,16 @@ const SplitRule kRolloutSplit[] = {
     {16, 2049, 4096, 4096, kMax, 0, kMax, -1, 1},     // maze16 -20 % at 4096
     {16, 16384, kMax, 4096, kMax, 0, kMax, -1, 1},    // maze16 -2...-3 % (at 8192: +6 %, hence the gap)
     {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // -43 % at 256, -24 % at 4096
+    {16, 12289, 65536, 0, 1535, 0, kMax, PCGRL_BINARY, 1},  // us a step one / two at 20 000, 40 000: 7 cells 6.4 / 6.2, 9.8 / 9.5, 15 cells 6.6 / 6.4, 10.8 / 10.2;
+                                                      // 200 001 (9) 38.8 / 40.2; others no gain (maze, 9 cells, 20 001 4.3 / 4.4)
+    {32, 4097, 5120, 0, 5999, 0, kMax, -1, 1},        // at 4097: maze (15) 3.5 / 3.0, dungeon (15) 4.0 / 3.4; at 6000 4.0 / 3.9, 4.7 / 4.8; dungeon (31) 4200 6.9 / 7.0
+    {32, 10240, kMax, 0, kMax, 0, kMax, PCGRL_MAZE, 1},      // at 8192, 12 288, 20 000: 15 cells 4.7 / 4.7, 6.5 / 6.0, 9.3 / 8.7, 31 cells 7.0 / 7.2, 12.5 / 11.6, 19.6 / 18.6
+    {32, 10240, 12800, 0, kMax, 0, kMax, PCGRL_DUNGEON, 1},  // 15 cells 5.5 / 5.6, 7.8 / 7.5, (14 001) 8.7 / 8.9, 23 cells 6.4 / 6.5, 11.5 / 10.6, 18.0 / 17.5
     {32, 4097, kMax, 0, kMax, 0, kMax, PCGRL_BINARY, 1},  // +10 % steps/s at 16 384 (dungeon: +-2 %)
     {64, 1, 8192, 0, kMax, 0, kMax, -1, 1},           // -6 %
+    {64, 8193, kMax, 0, 2047, 0, kMax, -1, 1},        // 15 cells at 8193, 10 000, 16 000: binary 6.0 / 5.7, 6.8 / 6.5, 9.6 / 9.5, maze 6.9 / 6.4, 7.8 / 7.4, 11.0 / 10.7, dungeon
+                                                      // 8.4 / 7.8, 9.5 / 9.0, 14.0 / 13.4; larger windows: binary (31) 9001 7.0 / 7.4, maze (23) 16 000 13.2 / 14.8
+    {64, 8193, 12288, 6000, kMax, 0, kMax, PCGRL_DUNGEON, 1},  // 31 cells 13.8 / 12.8, 16.4 / 15.5, 19.1 / 18.5; 23 cells 10.1 / 10.1, 11.4 / 11.9
     {0, 1, kMax, 0, kMax, 0, kMax, -1, 0},
 };
 template <size_t N>
