@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "pcgrl_api.hip")
 DEPS = [SRC, os.path.join(HERE, "csrc", "pcgrl_kernels.hip.h"), os.path.join(HERE, "csrc", "pcgrl_index.h"),
         os.path.join(HERE, "csrc", "pcgrl_relay.h"), os.path.join(HERE, "csrc", "pcgrl_spans.h"),
+        os.path.join(HERE, "csrc", "pcgrl_split.h"),
         os.path.join(os.path.dirname(HERE), "include", "pcgrl.h")]
 LIB_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIB_DIR, "libpcgrl.so")

@@ -28,7 +28,7 @@ struct pcgrl_ctx {
   int64_t span_room;  // pcgrl_rollout may be cut up along its steps (span_shape says when): levels that d_spans,
   void* d_spans;      // the states at the starts of the spans, has room for
   size_t span_lds;    // LDS bytes of an observation wavefront there
-  int split;         // pcgrl_step with an observation uses the metrics | observation kernel, with
+  int split[3];      // pcgrl_step with an observation uses the metrics | observation kernel (by how it stores, kStore*), with
   int split_m, split_o, split_groups;  // this many levels per metrics / observation wavefront and workgroups
   size_t split_lds_wave;  // LDS bytes of one observation wavefront there
   size_t obs_bytes;  // bytes of one level's observation in the chosen format
@@ -210,70 +210,6 @@ template <int S, int PROBLEM> struct LaunchExact {
 // what was refused stays refused.
 constexpr size_t kStaticMostParts = (size_t)1 << 18;
 
-// ---- launch shapes.  Results never depend on them; every row below is a measurement on MI355X
-// (per-step launches replayed from a HIP graph, rollouts of 100 steps; the figures are in the
-// design notes).  A rule table is read top down and the first row whose conditions all hold
-// decides; ranges are inclusive.
-constexpr int64_t kMax = INT64_MAX;
-constexpr int64_t kMB = (int64_t)1 << 20;
-struct SplitRule {
-  int S;                            // size class (16 / 32 / 64 rows), 0 = any
-  int64_t batch_lo, batch_hi;       // environments
-  int64_t obs_lo, obs_hi;           // bytes of one level's observation
-  int64_t step_lo, step_hi;         // bytes of one step's observations, whole batch
-  int problem;                      // -1 = any
-  int split;                        // 1: a metrics wavefront and observation wavefronts per workgroup
-};
-// pcgrl_step.  Two wavefronts per level group shorten the dependent chain of a launch at the price
-// of loading the level twice.
-const SplitRule kStepSplit[] = {
-    {16, 1, 8192, 0, kMax, 0, kMax, -1, 1},           // -10...-25 % per step at batches of 512...8192
-    {16, 8193, kMax, 3072, kMax, 256 * kMB + 1, 448 * kMB, -1, 0},  // stored through the cache: +17 %
-    {16, 8193, 12288, 0, kMax, 0, kMax, -1, 1},       // us one / two at 8193, 12 288, 20 000: binary (15 cells) 7.7 / 7.4, 8.3 / 8.2, 10.0 / 10.1, maze (15)
-                                                      // 6.3 / 5.6, 7.0 / 6.5, 8.5 / 8.6, dungeon (7) 6.4 / 5.9, 7.2 / 6.9, 8.8 / 9.0
-    {16, 8193, kMax, 1536, kMax, 0, kMax, -1, 1},     // maze16 -13 % at 12 288, -2...-4 % from 32 768; binary16 -3 % at 262 144
-    {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // dungeon32 -16 % at 256, -7 % at 4096
-    {32, 4097, 4608, 0, kMax, 0, kMax, -1, 1},        // us one / two at 4097: maze 6.18 / 5.96 (9 cells), binary 8.61 / 8.45, dungeon 6.84 / 6.54
-    {32, 4609, 6144, 1024, kMax, 0, kMax, -1, 1},     // at 5000 and 6000: maze (15 cells) 6.93 / 6.79, 7.24 / 7.08, (21) 7.30 / 6.91, 7.61 / 7.23; with
-                                                      // 9 cells dungeon 7.26 / 7.33, 7.64 / 7.64
-    {32, 4097, 16384, 2560, kMax, 0, kMax, -1, 1},    // us one / two, observation: maze 8192 10.2 / 9.7 (4.8 KB), 7.8 / 7.9 (2.2 KB),
-                                                      // 16 384 17.2 / 16.3, 11.9 / 12.3; dungeon 16 384 14.3 / 13.6 (3.5 KB); binary 8192 11.0 / 10.6 (2.9 KB)
-    {32, 16385, kMax, 2560, kMax, 0, 168 * kMB, -1, 1},  // us one / two: maze (31 cells) 16 385 17.2 / 15.9, 20 000 20.2 / 19.1, 32 768 32.1 / 31.0,
-                                                      // binary 20 000 15.7 / 15.5, 50 000 29.8 / 27.7, dungeon (21) 16 385 14.6 / 13.8, 32 768 24.1 /
-                                                      // 23.7, but 50 000 (179 MB a step) 38.7 / 44.6; smaller windows 16 385 maze (21 cells) 11.9 / 12.3
-    {64, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // maze64 -12 % at 256, -4 % at 4096; none from 8192 on
-    {64, 4097, 12288, 6000, kMax, 0, kMax, -1, 1},    // dungeon (7.7 KB) 4097 10.5 / 10.1, 8192 16.0 / 15.0, 12 288 20.7 / 19.5, binary (6.1 KB)
-                                                      // 10.3 / 9.9, 13.5 / 13.4, 17.4 / 16.8; maze (4.8 KB) 8.8 / 8.6, 12.1 / 12.3, 15.0 / 15.7
-    {0, 1, kMax, 0, kMax, 0, kMax, -1, 0},
-};
-// pcgrl_rollout (each wavefront keeps its own copy of the level for all the steps).
-const SplitRule kRolloutSplit[] = {
-    {16, 1, 2048, 0, kMax, 0, kMax, -1, 1},           // -35 % per step at 64 and 1024
-    {16, 2049, 12288, 0, 4095, 0, kMax, -1, 1},       // binary16 +39 % steps/s at 4096, +22 % at 8192
-    {16, 12289, kMax, 1536, 4095, 0, kMax, -1, 1},    // binary16 -5...-9 % per step from 16 384 to 131 072
-    {16, 2049, 4096, 4096, kMax, 0, kMax, -1, 1},     // maze16 -20 % at 4096
-    {16, 16384, kMax, 4096, kMax, 0, kMax, -1, 1},    // maze16 -2...-3 % (at 8192: +6 %, hence the gap)
-    {32, 1, 4096, 0, kMax, 0, kMax, -1, 1},           // -43 % at 256, -24 % at 4096
-    {16, 12289, 65536, 0, 1535, 0, kMax, PCGRL_BINARY, 1},  // us a step one / two at 20 000, 40 000: 7 cells 6.4 / 6.2, 9.8 / 9.5, 15 cells 6.6 / 6.4, 10.8 / 10.2;
-                                                      // 200 001 (9) 38.8 / 40.2; others no gain (maze, 9 cells, 20 001 4.3 / 4.4)
-    {32, 4097, 5120, 0, 5999, 0, kMax, -1, 1},        // at 4097: maze (15) 3.5 / 3.0, dungeon (15) 4.0 / 3.4; at 6000 4.0 / 3.9, 4.7 / 4.8; dungeon (31) 4200 6.9 / 7.0
-    {32, 10240, kMax, 0, kMax, 0, kMax, PCGRL_MAZE, 1},      // at 8192, 12 288, 20 000: 15 cells 4.7 / 4.7, 6.5 / 6.0, 9.3 / 8.7, 31 cells 7.0 / 7.2, 12.5 / 11.6, 19.6 / 18.6
-    {32, 10240, 12800, 0, kMax, 0, kMax, PCGRL_DUNGEON, 1},  // 15 cells 5.5 / 5.6, 7.8 / 7.5, (14 001) 8.7 / 8.9, 23 cells 6.4 / 6.5, 11.5 / 10.6, 18.0 / 17.5
-    {32, 4097, kMax, 0, kMax, 0, kMax, PCGRL_BINARY, 1},  // +10 % steps/s at 16 384 (dungeon: +-2 %)
-    {64, 1, 8192, 0, kMax, 0, kMax, -1, 1},           // -6 %
-    {64, 8193, kMax, 0, 2047, 0, kMax, -1, 1},        // 15 cells at 8193, 10 000, 16 000: binary 6.0 / 5.7, 6.8 / 6.5, 9.6 / 9.5, maze 6.9 / 6.4, 7.8 / 7.4, 11.0 / 10.7, dungeon
-                                                      // 8.4 / 7.8, 9.5 / 9.0, 14.0 / 13.4; larger windows: binary (31) 9001 7.0 / 7.4, maze (23) 16 000 13.2 / 14.8
-    {64, 8193, 12288, 6000, kMax, 0, kMax, PCGRL_DUNGEON, 1},  // 31 cells 13.8 / 12.8, 16.4 / 15.5, 19.1 / 18.5; 23 cells 10.1 / 10.1, 11.4 / 11.9
-    {0, 1, kMax, 0, kMax, 0, kMax, -1, 0},
-};
-template <size_t N>
-int first_match(const SplitRule (&table)[N], int S, int64_t batch, int64_t obs, int64_t step_bytes, int problem) {
-  for (const SplitRule& r : table)
-    if ((r.S == 0 || r.S == S) && batch >= r.batch_lo && batch <= r.batch_hi && obs >= r.obs_lo && obs <= r.obs_hi &&
-        step_bytes >= r.step_lo && step_bytes <= r.step_hi && (r.problem < 0 || r.problem == problem))
-      return r.split;
-  return 0;
-}
 // As many levels per wavefront (a power of two up to G) as still leave `min_groups` wavefronts.
 int levels_per_wave_for(int G, int batch, int min_groups) {
   int n = G;
@@ -507,11 +443,11 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
   }
   // One wavefront per level group, or a metrics wavefront and observation wavefronts: by table.
   const size_t obs_batch_bytes = ctx->obs_stride * (size_t)cfg->batch;
-  ctx->split = first_match(kStepSplit, ctx->S, cfg->batch, (int64_t)E, (int64_t)obs_batch_bytes, cfg->problem);
-  ctx->split_roll = first_match(kRolloutSplit, ctx->S, cfg->batch, (int64_t)E, (int64_t)obs_batch_bytes, cfg->problem);
+  const SplitCase sc = {ctx->S, cfg->problem, cfg->batch, (int64_t)E, (int64_t)obs_batch_bytes, (ctx->obs_stride & 127) == 0};
+  auto split_if = [&](int rule) { return cfg->split_step == PCGRL_SPLIT_AUTO ? rule : cfg->split_step == PCGRL_SPLIT_ON ? 1 : 0; };
+  for (int store : {kStoreCached, kStoreStream, kStoreThrough}) ctx->split[store] = split_if(split_step(sc, store));
+  ctx->split_roll = split_if(split_rollout(sc));
   const bool obs_heavy = E >= 4096;
-  if (cfg->split_step == PCGRL_SPLIT_OFF) ctx->split = ctx->split_roll = 0;
-  if (cfg->split_step == PCGRL_SPLIT_ON) ctx->split = ctx->split_roll = 1;
   // Shape of the split step: one metrics wavefront carries as many levels as the explicit choice
   // (or the automatic one above) says, and the observation can be shared out over several
   // wavefronts of split_o levels each (measured: within 3 % of one observation wavefront, which
@@ -718,7 +654,7 @@ int pcgrl_step(pcgrl_ctx* ctx, const int32_t* actions, uint8_t* obs, float* rewa
   a.reward = reward;
   a.done = done;
   if (obs && ctx->store_step_auto) a.stream_obs = step_store_kind(ctx, obs);
-  if (obs && ctx->split) {
+  if (obs && ctx->split[a.stream_obs]) {
     auto lg2 = [](int v) { return v == 4 ? 2 : v == 2 ? 1 : 0; };
     a.envs_per_wave_log2 = lg2(ctx->split_m) | (lg2(ctx->split_o) << 8);
     a.obs_lds_words = (int32_t)(ctx->split_lds_wave / 4);

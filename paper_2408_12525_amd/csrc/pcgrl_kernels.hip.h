@@ -17,6 +17,7 @@
 
 #include "pcgrl_index.h"
 #include "pcgrl_relay.h"
+#include "pcgrl_split.h"
 
 namespace pcgrl {
 
@@ -34,7 +35,6 @@ enum : int { kBinary = 0, kMaze = 1, kDungeon = 2 };
 enum : int { kPadBorder = 0, kPadWall = 1 };
 enum : int { kPosScan = 0, kPosRandom = 1 };
 enum : int { kRegionsIncremental = 0, kRegionsRecount = 1 };
-enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
 // step kernel variants: one step per launch; the same with the work of a wavefront split over a metrics
 // wavefront and observation wavefronts of one workgroup; n steps per launch; n steps per launch split the
 // same way; that with observation wavefronts that take the steps in turn; and that for one span of a rollout,

@@ -1,22 +1,18 @@
 """The library's rule for rollouts as a relay (csrc/pcgrl_relay.h), compiled for the host, and what a
 configuration hands to it."""
-import ctypes as C
-import functools
 import json
 import os
 import re
-import subprocess
-import tempfile
 
+import host_rule
 from paper_2408_12525_amd import binding, build, workloads as wl
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2408_12525_amd", "csrc")
 COMPUTE_UNITS = 256
 FIELDS = ("rows", "binary", "per_simd", "compute_units", "workgroups", "observers", "obs_bytes", "step_bytes", "lds_tables",
           "lds_observer", "steps", "slots")
 SOURCE = """
 #include "pcgrl_relay.h"
-extern "C" void shape(const int64_t* v, int* out) {
+extern "C" void rule(const int64_t* v, int64_t* out) {
   pcgrl::RelayCase c;
   c.rows = (int)v[0]; c.binary = v[1] != 0; c.per_simd = (int)v[2]; c.compute_units = (int)v[3]; c.workgroups = v[4];
   c.observers = (int)v[5]; c.obs_bytes = v[6]; c.step_bytes = v[7]; c.lds_tables = v[8]; c.lds_observer = v[9];
@@ -27,22 +23,10 @@ extern "C" void shape(const int64_t* v, int* out) {
 """
 
 
-@functools.lru_cache(None)
-def _lib():
-    with tempfile.TemporaryDirectory() as d:
-        with open(os.path.join(d, "relay.cpp"), "w") as f:
-            f.write(SOURCE)
-        so = os.path.join(d, "relay.so")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-I", CSRC, f.name, "-o", so], check=True)
-        return C.CDLL(so)
-
-
 def shape(**case):
     """(searchers, turns) of one case; every field of it has to be given."""
-    v, out = (C.c_int64 * len(FIELDS))(*[case[k] for k in FIELDS]), (C.c_int * 2)()
     assert set(case) == set(FIELDS)
-    _lib().shape(v, out)
-    return tuple(out)
+    return host_rule.call(SOURCE, [case[k] for k in FIELDS], 2)
 
 
 def resources(kernel):
@@ -77,8 +61,7 @@ def case_of(cfg, steps, slots):
             n *= 2
         return n
 
-    obs = wl.obs_bytes(dict(cfg, obs_pitch=0))
-    stride = wl.obs_bytes(cfg)
+    obs, stride = wl.obs_bytes(cfg), host_rule.obs_stride(cfg)
     levels = most
     while levels > 1 and -(-B // levels) < 1024:
         levels //= 2

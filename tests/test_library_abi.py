@@ -7,8 +7,10 @@ import re
 
 import pytest
 
+import host_rule
 import relay_rule
 import span_rule
+import split_rule
 from paper_2408_12525_amd import binding, build, workloads as wl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -322,3 +324,15 @@ def test_spans_cover_a_rollout_and_fit_their_room():
     assert shape(step_bytes=9 << 20) == (64, 4) and shape(step_bytes=(9 << 20) + 1) == (1, 256)
     assert shape(rows=64) == (32, 8) and shape(rows=64, steps=19) == (1, 19) and shape(rows=32, batch=1536, binary=0) == (2, 128)
     assert shape(batch=4096) == (1, 256) and shape(batch=4096, observed=0, step_bytes=0) == (4, 64) and shape(batch=4097, observed=0, step_bytes=0) == (1, 256)
+
+
+@pytest.mark.parametrize("problem,ow,pitch,batch,one,many", [
+    # (one: a single buffer, written through; many: a buffer for each step, so many that they do not fit the caches)
+    (wl.DUNGEON, 18, -1, 32768, 0, 0), (wl.DUNGEON, 19, -1, 32768, 0, 0), (wl.DUNGEON, 19, 0, 32768, 0, 1), (wl.DUNGEON, 20, -1, 28000, 0, 1), (wl.DUNGEON, 21, -1, 32768, 1, 1),
+    (wl.DUNGEON, 21, -1, 40000, 1, 0), (wl.DUNGEON, 23, -1, 32768, 1, 0), (wl.DUNGEON, 25, 0, 32768, 1, 1), (wl.MAZE, 23, -1, 40000, 0, 1),
+    (wl.MAZE, 25, -1, 40000, 1, 1), (wl.MAZE, 25, -1, 50000, 1, 0), (wl.MAZE, 29, 0, 40000, 1, 1), (wl.MAZE, 29, -1, 40000, 1, 0), (wl.MAZE, 31, -1, 32768, 1, 1), (wl.BINARY, 31, -1, 50000, 1, 1),
+    (wl.BINARY, 35, -1, 40000, 1, 0), (wl.DUNGEON, 23, 0, 50000, 0, 0), (wl.MAZE, 21, 0, 32768, 0, 0)])
+def test_steps_of_large_batches_take_two_wavefronts_where_that_is_ahead(problem, ow, pitch, batch, one, many):
+    cfg = wl.make_config(problem, batch, 32, ow, obs_pitch=pitch)
+    large = host_rule.obs_stride(cfg) * batch >= 128 << 20 and wl.obs_bytes(cfg) >= 3072
+    assert split_rule.step(cfg, "through") == one and split_rule.step(cfg, "cached" if large else "stream") == many
