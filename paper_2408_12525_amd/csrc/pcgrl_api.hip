@@ -20,7 +20,7 @@ struct pcgrl_ctx {
   int epw;  // distinct levels per wavefront (a divisor of G)
   size_t word_bytes;
   size_t lds_bytes;  // per wavefront
-  int split_roll;    // pcgrl_rollout with observations does the same, with its own shape:
+  int split_roll[4]; // pcgrl_rollout with observations does the same (by its ring, kRing*), with its own shape:
   int roll_m, roll_o, roll_groups, roll_turns;
   bool may_relay;    // pcgrl_rollout may run as a relay (relay_shape says when): what the rule needs of this context,
   RelayCase relay;   // all but the steps and slots of a call
@@ -240,7 +240,7 @@ int exact_waves_for(int nwaves, int copies, int S) {
 int prepare_relay(pcgrl_ctx* ctx, int compute_units) {
   const pcgrl_config& cfg = ctx->cfg;
   const bool long_episodes = !cfg.autoreset || (cfg.max_steps >= kRelaySteps && (cfg.max_changes == 0 || cfg.max_changes >= kRelaySteps));
-  ctx->may_relay = ctx->split_roll && cfg.rollout_turns == 0 && long_episodes;
+  ctx->may_relay = ctx->split_roll[kRingFits] && cfg.rollout_turns == 0 && long_episodes;
   if (!ctx->may_relay) return PCGRL_OK;
   hipFuncAttributes fa;
   const int rc = dispatch<RelayAttributes>(ctx->S, cfg.problem, &fa);
@@ -446,7 +446,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
   const SplitCase sc = {ctx->S, cfg->problem, cfg->batch, (int64_t)E, (int64_t)obs_batch_bytes, (ctx->obs_stride & 127) == 0};
   auto split_if = [&](int rule) { return cfg->split_step == PCGRL_SPLIT_AUTO ? rule : cfg->split_step == PCGRL_SPLIT_ON ? 1 : 0; };
   for (int store : {kStoreCached, kStoreStream, kStoreThrough}) ctx->split[store] = split_if(split_step(sc, store));
-  ctx->split_roll = split_if(split_rollout(sc));
+  for (int ring : {kRingFits, kRingSpills, kRingBeyond, kRingStreams}) ctx->split_roll[ring] = split_if(split_rollout(sc, ring));
   const bool obs_heavy = E >= 4096;
   // Shape of the split step: one metrics wavefront carries as many levels as the explicit choice
   // (or the automatic one above) says, and the observation can be shared out over several
@@ -483,7 +483,8 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
   if (cfg->split_obs_levels > 0) ctx->roll_o = ctx->split_o < ctx->roll_m ? ctx->split_o : ctx->roll_m;
   ctx->roll_groups = (cfg->batch + ctx->roll_m - 1) / ctx->roll_m;
   ctx->roll_lds_wave = lds_for(ctx->roll_o);
-  if (ctx->roll_lds_wave * (ctx->roll_m / ctx->roll_o) > 64 * 1024) ctx->split_roll = 0;
+  if (ctx->roll_lds_wave * (ctx->roll_m / ctx->roll_o) > 64 * 1024)
+    for (int& split : ctx->split_roll) split = 0;
   // A small batch leaves most SIMDs idle while every wavefront runs one long dependent chain per
   // step.  The observation wavefronts then take the steps in turn: each follows the level through
   // all the edits (a few dozen instructions a step) and builds the observation of every n-th step
@@ -703,7 +704,7 @@ int pcgrl_rollout(pcgrl_ctx* ctx, const int32_t* actions, int32_t n_steps, uint8
       return dispatch<LaunchSpans>(ctx->S, ctx->cfg.problem, ctx, a, span_args(ctx, s), static_cast<hipStream_t>(stream));
     }
   }
-  if (obs && ctx->split_roll) {
+  if (obs && ctx->split_roll[ring_of(a.stream_obs, (int64_t)a.obs_slots * (int64_t)ctx->obs_stride * ctx->cfg.batch)]) {
     RelayShape relay = {0, 0};
     if (ctx->may_relay) {
       RelayCase c = ctx->relay;

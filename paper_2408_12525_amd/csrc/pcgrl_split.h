@@ -10,21 +10,29 @@ namespace pcgrl {
 
 // How observations are stored: ordinary, non-temporal and write-through stores.
 enum : int { kStoreCached = 0, kStoreStream = 1, kStoreThrough = 2 };
+// Where a rollout's ring of observation slots goes: ordinary stores into one that stays in the memory-side cache of 256 MB,
+// into one that is somewhat larger, and into a much larger one; other stores.  (Of 64-row levels, 8 slots of 27 MB, two wavefronts
+// take 1.04 times as many a second as one into 219 MB, and 0.95 times as many into 220.)
+enum : int { kRingFits = 0, kRingSpills = 1, kRingBeyond = 2, kRingStreams = 3 };
+constexpr int ring_of(int store, int64_t ring_bytes) {
+  return store != kStoreCached ? kRingStreams : ring_bytes <= (int64_t)219 << 20 ? kRingFits : ring_bytes <= (int64_t)448 << 20 ? kRingSpills : kRingBeyond;
+}
 
 // Results never depend on a launch shape; every row below is a measurement on MI355X (per-step launches replayed
 // from a HIP graph, rollouts of 8 to 100 steps).  A table is read top down and the first row whose conditions all
 // hold decides; ranges are inclusive.
 constexpr int64_t kMax = INT64_MAX;
 constexpr int64_t kMB = (int64_t)1 << 20;
-// (each with whole 128-byte lines to a level's observation, and eight times that without)
-enum : int { kCached = 9 << kStoreCached, kStream = 9 << kStoreStream, kThrough = 9 << kStoreThrough, kAnyStore = 63, kNoLines = 56 };
+// (each with whole 128-byte lines to a level's observation, and sixteen times that without)
+enum : int { kCached = 17 << kStoreCached, kStream = 17 << kStoreStream, kThrough = 17 << kStoreThrough, kAnyStore = 255, kNoLines = 240 };
+enum : int { kSpills = 17 << kRingSpills, kBeyond = 17 << kRingBeyond };
 struct SplitRule {
   int S;                            // size class (16 / 32 / 64 rows), 0 = any
   int64_t batch_lo, batch_hi;       // environments
   int64_t obs_lo, obs_hi;           // bytes of one level's observation
   int64_t step_lo, step_hi;         // bytes of one step's observations, whole batch
   int problem;                      // -1 = any
-  int stores;                       // the ways of storing that it holds for
+  int stores;                       // the ways of storing, or rings, that it holds for
   int split;                        // 1: a metrics wavefront and observation wavefronts per workgroup
 };
 struct SplitCase {
@@ -75,27 +83,33 @@ inline constexpr SplitRule kRolloutSplit[] = {
     {32, 1, 4096, 0, kMax, 0, kMax, -1, kAnyStore, 1},           // -43 % at 256, -24 % at 4096
     {16, 12289, 65536, 0, 1535, 0, kMax, PCGRL_BINARY, kAnyStore, 1},  // us a step one / two at 20 000, 40 000: 7 cells 6.4 / 6.2, 9.8 / 9.5, 15 cells 6.6 / 6.4, 10.8 / 10.2;
                                                       // 200 001 (9) 38.8 / 40.2; others no gain (maze, 9 cells, 20 001 4.3 / 4.4)
+    {32, 4097, 5120, 4608, 5999, 0, kMax, PCGRL_DUNGEON, kBeyond, 0},  // 25 cells, one of two, 48 slots (1 GB) 4097 0.95...0.96, 5120 0.94...0.97; 16 slots 1.02...1.06, 8 slots 1.17...1.23
+    {32, 4353, 5120, 3840, 4607, 0, kMax, PCGRL_DUNGEON, kBeyond, 0},  // 23 cells, 48 slots 4097 1.03, 4608 0.96...0.97, 5120 0.94...0.96; 8 slots 1.09...1.12
     {32, 4097, 5120, 0, 5999, 0, kMax, -1, kAnyStore, 1},        // at 4097: maze (15) 3.5 / 3.0, dungeon (15) 4.0 / 3.4; at 6000 4.0 / 3.9, 4.7 / 4.8; dungeon (31) 4200 6.9 / 7.0
-    {32, 10240, kMax, 0, kMax, 0, kMax, PCGRL_MAZE, kAnyStore, 1},      // at 8192, 12 288, 20 000: 15 cells 4.7 / 4.7, 6.5 / 6.0, 9.3 / 8.7, 31 cells 7.0 / 7.2, 12.5 / 11.6, 19.6 / 18.6
-    {32, 10240, 12800, 0, kMax, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 15 cells 5.5 / 5.6, 7.8 / 7.5, (14 001) 8.7 / 8.9, 23 cells 6.4 / 6.5, 11.5 / 10.6, 18.0 / 17.5
+    {32, 10240, 131072, 0, 5999, 0, kMax, PCGRL_MAZE, kAnyStore, 1},  // 15 cells at 8192, 12 288, 20 000 4.7 / 4.7, 6.5 / 6.0, 9.3 / 8.7, 120 000 1.02, 31 cells 7.0 / 7.2, 12.5 / 11.6,
+                                                      // 19.6 / 18.6, 70 000 1.00...1.02; 45 cells 10 240 to 70 000 0.98...1.01
+    {32, 10240, 12800, 0, 8191, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 15 cells 5.5 / 5.6, 7.8 / 7.5, (14 001) 8.7 / 8.9, 23 cells 6.4 / 6.5, 11.5 / 10.6, 18.0 / 17.5, 31 cells 1.01...1.04
     {32, 4097, kMax, 0, kMax, 0, kMax, PCGRL_BINARY, kAnyStore, 1},  // +10 % steps/s at 16 384 (dungeon: +-2 %)
     {64, 1, 8192, 0, kMax, 0, kMax, -1, kAnyStore, 1},           // -6 %
-    {64, 8193, kMax, 0, 2047, 0, kMax, -1, kAnyStore, 1},        // 15 cells at 8193, 10 000, 16 000: binary 6.0 / 5.7, 6.8 / 6.5, 9.6 / 9.5, maze 6.9 / 6.4, 7.8 / 7.4, 11.0 / 10.7, dungeon
-                                                      // 8.4 / 7.8, 9.5 / 9.0, 14.0 / 13.4; larger windows: binary (31) 9001 7.0 / 7.4, maze (23) 16 000 13.2 / 14.8
-    {64, 8193, 12288, 6000, kMax, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 31 cells 13.8 / 12.8, 16.4 / 15.5, 19.1 / 18.5; 23 cells 10.1 / 10.1, 11.4 / 11.9
+    {64, 8193, kMax, 0, 2047, 16 * kMB + 1, kMax, -1, kSpills, 0},  // one of two, 8 slots: maze (20 cells) 24 001 0.88, (15) 32 768 0.95, binary (20) 24 001 0.95, (25) 20 000 0.88;
+                                                      // 16 slots: maze (20) 12 000 0.95; 48 slots of up to 9 MB are ahead as in the next row
+    {64, 8193, 24576, 0, 2047, 0, kMax, -1, kAnyStore, 1},       // 15 cells at 8193, 10 000, 16 000, 24 001: binary 6.4 / 6.1, 6.8 / 6.5, 10.1 / 9.9, 13.3 / 13.3 (48 slots 1.01), maze 6.8 / 6.3,
+                                                      // 7.8 / 7.4, 11.0 / 10.6, 15.3 / 15.2 (1.03), dungeon 8.2 / 7.5, 9.5 / 9.0, 13.9 / 13.4, (1.06); 32 768 0.95...1.01
+    {64, 24577, 32768, 0, 2047, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 5 to 15 cells at 32 768 1.03...1.06
+    {64, 8193, 12288, 6000, kMax, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 31 cells 13.8 / 12.8, 16.4 / 15.5, 19.1 / 18.5; 23 cells 10.1 / 10.1, 11.4 / 11.9; 41 cells, 48 slots 0.98...1.00
     {0, 1, kMax, 0, kMax, 0, kMax, -1, kAnyStore, 0},
 };
 
 template <size_t N>
-constexpr int first_match(const SplitRule (&table)[N], const SplitCase& c, int store) {
+constexpr int first_match(const SplitRule (&table)[N], const SplitCase& c, int how) {
   for (const SplitRule& r : table)
     if ((r.S == 0 || r.S == c.S) && c.batch >= r.batch_lo && c.batch <= r.batch_hi && c.obs_bytes >= r.obs_lo &&
         c.obs_bytes <= r.obs_hi && c.step_bytes >= r.step_lo && c.step_bytes <= r.step_hi && (r.problem < 0 || r.problem == c.problem) &&
-        ((r.stores >> (store + (c.whole_lines ? 0 : 3))) & 1) != 0)
+        ((r.stores >> (how + (c.whole_lines ? 0 : 4))) & 1) != 0)
       return r.split;
   return 0;
 }
 constexpr int split_step(const SplitCase& c, int store) { return first_match(kStepSplit, c, store); }
-constexpr int split_rollout(const SplitCase& c) { return first_match(kRolloutSplit, c, kStoreCached); }
+constexpr int split_rollout(const SplitCase& c, int ring) { return first_match(kRolloutSplit, c, ring); }
 
 }  // namespace pcgrl

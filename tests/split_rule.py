@@ -7,7 +7,7 @@ SOURCE = """
 #include "pcgrl_split.h"
 extern "C" void rule(const int64_t* v, int64_t* out) {
   const pcgrl::SplitCase c = {(int)v[0], (int)v[1], v[2], v[3], v[4], v[5] != 0};
-  out[0] = v[6] != 0 ? pcgrl::split_rollout(c) : pcgrl::split_step(c, (int)v[7]);
+  out[0] = v[6] != 0 ? pcgrl::split_rollout(c, pcgrl::ring_of((int)v[7], v[8])) : pcgrl::split_step(c, (int)v[7]);
 }
 """
 
@@ -20,4 +20,9 @@ def _case(cfg):
 
 def step(cfg, store):
     """Whether a step that stores its observations this way takes two wavefronts."""
-    return bool(host_rule.call(SOURCE, _case(cfg) + [0, STORES[store]], 1)[0])
+    return bool(host_rule.call(SOURCE, _case(cfg) + [0, STORES[store], 0], 1)[0])
+
+
+def rollout(cfg, slots, store):
+    """Whether a rollout into that many slots, stored this way, takes two wavefronts."""
+    return bool(host_rule.call(SOURCE, _case(cfg) + [1, STORES[store], slots * host_rule.obs_stride(cfg) * cfg["batch"]], 1)[0])

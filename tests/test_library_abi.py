@@ -336,3 +336,15 @@ def test_steps_of_large_batches_take_two_wavefronts_where_that_is_ahead(problem,
     cfg = wl.make_config(problem, batch, 32, ow, obs_pitch=pitch)
     large = host_rule.obs_stride(cfg) * batch >= 128 << 20 and wl.obs_bytes(cfg) >= 3072
     assert split_rule.step(cfg, "through") == one and split_rule.step(cfg, "cached" if large else "stream") == many
+
+
+@pytest.mark.parametrize("problem,rows,ow,pitch,batch,slots,store,two", [
+    # a ring that the cache holds, one that it does not, and one that is not stored through it
+    (wl.MAZE, 64, 20, 0, 14000, 8, "cached", 1), (wl.MAZE, 64, 20, 0, 16000, 8, "cached", 0), (wl.MAZE, 64, 20, 0, 12000, 16, "cached", 0), (wl.MAZE, 64, 20, 0, 24000, 48, "stream", 1),
+    (wl.BINARY, 64, 25, -1, 20000, 8, "cached", 0), (wl.BINARY, 64, 9, -1, 24001, 48, "cached", 1), (wl.BINARY, 64, 9, -1, 32768, 48, "cached", 0),
+    (wl.DUNGEON, 64, 9, 0, 32768, 8, "cached", 1), (wl.DUNGEON, 64, 9, 0, 50000, 8, "cached", 0), (wl.MAZE, 64, 9, 0, 50000, 8, "cached", 0),
+    (wl.DUNGEON, 32, 25, 0, 4097, 8, "cached", 1), (wl.DUNGEON, 32, 25, 0, 4097, 16, "cached", 1),
+    (wl.DUNGEON, 32, 25, 0, 4097, 48, "cached", 0), (wl.DUNGEON, 32, 23, -1, 4097, 48, "cached", 1), (wl.DUNGEON, 32, 23, -1, 4608, 48, "cached", 0), (wl.DUNGEON, 32, 21, -1, 5120, 48, "cached", 1), (wl.MAZE, 32, 25, -1, 5120, 48, "cached", 1), (wl.MAZE, 32, 15, 0, 120000, 8, "stream", 1),
+    (wl.MAZE, 32, 15, 0, 200000, 8, "stream", 0), (wl.MAZE, 32, 45, 0, 10240, 48, "cached", 0), (wl.DUNGEON, 32, 35, 0, 10240, 8, "cached", 0)])
+def test_rollouts_of_large_batches_take_two_wavefronts_where_that_is_ahead(problem, rows, ow, pitch, batch, slots, store, two):
+    assert split_rule.rollout(wl.make_config(problem, batch, rows, ow, obs_pitch=pitch), slots, store) == two
