@@ -520,7 +520,7 @@ int pcgrl_create(pcgrl_ctx** out, const pcgrl_config* cfg, int device) {
   // (a configuration that chooses the shape of the launches gets that shape)
   ctx->span_lds = lds_for(ctx->G);
   if (cfg->split_step == 0 && cfg->rollout_turns == 0 && cfg->levels_per_wave == 0 && cfg->split_obs_levels == 0 && ctx->span_lds <= 64 * 1024)
-    ctx->span_room = span_room(ctx->S, cfg->problem == PCGRL_BINARY, cfg->batch);
+    ctx->span_room = span_room(ctx->S, cfg->problem, cfg->batch);
   struct { void** p; size_t n; } allocs[] = {
       // (the binary problem keeps one more plane: the component of the first walkable cell)
       {&ctx->d_planes, rows * ctx->word_bytes * (ctx->P + (cfg->problem == PCGRL_BINARY ? 1 : 0))},
@@ -697,7 +697,10 @@ int pcgrl_rollout(pcgrl_ctx* ctx, const int32_t* actions, int32_t n_steps, uint8
   // (a slot that several steps write has to end with the last one's, and spans are not ordered among each other)
   if (ctx->span_room > 0 && (!obs || obs_slots == n_steps)) {
     const int64_t batch = ctx->cfg.batch;
-    const SpanShape s = span_shape({ctx->S, ctx->cfg.problem == PCGRL_BINARY, obs != nullptr, batch, n_steps, obs ? batch * (int64_t)ctx->obs_stride : 0});
+    const pcgrl_config& cfg = ctx->cfg;
+    const int64_t episode = !cfg.autoreset ? 0 : cfg.max_changes > 0 && cfg.max_changes < cfg.max_steps ? cfg.max_changes : cfg.max_steps;
+    const SpanShape s = span_shape({ctx->S, cfg.problem, obs != nullptr, batch, n_steps, (int64_t)ctx->obs_bytes,
+                                    obs ? batch * (int64_t)ctx->obs_stride : 0, episode});
     if (s.spans > 1 && s.spans * batch <= ctx->span_room) {
       a.envs_per_wave_log2 = lg2(ctx->G) | (lg2(ctx->G) << 8);
       a.obs_lds_words = (int32_t)(ctx->span_lds / 4);

@@ -4,14 +4,18 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "../../include/pcgrl.h"
+
 namespace pcgrl {
 
 struct SpanCase {
   int rows;                // of the size class
-  bool binary;             // the binary problem
+  int problem;             // PCGRL_BINARY / MAZE / DUNGEON
   bool observed;           // with observations, a slot for every step
   int64_t batch, steps;    // levels, steps of the rollout
+  int64_t obs_bytes;       // of one level's observation
   int64_t step_bytes;      // of the observations of a step
+  int64_t episode;         // steps that an episode has at the least; 0: a level never starts again
 };
 struct SpanShape {
   int spans, steps;  // of the rollout, and of a span; one span: not cut up
@@ -24,45 +28,71 @@ struct SpanShape {
 //   64 levels, 128 steps   16x16 binary 31.9 / 26.8 / 22.8 / 25.0     32x32 30.2 / 24.3 / 25.3 / 31.4   64x64 29.8 / 28.8 / 34.3 / 48.4
 //   512 levels, 64 steps   16x16 maze   82.6 / 47.5 / 31.1 / 31.3 / 33.2   32x32 58.2 / 37.9 / 34.2 / 37.6 / 42.5   64x64 59.7 / 49.0 / 50.4 / 57.7 / 75.8
 //   1024 levels, 32 steps  16x16 binary    - / 55.9 / 36.9 / 32.8 / 33.5   32x32 - / 64.4 / 53.1 / 41.8 / 46.5      64x64 - / 49.7 / 45.5 / 49.7 / 65.9
-inline int64_t span_levels(int rows, bool binary, bool observed, int64_t batch) {
+inline int64_t span_levels(int rows, int problem, bool observed, int64_t batch) {
+  const bool binary = problem == PCGRL_BINARY;
   if (rows == 16) return batch <= 128 ? 4096 : observed || batch <= 1024 ? 8192 : 16384;
   if (rows == 32) return batch <= 512 || (observed && !binary) ? 4096 : observed || batch <= 2048 ? 8192 : 16384;
   return batch <= 512 ? 2048 : observed ? 4096 : 8192;
 }
 
 // The most levels that any rollout of a context has side by side.
-inline int64_t span_room(int rows, bool binary, int64_t batch) {
-  const int64_t most = std::max(span_levels(rows, binary, false, batch), span_levels(rows, binary, true, batch)) / batch * batch;
+inline int64_t span_room(int rows, int problem, int64_t batch) {
+  const int64_t most = std::max(span_levels(rows, problem, false, batch), span_levels(rows, problem, true, batch)) / batch * batch;
   return batch <= 4096 && most >= 2 * batch ? most : 0;
 }
 
 // It pays where the batch leaves the machine idle and the rollout is long enough for what the cutting costs:
-// a second launch, 3 to 5 us in which one wavefront a level runs ahead, and the metrics from scratch.  Us as one / cut up,
-// 31-cell windows unless it says otherwise:
-//   16 rows  64 binary levels, 4 steps 8.0 / 11.5, 8 steps 12.4 / 12.3, 12 steps 13.8 / 12.8, 16 steps 17.5 / 13.4, 256 steps 147 / 31;
-//            64 maze levels, 12 steps 11.6 / 10.1; 1024 binary levels, 8 steps 20.8 / 19.4, 32 steps 53 / 33; 2048, 32 steps 62 / 47;
-//            3000, 16 steps 51 / 42; with 9 cells 4096 binary levels, 32 steps 63 / 67, maze levels 49.8 / 49.3
-//   32 rows  64 maze levels, 12 steps 11.7 / 12.3, 16 steps 13.8 / 12.6; 512 maze levels, 16 steps 18.7 / 19.2, 64 steps 47 / 34;
-//            1024 maze levels, 32 steps 46 / 34; 2048 (15 cells) 45.2 / 48.1, binary ones 64 / 56; 3000 binary levels (9 cells) 87 / 68
-//   64 rows  64 maze levels, 16 steps 16.4 / 15.1, 24 steps 20.9 / 16.3; 256 levels, 8 steps 13.6 / 17.3, 32 steps 26.9 / 26.4;
-//            512 levels, 16 steps 22.1 / 26.2, 64 steps 55 / 49; 1024 levels, 32 steps 50 / 49, 128 steps (9 cells) 137 / 114
-// Nor where the stores are what a rollout waits for: 1024 16x16 dungeon levels (7.9 MB a step) 53 / 43, 2048 maze levels
-// (9.8 MB) 61 / 58, 1500 dungeon levels (11.5 MB) 75 / 80; with 63 cells 256 16x16 maze levels (5 MB) 34 / 31, 512 (10 MB) 119 / 125.
+// a second launch, 3 to 5 us in which one wavefront a level runs ahead, and the metrics from scratch.  How long that is depends on
+// what a step costs otherwise, where a relay of 256 levels (a workgroup for each compute unit) is at its best.  Us as one / cut up,
+// 9-cell windows (with 31 cells the same within a few percent):
+//   16 rows  12 steps of 64 binary levels 15.0 / 12.4, maze 1.11 times as many a second, dungeon 1.02; of 256 dungeon levels (14) 1.08, (12) 0.98;
+//            of 1024 binary levels 25.0 / 21.2, of 2048 27.9 / 28.6 (14 steps 1.02), of 3072 maze levels 25.7 / 26.9 (1.01)
+//   32 rows  14 steps of 64 binary levels 1.21, maze 1.01, dungeon 1.00; 16 steps of 256 binary levels 1.18, maze 13.7 / 14.4, dungeon 15.0 / 16.5,
+//            22 steps 1.00, 1.00; 512 maze levels, 22 steps 1.06; with 15 cells 2048 maze levels, 32 steps 45.2 / 48.1
+//   64 rows  16 steps of 8 binary levels 1.19, maze 1.10, dungeon 1.00; 20 steps of 64 binary levels 1.08, maze 17.2 / 17.8 (25 steps 1.03),
+//            dungeon 19.1 / 22.0 (30 steps 1.02); 256 binary levels, 32 steps 1.16, maze 1.00 (37 steps 1.02), dungeon 27.9 / 30.3 (48 steps 1.05);
+//            1024 levels, 80 steps 1.21, 85 steps 1.08, 96 steps 1.08
 // Without observations a rollout is one wavefront a level group, which is the longer chain: 64 16x16 maze levels, 200 steps
 // 199 / 20 us, 4096 279 / 152, 2048 with 32 steps 44 / 27; 512 64x64 ones with 32 steps 47 / 28, 2048 57 / 57.
+// Nor where the stores are what a rollout waits for: 1024 16x16 dungeon levels (7.9 MB a step) 53 / 43, 2048 maze levels
+// (9.8 MB) 61 / 58, 1500 dungeon levels (11.5 MB) 75 / 80; 64x64 dungeon levels, 640 (4.9 MB) 1.08, 768 (5.9 MB) 0.94.  With wide windows and
+// all compute units busy a relay stores 5.9 TB/s into a ring that spills from the cache and spans 4.8: 256 16x16 maze levels with 63 cells,
+// 96 steps (490 MB) 85 / 104, 36 steps 1.05, but 320 of them 163 / 127; 448 of them (8.9 MB), 18 steps 27.3 / 30.9.
+// And less where levels start again on the way, which is one more draw in a row for the wavefront that runs ahead and a longer chain for
+// the span that has it: with a limit of 150 changes 64 64x64 dungeon levels, 30 steps 0.91, 45 steps 1.08, 256 32x32 ones, 22 steps 0.90, 33 steps
+// 1.01, 64 16x16 ones, 12 steps 0.97; with 40 changes or 30 steps 768 64x64 dungeon levels 0.87 to 1.02 however long, 1024
+// binary ones 0.92 to 1.27, 2048 levels without observations 0.91 to 1.02.
 inline SpanShape span_shape(const SpanCase& c) {
   const SpanShape whole = {1, (int)c.steps};
-  const int64_t B = c.batch;
-  int64_t most_batch, fewest;
-  if (c.observed) {
-    most_batch = c.rows == 16 ? 3072 : c.rows == 32 ? (c.binary ? 3072 : 1536) : 1024;
-    fewest = c.rows == 16 ? 12 : c.rows == 32 ? 14 + B / 96 : 16 + B / 16;
-  } else {
-    most_batch = 4096;
+  const int64_t B = c.batch, from32 = std::clamp<int64_t>(B - 32, 0, 32), MB = (int64_t)1 << 20;
+  const bool binary = c.problem == PCGRL_BINARY, dungeon = c.problem == PCGRL_DUNGEON;
+  const bool restarts = c.episode > 0 && c.episode < 400, often = c.episode > 0 && c.episode < 80;
+  int64_t most_batch = 4096, fewest, most_bytes = 9 * MB;
+  bool slower = false;  // when levels start again
+  if (!c.observed) {
+    if (c.rows == 64 && often) most_batch = 1024;
     fewest = c.rows == 16 ? 8 + B / 128 : c.rows == 32 ? 8 + B / 96 : 12 + B / 32;
+  } else if (c.rows == 16) {
+    most_batch = 3072;
+    fewest = (dungeon ? B > 64 && B < 512 : B > 1536) ? 14 : 12;
+    slower = B > 1536 || (dungeon && B <= 512);
+  } else if (c.rows == 32) {
+    most_batch = binary ? 3072 : 1536;
+    fewest = std::max<int64_t>(14 + B / 96, binary ? 0 : std::min<int64_t>(10 + B / 21, 22));
+    slower = binary ? B > 1536 : B <= (dungeon ? 512 : 768);
+  } else {
+    most_batch = !often ? 1024 : binary ? 900 : dungeon ? 320 : 640;
+    fewest = 16 + B / 16 + (binary ? 0 : dungeon ? from32 / 4 + std::min<int64_t>(B, 256) / 32 : from32 / 6);
+    if (dungeon) most_bytes = 5 * MB;
+    slower = true;
   }
-  if (B > most_batch || c.steps < fewest || c.step_bytes > ((int64_t)9 << 20)) return whole;
-  const int64_t spans = std::min(c.steps, span_levels(c.rows, c.binary, c.observed, B) / B);
+  if (restarts && slower) fewest = fewest * (dungeon ? (often ? 21 : 18) : often ? 18 : 16) / 12;
+  if (!binary && c.obs_bytes >= 8192) most_bytes = std::min(most_bytes, 8 * MB);
+  if (B > most_batch || c.steps < fewest || c.step_bytes > most_bytes) return whole;
+  const bool busy = 4 * B >= 3 * 256 * ((B + 255) / 256);
+  if (c.obs_bytes >= (c.rows == 16 ? 16000 : 10000) && busy && c.step_bytes > (binary ? 8 * MB : 15 * MB / 4) && c.step_bytes * c.steps > 300 * MB)
+    return whole;
+  const int64_t spans = std::min(c.steps, span_levels(c.rows, c.problem, c.observed, B) / B);
   if (spans < 2) return whole;
   SpanShape s;
   s.steps = (int)((c.steps + spans - 1) / spans);

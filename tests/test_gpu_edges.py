@@ -444,7 +444,7 @@ def test_every_shape_of_a_relay(problem, B, h, T, slots, shape, more):
     # one step a span, the last span of a rollout, several levels to a wavefront and some without one
     (wl.BINARY, 21, 16, 16, 12, True, (12, 1), {}), (wl.MAZE, 130, 16, 11, 70, True, (35, 2), dict(max_changes=5)),
     (wl.DUNGEON, 9, 32, 20, 131, True, (131, 1), dict(max_steps=40, n_frozen=2)), (wl.BINARY, 300, 30, 32, 33, True, (11, 3), dict(max_changes=3)),
-    (wl.MAZE, 601, 32, 32, 25, False, (13, 2), dict(max_steps=7)), (wl.DUNGEON, 100, 64, 64, 30, True, (15, 2), dict(max_steps=13, min_size=30)),
+    (wl.MAZE, 601, 32, 32, 25, False, (13, 2), dict(max_steps=7)), (wl.DUNGEON, 100, 64, 64, 60, True, (20, 3), dict(max_steps=13, min_size=30)),
     (wl.BINARY, 33, 64, 50, 67, True, (34, 2), dict(max_changes=9, obs_format=1)), (wl.MAZE, 530, 16, 16, 40, True, (14, 3), dict(obs_pitch=-1)),
     # several episodes within 64 steps, one that ends with every step, and none that ends
     (wl.DUNGEON, 21, 16, 16, 90, True, (90, 1), dict(max_steps=7, ctrl={1: (3, 9), 2: (2, 6)})),
