@@ -159,7 +159,9 @@ typedef struct {
 int pcgrl_config_default(int32_t problem, pcgrl_config* cfg);
 
 /* Creates a context on GPU `device` and allocates all device state (about
- * 3*S*8 + 170 bytes per environment, S = 16, 32 or 64 covering max_h and max_w): the many
+ * 3*S*8 + 170 bytes per environment, S = 16, 32 or 64 covering max_h and max_w; a batch of up to
+ * 4096 that leaves the shape of its launches open also has room for the states that its rollouts are
+ * cut up at, up to 256 for each environment and 18 MB in all, see pcgrl_rollout): the many
  * environments that are stepped in lockstep on one GPU (Methods / Jax implementation; no passage
  * defines the call itself).  The environments start as if pcgrl_reset(seed = 0) had been called.
  * Synchronises.

@@ -28,11 +28,17 @@ struct SpanShape {
 //   64 levels, 128 steps   16x16 binary 31.9 / 26.8 / 22.8 / 25.0     32x32 30.2 / 24.3 / 25.3 / 31.4   64x64 29.8 / 28.8 / 34.3 / 48.4
 //   512 levels, 64 steps   16x16 maze   82.6 / 47.5 / 31.1 / 31.3 / 33.2   32x32 58.2 / 37.9 / 34.2 / 37.6 / 42.5   64x64 59.7 / 49.0 / 50.4 / 57.7 / 75.8
 //   1024 levels, 32 steps  16x16 binary    - / 55.9 / 36.9 / 32.8 / 33.5   32x32 - / 64.4 / 53.1 / 41.8 / 46.5      64x64 - / 49.7 / 45.5 / 49.7 / 65.9
+// A level is cut into kMostSpans at the most, however few there are: the wavefronts that run ahead store a level's starts one after the
+// other.  One level, with at most 128 / 256 / 512 / any number of spans: 1000 steps 16x16 binary 40.1 / 42.1 / 53.9 / 77.8, 64x64 dungeon
+// 54.9 / 59.5 / 75.6 / 109, 4000 steps 115 / 108 / 111 / 286, 133 / 123 / 131 / 232; eight levels, 4000 steps 145 / 125 / 121 / 121.
+constexpr int64_t kMostSpans = 256;
 inline int64_t span_levels(int rows, int problem, bool observed, int64_t batch) {
   const bool binary = problem == PCGRL_BINARY;
-  if (rows == 16) return batch <= 128 ? 4096 : observed || batch <= 1024 ? 8192 : 16384;
-  if (rows == 32) return batch <= 512 || (observed && !binary) ? 4096 : observed || batch <= 2048 ? 8192 : 16384;
-  return batch <= 512 ? 2048 : observed ? 4096 : 8192;
+  int64_t levels;
+  if (rows == 16) levels = batch <= 128 ? 4096 : observed || batch <= 1024 ? 8192 : 16384;
+  else if (rows == 32) levels = batch <= 512 || (observed && !binary) ? 4096 : observed || batch <= 2048 ? 8192 : 16384;
+  else levels = batch <= 512 ? 2048 : observed ? 4096 : 8192;
+  return std::min(levels, kMostSpans * batch);
 }
 
 // The most levels that any rollout of a context has side by side.
