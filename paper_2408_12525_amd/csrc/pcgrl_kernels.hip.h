@@ -1702,6 +1702,7 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
     W v = (W)__hip_atomic_load(&set[0][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if constexpr (kWords == 2)
       v |= (W)__hip_atomic_load(&set[1][row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) << 32;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");  // (with the release below: every look is acted on)
     return v;
   };
   auto best_so_far = [&]() {
@@ -1732,7 +1733,6 @@ __global__ __launch_bounds__(1024) void exact_diameter_kernel(KArgs a, int32_t* 
   }
   for (bool first = true;; first = false) {
     todo = look(left);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");  // (with the release below)
     best = max(best, best_so_far());
     if (!first) {
       const int n = square_below(best);
