@@ -221,13 +221,14 @@ int levels_per_wave_for(int G, int batch, int min_groups) {
 // Two parts a level always (a copy of the level in a spare lane group is a part as well), more while
 // that takes no more than 4096 wavefronts, up to 8 parts of a 64-row level, 16 or 8 of a 32-row one and
 // 16 or 4 of a 16-row one, the larger number where there is no more than about a workgroup for every
-// other compute unit (32 rows) or two for each (16).  Measured on random levels, us for 1, 2, 4, 8, 16
-// wavefronts a workgroup: 4096 64x64 levels 198 / 144 / 142 / 180 / 284, 1024 of them 113 / 62 / 50 /
-// 61 / 86, 256 110 / 55 / 31 / 32 / 32, 64 92 / 60 / 32 / 34 / 42; 16 384 32x32 levels 199 / 162 /
-// 171 / 228 / 362, 1024 (two copies each) 41 / 26 / 29 / 35 / 49, 128 34 / 20 / 23 / 23 / 24; 16 384
-// 16x16 levels 62 / 50 / 54 / 71 / 112, 1024 (four copies each) 17 / 17 / 16 / 19 / 27.  Levels of one long loop, whose cost is the sweeps of half of its cells, gain from
-// every part: 16 of 32x32 332 with 8 parts, 238 with 16; 64 of 16x16 59 with 4, 34 with 16; 64x64 37
-// 800 with 1, 6700 with 8, 6200 with 16.
+// other compute unit (32 rows) or two for each (16).  Us for 1, 2, 4, 8, 16 wavefronts a workgroup, levels of 50 % walls:
+// 4096 64x64 levels 199 / 144 / 142 / 182 / 285, 2048 136 / 97 / 86 / 100 / 153, 1024 113 / 61 / 50 / 60 / 86, 256 110 / 54 / 30 /
+// 31 / 31, 64 92 / 60 / 31 / 33 / 42; 16 384 32x32 levels 202 / 164 / 176 / 234 / 383, 1024 (two copies each) 38 / 24 / 26 /
+// 33 / 49, 128 34 / 19 / 22 / 21 / 23; 16 384 16x16 levels 61 / 50 / 54 / 71 / 113, 1024 (four copies each) 17 / 17 / 16 / 19 / 27.
+// No number is the best for all kinds of levels.  1024 of 32x32, 1 / 2 / 4 / 8: 60 % walls 45 / 26 / 22 / 27, 30 % 83 / 72 / 60 / 65, rooms with
+// doors 23 / 23 / 28 / 37, a winding corridor 102 / 125 / 131 / 175; 2048 of 64x64, 1 / 2 / 4: 40 % walls 268 / 296 / 225, 45 % 174 / 95 / 109, rooms
+// 54 / 72 / 75, the corridor 490 / 727 / 857.  In small batches long paths gain from every part: a ring along the border of 64 64x64 levels
+// 627 / 350 / 205 / 135 / 118, of 64 32x32 ones 84 / 56 / 41 / 35 / 34.
 constexpr int kMostExactWavesLog2 = 4;  // a workgroup of 1024 threads
 int exact_waves_for(int nwaves, int copies, int S) {
   const int most = S == 64 ? 8 : S == 32 ? (nwaves <= 128 ? 16 : 8) : nwaves <= 512 ? 16 : 4;
