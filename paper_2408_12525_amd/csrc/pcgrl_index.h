@@ -31,8 +31,8 @@ struct GetPiece {
 };
 
 // The sizes of the arrays, with what stands for a division by each on the device, where one takes some twenty
-// vector instructions, and a 64-bit one hundreds: the largest 32-bit number over the divisor, times which the
-// upper half of a product is the quotient or up to two less.
+// vector instructions, and a 64-bit one hundreds: r, the largest 32-bit number over the divisor d.  The upper half of
+// n r is the quotient or one less, as r d >= 2^32 - d, so that n r / 2^32 > n / d - 1 for every n < 2^32.
 struct GetSizes {
   uint64_t total;                     // cells of all levels
   uint32_t cells, max_w;              // of a level, of its rows
@@ -42,14 +42,11 @@ constexpr GetSizes get_sizes(uint32_t batch, int cells, int max_w) {
   return {(uint64_t)batch * (uint64_t)cells, (uint32_t)cells, (uint32_t)max_w, 0xffffffffu / (uint32_t)cells, 0xffffffffu / (uint32_t)max_w};
 }
 constexpr uint32_t divided(uint32_t n, uint32_t by, uint32_t reciprocal, uint32_t& rest) {
-  uint32_t q = (uint32_t)(((uint64_t)n * reciprocal) >> 32);
+  const uint32_t q = (uint32_t)(((uint64_t)n * reciprocal) >> 32);
   rest = n - q * by;
-  for (int k = 0; k < 2; ++k) {
-    const uint32_t more = rest >= by ? 1u : 0u;
-    q += more;
-    rest -= more != 0 ? by : 0u;
-  }
-  return q;
+  const bool more = rest >= by;
+  rest -= more ? by : 0u;
+  return q + (more ? 1u : 0u);
 }
 
 // The piece of thread `thread` of workgroup (bx, by).

@@ -266,6 +266,22 @@ extern "C" void piece(uint32_t bx, uint32_t by, int thread, uint32_t batch, int 
   out[0] = (int64_t)p.at; out[1] = p.n; out[2] = p.env; out[3] = p.y; out[4] = p.x;
   out[5] = (int64_t)pcgrl::get_level(bx, by, thread);
 }
+// how often `divided` is wrong for this divisor, and by how much its product of reciprocals falls short at the most
+extern "C" void wrong(uint32_t by, int64_t* out) {
+  const uint32_t r = pcgrl::get_sizes(1, (int)by, (int)by).per_level, most = 0xffffffffu, last = most / by;
+  out[0] = out[1] = 0;
+  for (int i = 0; i < 64; ++i) {
+    const uint32_t k = i < 24 ? (uint32_t)i : i < 48 ? last - (uint32_t)(i - 24) : (uint32_t)((uint64_t)last * (uint64_t)(i - 47) / 17);
+    const uint32_t at[] = {k * by, k * by - 1, k * by + 1, most - (uint32_t)i};
+    for (uint32_t n : at) {
+      uint32_t rest = 0;
+      const uint32_t q = pcgrl::divided(n, by, r, rest);
+      const int64_t less = (int64_t)(n / by) - (int64_t)(((uint64_t)n * r) >> 32);
+      out[0] += q != n / by || rest != n % by;
+      out[1] = less > out[1] ? less : out[1];
+    }
+  }
+}
 """
 
 
@@ -280,7 +296,17 @@ def index(tmp_path_factory):
     u32, p64 = C.c_uint32, C.POINTER(C.c_int64 * 6)
     lib.grid.argtypes, lib.grid.restype = [u32, u32, C.c_int, C.POINTER(u32 * 2)], None
     lib.piece.argtypes, lib.piece.restype = [u32, u32, C.c_int, u32, C.c_int, C.c_int, p64], None
+    lib.wrong.argtypes, lib.wrong.restype = [u32, C.POINTER(C.c_int64 * 2)], None
     return lib
+
+
+def test_divisions_by_reciprocals_need_one_correction(index):
+    out, most = (C.c_int64 * 2)(), 0
+    for by in range(1, 4097):                      # cells of a level, and of a row
+        index.wrong(by, C.byref(out))
+        assert out[0] == 0, by
+        most = max(most, out[1])
+    assert most == 1
 
 
 @pytest.mark.parametrize("batch,h,w", [(1, 1, 1), (300, 1, 1), (5, 3, 7), (1, 64, 64), (37, 27, 45), (2051, 2, 64), (8388608, 64, 64), (8388609, 64, 64),
