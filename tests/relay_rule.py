@@ -75,3 +75,9 @@ def case_of(cfg, steps, slots):
     return dict(rows=rows, binary=int(cfg["problem"] == wl.BINARY), per_simd=wavefronts_per_simd(res["vgprs"]), compute_units=COMPUTE_UNITS,
                 workgroups=-(-B // levels), observers=levels // per_observer, obs_bytes=obs, step_bytes=stride * B, lds_tables=res["lds"],
                 lds_observer=(((120 + per_observer * (bits + 8) + 31) // 32 + 6) * 4 + 15) // 16 * 16, steps=steps, slots=slots)
+
+
+def relays(cfg, steps, slots):
+    """Whether such a rollout runs as a relay, whose pieces have no room for an episode that ends twice in one."""
+    ends = [cfg["max_steps"]] + [cfg["max_changes"]] * (cfg["max_changes"] > 0)
+    return (not cfg["autoreset"] or min(ends) >= 8) and shape(**case_of(cfg, steps, slots))[0] > 0

@@ -29,3 +29,9 @@ def case_of(cfg, steps, observed):
     ends = [cfg["max_steps"]] + [cfg["max_changes"]] * (cfg["max_changes"] > 0)
     return dict(rows=rows, problem=cfg["problem"], observed=observed, batch=cfg["batch"], steps=steps, obs_bytes=wl.obs_bytes(cfg),
                 step_bytes=host_rule.obs_stride(cfg) * cfg["batch"] if observed else 0, episode=min(ends) if cfg["autoreset"] else 0)
+
+
+def spans(cfg, steps, slots):
+    """Into how many spans a rollout with this many slots (0: without observations) is cut."""
+    opened = all(cfg.get(k, 0) == 0 for k in ("split_step", "rollout_turns", "levels_per_wave", "split_obs_levels"))
+    return shape(**case_of(cfg, steps, slots > 0))[0] if opened and slots in (0, steps) else 1

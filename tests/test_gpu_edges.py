@@ -395,22 +395,23 @@ def _rollouts_against_steps(cfg, T, S, observed=True):
     gpu.close()
 
 
-@pytest.mark.parametrize("problem,h,w,T,more", [
-    (wl.BINARY, 16, 16, 1, {}), (wl.BINARY, 16, 16, 7, dict(max_steps=8)), (wl.MAZE, 16, 16, 8, dict(max_steps=8)),
-    (wl.DUNGEON, 11, 16, 9, dict(max_steps=9, n_frozen=2)), (wl.BINARY, 32, 20, 17, dict(max_steps=11, min_size=5, min_w=5)),
-    (wl.MAZE, 32, 32, 16, dict(max_changes=8, obs_format=1)), (wl.DUNGEON, 32, 32, 33, dict(max_steps=8, max_changes=8, pos_mode=wl.POS_SCAN)),
-    (wl.BINARY, 64, 64, 24, dict(max_steps=13, n_frozen=3, min_size=20)), (wl.MAZE, 64, 40, 15, dict(autoreset=0, max_steps=4)),
-    (wl.DUNGEON, 64, 64, 25, dict(max_steps=10, regions_mode=wl.REGIONS_RECOUNT)),
-    # episodes that end twice within a piece of a relay
-    (wl.BINARY, 16, 16, 20, dict(max_steps=3)), (wl.MAZE, 32, 32, 20, dict(max_changes=2))])
+@pytest.mark.parametrize("problem,h,w,T,relay,more", [
+    (wl.BINARY, 16, 16, 1, 0, {}), (wl.BINARY, 16, 16, 7, 1, dict(max_steps=8)), (wl.MAZE, 16, 16, 8, 1, dict(max_steps=8)),
+    (wl.DUNGEON, 11, 16, 9, 1, dict(max_steps=9, n_frozen=2)), (wl.BINARY, 32, 20, 17, 1, dict(max_steps=11, min_size=5, min_w=5)),
+    (wl.MAZE, 32, 32, 16, 1, dict(max_changes=8, obs_format=1)), (wl.DUNGEON, 32, 32, 33, 1, dict(max_steps=8, max_changes=8, pos_mode=wl.POS_SCAN)),
+    (wl.BINARY, 64, 64, 24, 1, dict(max_steps=13, n_frozen=3, min_size=20)), (wl.MAZE, 64, 40, 15, 1, dict(autoreset=0, max_steps=4)),
+    (wl.DUNGEON, 64, 64, 25, 1, dict(max_steps=10, regions_mode=wl.REGIONS_RECOUNT)),
+    # episodes that would end twice within a piece of a relay: turns without one
+    (wl.BINARY, 16, 16, 20, 0, dict(max_steps=3)), (wl.MAZE, 32, 32, 20, 0, dict(max_changes=2))])
 @pytest.mark.parametrize("slots", ["all", "two"])
-def test_rollouts_in_pieces(problem, h, w, T, more, slots):
+def test_rollouts_in_pieces(problem, h, w, T, relay, more, slots):
     """Rollouts of a small batch around the sizes of the pieces that their wavefronts hand on to each
     other, episodes that end in every one of them, three in a row and single steps in between: what
-    they leave behind is what the next one starts from."""
-    B = 21
-    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=50, pos_mode=wl.POS_RANDOM), **more))
-    _rollouts_against_steps(cfg, T, T if slots == "all" else min(2, T))
+    they leave behind is what the next one starts from.  (Two wavefronts are asked for, so that none is cut into spans.)"""
+    B, n_slots = 21, T if slots == "all" else min(2, T)
+    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=50, pos_mode=wl.POS_RANDOM, split_step=2), **more))
+    assert relay_rule.relays(cfg, T, n_slots) == bool(relay) and span_rule.spans(cfg, T, n_slots) == 1
+    _rollouts_against_steps(cfg, T, n_slots)
 
 
 @pytest.mark.parametrize("problem,B,h,T,slots,shape,more", [
@@ -460,6 +461,62 @@ def test_rollouts_cut_into_spans(problem, B, h, w, T, observed, shape, more):
     cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=500, pos_mode=wl.POS_RANDOM), **more))
     assert span_rule.shape(**span_rule.case_of(cfg, T, observed)) == shape
     _rollouts_against_steps(cfg, T, T, observed)
+
+
+@pytest.mark.parametrize("problem,B,h,w,T,more", [
+    (wl.MAZE, 70, 16, 13, (24, 41, 17), {}), (wl.DUNGEON, 40, 30, 32, (30, 19, 64), dict(ctrl={1: (3, 9)}, max_changes=11)),
+    (wl.BINARY, 20, 64, 50, (40, 30, 70), dict(max_steps=29, obs_frozen_channel=1))])
+def test_rollouts_cut_into_spans_from_a_state_of_the_callers(problem, B, h, w, T, more):
+    """Levels of mixed shapes with pinpoints, in a context configured without any, and targets of the caller's: what runs ahead,
+    the spans and the end of a rollout take both from there.  Rollouts of several lengths, one of them without
+    observations, share the room for the starts; then one is captured and replayed."""
+    cfg = wl.make_config(problem, B, h, 9, **dict(dict(max_w=w, max_steps=500, pos_mode=wl.POS_RANDOM), **more))
+    gpu, cpu = binding.Pcgrl(cfg, 0), oracle.Oracle(cfg)
+    rng = np.random.default_rng(B)
+    gpu.pcgrl_reset(6)
+    cpu.reset(6)
+    M, K = gpu.pcgrl_metrics().shape[1], gpu.K
+    tiles = rng.integers(0, K, (B, h, w)).astype(np.int8)
+    frozen = (rng.random((B, h, w)) < 0.3).astype(np.uint8)
+    hw = np.stack([rng.integers(2, h + 1, B), rng.integers(2, w + 1, B)], 1).astype(np.int16)
+    pos = np.stack([rng.integers(0, hw[:, 0]), rng.integers(0, hw[:, 1])], 1).astype(np.int16)
+    lo = rng.integers(0, 20, (B, M))
+    targets = np.stack([lo, lo + rng.integers(0, 30, (B, M))], 2).astype(np.int32)
+    gpu.pcgrl_set_state(*(torch.from_numpy(a).to(DEV) for a in (tiles, frozen, hw, pos)))
+    cpu.set_state(tiles, frozen, hw, pos)
+    gpu.pcgrl_set_targets(torch.from_numpy(targets).to(DEV))
+    cpu.set_targets(targets)
+
+    def check(acts, obs, rew, done, turn):
+        for t in range(len(acts)):
+            o, r, d = cpu.step(acts[t])
+            assert np.array_equal(rew[t].cpu().numpy(), r) and np.array_equal(done[t].cpu().numpy(), d), f"{turn} step {t}"
+            if obs is not None:
+                check_obs(gpu, obs[t], o, f"{turn} step {t}")
+        assert_same("metrics", gpu.pcgrl_metrics(), cpu.metrics(), turn)
+        assert_same("targets", gpu.pcgrl_get_targets(), cpu.get_targets(), turn)
+        compare_state(gpu, cpu, turn)
+
+    buffers = lambda n: (torch.zeros((n,) + tuple(gpu.obs_shape), dtype=torch.uint8, device=DEV), torch.empty((n, B), dtype=torch.float32, device=DEV),  # noqa: E731
+                         torch.empty((n, B), dtype=torch.uint8, device=DEV))
+    for turn, n in enumerate(T):
+        assert span_rule.spans(cfg, n, 0 if turn == 1 else n) > 1
+        acts = wl.random_actions(cfg, 40 + turn, n, bad_fraction=0.05)
+        obs, rew, done = buffers(n)
+        gpu.pcgrl_rollout(torch.from_numpy(acts).to(DEV), None if turn == 1 else obs, rew, done)
+        check(acts, None if turn == 1 else obs, rew, done, f"rollout {turn}")
+    acts = wl.random_actions(cfg, 50, T[0])
+    on_gpu, (obs, rew, done) = torch.from_numpy(acts).to(DEV), buffers(T[0])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.pcgrl_rollout(on_gpu, obs, rew, done)
+    for replay in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        check(acts, obs, rew, done, f"replay {replay}")
+        (obs.float().sum() + 1).item()                             # unrelated eager work between replays
+    gpu.close()
 
 
 @pytest.mark.parametrize("n,corridor", [(64, 40), (32, 25)])
