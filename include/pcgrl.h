@@ -143,7 +143,9 @@ typedef struct {
                            many observation wavefronts take the steps of a pcgrl_rollout in turn
                            (each keeps its own copy of the levels and writes the observation of
                            every n-th step).  Pays where the batch leaves most of the chip idle.
-                           The automatic choice shares the searches for the metrics out in the same
+                           The automatic choice cuts a rollout of a small batch up along its steps
+                           (see pcgrl_rollout) where it can and that was measured to pay; else it
+                           shares the searches for the metrics out in the same
                            way while a compute unit has few workgroups, by what was measured for each size
                            class, and otherwise takes turns while the launch stays at two or three
                            wavefronts a SIMD; a workgroup holds at most four observation wavefronts */
@@ -200,10 +202,16 @@ int pcgrl_reset(pcgrl_ctx* ctx, uint64_t seed, uint8_t* obs, void* stream);
 int pcgrl_step(pcgrl_ctx* ctx, const int32_t* actions, uint8_t* obs, float* reward, uint8_t* done,
                void* stream);
 
-/* n_steps consecutive environment steps in ONE launch, with results identical to n_steps calls of
- * pcgrl_step; the levels stay in registers in between, so per step only the action is read and
- * the outputs are written (the random-agent rollout of Results / Speed comparison, and the remedy
- * for batches too small to hide a launch per step).
+/* n_steps consecutive environment steps, with results identical to n_steps calls of pcgrl_step
+ * (the random-agent rollout of Results / Speed comparison, and the remedy for batches too small to
+ * hide a launch per step).  One launch in which the levels stay in registers from step to step, so
+ * that per step only the action is read and the outputs are written; or, for batches of up to 4096
+ * whose observations all have a slot of their own (obs_slots = n_steps) or are not written, and
+ * rollouts long enough for it to pay, two: the first takes the levels ahead through all edits and
+ * writes down, in room that the context has for it, the states at which the rollout is cut into
+ * spans, the second takes all spans through their steps side by side, beginning with their
+ * metrics from scratch.  Any of levels_per_wave, split_step, split_obs_levels and rollout_turns that
+ * is not 0 keeps rollouts in one launch.  Both forms may be captured into a HIP graph.
  *   actions: device, int32 [n_steps][batch]
  *   obs    : device, uint8 [obs_slots][batch][C][obs_w][obs_w]; step t writes slot t % obs_slots
  *            (obs_slots = n_steps keeps every observation, 1 keeps only the last).  May be NULL.
@@ -224,8 +232,8 @@ int pcgrl_metrics(pcgrl_ctx* ctx, int32_t* out, void* stream);
  * sweeps, from those cells only that an upper bound on their distances does not rule out; the
  * components of a level, and what cells such bounds leave of them, are shared out over the wavefronts
  * of a workgroup.  The cost is that of a few sweeps for most levels (a thousand random 64x64 levels
- * 0.08 ms); on a loop, where nothing is ruled out, half of its cells are swept (one to 256 64x64 levels
- * with a loop of 2080 cells 7 ms).  out: device, int32 [batch]. */
+ * 0.05 ms); on a loop, where nothing is ruled out, half of its cells are swept (one to 256 64x64 levels
+ * with a loop of 2080 cells 6 ms).  out: device, int32 [batch]. */
 int pcgrl_exact_diameter(pcgrl_ctx* ctx, int32_t* out, void* stream);
 
 /* pcgrl_exact_diameter with the number of wavefronts chosen by the caller.  Neither call allocates

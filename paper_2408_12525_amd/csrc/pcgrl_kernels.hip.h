@@ -405,9 +405,10 @@ constexpr int kShortTrips = 2;
 // are worked out from afterwards: the cells at the end of its last trip that still grew (`base`), those one
 // layer before (`before`), and how many layers that is.  Kept once a trip and for the level as a whole, where a lane
 // for itself would have to be looked at after every second layer: for 32-row levels, whose floods are long.  Us without / with:
-// steps of 16 384 32x32 binary levels 12.4 / 12.1, of 4096 8.3 / 8.15, 4096 exact diameters 61.5 / 60.1, 16 384
-// levels installed and read back 31.6 / 30.8; 16-row levels, four to a wavefront, are faster where a batch is small (8192 with 15 cells 6.9 / 6.7) and
-// slower where it is large (65 536 19.1 / 19.7), and their rollouts would lose a wavefront a SIMD to the registers.  Nor for
+// steps of 4096 32x32 binary levels with 15 cells 8.99 / 8.84, of 8192 10.9 / 10.3, 16 384 13.1 / 12.6, 32 768 18.6 / 18.1, of 16 384 levels of random
+// shapes from 8x8 on 13.0 / 12.8; 512 levels cut into spans, 32 steps 36.7 / 35.0; 1024 exact diameters 27.6 / 26.3, but 4096 59.5 / 59.8, 16 384
+// 160.6 / 163.3; levels installed or reset the same.  16-row levels, four to a wavefront, are faster where a batch is small (8192 with 15 cells 6.9 /
+// 6.7) and slower where it is large (65 536 19.1 / 19.7), and their rollouts would lose a wavefront a SIMD to the registers.  Nor for
 // rollouts of large batches (65 536 32x32 levels 19.5 / 19.7 us a step).
 template <int S>
 __device__ __forceinline__ int flood_to_end(const Lanes<S>& L, typename RowWord<S>::T seed, typename RowWord<S>::T pass,
@@ -1642,10 +1643,9 @@ __device__ __forceinline__ typename RowWord<S>::T inside_few(const Lanes<S>& L, 
 // of all rims is shared out cell by cell once nobody has a component left.  Lane groups work at their
 // own pace (a group that has nothing to do in a sweep has no seed); every loop ends because each turn
 // takes cells out of a finite set.
-// Some 1400 flood layers for a random 64x64 level of 50 % walls (540 of them the first sweeps of 22 components; 1800
-// and 50 components before inside_few, and while a part told the others its finds only once it was done with
-// a component), bound by the latency of one after the other in small batches and by vector instructions from
-// 1024 levels on: a sweep from each of its 2000 open cells instead took 1350 us for 1024 levels (a launch of 4096
+// 1420 flood layers in 66 floods for a random 64x64 level of 50 % walls (1890 in 101 before inside_few, and while a
+// part told the others its finds only once it was done with a component), bound by the latency of one after the other
+// in small batches and by that and vector instructions (60 % of the issue slots) from 1024 levels on: a sweep from each of its 2000 open cells instead took 1350 us for 1024 levels (a launch of 4096
 // wavefronts and one that folded their results); this takes 51 (76.9 before inside_few and sweep_alone).  A loop of 2080 cells
 // is the worst there is, 1040 sweeps of 1040 layers and bound by instructions: 64 such levels 5.9 ms
 // (37.8 while the owner swept the whole rim, 6.5 from each cell on 4096 wavefronts; one level alone takes
@@ -3087,7 +3087,7 @@ struct SpanArgs {
 // tile's code before and after, so that the edits of any run of steps go into the bit-planes in LDS at once,
 // in any order.  A step that ends an episode ends the 64 steps early: what later ones did to the level is
 // of no consequence, the new level takes its place.
-// Bound by latency: 256 steps of 64 16x16 binary levels, 64 spans, 7.4 us, 32 steps of 512 64x64 dungeon levels 5.1, of which
+// Bound by latency: 256 steps of 64 16x16 binary levels, 64 spans, 10.0 us, 32 steps of 64 64x64 maze levels 5.4, of which
 // 3 are the launch, its loads and its stores.  The spans are shared out over kSpanStartWaves wavefronts, which all follow all
 // steps (with one of them 9.8 us; each span is some 400 clocks of reading back and storing).
 constexpr int kSpanStartWaves = 4;
