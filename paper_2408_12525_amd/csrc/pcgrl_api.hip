@@ -700,7 +700,8 @@ int pcgrl_rollout(pcgrl_ctx* ctx, const int32_t* actions, int32_t n_steps, uint8
     const int64_t batch = ctx->cfg.batch;
     const pcgrl_config& cfg = ctx->cfg;
     const int64_t episode = !cfg.autoreset ? 0 : cfg.max_changes > 0 && cfg.max_changes < cfg.max_steps ? cfg.max_changes : cfg.max_steps;
-    const SpanShape s = span_shape({ctx->S, cfg.problem, obs != nullptr, batch, n_steps, (int64_t)ctx->obs_bytes,
+    const int64_t cells = ((int64_t)(cfg.min_h + cfg.max_h) * (cfg.min_w + cfg.max_w) / 4 + cfg.max_h * cfg.max_w) / 2;
+    const SpanShape s = span_shape({ctx->S, cfg.problem, obs != nullptr, batch, n_steps, cells, cfg.max_w, (int64_t)ctx->obs_bytes, (int64_t)ctx->C * cfg.obs_w * cfg.obs_w,
                                     obs ? batch * (int64_t)ctx->obs_stride : 0, episode});
     if (s.spans > 1 && s.spans * batch <= ctx->span_room) {
       a.envs_per_wave_log2 = lg2(ctx->G) | (lg2(ctx->G) << 8);

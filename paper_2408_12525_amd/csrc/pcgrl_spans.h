@@ -13,7 +13,9 @@ struct SpanCase {
   int problem;             // PCGRL_BINARY / MAZE / DUNGEON
   bool observed;           // with observations, a slot for every step
   int64_t batch, steps;    // levels, steps of the rollout
+  int64_t cells, max_w;    // of a level, half way between the mean and the largest shape; the width of the largest
   int64_t obs_bytes;       // of one level's observation
+  int64_t window_bits;     // its cells times channels
   int64_t step_bytes;      // of the observations of a step
   int64_t episode;         // steps that an episode has at the least; 0: a level never starts again
 };
@@ -58,6 +60,9 @@ inline int64_t span_room(int rows, int problem, int64_t batch) {
 //   64 rows  16 steps of 8 binary levels 1.19, maze 1.10, dungeon 1.00; 20 steps of 64 binary levels 1.08, maze 17.2 / 17.8 (25 steps 1.03),
 //            dungeon 19.1 / 22.0 (30 steps 1.02); 256 binary levels, 32 steps 1.16, maze 1.00 (37 steps 1.02), dungeon 27.9 / 30.3 (48 steps 1.05);
 //            1024 levels, 80 steps 1.21, 85 steps 1.08, 96 steps 1.08
+// Beyond 256 levels, and with windows that a relay does not take, cutting pays from the start: 345 32x32 dungeon levels with 38 cells, 32 steps 56 / 33,
+// 231 64x56 ones with 63 cells 46 / 42, 917 16x16 ones with 34 cells, 16 steps 38 / 29.
+// (Smaller levels have less to find from scratch: 64 dungeon levels of 48x48, 20 steps 0.95, of 64x32 0.99, of 8x64 1.20; 256 of 32x17, 16 steps 0.99.)
 // Without observations a rollout is one wavefront a level group, which is the longer chain: 64 16x16 maze levels, 200 steps
 // 199 / 20 us, 4096 279 / 152, 2048 with 32 steps 44 / 27; 512 64x64 ones with 32 steps 47 / 28, 2048 57 / 57.
 // Nor where the stores are what a rollout waits for: 1024 16x16 dungeon levels (7.9 MB a step) 53 / 43, 2048 maze levels
@@ -67,33 +72,47 @@ inline int64_t span_room(int rows, int problem, int64_t batch) {
 // And less where levels start again on the way, which is one more draw in a row for the wavefront that runs ahead and a longer chain for
 // the span that has it: with a limit of 150 changes 64 64x64 dungeon levels, 30 steps 0.91, 45 steps 1.08, 256 32x32 ones, 22 steps 0.90, 33 steps
 // 1.01, 64 16x16 ones, 12 steps 0.97; with 40 changes or 30 steps 768 64x64 dungeon levels 0.87 to 1.02 however long, 1024
-// binary ones 0.92 to 1.27, 2048 levels without observations 0.91 to 1.02.
+// binary ones 0.92 to 1.27, 2048 levels without observations 0.91 to 1.02.  (A lane draws a row: 64 dungeon levels of 64x8, 20 steps 1.12, of 64x32 0.91.)
 inline SpanShape span_shape(const SpanCase& c) {
   const SpanShape whole = {1, (int)c.steps};
-  const int64_t B = c.batch, from32 = std::clamp<int64_t>(B - 32, 0, 32), MB = (int64_t)1 << 20;
+  const int64_t B = c.batch, MB = (int64_t)1 << 20;
   const bool binary = c.problem == PCGRL_BINARY, dungeon = c.problem == PCGRL_DUNGEON;
-  const bool restarts = c.episode > 0 && c.episode < 400, often = c.episode > 0 && c.episode < 80;
-  int64_t most_batch = 4096, fewest, most_bytes = 9 * MB;
-  bool slower = false;  // when levels start again
+  const bool restarts = c.episode > 0 && c.episode < 400, often = c.episode > 0 && c.episode < 60;
+  const bool one_each = B <= 256;  // workgroups of a relay for a compute unit
+  // the fewest steps; how many more where a relay is at its best; and twelfths of them more where levels start again
+  int64_t most_batch = 4096, most_bytes = 9 * MB, fewest, more = 0, again = 0;
   if (!c.observed) {
     if (c.rows == 64 && often) most_batch = 1024;
     fewest = c.rows == 16 ? 8 + B / 128 : c.rows == 32 ? 8 + B / 96 : 12 + B / 32;
   } else if (c.rows == 16) {
     most_batch = 3072;
-    fewest = (dungeon ? B > 64 && B < 512 : B > 1536) ? 14 : 12;
-    slower = B > 1536 || (dungeon && B <= 512);
+    fewest = 12;
+    if (dungeon ? B > 64 && one_each : binary ? B > 1536 && B <= 2048 : B > 2048) more = 2;
+    if (more > 0 || (dungeon && B <= 512)) again = 2;
   } else if (c.rows == 32) {
     most_batch = binary ? 3072 : 1536;
-    fewest = std::max<int64_t>(14 + B / 96, binary ? 0 : std::min<int64_t>(10 + B / 21, 22));
-    slower = binary ? B > 1536 : B <= (dungeon ? 512 : 768);
+    fewest = 14 + B / 96;
+    if (binary) {
+      again = B > 1536 ? 4 : 0;
+    } else {
+      if (one_each && c.cells > 700) more = std::max<int64_t>(std::min<int64_t>(9 + B / 20, 22) - fewest, 0);
+      again = one_each ? (dungeon ? (often ? 9 : 6) : 3) : B <= (dungeon ? 512 : 768) ? (often ? 5 : 2) : 0;
+    }
   } else {
-    most_batch = !often ? 1024 : binary ? 900 : dungeon ? 320 : 640;
-    fewest = 16 + B / 16 + (binary ? 0 : dungeon ? from32 / 4 + std::min<int64_t>(B, 256) / 32 : from32 / 6);
-    if (dungeon) most_bytes = 5 * MB;
-    slower = true;
+    const int64_t from32 = std::clamp<int64_t>(B - 32, 0, 32);
+    if (one_each && !binary)
+      more = (dungeon ? from32 / 4 + B / 32 : from32 / 8) * std::clamp<int64_t>(c.cells - 1536, 0, 2560) / 2560;
+    fewest = 16 + B / 16;
+    if (dungeon && B > 700) most_bytes = 5 * MB;
+    if (dungeon && c.max_w > 16) again = one_each || often ? (B <= 384 ? 5 : 24) : B <= 384 ? 3 : 9;
+    if (!dungeon && !binary && c.max_w > 32) again = one_each ? 3 : often ? 8 : 0;
+    most_batch = !often ? 1024 : binary ? 900 : again == 0 ? 1024 : 640;
   }
-  if (restarts && slower) fewest = fewest * (dungeon ? (often ? 21 : 18) : often ? 18 : 16) / 12;
-  if (!binary && c.obs_bytes >= 8192) most_bytes = std::min(most_bytes, 8 * MB);
+  // (a wide window makes the steps themselves longer)
+  const int64_t narrow = std::clamp<int64_t>(9500 - c.window_bits, 0, 1500);
+  fewest += more * narrow / 1500;
+  if (restarts) fewest += fewest * again * narrow / (12 * 1500);
+  if (!binary && !dungeon && c.obs_bytes >= 8192) most_bytes = std::min(most_bytes, 8 * MB);
   if (B > most_batch || c.steps < fewest || c.step_bytes > most_bytes) return whole;
   const bool busy = 4 * B >= 3 * 256 * ((B + 255) / 256);
   if (c.obs_bytes >= (c.rows == 16 ? 16000 : 10000) && busy && c.step_bytes > (binary ? 8 * MB : 15 * MB / 4) && c.step_bytes * c.steps > 300 * MB)

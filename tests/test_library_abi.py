@@ -338,7 +338,7 @@ def test_spans_cover_a_rollout_and_fit_their_room():
     for _ in range(20000):
         batch, steps = int(2 ** rng.uniform(0, 24)), int(2 ** rng.uniform(0, 20))
         case = dict(rows=rng.choice([16, 32, 64]), problem=rng.choice([wl.BINARY, wl.MAZE, wl.DUNGEON]), observed=rng.random() < .5, batch=batch, steps=steps,
-                    obs_bytes=rng.choice([75, 4864, 19845]), episode=rng.choice([0, 30, 150, 1000]))
+                    cells=rng.choice([9, 300, 1024, 4096]), max_w=rng.choice([3, 16, 40, 64]), obs_bytes=rng.choice([75, 4864, 19845]), window_bits=rng.choice([75, 8000, 19845]), episode=rng.choice([0, 30, 150, 1000]))
         case["step_bytes"] = case["obs_bytes"] * batch if case["observed"] else 0
         spans, each, room = span_rule.shape_and_room(**case)
         assert spans == 1 and each == steps or spans > 1 and (spans - 1) * each < steps <= spans * each, case
@@ -346,7 +346,7 @@ def test_spans_cover_a_rollout_and_fit_their_room():
         cut += spans > 1
     assert cut > 2000
     # where cutting up begins to pay, and where the stores are what a rollout waits for
-    shape = lambda **more: span_rule.shape(**dict(dict(rows=16, problem=wl.BINARY, observed=1, batch=64, steps=256, obs_bytes=1922, step_bytes=64 * 1922, episode=1000), **more))  # noqa: E731
+    shape = lambda **more: span_rule.shape(**dict(dict(rows=16, problem=wl.BINARY, observed=1, batch=64, steps=256, cells=256, max_w=16, obs_bytes=1922, window_bits=1922, step_bytes=64 * 1922, episode=1000), **more))  # noqa: E731
     assert shape() == (64, 4) and shape(steps=11) == (1, 11) and shape(steps=12) == (12, 1)
     assert shape(step_bytes=9 << 20) == (64, 4) and shape(step_bytes=(9 << 20) + 1) == (1, 256)
     assert shape(rows=64) == (32, 8) and shape(rows=64, steps=19) == (1, 19) and shape(rows=32, batch=1536, problem=wl.MAZE) == (2, 128)
@@ -356,16 +356,21 @@ def test_spans_cover_a_rollout_and_fit_their_room():
 @pytest.mark.parametrize("problem,rows,ow,batch,whole,cut,more", [
     # (rollouts of so many steps: one that is faster in one piece, one that is faster cut up)
     (wl.DUNGEON, 64, 9, 64, 20, 30, {}), (wl.DUNGEON, 64, 31, 256, 42, 50, {}), (wl.MAZE, 64, 9, 64, 20, 30, {}), (wl.MAZE, 64, 9, 256, 34, 51, {}),
-    (wl.BINARY, 64, 9, 64, 16, 20, {}), (wl.DUNGEON, 64, 31, 768, 256, None, {}), (wl.DUNGEON, 64, 31, 640, 71, 108, {}),
+    (wl.BINARY, 64, 9, 64, 16, 20, {}), (wl.DUNGEON, 64, 31, 768, 256, None, {}), (wl.DUNGEON, 64, 31, 640, 50, 72, {}), (wl.DUNGEON, 16, 34, 917, 10, 16, {}), (wl.DUNGEON, 64, 63, 231, 24, 32, dict(h=64, max_w=56)),
     (wl.MAZE, 32, 9, 256, 16, 24, {}), (wl.DUNGEON, 32, 9, 256, 20, 24, {}), (wl.BINARY, 32, 31, 64, 12, 16, {}),
     (wl.DUNGEON, 16, 9, 256, 12, 18, {}), (wl.MAZE, 16, 9, 3072, 12, 18, {}), (wl.BINARY, 16, 9, 2048, 12, 18, {}), (wl.BINARY, 16, 9, 1536, 10, 12, {}),
+    # smaller levels
+    (wl.DUNGEON, 64, 31, 165, 24, 36, dict(h=8, max_w=54)), (wl.DUNGEON, 64, 49, 261, 24, 32, dict(h=32, max_w=48)), (wl.DUNGEON, 32, 9, 256, 14, 18, dict(max_w=17)),
+    (wl.DUNGEON, 64, 9, 64, 18, 20, dict(max_w=8, max_changes=40)), (wl.DUNGEON, 64, 9, 64, 18, 25, dict(min_size=8, min_w=8)),
     # stores that spill from the cache
     (wl.MAZE, 16, 63, 256, 96, 36, {}), (wl.MAZE, 16, 63, 320, 10, 96, {}), (wl.MAZE, 16, 63, 448, 18, None, {}), (wl.DUNGEON, 16, 63, 256, 42, 21, {}),
     # levels that start again on the way
-    (wl.DUNGEON, 64, 9, 64, 36, 45, dict(max_changes=150)), (wl.DUNGEON, 64, 9, 768, 640, None, dict(max_changes=40)), (wl.MAZE, 64, 9, 512, 73, 159, dict(max_steps=30)), (wl.BINARY, 64, 9, 1024, 120, None, dict(max_steps=30)),
-    (wl.DUNGEON, 64, 9, 64, 20, 30, dict(max_steps=30, autoreset=0)), (wl.DUNGEON, 32, 9, 256, 29, 43, dict(max_changes=150)), (wl.DUNGEON, 16, 9, 64, 14, 18, dict(max_changes=150))])
+    (wl.DUNGEON, 64, 9, 64, 36, 45, dict(max_changes=150)), (wl.DUNGEON, 64, 9, 768, 640, None, dict(max_changes=40)), (wl.DUNGEON, 64, 31, 397, 60, 246, dict(h=30, max_w=48, max_changes=63, obs_format=1)), (wl.MAZE, 64, 9, 512, 73, 159, dict(max_steps=30)), (wl.BINARY, 64, 9, 1024, 120, None, dict(max_steps=30)),
+    (wl.DUNGEON, 64, 9, 64, 20, 30, dict(max_steps=30, autoreset=0)), (wl.DUNGEON, 32, 9, 256, 29, 43, dict(max_changes=150)), (wl.DUNGEON, 16, 9, 64, 13, 18, dict(max_changes=150)), (wl.DUNGEON, 64, 15, 634, 72, 116, dict(max_changes=74)),
+    (wl.DUNGEON, 32, 38, 345, 14, 32, dict(max_changes=195))])
 def test_rollouts_are_cut_into_spans_where_that_is_ahead(problem, rows, ow, batch, whole, cut, more):
-    cfg = wl.make_config(problem, batch, rows, ow, obs_pitch=-1, **more)
+    more = dict(more)
+    cfg = wl.make_config(problem, batch, more.pop("h", rows), ow, obs_pitch=-1, **more)
     for steps, spans in ((whole, 0), (cut, 1)):
         assert steps is None or (span_rule.shape(**span_rule.case_of(cfg, steps, True))[0] > 1) == spans
 
