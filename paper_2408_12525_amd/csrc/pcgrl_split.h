@@ -91,11 +91,12 @@ inline constexpr SplitRule kRolloutSplit[] = {
     {32, 10240, 12800, 0, 8191, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 15 cells 5.5 / 5.6, 7.8 / 7.5, (14 001) 8.7 / 8.9, 23 cells 6.4 / 6.5, 11.5 / 10.6, 18.0 / 17.5, 31 cells 1.01...1.04
     {32, 4097, kMax, 0, kMax, 0, kMax, PCGRL_BINARY, kAnyStore, 1},  // +10 % steps/s at 16 384 (dungeon: +-2 %)
     {64, 1, 8192, 0, kMax, 0, kMax, -1, kAnyStore, 1},           // -6 %
+    {64, 8193, kMax, 0, 2047, 32 * kMB + 1, kMax, PCGRL_DUNGEON, kSpills, 0},  // one of two: 15 cells, 8 slots at 20 000 (34 MB a step) 0.98, 24 001 0.95...1.01, 13 cells at 32 768 0.96
+    {64, 8193, 32768, 0, 2047, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 15 cells at 8193, 10 000, 16 000 8.2 / 7.5, 9.5 / 9.0, 13.9 / 13.4, at 32 768 1.03...1.06; 14 cells, 16 slots at 10 887 9.1 / 8.5
     {64, 8193, kMax, 0, 2047, 16 * kMB + 1, kMax, -1, kSpills, 0},  // one of two, 8 slots: maze (20 cells) 24 001 0.88, (15) 32 768 0.95, binary (20) 24 001 0.95, (25) 20 000 0.88;
                                                       // 16 slots: maze (20) 12 000 0.95; 48 slots of up to 9 MB are ahead as in the next row
     {64, 8193, 24576, 0, 2047, 0, kMax, -1, kAnyStore, 1},       // 15 cells at 8193, 10 000, 16 000, 24 001: binary 6.4 / 6.1, 6.8 / 6.5, 10.1 / 9.9, 13.3 / 13.3 (48 slots 1.01), maze 6.8 / 6.3,
-                                                      // 7.8 / 7.4, 11.0 / 10.6, 15.3 / 15.2 (1.03), dungeon 8.2 / 7.5, 9.5 / 9.0, 13.9 / 13.4, (1.06); 32 768 0.95...1.01
-    {64, 24577, 32768, 0, 2047, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 5 to 15 cells at 32 768 1.03...1.06
+                                                      // 7.8 / 7.4, 11.0 / 10.6, 15.3 / 15.2 (1.03); 32 768 0.95...1.01
     {64, 8193, 12288, 6000, kMax, 0, kMax, PCGRL_DUNGEON, kAnyStore, 1},  // 31 cells 13.8 / 12.8, 16.4 / 15.5, 19.1 / 18.5; 23 cells 10.1 / 10.1, 11.4 / 11.9; 41 cells, 48 slots 0.98...1.00
     {0, 1, kMax, 0, kMax, 0, kMax, -1, kAnyStore, 0},
 };

@@ -391,7 +391,7 @@ def test_steps_of_large_batches_take_two_wavefronts_where_that_is_ahead(problem,
     # a ring that the cache holds, one that it does not, and one that is not stored through it
     (wl.MAZE, 64, 20, 0, 14000, 8, "cached", 1), (wl.MAZE, 64, 20, 0, 16000, 8, "cached", 0), (wl.MAZE, 64, 20, 0, 12000, 16, "cached", 0), (wl.MAZE, 64, 20, 0, 24000, 48, "stream", 1),
     (wl.BINARY, 64, 25, -1, 20000, 8, "cached", 0), (wl.BINARY, 64, 9, -1, 24001, 48, "cached", 1), (wl.BINARY, 64, 9, -1, 32768, 48, "cached", 0),
-    (wl.DUNGEON, 64, 9, 0, 32768, 8, "cached", 1), (wl.DUNGEON, 64, 9, 0, 50000, 8, "cached", 0), (wl.MAZE, 64, 9, 0, 50000, 8, "cached", 0),
+    (wl.DUNGEON, 64, 9, 0, 32768, 8, "cached", 1), (wl.DUNGEON, 64, 14, 0, 10887, 16, "cached", 1), (wl.DUNGEON, 64, 15, 0, 20000, 8, "cached", 0), (wl.DUNGEON, 64, 9, 0, 50000, 8, "cached", 0), (wl.MAZE, 64, 9, 0, 50000, 8, "cached", 0),
     (wl.DUNGEON, 32, 25, 0, 4097, 8, "cached", 1), (wl.DUNGEON, 32, 25, 0, 4097, 16, "cached", 1),
     (wl.DUNGEON, 32, 25, 0, 4097, 48, "cached", 0), (wl.DUNGEON, 32, 23, -1, 4097, 48, "cached", 1), (wl.DUNGEON, 32, 23, -1, 4608, 48, "cached", 0), (wl.DUNGEON, 32, 21, -1, 5120, 48, "cached", 1), (wl.MAZE, 32, 25, -1, 5120, 48, "cached", 1), (wl.MAZE, 32, 15, 0, 120000, 8, "stream", 1),
     (wl.MAZE, 32, 15, 0, 200000, 8, "stream", 0), (wl.MAZE, 32, 45, 0, 10240, 48, "cached", 0), (wl.DUNGEON, 32, 35, 0, 10240, 8, "cached", 0)])
